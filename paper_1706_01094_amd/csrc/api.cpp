@@ -15,6 +15,7 @@
 #include "d2q9.h"
 #include "device.h"
 #include "moments.h"
+#include "regplan.h"
 #include "tables.h"
 
 using namespace mclg;
@@ -34,10 +35,12 @@ struct Layout {
   uint64_t total_sites = 0, max_tiles = 0;
   // workspace byte offsets
   uint64_t o_ctrl, o_slots, o_tslot, o_tiles, o_list, o_pdesc, o_pool, o_idesc, o_over, o_ipool,
-      o_rowbase, o_rowdesc, o_thr, o_fixed, o_row16, ws_bytes;
+      o_rowdesc, o_thr, o_row16, ws_bytes;
   // moment kernels: segments, runs (one per slot), partial records, results
   MomPlan mplan;
   uint64_t o_mseg, o_mrun, o_mslot, o_mpart, o_mout;
+  // steps on sites in registers: units, their blocks, strips and their counts
+  uint64_t o_units, o_ufirst, o_strips, o_sdata;
 };
 
 bool compute_layout(uint32_t n, const uint64_t *L, const CollisionTables *tab, Layout &lay) {
@@ -81,11 +84,13 @@ bool compute_layout(uint32_t n, const uint64_t *L, const CollisionTables *tab, L
   lay.o_pool = take(sizeof(uint32_t) * kPoisCap * 3 * n);
   lay.o_idesc = take(sizeof(ImageDesc) * n);
   lay.o_over = take(kOverflowBytes);
+  lay.o_units = take(sizeof(UnitDev) * max_units(n));
+  lay.o_ufirst = take(sizeof(uint32_t) * (kPlanBlocks + 1));
+  lay.o_strips = take(sizeof(StripDev) * kMaxStrips);
+  lay.o_sdata = take((uint64_t)kMaxStrips * 6 * kMaxHalo * sizeof(uint16_t));
   lay.o_ipool = take((uint64_t)kMaxImage * n);
-  lay.o_rowbase = take(sizeof(uint32_t) * tab->rowbase.size());
   lay.o_rowdesc = take(sizeof(uint32_t) * tab->rowdesc.size());
   lay.o_thr = take(sizeof(uint32_t) * (tab->thr.size() + 16));  // +16: see count_le_16
-  lay.o_fixed = take(sizeof(uint32_t) * tab->fixed.size());
   lay.o_row16 = take(sizeof(uint16_t) * tab->row16.size());
   lay.ws_bytes = o;
   return true;
@@ -152,7 +157,10 @@ struct mclg_ctx {
   // looked up in mclg_init with the context's device current
   unsigned long long *scratch = nullptr;
   double coverage = 0.0;                // expected LDS hit fraction (site-weighted)
-  bool use_row16 = false;               // resolve misses from the 64-byte rows
+  bool one_image = false;               // every replica uses the same image
+  // steps on sites in registers (kernels_reg.hip)
+  UnitPlan units;
+  std::vector<RegWay> ways;
 
   uint32_t *err() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl); }
   uint32_t *ticket() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl) + 1; }
@@ -176,6 +184,53 @@ struct mclg_ctx {
     if (!e) t_pending = 0;
     return e;
   }
+  // The launch choices mclg_set_schedule, mclg_set_drain and
+  // mclg_set_grid_limit make belong to the kernels that keep the state in
+  // memory: with any of them set, those kernels run.
+  bool default_launch() const {
+    return sch.threads == 1024 && sch.lds_budget == Schedule().lds_budget &&
+           drain_policy == MCLG_DRAIN_AUTO && grid_limit == 0;
+  }
+  // `steps` steps of every replica in one launch of way `w`.
+  hipError_t launch_reg(const RegWay &w, uint32_t steps) {
+    const StepLaunch a = launch_args(0, (uint32_t)tiles.size(), 0, n, t_pending);
+    if (w.kind == RegWay::kRing) {
+      RingLaunch r;
+      r.order = reinterpret_cast<const uint32_t *>(ws + lay.o_list);
+      r.n = n;
+      r.team = w.team;
+      r.steps = steps;
+      return launch_ring(stream, a, r, w.Q, 16);
+    }
+    TileLaunch tl;
+    tl.units = reinterpret_cast<const UnitDev *>(ws + lay.o_units);
+    tl.unit_first = reinterpret_cast<const uint32_t *>(ws + lay.o_ufirst);
+    tl.strips = reinterpret_cast<const StripDev *>(ws + lay.o_strips);
+    tl.strip_data = reinterpret_cast<uint16_t *>(ws + lay.o_sdata);
+    tl.n_strips = (uint32_t)units.strips.size();
+    tl.kh = w.kh;
+    tl.steps = steps;
+    return launch_tiles(stream, a, tl, w.Q, 16, (uint32_t)units.first.size() - 1);
+  }
+  // n_steps steps of every replica by the quickest way, if there is one.
+  hipError_t step_reg(uint64_t n_steps, bool &done) {
+    done = false;
+    if (!default_launch() || ways.empty()) return hipSuccess;
+    const RegWay *w = pick_way(ways, n_steps, single_step_us(lay.total_sites));
+    if (!w) return hipSuccess;
+    const uint64_t most = w->most;
+    for (uint64_t launches = (n_steps + most - 1) / most; launches; --launches) {
+      const uint32_t k = (uint32_t)((n_steps + launches - 1) / launches);
+      hipError_t e = t_pending >= (1u << 30) ? flush_t() : hipSuccess;
+      if (!e) e = launch_reg(*w, k);
+      if (e) return e;
+      t_pending += k;
+      for (auto &x : t) x += k;
+      n_steps -= k;
+    }
+    done = true;
+    return hipSuccess;
+  }
   TileDev *tiles_dev() { return reinterpret_cast<TileDev *>(ws + lay.o_tiles); }
   // The moment kernels' arguments; partial records and results go to
   // `partial` and `out` (device).
@@ -196,11 +251,10 @@ struct mclg_ctx {
   }
   TableDev table() {
     TableDev d;
-    d.rowbase = reinterpret_cast<const uint32_t *>(ws + lay.o_rowbase);
     d.rowdesc = reinterpret_cast<const uint2 *>(ws + lay.o_rowdesc);
     d.thr = reinterpret_cast<const uint32_t *>(ws + lay.o_thr);
-    d.fixed = tab->fixed.empty() ? nullptr : reinterpret_cast<const uint4 *>(ws + lay.o_fixed);
     d.row16 = tab->row16.empty() ? nullptr : reinterpret_cast<const uint4 *>(ws + lay.o_row16);
+    d.row_words = tab->max_q <= 24 ? 12u : 16u;
     return d;
   }
   StepParams params() const {
@@ -259,7 +313,6 @@ struct mclg_ctx {
     }
     a.err = err();
     a.tab = table();
-    if (!use_row16) a.tab.row16 = nullptr;
     a.p = params();
     uint64_t bytes = 0;  // state the launch streams: 6 bytes per site
     for (uint32_t s = slot_first; s < slot_first + n_slots; ++s) bytes += 6ull * L[s];
@@ -318,11 +371,12 @@ struct mclg_ctx {
       d.dim_c = im.dim_c;
       d.b_lo = im.b_lo;
       d.nb = im.nb;
+      d.fixed = im.fixed ? 1u : 0u;
       cov += im.coverage * (double)L[r];
       sites += (double)L[r];
     }
     coverage = sites > 0 ? cov / sites : 0.0;
-    use_row16 = use_compact_rows(1.0 - coverage, (uint32_t)ims.size());
+    one_image = ims.size() == 1;
     if (img_pool.size() > (uint64_t)kMaxImage * n) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     if (!img_pool.empty())
@@ -331,6 +385,11 @@ struct mclg_ctx {
                                hipMemcpyHostToDevice, stream);
     if (!e) e = hipStreamSynchronize(stream);
     if (!e) e = step_occupancy(sch, lds_bytes, n_cu, max_blocks);
+    if (!e) e = reg_setup(lds_bytes);
+    ways.clear();
+    // (their kernels take images of fixed records only)
+    if (!e && default_launch() && (C == 0 || ims[0].fixed))
+      ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0);
     return e;
   }
   void drop_graphs() {
@@ -420,6 +479,9 @@ int mclg_init(const mclg_config *cfg, const mclg_init_spec *init, mclg_ctx **out
     slots[r].pad = 0;
     list[r] = r;
   }
+  // longest first, so that the last blocks of a launch are short
+  std::stable_sort(list.begin(), list.end(),
+                   [&](uint32_t x, uint32_t y) { return c->L[x] > c->L[y]; });
   std::vector<uint32_t> ctrl(64, 0), tz(c->n, 0);
   // Poisson laws (host) for the initial state
   std::vector<PoisDesc> pdesc(3 * c->n);
@@ -462,10 +524,8 @@ int mclg_init(const mclg_config *cfg, const mclg_init_spec *init, mclg_ctx **out
   if (!e) e = up(lay.o_mseg, lay.mplan.segs.data(), sizeof(MomSeg) * lay.mplan.segs.size());
   if (!e) e = up(lay.o_mrun, lay.mplan.run_seg.data(), sizeof(uint32_t) * lay.mplan.run_seg.size());
   if (!e) e = up(lay.o_mslot, lay.mplan.run_slot.data(), sizeof(uint32_t) * lay.mplan.run_slot.size());
-  if (!e) e = up(lay.o_rowbase, tab->rowbase.data(), sizeof(uint32_t) * tab->rowbase.size());
   if (!e) e = up(lay.o_rowdesc, tab->rowdesc.data(), sizeof(uint32_t) * tab->rowdesc.size());
   if (!e) e = up(lay.o_thr, tab->thr.data(), sizeof(uint32_t) * tab->thr.size());
-  if (!e && !tab->fixed.empty()) e = up(lay.o_fixed, tab->fixed.data(), sizeof(uint32_t) * tab->fixed.size());
   if (!e && !tab->row16.empty()) e = up(lay.o_row16, tab->row16.data(), sizeof(uint16_t) * tab->row16.size());
   const uint32_t ts = c->sch.tile_sites();
   if (init->kind == MCLG_INIT_POISSON) {
@@ -488,11 +548,17 @@ int mclg_init(const mclg_config *cfg, const mclg_init_spec *init, mclg_ctx **out
   int dev = 0, v = 0;
   e = hipGetDevice(&dev);
   if (!e) e = hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-  if (!e) c->lds_limit = (uint32_t)std::max(0, v - 64);  // the block's two counters
+  if (!e) c->lds_limit = (uint32_t)std::max(0, v - 192);  // counters and exchange buffers
   if (!e) e = hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev);
   if (!e) c->n_cu = (uint32_t)std::max(1, v);
   if (e) return c->hip(e);
   if (c->n_cu > 256) return MCLG_E_UNSUPPORTED;  // overflow region sized for 256 CUs
+  c->units = plan_units(c->L.data(), c->n, c->n_cu);
+  if (c->units.units.size() > max_units(c->n)) return MCLG_E_INTERNAL;
+  e = up(lay.o_units, c->units.units.data(), sizeof(UnitDev) * c->units.units.size());
+  if (!e) e = up(lay.o_ufirst, c->units.first.data(), sizeof(uint32_t) * c->units.first.size());
+  if (!e) e = up(lay.o_strips, c->units.strips.data(), sizeof(StripDev) * c->units.strips.size());
+  if (e) return c->hip(e);
   e = moments_scratch(&c->scratch);
   if (e) return c->hip(e);
   // what density and velocity each replica's image should target
@@ -665,6 +731,11 @@ int mclg_set_blocked(mclg_ctx *c, uint32_t steps, uint32_t tile, void *scratch,
 int mclg_step(mclg_ctx *c, uint64_t n_steps) {
   if (!c) return MCLG_E_INVAL;
   if (c->d2) return d2q9_step(*c->d2, n_steps);
+  if (c->tb.steps <= 1) {
+    bool done = false;
+    hipError_t e = c->step_reg(n_steps, done);
+    if (e || done) return c->hip(e);
+  }
   // whole blocks of tb.steps steps first
   const uint32_t K = c->tb.steps;
   if (K > 1) {

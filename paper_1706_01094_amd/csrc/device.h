@@ -64,33 +64,27 @@ inline uint32_t auto_drain(uint64_t launch_state_bytes) {
   return launch_state_bytes > kCachedStateBytes ? kDrainPatch : kDrainDeferred;
 }
 
-// Stride (uint32) of the fixed-stride copy of the collision rows: a header
-// k_first | q << 16 and up to 19 thresholds.
-constexpr uint32_t kFixedStride = 20;
+// Index of the collision row of a site with N particles, n0 = b of them at
+// rest and a = min(n_-1, n_+1): rows are ordered by N, then s = N - b, then a
+// = 0 .. s / 2, so floor((s + 1)^2 / 4) rows of N precede those of s, and
+// sum_{k <= N + 1} floor(k^2 / 4) = floor((N + 1)(N + 3)(2 N + 1) / 24) rows
+// those of N.  (In 32 bits for N <= 1023.)
+__host__ __device__ inline uint32_t collision_row(uint32_t N, uint32_t b, uint32_t a) {
+  const uint32_t s1 = N - b + 1u;
+  return (N + 1u) * (N + 3u) * (2u * N + 1u) / 24u + ((s1 * s1) >> 2) + a;
+}
 
-// uint16 values per row of the 64-byte copy of the collision rows: k_first,
-// q and the top 16 bits of up to 30 thresholds (0xFFFF beyond q - 1).
+// uint16 values per row of the 64-byte copy of the collision rows: k_first
+// and the top 15 bits of up to 31 thresholds.
 constexpr uint32_t kRow16 = 32;
 
 struct TableDev {
-  const uint32_t *rowbase = nullptr;
   const uint2 *rowdesc = nullptr;
   const uint32_t *thr = nullptr;
-  const uint4 *fixed = nullptr;  // rows at a fixed stride of kFixedStride uint32, or null
   const uint4 *row16 = nullptr;  // rows of kRow16 uint16 (64 bytes), or null
+  uint32_t row_words = 16;       // words of such a row that hold thresholds: 12 or 16
+  uint32_t pad = 0;
 };
-
-// The 64-byte rows cost a missed draw fewer memory bytes than the 80-byte
-// ones but about 60 more VALU instructions.  They pay when the missed rows
-// come from memory rather than the L2: when the draws of many densities miss
-// (a batch of replicas with their own images), or when one density misses
-// very often.  Measured on MI355X at L = 2^27 (us per step, 80-byte / 64-byte
-// rows): rho = 50, 0.5 % misses 346 / 356; rho = 80, 1.6 % misses 364 / 379;
-// rho = 100, u = 0.2, 10 % misses 447 / 420; the 1024-replica batch (2 %
-// misses over 1024 images) 495 / 465.
-inline bool use_compact_rows(double miss_fraction, uint32_t n_images) {
-  return miss_fraction > 0.06 || (n_images >= 16 && miss_fraction > 0.01);
-}
 
 // Where a slot's LDS image lives in the image pool (see LdsImage).
 struct ImageDesc {
@@ -98,6 +92,8 @@ struct ImageDesc {
   uint32_t bytes = 0;      // every slot has one (at least the two special slots)
   uint32_t dir_bytes = 0;
   uint32_t dim_a = 0, dim_c = 0, b_lo = 0, nb = 0;
+  uint32_t fixed = 0;      // records with the window of moves around none (see LdsImage)
+  uint32_t pad = 0;
 };
 
 struct PoisDesc {
@@ -223,6 +219,44 @@ hipError_t step_occupancy(const Schedule &sch, uint32_t lds_bytes, uint32_t n_cu
                           uint32_t &max_blocks);
 // Dynamic LDS of one block: image (rounded to 16 bytes) + miss queues.
 uint32_t step_lds_bytes(const Schedule &sch, uint32_t image_bytes);
+
+// ---- Steps on sites held in registers (kernels_reg.hip) -----------------
+// Ring: lattices order[0 .. n) that fit a block's registers, `steps` steps
+// in one launch.  A wave holds up to 256 Q sites.  team = 0: a block per
+// lattice; team = k: k lattices of at most 256 Q sites per block, a wave
+// each, all with the same image.
+struct RingLaunch {
+  const uint32_t *order = nullptr;  // slots
+  uint32_t n = 0, team = 0, steps = 0;
+};
+// Tiles: block b advances units[unit_first[b] .. unit_first[b + 1]), each a
+// whole lattice (split = 0: x0 = 0, x1 = L) or a part of one between two
+// strips el and er, `steps` <= kh steps (kh - 8 when some lattice's sites are
+// no multiple of 8: the positions after its last site take their place).  x0, and x1 unless it is L, are
+// multiples of 8, and a part holds at least kh sites.
+struct UnitDev {
+  uint32_t slot = 0, x0 = 0, x1 = 0, split = 0, el = 0, er = 0;
+};
+// The boundary after the part of `slot` that ends at x.
+struct StripDev {
+  uint32_t slot = 0, x = 0;
+};
+constexpr uint32_t kMaxHalo = 128;  // kh, at most
+struct TileLaunch {
+  const UnitDev *units = nullptr;
+  const uint32_t *unit_first = nullptr;
+  const StripDev *strips = nullptr;
+  uint16_t *strip_data = nullptr;   // n_strips x 3 x 2 kh
+  uint32_t n_strips = 0, kh = 0, steps = 0;
+};
+constexpr uint32_t kRingExchangeBytes = 128;
+uint32_t reg_lds_bytes(uint32_t image_bytes, uint32_t waves);
+// Allows the kernels the LDS of a 16-wave block with images of image_bytes.
+hipError_t reg_setup(uint32_t image_bytes);
+hipError_t launch_ring(hipStream_t s, const StepLaunch &a, const RingLaunch &rl, uint32_t Q,
+                       uint32_t waves);
+hipError_t launch_tiles(hipStream_t s, const StepLaunch &a, const TileLaunch &tl, uint32_t Q,
+                        uint32_t waves, uint32_t grid);
 
 hipError_t launch_init_poisson(hipStream_t s, uint16_t *state, const SlotDev *slots,
                                const uint32_t *tslot, const TileDev *tiles, uint32_t n_tiles,

@@ -9,6 +9,7 @@
 // same three physical locations -- streaming is the shift of the layout.
 // Algorithmic traffic: 6 B read + 6 B written per site update; there is no
 // dense contraction, so no MFMA.
+#include "collide.h"
 #include "device.h"
 #include "mom3_sum.h"
 #include "rng.h"
@@ -19,271 +20,9 @@
 namespace mclg {
 namespace {
 
-// Galilean-invariant acceptance of fiber (N, |J|) as a numerator over 2^32:
-// floor(g num / den) with g = floor(2^32 N / sqrt(N^2 + 3 J^2)), both exact:
-// each is estimated in double and corrected by integer tests that use only
-// products (g is the largest integer with g^2 (N^2 + 3 J^2) <= 2^64 N^2).
-__device__ uint64_t galilean_lambda(uint32_t num, uint32_t den, uint32_t N, uint32_t absJ) {
-  using u128 = unsigned __int128;
-  uint64_t g = 1ull << 32;
-  if (absJ) {
-    const uint64_t n2 = (uint64_t)N * N, d = n2 + 3ull * absJ * absJ;
-    const u128 bound = (u128)n2 << 64;
-    uint64_t s = (uint64_t)(4294967296.0 * (double)N / __dsqrt_rn((double)d));
-    while (s && (u128)s * s * d > bound) --s;
-    while ((u128)(s + 1) * (s + 1) * d <= bound) ++s;
-    g = s;
-  }
-  const uint64_t gn = g * num;  // < 2^61
-  uint64_t q = (uint64_t)((double)gn / (double)den);
-  while (q && (u128)q * den > gn) --q;
-  while ((u128)(q + 1) * den <= gn) ++q;
-  return q;
-}
-
-// The paper's C sub-collisions one by one (Eq. (select), Eq. (omega)); used
-// for sites with N > n_max.  Returns the new rest count.  GAL selects the
-// Galilean-invariant acceptance (its own kernel instantiation, so that the
-// plain kernel carries none of its code).
-template <bool GAL>
-__device__ __forceinline__ uint32_t collide_direct(uint32_t a, uint32_t b, uint32_t c,
-                                                const StepParams &p, uint32_t x, uint32_t t,
-                                                uint32_t rid) {
-  WordStream ws;
-  ws.key = make_uint2((uint32_t)p.seed, (uint32_t)(p.seed >> 32));
-  ws.x = x; ws.t = t; ws.rid = rid; ws.block = 0; ws.used = 4;
-  const uint32_t N = a + b + c;
-  if constexpr (GAL) {
-    // lambda = lq / 2^32: a {-1,+1} pair is accepted when a word is below lq,
-    // a {0,0} pair (lambda / 8) when a 35-bit uniform (w1 * 8 + w2 >> 29) is.
-    const uint64_t lq = galilean_lambda(p.lam_p, p.lam_q, N, c > a ? c - a : a - c);
-    for (int32_t s = 0; s < p.C; ++s) {
-      const uint32_t r1 = ws.uniform(N);
-      uint32_t r2 = ws.uniform(N - 1);
-      r2 += (r2 >= r1);
-      const int v1 = r1 < a ? -1 : (r1 < a + b ? 0 : 1);
-      const int v2 = r2 < a ? -1 : (r2 < a + b ? 0 : 1);
-      if (v1 + v2 == 0 && v1 != 0) {
-        if ((uint64_t)ws.next() < lq) { a -= 1; c -= 1; b += 2; }
-      } else if (v1 == 0 && v2 == 0) {
-        const uint64_t w1 = ws.next();
-        const uint32_t w2 = ws.next();
-        if (((w1 << 3) | (w2 >> 29)) < lq) { b -= 2; a += 1; c += 1; }
-      }
-    }
-    return b;
-  }
-  for (int32_t s = 0; s < p.C; ++s) {
-    const uint32_t r1 = ws.uniform(N);
-    uint32_t r2 = ws.uniform(N - 1);
-    r2 += (r2 >= r1);
-    const int v1 = r1 < a ? -1 : (r1 < a + b ? 0 : 1);
-    const int v2 = r2 < a ? -1 : (r2 < a + b ? 0 : 1);
-    if (v1 + v2 == 0 && v1 != 0) {
-      if (ws.uniform(p.lam_q) < p.lam_p) { a -= 1; c -= 1; b += 2; }
-    } else if (v1 == 0 && v2 == 0) {
-      if (ws.uniform(8u * p.lam_q) < p.lam_p) { b -= 2; a += 1; c += 1; }
-    }
-  }
-  return b;
-}
-
-// Index of the first row of fiber (N, |J|) in the global tables, in closed
-// form: fibers are stored by N, then |J|, and fiber (N, j) holds
-// floor((N - j) / 2) + 1 rows, so with S(M) = M + 1 + floor(M^2 / 4) rows in
-// the fibers (M, 0..M) and T(K) = sum_{M <= K} floor(M^2 / 4), the base is
-// N (N + 1) / 2 + T(N - 1) + S(N) - S(N - j).  (Saves a dependent load.)
-__device__ __forceinline__ uint32_t fiber_base(uint32_t N, uint32_t absJ) {
-  auto S = [](uint32_t M) { return M + 1u + ((M * M) >> 2); };
-  uint32_t T = 0;
-  if (N >= 1u) {
-    const uint32_t K = N - 1u, i = K >> 1;
-    T = (K & 1u) ? i * (i + 1u) * (4u * i + 5u) / 6u : i * (i + 1u) * (4u * i - 1u) / 6u;
-  }
-  return ((N * (N + 1u)) >> 1) + T + S(N) - S(N - absJ);
-}
-
-// Number of entries <= r of an ascending array of n values: probe seven
-// evenly spaced pivots at once, then count the one bucket left (all its
-// loads at once) -- two rounds of independent loads for n <= 64.
-__device__ __forceinline__ uint32_t count_le_wide(const uint32_t *__restrict__ t, uint32_t n,
-                                                  uint32_t r) {
-  uint32_t lo = 0;
-  while (n > 8u) {
-    const uint32_t s = (n + 7u) >> 3;  // bucket width; pivots t[lo + j s - 1]
-    uint32_t c = 0;
-#pragma unroll
-    for (uint32_t j = 1; j < 8; ++j)
-      c += (j * s <= n && t[lo + j * s - 1u] <= r) ? 1u : 0u;
-    lo += c * s;
-    n = min(s, n - c * s);
-  }
-  uint32_t c = 0;
-#pragma unroll
-  for (uint32_t j = 0; j < 8; ++j) c += (j < n && t[lo + j] <= r) ? 1u : 0u;
-  return lo + c;
-}
-
-// Exact row of the global tables: the number of thresholds <= r.
-// Rows of up to 16 thresholds (every row of C <= 7, most of larger C) are
-// counted from four 16-byte loads issued together; the threshold pool is
-// padded by 16 values so that these loads stay inside it.
-__device__ __forceinline__ uint32_t count_le_16(const uint32_t *t, uint32_t n, uint32_t r) {
-  uint4 q[4];
-  for (int j = 0; j < 4; ++j) __builtin_memcpy(&q[j], t + 4 * j, 16);  // 4-byte aligned
-  uint32_t c = 0;
-#pragma unroll
-  for (uint32_t j = 0; j < 16; ++j) {
-    const uint4 &v = q[j >> 2];
-    const uint32_t x = (j & 3) == 0 ? v.x : (j & 3) == 1 ? v.y : (j & 3) == 2 ? v.z : v.w;
-    c += (j < n && x <= r) ? 1u : 0u;
-  }
-  return c;
-}
-
-// Two 16-bit lanes of a 32-bit register.
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t global_outcome(const TableDev &tab, uint32_t N, uint32_t absJ,
-                                                   uint32_t b, uint32_t par, uint32_t r) {
-  const uint32_t row = fiber_base(N, absJ) + ((b - par) >> 1);  // states ascend in n0
-  if (tab.row16) {
-    // one 64-byte row of 16-bit values: k_first, q, the thresholds' top 16
-    // bits (0xFFFF padding); the outcome is k_first + #{t < rh} unless some
-    // t equals rh, when only the full 32-bit threshold decides (the rows
-    // below)
-    const uint4 *q = tab.row16 + (size_t)row * (kRow16 / 8);
-    const uint4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
-    const uint32_t w[16] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w,
-                            q2.x, q2.y, q2.z, q2.w, q3.x, q3.y, q3.z, q3.w};
-    const uint32_t rr = (r >> 16) * 0x10001u;
-    const u16x2 R = __builtin_bit_cast(u16x2, rr), one = {1, 1};
-    u16x2 acc = {0, 0};
-    uint32_t eq = 0;
-#pragma unroll
-    for (int j = 1; j < 16; ++j) {
-      acc += __builtin_elementwise_min(__builtin_elementwise_sub_sat(R, __builtin_bit_cast(u16x2, w[j])),
-                                       one);
-      const uint32_t x = w[j] ^ rr;  // a zero half: that threshold's top bits equal rh
-      eq |= (x - 0x00010001u) & ~x & 0x80008000u;
-    }
-    if (eq == 0u) return (w[0] & 0xffffu) + (uint32_t)acc.x + (uint32_t)acc.y;
-  }
-  if (tab.fixed) {
-    // header and up to 19 thresholds, all five 16-byte pieces at once
-    const uint4 *q = tab.fixed + (size_t)row * (kFixedStride / 4);
-    const uint4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3], q4 = q[4];
-    const uint32_t w[20] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w, q2.x, q2.y,
-                            q2.z, q2.w, q3.x, q3.y, q3.z, q3.w, q4.x, q4.y, q4.z, q4.w};
-    const uint32_t n = (w[0] >> 16) - 1u;
-    uint32_t c = 0;
-#pragma unroll
-    for (uint32_t j = 0; j < kFixedStride - 1; ++j) c += (j < n && w[1 + j] <= r) ? 1u : 0u;
-    return (w[0] & 0xffffu) + c;
-  }
-  const uint2 d = tab.rowdesc[row];
-  const uint32_t n = (d.y >> 16) - 1u;
-  return (d.y & 0xffffu) +
-         (n <= 16u ? count_le_16(tab.thr + d.x, n, r) : count_le_wide(tab.thr + d.x, n, r));
-}
-
-// The slot's collision image in LDS: a directory of (min(a,c), max(a,c))
-// pairs whose last row and column stand for every pair out of range, then
-// 16-byte records, nb + 1 per pair (the last one for every b out of range).
-// A record decides the outcome exactly whenever the top 16 bits of r lie in
-// its window and differ from every inner value.
-// The image sits at LDS address 0 (the step kernel has no static LDS, so its
-// dynamic LDS starts there) and is read by byte address.
-struct LdsView {
-  // dim_a, dim_c, dim_c + 1, b_lo and nb, each in both 16-bit halves
-  uint32_t da2, dc2, w2, blo2, nb2;
-};
-typedef __attribute__((address_space(3))) const uint16_t lds_c16;
-typedef uint32_t lds_v4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) const lds_v4 lds_c4;
-__device__ __forceinline__ uint16_t lds_u16(uint32_t addr) {
-  return *(lds_c16 *)(size_t)addr;
-}
-__device__ __forceinline__ uint4 lds_u4(uint32_t addr) {
-  const lds_v4 v = *(lds_c4 *)(size_t)addr;
-  return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
-// ---------------------------------------------------------------------------
-// Wave-level helpers
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t get16(const uint32_t (&w)[4], int e) {
-  return (e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu);
-}
-__device__ __forceinline__ void set16(uint32_t (&w)[4], int e, uint32_t v) {
-  if (e & 1) w[e >> 1] = (w[e >> 1] & 0xffffu) | (v << 16);
-  else w[e >> 1] = (w[e >> 1] & 0xffff0000u) | (v & 0xffffu);
-}
-// A slot's three arrays through one buffer resource: byte address =
-// voff (per lane) + soff (wave-uniform, a scalar register).  Offsets stay
-// 32-bit, and the per-lane part of a chunk's vector accesses is the same
-// 16 * lane for every window.
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-constexpr int kRsrcWord3 = 0x00020000;  // raw buffer, 32-bit data format (gfx9)
-// CP: the cache policy bits of the access (0, or kStreamingPolicy for
-// states that do not fit the caches: non-temporal, the lines are not
-// expected to be reused before they leave).
-constexpr int kStreamingPolicy = 2;  // nt
-// sc1: coherent across the device's L2s (data another block reads in the
-// same launch)
-constexpr int kDevicePolicy = 16;
-template <int CP = 0>
-__device__ __forceinline__ void bload4(Rsrc r, uint32_t voff, uint32_t soff, uint32_t (&v)[4]) {
-  const auto q = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, CP);
-  v[0] = q[0]; v[1] = q[1]; v[2] = q[2]; v[3] = q[3];
-}
-template <int CP = 0>
-__device__ __forceinline__ void bstore4(Rsrc r, uint32_t voff, uint32_t soff,
-                                        const uint32_t (&v)[4]) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  const u32x4 q = {v[0], v[1], v[2], v[3]};
-  __builtin_amdgcn_raw_buffer_store_b128(q, r, (int)voff, (int)soff, CP);
-}
-__device__ __forceinline__ uint32_t bload2(Rsrc r, uint32_t voff, uint32_t soff) {
-  return __builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
-}
-__device__ __forceinline__ void bstore2(Rsrc r, uint32_t voff, uint32_t soff, uint32_t v) {
-  __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v, r, (int)voff, (int)soff, 0);
-}
-__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 // Per-wave queue of draws the LDS image could not decide (or sites with
 // N > n_max); drained by all lanes at once.
 constexpr uint32_t kOverflow = kOverflowPerWave;
-
-// Exact outcome for a queued site: global row, or the literal loop.  It is
-// only reached from the drain, outside the unrolled per-site code, so the
-// hot loop stays small enough for the instruction cache.
-template <bool GAL>
-__device__ __forceinline__ uint32_t resolve_queued(const uint4 e, const StepParams &p,
-                                                const TableDev &tab, uint32_t t, uint32_t rid,
-                                                uint32_t *err) {
-  const uint32_t x = e.x, a = e.y & 0xffffu, b = e.y >> 16, c = e.z, r = e.w;
-  const uint32_t N = a + b + c;
-  if (N > 65535u) {  // a post-collision count might not fit: flagged, kept
-    atomicOr(err, kErrOverflow);
-    return b;
-  }
-  if (p.C == 0 || N < 2u) return b;  // no collision
-  if (N <= p.n_max) {
-    const uint32_t absJ = (uint32_t)abs((int32_t)c - (int32_t)a);
-    const uint32_t par = (N - absJ) & 1u;
-    return par + 2u * global_outcome(tab, N, absJ, b, par, r);
-  }
-  if (p.C < 0) {
-    atomicOr(err, kErrEqRange);
-    return b;
-  }
-  return collide_direct<GAL>(a, b, c, p, x, t, rid);
-}
 
 // Where a slot's three arrays are and how they are shifted at step t.
 struct SlotView {
@@ -308,67 +47,6 @@ struct SlotView {
   }
 };
 
-// Decision of one site from the LDS image, in three phases so that the LDS
-// reads of several sites are in flight together: (1) directory read, (2)
-// record read, (3) decision.  There is no branch and no range test per site:
-// the directory clamps min(a, c) to dim_a and max(a, c) to dim_c, whose row
-// and column lead to never records, and b - b_lo (mod 2^16) is clamped to nb,
-// every pair's never record.  A site outside the image (or of an absent
-// pair, or with N > n_max) thus reads a never record, a site with N < 2 a
-// record of move 0, and a site whose N does not fit 16 bits lies outside
-// (the image holds N < 3072 only).  A record holds (b >> 1) - k_s, a lower
-// bound L, inner values t2..t6 and an upper bound U (top 16 bits of seven
-// consecutive thresholds of the site's fiber row, L rounded up); with the
-// top half rh of the draw in [L, U) and equal to none of t2..t6 the drawn
-// state index is k_s + #{t2..t6 < rh}, and the move of Eq. (collcons) is
-// d = (b - b') / 2 = (b >> 1) - k_s - #{t2..t6 < rh}  (b' has b's parity).
-struct SiteLook {
-  uint4 q;
-};
-
-// Phase 1 of sites 2J and 2J + 1 with 16-bit packed arithmetic.
-template <int J>
-__device__ __forceinline__ void site_dir_pair(uint32_t &row0, uint32_t &row1, u16x2 &bis,
-                                              const uint32_t (&va)[4],
-                                              const uint32_t (&vb)[4], const uint32_t (&vc)[4],
-                                              const LdsView &lv) {
-  const u16x2 a = __builtin_bit_cast(u16x2, va[J]), b = __builtin_bit_cast(u16x2, vb[J]),
-              c = __builtin_bit_cast(u16x2, vc[J]);
-  const u16x2 lo = __builtin_elementwise_min(__builtin_elementwise_min(a, c),
-                                             __builtin_bit_cast(u16x2, lv.da2));
-  const u16x2 hi = __builtin_elementwise_min(__builtin_elementwise_max(a, c),
-                                             __builtin_bit_cast(u16x2, lv.dc2));
-  const uint32_t slot = __builtin_bit_cast(uint32_t, lo * __builtin_bit_cast(u16x2, lv.w2) + hi);
-  const uint32_t bi = __builtin_bit_cast(
-      uint32_t, __builtin_elementwise_min(b - __builtin_bit_cast(u16x2, lv.blo2),
-                                          __builtin_bit_cast(u16x2, lv.nb2)));
-  const uint32_t off = __builtin_bit_cast(uint32_t, slot + slot);  // byte offsets
-  row0 = lds_u16(off & 0xffffu);
-  row1 = lds_u16(off >> 16);
-  bis = __builtin_bit_cast(u16x2, bi);
-}
-
-// Phase 2 of sites 2J and 2J + 1: record indices add in 16-bit lanes.
-__device__ __forceinline__ void rec_pair(SiteLook &s0, SiteLook &s1, uint32_t row0, uint32_t row1,
-                                         u16x2 bis) {
-  const u16x2 rows = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(row1, row0, 0x05040100u));
-  const uint32_t idx = __builtin_bit_cast(uint32_t, rows + bis);
-  s0.q = lds_u4((idx & 0xffffu) << 4);
-  s1.q = lds_u4((idx >> 16) << 4);
-}
-
-// Phase 3: whether the record decides the draw, and d in the low 16 bits
-// (meaningless when it does not).
-__device__ __forceinline__ uint32_t site_finish(const SiteLook &s, uint32_t r, bool &hit) {
-  const uint4 q = s.q;
-  const uint32_t rh = r >> 16;
-  const uint32_t lb = q.x >> 16, t2 = q.y & 0xffffu, t3 = q.y >> 16, t4 = q.z & 0xffffu,
-                 t5 = q.z >> 16, t6 = q.w & 0xffffu, ub = q.w >> 16;
-  hit = (rh >= lb) & (rh < ub) & (rh != t2) & (rh != t3) & (rh != t4) & (rh != t5) & (rh != t6);
-  return q.x - (uint32_t)(t2 < rh) - (uint32_t)(t3 < rh) - (uint32_t)(t4 < rh) -
-         (uint32_t)(t5 < rh) - (uint32_t)(t6 < rh);
-}
-
 // The wave's queue of undecided draws: a virtual array of kQueue entries in
 // LDS followed by kOverflow entries in global memory, filled to F
 // (wave-uniform).  An entry is (x, a | b << 16, c, r) with the site's
@@ -378,19 +56,18 @@ __device__ __forceinline__ uint32_t site_finish(const SiteLook &s, uint32_t r, b
 // is instead the site's position in the chunk, 8 lane + K.
 static_assert(kDrainAt + 512 <= kQueue + kOverflow, "a chunk's draws must fit the queue");
 
-// Site K of every lane whose draw was not decided (and, in a chunk that
+// Site K of every lane in mk, whose draw was not decided (and, in a chunk that
 // passes the end of the lattice, that exists) goes to the queue, in lane
 // order.  wa, wb, wc are the words holding the site's pre-collision counts;
 // `slow` is wave-uniform.
 template <int K, bool PATCH>
-__device__ __forceinline__ void push_site(uint4 *queue, Rsrc over, uint32_t &F, bool hit,
+__device__ __forceinline__ void push_site(uint4 *queue, Rsrc over, uint32_t &F, uint64_t mk,
                                           bool slow, uint32_t x8, uint32_t L, uint32_t wa,
                                           uint32_t wb, uint32_t wc, uint32_t r, uint32_t xs) {
-  uint64_t mk = __ballot(!hit);
   if (mk == 0) return;
-  if (slow) mk &= __builtin_amdgcn_uicmpl(x8 + K, L, 36);  // lanes with x8 + K < L
+  if (slow) mk &= lanes_gt(L, x8 + K);
   const uint32_t n = (uint32_t)__popcll(mk);
-  if (!hit && (!slow || x8 + K < L)) {
+  if (__builtin_amdgcn_inverse_ballot_w64(mk)) {
     const uint32_t pos = F + lanes_below(mk);
     const uint32_t ab = (K & 1) ? __builtin_amdgcn_perm(wb, wa, 0x07060302u)
                                 : __builtin_amdgcn_perm(wb, wa, 0x05040100u);
@@ -411,21 +88,6 @@ __device__ __forceinline__ void push_site(uint4 *queue, Rsrc over, uint32_t &F, 
     }
   }
   F += n;
-}
-
-// Phase 3 of sites 2J and 2J + 1: d of both in one word (16-bit lanes) and
-// whether each was decided.
-__device__ __forceinline__ uint32_t finish_pair(const SiteLook &s0, const SiteLook &s1,
-                                                uint32_t r0, uint32_t r1, bool &h0, bool &h1) {
-  const uint32_t d0 = site_finish(s0, r0, h0), d1 = site_finish(s1, r1, h1);
-  return __builtin_amdgcn_perm(d1, d0, 0x05040100u);
-}
-// Sites 2J and 2J + 1 move by d: n_-1 and n_+1 gain d, n_0 loses 2d.
-__device__ __forceinline__ void apply_pair(uint32_t &a, uint32_t &b, uint32_t &c, uint32_t dp) {
-  const u16x2 d = __builtin_bit_cast(u16x2, dp);
-  a = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) + d);
-  c = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, c) + d);
-  b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, b) - (d + d));
 }
 
 // All eight sites of the lane: directory reads of all eight first, the
@@ -450,11 +112,11 @@ __device__ __forceinline__ void decide_eight(uint4 &w0, uint4 &w1, uint2 key,
   rec_pair(s2, s3, r2, r3, b23);
   rec_pair(s4, s5, r4, r5, b45);
   rec_pair(s6, s7, r6, r7, b67);
-  bool h0, h1, h2, h3, h4, h5, h6, h7;
-  const uint32_t d01 = finish_pair(s0, s1, w0.x, w0.y, h0, h1);
-  const uint32_t d23 = finish_pair(s2, s3, w0.z, w0.w, h2, h3);
-  const uint32_t d45 = finish_pair(s4, s5, w1.x, w1.y, h4, h5);
-  const uint32_t d67 = finish_pair(s6, s7, w1.z, w1.w, h6, h7);
+  uint64_t h0, h1, h2, h3, h4, h5, h6, h7;  // lanes whose site is undecided
+  const uint32_t d01 = finish_pair<false>(s0, s1, w0.x, w0.y, lv, h0, h1);
+  const uint32_t d23 = finish_pair<false>(s2, s3, w0.z, w0.w, lv, h2, h3);
+  const uint32_t d45 = finish_pair<false>(s4, s5, w1.x, w1.y, lv, h4, h5);
+  const uint32_t d67 = finish_pair<false>(s6, s7, w1.z, w1.w, lv, h6, h7);
   uint32_t na[4] = {va[0], va[1], va[2], va[3]}, nb[4] = {vb[0], vb[1], vb[2], vb[3]},
            nc[4] = {vc[0], vc[1], vc[2], vc[3]};
   apply_pair(na[0], nb[0], nc[0], d01);
@@ -488,9 +150,9 @@ __device__ __forceinline__ void queue_saturated(const uint32_t (&va)[4], const u
                       __builtin_elementwise_add_sat(__builtin_bit_cast(u16x2, va[J]),            \
                                                     __builtin_bit_cast(u16x2, vb[J])),           \
                       __builtin_bit_cast(u16x2, vc[J])));                                        \
-    push_site<2 * J, PATCH>(queue, over, F, (N2 & 0xffffu) != 0xffffu, slow, x8, L, va[J],      \
+    push_site<2 * J, PATCH>(queue, over, F, lanes_eq(N2 & 0xffffu, 0xffffu), slow, x8, L, va[J],      \
                             vb[J], vc[J], 0u, xs);                                               \
-    push_site<2 * J + 1, PATCH>(queue, over, F, (N2 >> 16) != 0xffffu, slow, x8, L, va[J],      \
+    push_site<2 * J + 1, PATCH>(queue, over, F, lanes_eq(N2 >> 16, 0xffffu), slow, x8, L, va[J],      \
                                 vb[J], vc[J], 0u, xs);                                           \
   }
   MCLG_SAT(0) MCLG_SAT(1) MCLG_SAT(2) MCLG_SAT(3)
@@ -534,13 +196,12 @@ __device__ __forceinline__ void drain_queue(const uint4 *queue, const uint4 *ove
 __device__ __forceinline__ uint32_t image_move(uint32_t a, uint32_t b, uint32_t c, uint32_t r,
                                                const LdsView &lv) {
   const uint32_t lo = min(min(a, c), lv.da2 & 0xffffu), hi = min(max(a, c), lv.dc2 & 0xffffu);
-  const uint32_t slot = (lo * (lv.w2 & 0xffffu) + hi) & 0xffffu;
-  const uint32_t row = lds_u16((2u * slot) & 0xffffu);
+  const uint32_t row = lds_u32((lo * (lv.w4 & 0xffffu) + 4u * hi) & 0xffffu);
   const uint32_t bi = min((b - (lv.blo2 & 0xffffu)) & 0xffffu, lv.nb2 & 0xffffu);
   SiteLook sl;
-  sl.q = lds_u4(((row + bi) & 0xffffu) << 4);
-  bool hit;
-  return site_finish(sl, r, hit) & 0xffffu;
+  sl.q = lds_u4(row + 16u * bi);
+  uint64_t miss;
+  return site_finish<false>(sl, r, lv, miss) & 0xffffu;
 }
 
 // Resolve the draws queued by the current chunk before its store
@@ -816,7 +477,7 @@ __global__ void __launch_bounds__(MAXT) k_step(StepLaunch a) {
   sv.xoff = 0;
   sv.lg = 1;
   LdsView lv;
-  lv.da2 = lv.dc2 = lv.w2 = lv.blo2 = lv.nb2 = 0;
+  lv = image_view(ImageDesc{});
 
   for (uint32_t i = cb;;) {
     TileDev t0;
@@ -886,11 +547,7 @@ __global__ void __launch_bounds__(MAXT) k_step(StepLaunch a) {
         for (uint32_t j = 1; j < 10; ++j)
           if (b0 + j * bd < n16) lds[b0 + j * bd] = v[j];
       }
-      lv.da2 = im.dim_a * 0x10001u;
-      lv.dc2 = im.dim_c * 0x10001u;
-      lv.w2 = (im.dim_c + 1u) * 0x10001u;
-      lv.blo2 = im.b_lo * 0x10001u;
-      lv.nb2 = im.nb * 0x10001u;
+      lv = image_view(im);
     }
     __syncthreads();  // the image and the counter are in place
     const uint32_t L = sv.L, tm = sv.tm, t = sv.t;  // of the segment's slot
@@ -992,35 +649,6 @@ __global__ void __launch_bounds__(MAXT) k_step(StepLaunch a) {
       a.tslot[s] += 1u;
     }
     if (threadIdx.x == 0) atomicExch(a.ticket, 0u);
-  }
-}
-
-// Eight consecutive elements pos .. pos + 7 (mod n) of the array at byte
-// offset `arr` of r: one 16-byte access unless they wrap around n.
-__device__ __forceinline__ void load8_wrap(Rsrc r, uint32_t arr, uint32_t pos, uint32_t n,
-                                           uint32_t (&v)[4]) {
-  if (pos + 8u <= n) {
-    bload4(r, 2u * pos, arr, v);
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    uint32_t q = pos + (uint32_t)e;
-    q -= q >= n ? n : 0u;
-    set16(v, e, bload2(r, 2u * q, arr));
-  }
-}
-__device__ __forceinline__ void store8_wrap(Rsrc r, uint32_t arr, uint32_t pos, uint32_t n,
-                                            const uint32_t (&v)[4]) {
-  if (pos + 8u <= n) {
-    bstore4(r, 2u * pos, arr, v);
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    uint32_t q = pos + (uint32_t)e;
-    q -= q >= n ? n : 0u;
-    bstore2(r, 2u * q, arr, get16(v, e));
   }
 }
 
@@ -1302,11 +930,7 @@ __global__ void __launch_bounds__(MAXT) k_step_tb(StepLaunch a, TbLaunch tb) {
     const uint4 *src = reinterpret_cast<const uint4 *>(a.image_pool + im.off);
     const uint32_t n16 = im.bytes / 16u, bd = blockDim.x;
     for (uint32_t b0 = threadIdx.x; b0 < n16; b0 += bd) lds[b0] = src[b0];
-    lv.da2 = im.dim_a * 0x10001u;
-    lv.dc2 = im.dim_c * 0x10001u;
-    lv.w2 = (im.dim_c + 1u) * 0x10001u;
-    lv.blo2 = im.b_lo * 0x10001u;
-    lv.nb2 = im.nb * 0x10001u;
+    lv = image_view(im);
   }
   // (2) every block has read the state (and its step counter) before any
   // writes it; the launch advances the counter itself
@@ -1465,11 +1089,7 @@ __global__ void __launch_bounds__(MAXT) k_step_tt(StepLaunch a, TbLaunch tb) {
     const uint4 *src = reinterpret_cast<const uint4 *>(a.image_pool + im.off);
     const uint32_t n16 = im.bytes / 16u, bd = blockDim.x;
     for (uint32_t b0 = threadIdx.x; b0 < n16; b0 += bd) lds[b0] = src[b0];
-    lv.da2 = im.dim_a * 0x10001u;
-    lv.dc2 = im.dim_c * 0x10001u;
-    lv.w2 = (im.dim_c + 1u) * 0x10001u;
-    lv.blo2 = im.b_lo * 0x10001u;
-    lv.nb2 = im.nb * 0x10001u;
+    lv = image_view(im);
   }
   // (2) every block's side areas are written and every block has read its
   // step counter before any block writes the state
@@ -1637,11 +1257,7 @@ __global__ void __launch_bounds__(MAXT) k_step_tr(StepLaunch a, TbLaunch tb) {
       const uint4 *src = reinterpret_cast<const uint4 *>(a.image_pool + im.off);
       const uint32_t n16 = im.bytes / 16u;
       for (uint32_t b0 = threadIdx.x; b0 < n16; b0 += blockDim.x) lds[b0] = src[b0];
-      lv.da2 = im.dim_a * 0x10001u;
-      lv.dc2 = im.dim_c * 0x10001u;
-      lv.w2 = (im.dim_c + 1u) * 0x10001u;
-      lv.blo2 = im.b_lo * 0x10001u;
-      lv.nb2 = im.nb * 0x10001u;
+      lv = image_view(im);
       loaded = im.off;
     }
     // (1) the replica at step t0 into the copy, in logical order; a group of

@@ -1,0 +1,182 @@
+#include "regplan.h"
+
+#include <algorithm>
+#include <cmath>
+#include <numeric>
+
+namespace mclg {
+
+namespace {
+constexpr uint64_t kMinPart = 256;  // sites of a part, at least (>= kMaxHalo)
+static_assert(kMinPart >= kMaxHalo, "a part holds the sites of both its strips' halves");
+}  // namespace
+
+UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks) {
+  UnitPlan P;
+  blocks = std::min(blocks, kPlanBlocks);
+  uint64_t total = 0;
+  for (uint32_t r = 0; r < n; ++r) total += L[r];
+  const uint64_t target = std::max<uint64_t>(kMinPart, (total + blocks - 1) / blocks);
+  std::vector<UnitDev> all;
+  for (uint32_t r = 0; r < n; ++r) {
+    // a lattice of up to 5/4 of a block's share stays whole
+    uint64_t parts = 4 * L[r] <= 5 * target ? 1 : (L[r] + target - 1) / target;
+    if (P.strips.size() + parts > kMaxStrips) parts = 1;
+    const uint64_t len = (((L[r] + parts - 1) / parts) + 7) / 8 * 8;
+    parts = (L[r] + len - 1) / len;
+    if (parts > 1 && L[r] - (parts - 1) * len < kMaxHalo) --parts;  // (the last part takes the rest)
+    const uint32_t s0 = (uint32_t)P.strips.size();
+    for (uint64_t j = 0; j < parts; ++j) {
+      UnitDev u;
+      u.slot = r;
+      u.x0 = (uint32_t)(j * len);
+      u.x1 = (uint32_t)(j + 1 < parts ? (j + 1) * len : L[r]);
+      if (parts > 1) {
+        u.split = 1;
+        u.el = s0 + (uint32_t)((j + parts - 1) % parts);
+        u.er = s0 + (uint32_t)j;
+        P.strips.push_back(StripDev{r, u.x1});
+      }
+      all.push_back(u);
+    }
+  }
+  // longest first to the block with the least (a unit's fixed cost counts as
+  // 2048 sites); a block's units keep the order of the lattices, so that
+  // units of one image follow each other
+  std::vector<uint32_t> order(all.size());
+  std::iota(order.begin(), order.end(), 0u);
+  auto work = [&](uint32_t i) { return (uint64_t)(all[i].x1 - all[i].x0) + 2048u; };
+  std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return work(x) > work(y); });
+  std::vector<std::pair<uint64_t, uint32_t>> heap;
+  for (uint32_t b = 0; b < blocks; ++b) heap.push_back({0, b});
+  auto more = [](const std::pair<uint64_t, uint32_t> &x, const std::pair<uint64_t, uint32_t> &y) { return x > y; };
+  std::make_heap(heap.begin(), heap.end(), more);
+  std::vector<std::vector<uint32_t>> lists(blocks);
+  for (uint32_t i : order) {
+    std::pop_heap(heap.begin(), heap.end(), more);
+    heap.back().first += work(i);
+    lists[heap.back().second].push_back(i);
+    std::push_heap(heap.begin(), heap.end(), more);
+  }
+  for (auto &l : lists) {
+    std::sort(l.begin(), l.end());
+    P.first.push_back((uint32_t)P.units.size());
+    for (uint32_t i : l) P.units.push_back(all[i]);
+  }
+  P.first.push_back((uint32_t)P.units.size());
+  return P;
+}
+
+namespace {
+// Times on MI355X (us), fitted to measured steps of lattices of 256 to 2^27
+// sites at rho = 50.  A wave that is alone on its SIMD takes 0.72 + 0.58 Q for
+// a step of its 256 Q sites (latency), and a SIMD with many of them 0.27 +
+// 0.28 Q for each (issue); `per_simd` waves in `turns` turns take a little
+// more than the larger of the two.
+double tile_step_us(uint32_t Q, double per_simd, double turns) {
+  const double issue = per_simd * (0.27 + 0.28 * Q), wait = turns * (0.72 + 0.58 * Q);
+  return std::sqrt(std::sqrt(issue * issue * issue * issue + wait * wait * wait * wait));
+}
+// A lattice in one block's registers: without the private areas and the
+// extra sites, but with a barrier per step when several waves hold it.
+double ring_step_us(uint32_t Q, uint32_t waves, bool together) {
+  const double issue = (waves + 3) / 4 * (0.27 + 0.28 * Q), wait = 0.55 + 0.5 * Q;
+  const double step = std::sqrt(std::sqrt(issue * issue * issue * issue + wait * wait * wait * wait));
+  return step + (together && waves > 1 ? 0.5 + 0.1 * Q : 0.0);
+}
+constexpr double kRingLaunch = 5.0;   // launch, image and the sites' way in and out
+constexpr double kTileLaunch = 9.0;   // the same for the tiles
+constexpr double kStripsLaunch = 2.5;
+constexpr double kUnit = 4.0;         // every further unit of a block: image and barriers
+}  // namespace
+
+std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t n, uint32_t blocks,
+                              bool one_image, bool galilean) {
+  std::vector<RegWay> ways;
+  blocks = std::min(blocks, kPlanBlocks);
+  uint64_t longest = 0, shortest = ~0ull, total = 0;
+  bool ragged = false;
+  for (uint32_t r = 0; r < n; ++r) {
+    longest = std::max(longest, L[r]);
+    shortest = std::min(shortest, L[r]);
+    total += L[r];
+    ragged |= L[r] % 8 != 0;
+  }
+  for (uint32_t Q : {1u, 2u, 4u, 6u}) {
+    if (galilean && Q > 2) continue;  // (its literal loop needs the registers)
+    const uint64_t hold = 256ull * Q;
+    if (longest <= 16 * hold) {
+      RegWay y;
+      y.kind = RegWay::kRing;
+      y.Q = Q;
+      y.most = 1u << 20;
+      // the lattices in the order of their sizes, one per block
+      double sum = 0, most = 0;
+      for (uint32_t r = 0; r < n; ++r) {
+        const double us = ring_step_us(Q, (uint32_t)((L[r] + hold - 1) / hold), true);
+        sum += us;
+        most = std::max(most, us);
+      }
+      const double rounds = std::max(1.0, (double)n / blocks);
+      y.launch_us = kRingLaunch * rounds;
+      y.step_us = std::max(most, n > blocks ? sum / blocks + 0.5 * most : 0.0);
+      ways.push_back(y);
+      if (one_image && n > blocks && longest <= hold) {
+        y.team = std::min<uint32_t>(16u, (n + blocks - 1) / blocks);
+        const double r2 = std::max(1.0, (double)n / ((double)y.team * blocks));
+        y.launch_us = kRingLaunch * r2;
+        y.step_us = std::ceil(r2) * ring_step_us(Q, y.team, false);
+        ways.push_back(y);
+      }
+    }
+    // (a tile with its extra sites is shorter than the lattice)
+    if (shortest < 512) continue;
+    for (uint32_t kh : {8u, 16u, 32u, 64u, 128u}) {
+      if (2 * kh >= hold) continue;
+      RegWay y;
+      y.kind = RegWay::kTile;
+      y.Q = Q;
+      y.kh = kh;
+      y.most = ragged ? kh - 8 : kh;
+      if (y.most == 0) continue;
+      const uint64_t tmax = hold - 2 * kh;
+      double worst = 0, images = 0;
+      for (size_t b = 0; b + 1 < plan.first.size(); ++b) {
+        double us = 0;
+        for (uint32_t i = plan.first[b]; i < plan.first[b + 1]; ++i) {
+          const uint64_t len = plan.units[i].x1 - plan.units[i].x0;
+          const uint64_t nt = ((len + tmax - 1) / tmax + 3) / 4;  // per SIMD
+          us += tile_step_us(Q, (double)nt, (double)((nt + 3) / 4));
+        }
+        worst = std::max(worst, us);
+        images = std::max(images, (double)(plan.first[b + 1] - plan.first[b]));
+      }
+      y.launch_us = kTileLaunch + (plan.strips.empty() ? 0.0 : kStripsLaunch) +
+                    std::max(0.0, images - 1.0) * kUnit +
+                    2.0e-6 * (double)std::min<uint64_t>(total, 1u << 25);
+      y.step_us = worst;
+      ways.push_back(y);
+    }
+  }
+  return ways;
+}
+
+const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, double single_us) {
+  const RegWay *best = nullptr;
+  double least = (double)steps * single_us;
+  for (const RegWay &w : ways) {
+    const double launches = w.kind == RegWay::kTile ? (double)((steps + w.most - 1) / w.most) : 1.0;
+    const double us = launches * w.launch_us + (double)steps * w.step_us;
+    if (us < least) {
+      least = us;
+      best = &w;
+    }
+  }
+  return best;
+}
+
+double single_step_us(uint64_t sites) {
+  return sites > (44ull << 20) ? 2.6e-6 * (double)sites : 8.0 + 2.0e-6 * (double)sites;
+}
+
+}  // namespace mclg

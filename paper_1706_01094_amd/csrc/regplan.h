@@ -1,0 +1,45 @@
+// How the steps of a context's lattices are laid out for the kernels that
+// hold sites in registers (host side): the parts each block takes, and which
+// kernel, how many sites per lane and how many steps per launch a call takes.
+#pragma once
+#include <cstdint>
+#include <vector>
+
+#include "device.h"
+
+namespace mclg {
+
+constexpr uint32_t kPlanBlocks = 256;      // blocks of a tile launch, at most
+constexpr uint32_t kMaxStrips = 4 * kPlanBlocks;
+inline uint64_t max_units(uint32_t n) { return (uint64_t)n + kMaxStrips; }
+
+// The units of the tile kernel: every lattice whole or in equal parts, dealt
+// to the blocks longest first.
+struct UnitPlan {
+  std::vector<UnitDev> units;
+  std::vector<uint32_t> first;   // blocks + 1
+  std::vector<StripDev> strips;
+};
+UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks);
+
+// One way to take steps: the kernel, its sites per lane (4 Q) and, for the
+// tiles, the sites on each side (steps per launch, at most).
+struct RegWay {
+  enum Kind : uint32_t { kNone = 0, kRing, kTile } kind = kNone;
+  uint32_t Q = 0, kh = 0, team = 0;
+  uint32_t most = 0;                  // steps per launch, at most
+  double launch_us = 0, step_us = 0;  // per launch and per step, estimated
+};
+
+// The ways open to a context, with their estimated times; one_image: all
+// lattices share one.
+std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t n, uint32_t blocks,
+                              bool one_image, bool galilean);
+
+// The quickest way for `steps` steps, or nullptr when one step per launch of
+// the kernels that keep the state in memory (single_us per step) is quicker.
+const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, double single_us);
+// Estimated time of one such step over `sites` sites.
+double single_step_us(uint64_t sites);
+
+}  // namespace mclg

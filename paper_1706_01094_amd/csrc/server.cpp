@@ -34,7 +34,7 @@ inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
 struct SrvLayout {
   uint64_t o_ctrl, o_slots, o_tslot, o_tiles, o_list, o_pdesc, o_pool, o_idesc, o_over, o_ipool,
-      o_rowbase, o_rowdesc, o_thr, o_fixed, o_row16, bytes, max_tiles;
+      o_rowdesc, o_thr, o_row16, bytes, max_tiles;
   // moments of retiring jobs: segments, runs, partial records, results
   uint64_t o_mseg, o_mrun, o_mslot, o_mpart, o_mout, max_mom_segs;
 };
@@ -67,10 +67,8 @@ SrvLayout srv_layout(const mclg_server_config *cfg, const CollisionTables *tab,
   l.o_idesc = take(sizeof(ImageDesc) * n);
   l.o_over = take(kOverflowBytes);
   l.o_ipool = take((uint64_t)kImage * n);
-  l.o_rowbase = take(sizeof(uint32_t) * tab->rowbase.size());
   l.o_rowdesc = take(sizeof(uint32_t) * tab->rowdesc.size());
   l.o_thr = take(sizeof(uint32_t) * (tab->thr.size() + 16));  // +16: see count_le_16
-  l.o_fixed = take(sizeof(uint32_t) * tab->fixed.size());
   l.o_row16 = take(sizeof(uint16_t) * tab->row16.size());
   l.bytes = o;
   return l;
@@ -112,7 +110,7 @@ struct mclg_server {
   // cached bytes stay alive while their upload is in flight.
   struct CachedImage {
     std::vector<uint8_t> blob;
-    uint32_t dir_bytes = 0, dim_a = 0, dim_c = 0, b_lo = 0, nb = 0;
+    uint32_t dir_bytes = 0, dim_a = 0, dim_c = 0, b_lo = 0, nb = 0, fixed = 0;
   };
   std::map<std::pair<double, double>, CachedImage> image_cache;
   uint32_t n_tiles = 0, n_active = 0;
@@ -127,11 +125,10 @@ struct mclg_server {
   uint32_t *d_list() { return reinterpret_cast<uint32_t *>(ws + lay.o_list); }
   TableDev table() {
     TableDev d;
-    d.rowbase = reinterpret_cast<const uint32_t *>(ws + lay.o_rowbase);
     d.rowdesc = reinterpret_cast<const uint2 *>(ws + lay.o_rowdesc);
     d.thr = reinterpret_cast<const uint32_t *>(ws + lay.o_thr);
-    d.fixed = tab->fixed.empty() ? nullptr : reinterpret_cast<const uint4 *>(ws + lay.o_fixed);
     d.row16 = tab->row16.empty() ? nullptr : reinterpret_cast<const uint4 *>(ws + lay.o_row16);
+    d.row_words = tab->max_q <= 24 ? 12u : 16u;
     return d;
   }
   int hip(hipError_t e) {
@@ -285,6 +282,7 @@ struct mclg_server {
         c.dim_c = im.dim_c;
         c.b_lo = im.b_lo;
         c.nb = im.nb;
+        c.fixed = im.fixed ? 1u : 0u;
         ci = image_cache.emplace(key, std::move(c)).first;
       }
       const CachedImage &img = ci->second;
@@ -296,6 +294,7 @@ struct mclg_server {
       idd.dim_c = img.dim_c;
       idd.b_lo = img.b_lo;
       idd.nb = img.nb;
+      idd.fixed = img.fixed;
       if (idd.bytes) {
         hipError_t e = hipMemcpyAsync(ws + lay.o_ipool + idd.off, img.blob.data(), img.blob.size(),
                                       hipMemcpyHostToDevice, s);
@@ -435,10 +434,8 @@ int mclg_server_create(const mclg_server_config *cfg, mclg_server **out) {
   const CollisionTables &t = *sv->tab;
   hipError_t e = sv->up(sv->ws + sv->lay.o_ctrl, ctrl.data(), 256);
   if (!e) e = sv->up(sv->d_tslot(), tz.data(), 4 * tz.size());
-  if (!e) e = sv->up(sv->ws + sv->lay.o_rowbase, t.rowbase.data(), 4 * t.rowbase.size());
   if (!e) e = sv->up(sv->ws + sv->lay.o_rowdesc, t.rowdesc.data(), 4 * t.rowdesc.size());
   if (!e) e = sv->up(sv->ws + sv->lay.o_thr, t.thr.data(), 4 * t.thr.size());
-  if (!e && !t.fixed.empty()) e = sv->up(sv->ws + sv->lay.o_fixed, t.fixed.data(), 4 * t.fixed.size());
   if (!e && !t.row16.empty()) e = sv->up(sv->ws + sv->lay.o_row16, t.row16.data(), 2 * t.row16.size());
   if (!e) e = hipStreamSynchronize(sv->s);
   if (e) return sv->hip(e);

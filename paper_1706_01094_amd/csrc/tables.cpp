@@ -24,7 +24,7 @@
 // and then lambda = p / 2^32 exactly (q = 2^32 in the weights above).
 #include "tables.h"
 
-#include "device.h"  // kFixedStride
+#include "device.h"  // collision_row, kRow16
 
 #include <algorithm>
 #include <atomic>
@@ -328,6 +328,11 @@ CompactLaw compact(uint32_t k_lo, const std::vector<uint64_t> &full) {
   return c;
 }
 
+// Record value of a threshold: its top 15 bits, and bit 15.
+static inline uint16_t rec15(uint64_t v) {
+  return (uint16_t)(0x8000u | std::min<uint64_t>(v >> 17, 0x7FFF));
+}
+
 std::shared_ptr<const CollisionTables> collision_tables(int32_t C, uint32_t lam_p,
                                                         uint32_t lam_q, uint32_t n_max,
                                                         bool galilean) {
@@ -354,14 +359,20 @@ std::shared_ptr<const CollisionTables> collision_tables(int32_t C, uint32_t lam_
       int N = next.fetch_sub(1);
       if (N < 0) break;
       Piece &pc = pieces[N];
+      pc.rows = collision_row((uint32_t)N + 1, (uint32_t)N + 1, 0) - collision_row((uint32_t)N, (uint32_t)N, 0);
+      pc.rowdesc_rel.resize(2 * (size_t)pc.rows);
       for (uint32_t absJ = 0; absJ <= (uint32_t)N && pc.ok; ++absJ) {
         Fiber f = fiber((uint32_t)N, absJ);
         uint32_t shared_off = 0, shared_q = 0, shared_first = 0;
+        const uint32_t par = ((uint32_t)N - absJ) & 1u;
         for (uint32_t k = 0; k < f.m; ++k) {
           bool ok = true;
+          const uint32_t n0 = par + 2 * k, a = ((uint32_t)N - n0 - absJ) / 2;
+          uint32_t *const desc = &pc.rowdesc_rel[2 * (size_t)(collision_row((uint32_t)N, n0, a) -
+                                                              collision_row((uint32_t)N, (uint32_t)N, 0))];
           if (N < 2 || C == 0) {
-            pc.rowdesc_rel.push_back((uint32_t)pc.thr.size());
-            pc.rowdesc_rel.push_back(k | (1u << 16));
+            desc[0] = (uint32_t)pc.thr.size();
+            desc[1] = k | (1u << 16);
             pc.max_q = std::max(pc.max_q, 1u);
             continue;
           }
@@ -374,8 +385,8 @@ std::shared_ptr<const CollisionTables> collision_tables(int32_t C, uint32_t lam_
               shared_q = (uint32_t)cl.thr.size() + 1;
               pc.thr.insert(pc.thr.end(), cl.thr.begin(), cl.thr.end());
             }
-            pc.rowdesc_rel.push_back(shared_off);
-            pc.rowdesc_rel.push_back(shared_first | (shared_q << 16));
+            desc[0] = shared_off;
+            desc[1] = shared_first | (shared_q << 16);
             pc.max_q = std::max(pc.max_q, shared_q);
           } else {
             ok = galilean ? row_finite(f, C, galilean_lambda_q(lam_p, lam_q, (uint32_t)N, absJ),
@@ -383,14 +394,13 @@ std::shared_ptr<const CollisionTables> collision_tables(int32_t C, uint32_t lam_
                           : row_finite(f, C, lam_p, lam_q, k, full, va, vb);
             CompactLaw cl = compact(0, full);
             uint32_t qn = (uint32_t)cl.thr.size() + 1;
-            pc.rowdesc_rel.push_back((uint32_t)pc.thr.size());
-            pc.rowdesc_rel.push_back(cl.k_first | (qn << 16));
+            desc[0] = (uint32_t)pc.thr.size();
+            desc[1] = cl.k_first | (qn << 16);
             pc.thr.insert(pc.thr.end(), cl.thr.begin(), cl.thr.end());
             pc.max_q = std::max(pc.max_q, qn);
           }
           if (!ok) { pc.ok = false; break; }
         }
-        pc.rows += f.m;
       }
     }
   };
@@ -405,7 +415,6 @@ std::shared_ptr<const CollisionTables> collision_tables(int32_t C, uint32_t lam_
   tab->lam_q = lam_q;
   tab->galilean = galilean;
   tab->n_max = n_max;
-  tab->rowbase.resize((size_t)(n_max + 1) * (n_max + 2) / 2);
   uint64_t rows = 0, thr_total = 0;
   for (uint32_t N = 0; N <= n_max; ++N) {
     if (!pieces[N].ok) return nullptr;
@@ -415,41 +424,24 @@ std::shared_ptr<const CollisionTables> collision_tables(int32_t C, uint32_t lam_
   if (thr_total >= (1ull << 32) || rows >= (1ull << 32)) return nullptr;
   tab->rowdesc.reserve(2 * rows);
   tab->thr.reserve(thr_total);
-  uint32_t row = 0;
   for (uint32_t N = 0; N <= n_max; ++N) {
     const Piece &pc = pieces[N];
     uint32_t thr_base = (uint32_t)tab->thr.size();
-    uint32_t r = 0;
-    for (uint32_t absJ = 0; absJ <= N; ++absJ) {
-      tab->rowbase[(size_t)N * (N + 1) / 2 + absJ] = row + r;
-      r += (N - absJ) / 2 + 1;
-    }
     for (size_t i = 0; i < pc.rowdesc_rel.size(); i += 2) {
       tab->rowdesc.push_back(pc.rowdesc_rel[i] + thr_base);
       tab->rowdesc.push_back(pc.rowdesc_rel[i + 1]);
     }
     tab->thr.insert(tab->thr.end(), pc.thr.begin(), pc.thr.end());
     tab->max_q = std::max(tab->max_q, pc.max_q);
-    row += pc.rows;
   }
   const size_t nrows = tab->rowdesc.size() / 2;
-  if (tab->max_q <= kFixedStride && (uint64_t)nrows * kFixedStride * 4 < (1ull << 31)) {
-    tab->fixed.assign(nrows * kFixedStride, 0u);
-    for (size_t r = 0; r < nrows; ++r) {
-      uint32_t *row = &tab->fixed[r * kFixedStride];
-      const uint32_t off = tab->rowdesc[2 * r], hdr = tab->rowdesc[2 * r + 1];
-      row[0] = hdr;
-      for (uint32_t j = 0; j + 1 < (hdr >> 16); ++j) row[1 + j] = tab->thr[off + j];
-    }
-  }
-  if (tab->max_q <= kRow16 - 1 && (uint64_t)nrows * kRow16 * 2 < (1ull << 31)) {
+  if (tab->max_q <= kRow16 && (uint64_t)nrows * kRow16 * 2 < (1ull << 31)) {
     tab->row16.assign(nrows * kRow16, (uint16_t)0xFFFF);
     for (size_t r = 0; r < nrows; ++r) {
       uint16_t *row = &tab->row16[r * kRow16];
       const uint32_t off = tab->rowdesc[2 * r], hdr = tab->rowdesc[2 * r + 1];
-      row[0] = (uint16_t)(hdr & 0xFFFFu);  // k_first
-      row[1] = (uint16_t)(hdr >> 16);      // q
-      for (uint32_t j = 0; j + 1 < (hdr >> 16); ++j) row[2 + j] = (uint16_t)(tab->thr[off + j] >> 16);
+      row[0] = (uint16_t)(0x8000u | (hdr & 0xFFFFu));  // k_first
+      for (uint32_t j = 0; j + 1 < (hdr >> 16); ++j) row[1 + j] = rec15(tab->thr[off + j]);
     }
   }
   std::shared_ptr<const CollisionTables> res = tab;
@@ -460,7 +452,7 @@ std::shared_ptr<const CollisionTables> collision_tables(int32_t C, uint32_t lam_
 
 std::vector<uint8_t> LdsImage::blob() const {
   std::vector<uint8_t> out(dir_bytes() + records.size() * 2, 0);
-  std::memcpy(out.data(), dir.data(), dir.size() * 2);
+  std::memcpy(out.data(), dir.data(), dir.size() * 4);
   std::memcpy(out.data() + dir_bytes(), records.data(), records.size() * 2);
   return out;
 }
@@ -481,12 +473,6 @@ inline uint64_t full_thr(const uint32_t *thr, uint32_t k_first, uint32_t q, long
   if (j >= (long)(k_first + q - 1)) return (uint64_t)1 << 32;
   return thr[j - k_first];
 }
-inline uint16_t top16(uint64_t v) { return (uint16_t)std::min<uint64_t>(v >> 16, 0xFFFF); }
-// ceil(v / 2^16), clamped to 0xFFFF (no draw reaches it: the upper bound is
-// at most 0xFFFF and strict)
-inline uint16_t top16_up(uint64_t v) {
-  return (uint16_t)std::min<uint64_t>((v + 0xFFFF) >> 16, 0xFFFF);
-}
 }  // namespace
 
 LdsImage build_image(const CollisionTables &tab, double rho, double u, uint32_t budget) {
@@ -494,7 +480,7 @@ LdsImage build_image(const CollisionTables &tab, double rho, double u, uint32_t 
   // directory of (dim_a + 1) x (dim_c + 1) entries, then (np + 1) rows of
   // nb + 1 records (the last row and the last record of every row: never)
   auto image_bytes = [](uint32_t da, uint32_t dc, uint32_t np, uint32_t nb) {
-    return (uint64_t)((da + 1) * (dc + 1) * 2 + 15) / 16 * 16 + (uint64_t)(np + 1) * (nb + 1) * 16;
+    return (uint64_t)((da + 1) * (dc + 1) * 4 + 15) / 16 * 16 + (uint64_t)(np + 1) * (nb + 1) * 16;
   };
   uint32_t dim_a = 0, dim_c = 0, best_lo = 0, best_nb = 1, best_np = 0;
   std::vector<double> pb;
@@ -524,7 +510,7 @@ LdsImage build_image(const CollisionTables &tab, double rho, double u, uint32_t 
     for (;;) {
       const uint32_t nb = hi - lo + 1;
       // directory size is bounded by the pairs' extent; reserve it generously
-      const long room = (long)budget - 2048 - 16 * (long)(nb + 1);
+      const long room = (long)budget - 4096 - 16 * (long)(nb + 1);
       const uint32_t np =
           room > 0 ? (uint32_t)std::min<size_t>(pairs.size(), room / (16 * (nb + 1))) : 0;
       if (np == 0) break;
@@ -544,12 +530,10 @@ LdsImage build_image(const CollisionTables &tab, double rho, double u, uint32_t 
     };
     extent(best_np);
     // shrink the pair count until directory + records fit the budget and
-    // every directory byte offset and record index (in 16-byte units from
-    // the image start) fits 16 bits
+    // every directory byte offset fits 16 bits
     auto fits = [&](uint32_t np) {
       const uint64_t bytes = image_bytes(dim_a, dim_c, np, best_nb);
-      return bytes <= budget && (uint64_t)(dim_a + 1) * (dim_c + 1) * 2 <= 0xFFFF &&
-             bytes / 16 <= 0xFFFF;
+      return bytes <= budget && (uint64_t)(dim_a + 1) * (dim_c + 1) * 4 <= 0xFFFF;
     };
     while (best_np > 0 && !fits(best_np)) extent(--best_np);
     if (best_np == 0) {
@@ -563,52 +547,57 @@ LdsImage build_image(const CollisionTables &tab, double rho, double u, uint32_t 
   im.dim_c = dim_c;
   im.b_lo = best_lo;
   im.nb = nb;
-  // directory entries are record indices in 16-byte units from the image
-  // start; absent pairs and the clamped row and column: the never row
-  const uint32_t rec0 = im.dir_bytes() / 16;
-  im.dir.assign((size_t)(dim_a + 1) * (dim_c + 1), (uint16_t)(rec0 + np * rs));
+  im.fixed = tab.C > 0 && tab.C <= 20;
+  // directory entries are byte offsets of a pair's first record from the
+  // image start; absent pairs and the clamped row and column: the never row
+  const uint32_t rec0 = im.dir_bytes();
+  im.dir.assign((size_t)(dim_a + 1) * (dim_c + 1), rec0 + 16u * np * rs);
   im.records.assign((size_t)(np + 1) * rs * 8, 0);
-  auto set_never = [&](size_t rec) {  // lower bound 0xFFFF, upper 0: no draw
+  auto set_never = [&](size_t rec) {  // every value 0: none is above a draw
     uint16_t *r = &im.records[rec * 8];
-    std::fill(r, r + 8, (uint16_t)0);
-    r[1] = 0xFFFF;
+    std::fill(r, r + 8, (uint16_t)0x8000);
   };
   for (size_t k = 0; k < (size_t)(np + 1) * rs; ++k) set_never(k);
+  // where T_0 .. T_7 stand in a record (the last: the first move, if not fixed)
+  static constexpr int kAt[8] = {0, 2, 3, 4, 5, 6, 7, 1};
   double covered = 0.0;
   for (uint32_t pi = 0; pi < np; ++pi) {
     const Pair &pr = pairs[pi];
-    im.dir[(size_t)pr.a * (dim_c + 1) + pr.c] = (uint16_t)(rec0 + pi * rs);
+    im.dir[(size_t)pr.a * (dim_c + 1) + pr.c] = rec0 + 16u * pi * rs;
     for (uint32_t bi = 0; bi < nb; ++bi) {
       const uint32_t b = best_lo + bi;
       uint16_t *rec = &im.records[((size_t)pi * rs + bi) * 8];
       const uint32_t N = pr.a + b + pr.c, absJ = pr.c - pr.a;
-      if (N < 2) {  // no collision: move 0 for every draw below 0xFFFF << 16
-        rec[0] = 0;
-        rec[1] = 0;
-        for (int j = 2; j < 8; ++j) rec[j] = 0xFFFF;
+      if (N < 2) {  // no collision: move 0 for (almost) every draw
+        for (int j = 0; j < 8; ++j)
+          rec[kAt[j]] = (uint16_t)(j < (im.fixed ? 4 : 1) ? 0x8000 : 0xFFFF);
+        if (!im.fixed) rec[kAt[7]] = 0;
         covered += pr.p * pb[b];
         continue;
       }
       if (N > tab.n_max) continue;  // never decided here
-      const uint32_t par = (N - absJ) & 1u;
       const uint32_t m = (N - absJ) / 2 + 1;
-      const uint32_t row = tab.rowbase[(size_t)N * (N + 1) / 2 + absJ] + (b - par) / 2;
+      const uint32_t row = collision_row(N, b, pr.a);
       const uint32_t off = tab.rowdesc[2 * (size_t)row];
       const uint32_t kf = tab.rowdesc[2 * (size_t)row + 1] & 0xFFFF;
       const uint32_t q = tab.rowdesc[2 * (size_t)row + 1] >> 16;
       const uint32_t *thr = tab.thr.data() + off;
-      // window start with the most mass
-      long best_ks = 0;
+      long best_ks = (long)(b >> 1) - 3;  // fixed: moves 3 .. -3
       uint64_t best_w = 0;
-      const long ks_hi = m > 6 ? (long)m - 6 : 0;
-      for (long ks = 0; ks <= ks_hi; ++ks) {
-        const uint64_t w = full_thr(thr, kf, q, ks + 5) - full_thr(thr, kf, q, ks - 1);
-        if (ks == 0 || w > best_w) { best_w = w; best_ks = ks; }
+      if (im.fixed) {
+        best_w = full_thr(thr, kf, q, best_ks + 6) - full_thr(thr, kf, q, best_ks - 1);
+      } else {
+        // window start with the most mass
+        const long ks_hi = m > 6 ? (long)m - 6 : 0;
+        for (long ks = 0; ks <= ks_hi; ++ks) {
+          const uint64_t w = full_thr(thr, kf, q, ks + 5) - full_thr(thr, kf, q, ks - 1);
+          if (ks == 0 || w > best_w) { best_w = w; best_ks = ks; }
+        }
+        // the move of the window's first state
+        rec[kAt[7]] = (uint16_t)(int16_t)((long)(b >> 1) - best_ks);
       }
-      // the kernel's move for the window's first state: (b >> 1) - k_s
-      rec[0] = (uint16_t)(int16_t)((long)(b >> 1) - best_ks);
-      rec[1] = top16_up(full_thr(thr, kf, q, best_ks - 1));
-      for (int j = 1; j < 7; ++j) rec[1 + j] = top16(full_thr(thr, kf, q, best_ks - 1 + j));
+      for (int j = 0; j < (im.fixed ? 8 : 7); ++j)
+        rec[kAt[j]] = rec15(full_thr(thr, kf, q, best_ks - 1 + j));
       covered += pr.p * pb[b] * (double)best_w / 4294967296.0;
     }
   }

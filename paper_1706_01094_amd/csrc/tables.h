@@ -12,27 +12,22 @@
 namespace mclg {
 
 // Device image of the collision tables (copied verbatim to the workspace).
-//   rowbase[N (N + 1) / 2 + |J|] = index of the fiber's first row
-//   rowdesc[rowbase + (n0 - par) / 2] = {thr offset, k_first | q << 16},
-//     par = (N - |J|) mod 2 (fiber states ascend in n0 = par + 2k)
+//   rowdesc[collision_row(N, n0, min(n_-1, n_+1))] = {thr offset,
+//     k_first | q << 16} (device.h states the order of the rows)
 //   thr[offset .. offset + q - 2] ascending uint32 thresholds
 // Sampling: n0' = ((N - |J|) & 1) + 2 (k_first + #{i : thr[offset + i] <= r}).
 struct CollisionTables {
   int32_t C = 0;
   uint32_t lam_p = 1, lam_q = 1, n_max = 0;
   bool galilean = false;          // per-fiber lambda of galilean_lambda_q
-  std::vector<uint32_t> rowbase;
   std::vector<uint32_t> rowdesc;  // pairs (offset, k_first | q << 16)
   std::vector<uint32_t> thr;
   uint32_t max_q = 0;             // largest number of outcomes in a row
-  // The same rows at a fixed stride of kFixedStride uint32 (when max_q allows):
-  // row r = {k_first | q << 16, thresholds..., zero padding}, so that a row
-  // is found from (N, |J|, n0) by arithmetic and read in one round of loads.
-  std::vector<uint32_t> fixed;    // empty when not built
-  // The same rows as 64 bytes of 16-bit values: k_first, q, the top 16 bits
-  // of the q - 1 thresholds, then 0xFFFF (when max_q <= 31).  A draw r whose
-  // top 16 bits equal none of them is decided by the row alone: a threshold
-  // with smaller top bits is <= r, one with larger top bits is > r.
+  // The same rows as 64 bytes of 16-bit values, each with bit 15 set: k_first,
+  // then the top 15 bits of the q - 1 thresholds, padded with 0x7FFF (when
+  // max_q <= 32).  A draw r whose top 15 bits equal none of them is decided by
+  // the row alone: a threshold with smaller top bits is <= r, one with larger
+  // top bits is > r.
   std::vector<uint16_t> row16;    // empty when not built
 };
 
@@ -69,31 +64,39 @@ bool poisson_full(double mu, uint32_t &k_lo, std::vector<uint64_t> &thr);
 // np + 1 rows of nb + 1: row p holds the pair's records for b = b_lo ..
 // b_lo + nb - 1, then one never record; row np is all never records.  `dir`
 // holds (dim_a + 1) x (dim_c + 1) entries: dir[a' (dim_c + 1) + c'] is the
-// index of the first record of an (a', c') pair (in 16-byte units from the
-// start of the image, whose directory comes first), that of row np for an
-// absent pair, and row dim_a and column dim_c are absent pairs, so that a
-// site's record is image16[dir[min(a', dim_a) (dim_c + 1) + min(c', dim_c)] +
-// min(b - b_lo mod 2^16, nb)] without a range test.  A record is eight
-// uint16: (b >> 1) - k_s as int16, then a lower bound L = ceil(thr_{k_s-1} /
-// 2^16), the top 16 bits of thr_{k_s} .. thr_{k_s+4} (inner values), and the
-// top 16 bits of thr_{k_s+5} as upper bound U (thr_{-1} = 0, thr_{>= m - 1} =
-// 2^32; all clamped to 0xFFFF).  With rh = r >> 16 the draw is decided in LDS
-// when L <= rh < U and no inner value equals rh; then the outcome index is
-// k_s + #{inner value < rh}, i.e. the site's n0 moves by -2 ((b >> 1) - k_s -
-// #{inner value < rh}).  Never records have L = 0xFFFF and U = 0 and decide
-// nothing: the exact global row decides.  A pair with N < 2 (no collision)
-// gets records (0, 0, 0xFFFF x 6): move 0 for every rh < 0xFFFF.  Without room
-// for any pair the image is a one-entry directory and two never records
+// byte offset of the first record of an (a', c') pair (from the start of the
+// image, whose directory comes first), that of row np for an absent pair, and
+// row dim_a and column dim_c are absent pairs, so that a site's record is at
+// dir[min(a', dim_a) (dim_c + 1) + min(c', dim_c)] + 16 min(b - b_lo mod
+// 2^16, nb) without a range test.
+//
+// A record is eight uint16, of which T_j stands at {0, 2, 3, 4, 5, 6, 7, 1}[j]:
+// T_j = 2^15 + the top 15 bits of thr_{k_s - 1 + j} (thr_{< 0} = 0, thr_{>=
+// m - 1} = 2^32 clamped).  With rh the top 15 bits of a draw the outcome is
+// state k_s + #{T_j - 2^15 < rh} - 1 when that number is at least 1 and at
+// most the window's length, and no T_j - 2^15 equals rh.
+//   fixed (0 < C <= 20): k_s = (b >> 1) - 3, all eight T_j: the window of the
+//     moves 3 .. -3 of n0 by -2.  At rho = 50, C = 10 it misses 0.11 % of the
+//     draws of its pairs, where six moves wherever they hold the most miss
+//     0.30 %: near equilibrium the law is centred on no move.
+//   else: k_s is the window of six moves with the most mass, T_7 holds
+//     (b >> 1) - k_s as int16.  With more sub-collisions the law leaves the
+//     incoming count (C = 30 at rho = 30: six moves 1.1 %, seven fixed ones
+//     1.4 %; C = infinity 1.7 % and 4.8 %).
+// Never records hold T_j = 2^15 only and decide nothing: the exact global row
+// decides.  A pair with N < 2 (no collision) gets records of move 0.  Without
+// room for any pair the image is a one-entry directory and two never records
 // (np = 0, nb = 1).
 struct LdsImage {
   uint32_t dim_a = 0, dim_c = 0, b_lo = 0, nb = 0;
-  std::vector<uint16_t> dir;      // (dim_a + 1) * (dim_c + 1)
+  bool fixed = false;
+  std::vector<uint32_t> dir;      // (dim_a + 1) * (dim_c + 1)
   std::vector<uint16_t> records;  // 8 per record
   double coverage = 0.0;          // expected fraction of site updates decided in LDS
   // serialised: dir padded to 16 bytes, then the records
   std::vector<uint8_t> blob() const;
   uint32_t dir_bytes() const {
-    return (uint32_t)(((dim_a + 1) * (dim_c + 1) * 2 + 15) / 16 * 16);
+    return (uint32_t)(((dim_a + 1) * (dim_c + 1) * 4 + 15) / 16 * 16);
   }
 };
 

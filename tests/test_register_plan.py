@@ -1,0 +1,64 @@
+"""How lattices are laid out for the kernels that hold sites in registers
+(host side, compiled here): every lattice is covered once, parts meet the
+kernels' limits, and the parts' strips join neighbours."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(__file__)), "paper_1706_01094_amd", "csrc")
+
+MAIN = r"""
+#include <cstdio>
+#include <random>
+#include "regplan.h"
+using namespace mclg;
+#define REQUIRE(x) if (!(x)) { std::printf("case %d: %s\n", c, #x); return 1; }
+int main() {
+  std::mt19937_64 g(7);
+  for (int c = 0; c < 400; ++c) {
+    const uint32_t n = c < 100 ? 1 : 1 + g() % (c % 3 ? 40 : 1500), blocks = c % 5 ? 256 : 1 + g() % 300;
+    std::vector<uint64_t> L(n);
+    for (auto &l : L) l = 1 + g() % (1ull << (1 + g() % (n == 1 ? 29 : 21)));
+    const UnitPlan P = plan_units(L.data(), n, blocks);
+    const uint32_t nb = blocks < kPlanBlocks ? blocks : kPlanBlocks;
+    REQUIRE(P.first.size() == nb + 1 && P.first[0] == 0 && P.first[nb] == P.units.size());
+    REQUIRE(P.units.size() <= max_units(n) && P.strips.size() <= kMaxStrips);
+    std::vector<uint64_t> seen(n, 0);
+    for (const UnitDev &u : P.units) {
+      REQUIRE(u.slot < n && u.x0 < u.x1 && u.x1 <= L[u.slot]);
+      REQUIRE(u.x0 % 8 == 0 && (u.x1 % 8 == 0 || u.x1 == L[u.slot]));
+      seen[u.slot] += u.x1 - u.x0;
+      if (!u.split) { REQUIRE(u.x0 == 0 && u.x1 == L[u.slot]); continue; }
+      REQUIRE(u.x1 - u.x0 >= kMaxHalo && u.el < P.strips.size() && u.er < P.strips.size());
+      REQUIRE(P.strips[u.er].slot == u.slot && P.strips[u.er].x == u.x1);
+      REQUIRE(P.strips[u.el].slot == u.slot && P.strips[u.el].x == (u.x0 ? u.x0 : L[u.slot]));
+    }
+    for (uint32_t r = 0; r < n; ++r) REQUIRE(seen[r] == L[r]);
+    for (const RegWay &w : plan_ways(P, L.data(), n, blocks, c % 2, c % 7 == 0)) {
+      REQUIRE(w.kind != RegWay::kNone && w.most >= 1 && w.step_us > 0 && w.launch_us > 0);
+      uint64_t longest = 0, shortest = ~0ull;
+      bool ragged = false;
+      for (uint64_t l : L) { longest = l > longest ? l : longest; shortest = l < shortest ? l : shortest; ragged |= l % 8 != 0; }
+      if (w.kind == RegWay::kRing) {
+        REQUIRE(longest <= 4096ull * w.Q && (w.team == 0 || (longest <= 256ull * w.Q && w.team <= 16)));
+      } else {
+        // a tile's positions fit a wave and, with its extra sites, the lattice
+        REQUIRE(2 * w.kh < 256 * w.Q && w.kh <= kMaxHalo && w.kh % 8 == 0);
+        REQUIRE(w.most + (ragged ? 8 : 0) <= w.kh && shortest >= 512);
+      }
+    }
+  }
+  std::puts("ok");
+}
+"""
+
+
+def test_units_and_ways(tmp_path):
+    src = tmp_path / "main.cpp"
+    src.write_text(MAIN)
+    exe = tmp_path / "main"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC,
+                    "-o", str(exe), str(src), os.path.join(CSRC, "regplan.cpp")], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout
