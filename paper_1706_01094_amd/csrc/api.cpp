@@ -147,11 +147,7 @@ struct mclg_ctx {
   std::vector<uint8_t> img_pool;
   uint32_t lds_bytes = 0, max_blocks = 1, lds_limit = 64 * 1024, n_cu = 1;
   uint32_t grid_limit = 0;  // 0: occupancy-derived grid
-  // several steps per launch (mclg_set_blocked): geometry, grid, caller's
-  // scratch; tb.steps <= 1 means one step per launch
-  TbLaunch tb;
-  uint32_t tb_grid = 0;
-  uint32_t tb_arrivals = 0;  // blocks of every blocked launch so far (the barrier's count)
+  bool blocked = false;     // mclg_set_blocked: several steps per launch asked for
   uint32_t drain_policy = MCLG_DRAIN_AUTO;
   // the device address of this device's static scratch area (moments.hip),
   // looked up in mclg_init with the context's device current
@@ -164,18 +160,6 @@ struct mclg_ctx {
 
   uint32_t *err() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl); }
   uint32_t *ticket() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl) + 1; }
-  uint32_t *barrier() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl) + 2; }
-  // One launch of tb.steps steps (temporal blocking) at step t + t_pending.
-  hipError_t launch_blocked(TbLaunch b) {
-    b.bar = barrier();
-    b.bar_target = tb_arrivals + tb_grid;
-    hipError_t e = launch_step_blocked(sch, stream,
-                                       launch_args(0, (uint32_t)tiles.size(), 0, n, t_pending), b,
-                                       tb_grid);
-    // (the replicas' kernel has no barrier)
-    if (!e && !b.reps) tb_arrivals += b.n_logs ? 2u * tb_grid : tb_grid;
-    return e;
-  }
   SlotDev *slots() { return reinterpret_cast<SlotDev *>(ws + lay.o_slots); }
   uint32_t *tslot() { return reinterpret_cast<uint32_t *>(ws + lay.o_tslot); }
   hipError_t flush_t() {
@@ -186,21 +170,27 @@ struct mclg_ctx {
   }
   // The launch choices mclg_set_schedule, mclg_set_drain and
   // mclg_set_grid_limit make belong to the kernels that keep the state in
-  // memory: with any of them set, those kernels run.
-  bool default_launch() const {
+  // memory: with any of them set, those kernels run, unless several steps per
+  // launch were asked for as well.
+  bool reg_launch() const {
     return sch.threads == 1024 && sch.lds_budget == Schedule().lds_budget &&
-           drain_policy == MCLG_DRAIN_AUTO && grid_limit == 0;
+           (blocked || (drain_policy == MCLG_DRAIN_AUTO && grid_limit == 0));
   }
-  // `steps` steps of every replica in one launch of way `w`.
-  hipError_t launch_reg(const RegWay &w, uint32_t steps) {
+  // `steps` steps of every replica in one launch of way `w`, with the logs
+  // lg.first, ... of them.
+  hipError_t launch_reg(const RegWay &w, uint32_t steps, const RegLog &lg) {
     const StepLaunch a = launch_args(0, (uint32_t)tiles.size(), 0, n, t_pending);
+    const uint32_t *order = reinterpret_cast<const uint32_t *>(ws + lay.o_list);
+    RingLaunch r;
+    r.steps = steps;
     if (w.kind == RegWay::kRing) {
-      RingLaunch r;
-      r.order = reinterpret_cast<const uint32_t *>(ws + lay.o_list);
+      r.order = order;
       r.n = n;
       r.team = w.team;
-      r.steps = steps;
-      return launch_ring(stream, a, r, w.Q, 16);
+      r.log = lg;
+      r.log.stride = log_records(w);
+      r.log.hold = w.team ? 0u : 256u * w.Q;
+      return launch_ring(stream, a, r, w.Q, kRegWaves);
     }
     TileLaunch tl;
     tl.units = reinterpret_cast<const UnitDev *>(ws + lay.o_units);
@@ -210,26 +200,58 @@ struct mclg_ctx {
     tl.n_strips = (uint32_t)units.strips.size();
     tl.kh = w.kh;
     tl.steps = steps;
-    return launch_tiles(stream, a, tl, w.Q, 16, (uint32_t)units.first.size() - 1);
-  }
-  // n_steps steps of every replica by the quickest way, if there is one.
-  hipError_t step_reg(uint64_t n_steps, bool &done) {
-    done = false;
-    if (!default_launch() || ways.empty()) return hipSuccess;
-    const RegWay *w = pick_way(ways, n_steps, single_step_us(lay.total_sites));
-    if (!w) return hipSuccess;
-    const uint64_t most = w->most;
-    for (uint64_t launches = (n_steps + most - 1) / most; launches; --launches) {
-      const uint32_t k = (uint32_t)((n_steps + launches - 1) / launches);
-      hipError_t e = t_pending >= (1u << 30) ? flush_t() : hipSuccess;
-      if (!e) e = launch_reg(*w, k);
-      if (e) return e;
-      t_pending += k;
-      for (auto &x : t) x += k;
-      n_steps -= k;
+    tl.log = lg;
+    tl.log.stride = log_records(w);
+    hipError_t e = launch_tiles(stream, a, tl, w.Q, kRegWaves, (uint32_t)units.first.size() - 1, order);
+    if (!e && units.n_long < n) {  // the lattices too short for tiles, last in the order
+      r.order = order + units.n_long;
+      r.n = n - units.n_long;
+      e = launch_ring(stream, a, r, 2, kRegWaves);
     }
-    done = true;
+    return e;
+  }
+  // Records per log and lattice, and the logs a launch has room for (the
+  // second half of the overflow region; the tiles' private areas use the
+  // first).
+  uint32_t log_records(const RegWay &w) const {
+    return w.kind == RegWay::kTile ? ((uint32_t)units.first.size() - 1u) * kRegWaves
+           : w.team                ? 1u
+                                   : kRegWaves;
+  }
+  static_assert((uint64_t)kPlanBlocks * kRegWaves * kOverflowPerWave * 16 <= kOverflowBytes / 2,
+                "the private areas stay in the first half");
+  uint64_t log_room(const RegWay &w) const {
+    return kOverflowBytes / 2 / (sizeof(uint64_t) * kMom3Rec * n * log_records(w));
+  }
+  // `total` steps of every replica by way `w`; with every > 0 also the logs
+  // after steps every, 2 every, ..., into out.
+  hipError_t step_way(const RegWay &w, uint64_t total, uint64_t every, RegLog lg, long long *out) {
+    const uint64_t room = every ? log_room(w) : 0;
+    for (uint64_t done = 0; done < total;) {
+      const uint64_t left = total - done, launches = (left + w.most - 1) / w.most;
+      uint64_t k = (left + launches - 1) / launches;
+      if (every) {
+        const uint64_t first = every - done % every;  // the next log
+        k = std::min(k, first + (room - 1) * every);
+        lg.n = k >= first ? (uint32_t)((k - first) / every + 1) : 0u;
+        lg.first = (uint32_t)first;
+        lg.every = (uint32_t)std::min<uint64_t>(every, w.most);  // (one log when it is less)
+        lg.records = reinterpret_cast<unsigned long long *>(ws + lay.o_over + kOverflowBytes / 2);
+        lg.out = out + ((done + first) / every - 1) * n * kMom3Out;
+        if (!lg.n) lg.first = 0;
+      }
+      hipError_t e = t_pending >= (1u << 30) ? flush_t() : hipSuccess;
+      if (!e) e = launch_reg(w, (uint32_t)k, lg);
+      if (e) return e;
+      t_pending += (uint32_t)k;
+      for (auto &x : t) x += (int64_t)k;
+      done += k;
+    }
     return hipSuccess;
+  }
+  // The way for `steps` steps, or nullptr for one step per launch.
+  const RegWay *way(uint64_t steps, bool logs) const {
+    return reg_launch() ? pick_way(ways, steps, logs, single_step_us(lay.total_sites)) : nullptr;
   }
   TileDev *tiles_dev() { return reinterpret_cast<TileDev *>(ws + lay.o_tiles); }
   // The moment kernels' arguments; partial records and results go to
@@ -386,10 +408,8 @@ struct mclg_ctx {
     if (!e) e = hipStreamSynchronize(stream);
     if (!e) e = step_occupancy(sch, lds_bytes, n_cu, max_blocks);
     if (!e) e = reg_setup(lds_bytes);
-    ways.clear();
-    // (their kernels take images of fixed records only)
-    if (!e && default_launch() && (C == 0 || ims[0].fixed))
-      ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0);
+    ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0,
+                     images_fixed(C));
     return e;
   }
   void drop_graphs() {
@@ -581,7 +601,7 @@ int mclg_init(const mclg_config *cfg, const mclg_init_spec *init, mclg_ctx **out
   e = hipMemcpy(&err, c->err(), sizeof(err), hipMemcpyDeviceToHost);
   if (e) return c->hip(e);
   *out = c.release();
-  return (err & 4u) ? MCLG_E_INTERNAL : err ? MCLG_E_RANGE : MCLG_OK;
+  return err ? MCLG_E_RANGE : MCLG_OK;
 }
 
 // One step of the slots [slot_first, slot_first + n_slots) (their tiles are
@@ -593,77 +613,45 @@ static int step_range(mclg_ctx *c, uint32_t tile_lo, uint32_t tile_hi, uint32_t 
   return c->hip(e);
 }
 
-// The geometry of `steps` steps per launch for the context's one lattice:
-// every block of the grid resident at once, R owned sites per block (a
-// multiple of 8), kh = steps rounded up to 8 extra sites on each side.
-// Whole regions: each block's copy holds its R + 2 kh sites; tiles: copies
-// of `tile` sites, T = tile - 2 kh of them the tile's own (tile = 0 picks
-// whole regions while all copies fit kTbCachedCopies bytes, else tiles of
-// kTbTileSites).  The scratch holds the blocks' areas, then the partial
-// records of up to `steps` logs per launch (records_at bytes in).
+// The scratch mclg_set_blocked asks for, and the calls it refuses.  The
+// kernels hold the sites in registers and need no scratch; its size stays
+// what programs lay out for: copies of the blocks' ranges (or tiles, or of the
+// largest replica) with `steps` sites, rounded up to 8, on each side.
 constexpr uint64_t kTbCachedCopies = 128ull << 20;
-constexpr uint32_t kTbTileSites = 65536;  // 128 chunks of 512: 100 MB of copies in all
-static int blocked_geometry(mclg_ctx *c, uint32_t steps, uint32_t tile, TbLaunch &tb,
-                            uint32_t &grid, uint64_t &bytes, uint64_t &records_at) {
+constexpr uint32_t kTbTileSites = 65536;
+constexpr uint32_t kTbMaxSteps = 256;
+static int blocked_bytes(const mclg_ctx *c, uint32_t steps, uint32_t tile, uint64_t &bytes) {
   if (c->d2) return MCLG_E_UNSUPPORTED;
   if (steps < 2 || steps > kTbMaxSteps) return MCLG_E_INVAL;
   if (c->sch.threads != 1024) return MCLG_E_UNSUPPORTED;
-  uint32_t g = 0;
-  hipError_t e = step_blocked_occupancy(c->sch, c->lds_bytes, c->n_cu, g);
-  if (e) return c->hip(e);
-  g = std::min(g, kOverflowWaves / (c->sch.threads / 64u));  // waves with an overflow area
+  const uint64_t g = std::min(c->max_blocks, kOverflowWaves / (c->sch.threads / 64u));
   if (c->n > 1) {
-    // replicas: each block copies whole replicas, so its copy area holds
-    // the largest; then the blocks' replica lists (records_at: where)
     if (tile > 1) return MCLG_E_INVAL;
-    const uint64_t maxL = *std::max_element(c->L.begin(), c->L.end());
-    TbLaunch t;
-    t.steps = steps;
-    t.reps = 1;
-    t.stride = (uint32_t)align_up(maxL + 8u, 64);
-    t.bstride = 3ull * t.stride;
-    if (6ull * t.stride >= (1ull << 31)) return MCLG_E_UNSUPPORTED;
-    tb = t;
-    grid = g;
-    records_at = align_up((uint64_t)g * t.bstride * sizeof(uint16_t), 256);
-    bytes = records_at + sizeof(uint32_t) * ((uint64_t)c->n + g + 1u);
+    const uint64_t stride = align_up(*std::max_element(c->L.begin(), c->L.end()) + 8u, 64);
+    if (6 * stride >= (1ull << 31)) return MCLG_E_UNSUPPORTED;
+    bytes = align_up(g * 3 * stride * sizeof(uint16_t), 256) + sizeof(uint32_t) * ((uint64_t)c->n + g + 1u);
     return MCLG_OK;
   }
-  if (c->L[0] % 8 != 0) return MCLG_E_UNSUPPORTED;
   const uint64_t L = c->L[0];
-  TbLaunch t;
-  t.R = (uint32_t)(((L + g - 1) / g + 7) / 8 * 8);
-  t.kh = (steps + 7u) / 8u * 8u;
-  t.steps = steps;
-  if (tile == 0)
-    tile = (uint64_t)g * (t.R + 2u * t.kh) * 6u > kTbCachedCopies ? kTbTileSites : 1u;
-  if (tile == 1) {
-    t.es = t.R + 2u * t.kh;
-    t.stride = (t.es + 63u) / 64u * 64u;
-    t.bstride = 3ull * t.stride;
-  } else {
-    if (tile % 8u != 0 || tile <= 2u * t.kh || tile > (1u << 20)) return MCLG_E_INVAL;
-    t.T = tile - 2u * t.kh;
-    t.es = tile;
-    t.stride = (t.es + 63u) / 64u * 64u;
-    t.bstride = align_up(3ull * t.stride + 18ull * t.kh, 128);
-    if (2ull * t.bstride * g >= (1ull << 31)) return MCLG_E_UNSUPPORTED;
+  if (L % 8 != 0) return MCLG_E_UNSUPPORTED;
+  const uint64_t R = ((L + g - 1) / g + 7) / 8 * 8, kh = (steps + 7u) / 8u * 8u;
+  if (tile == 0) tile = g * (R + 2u * kh) * 6u > kTbCachedCopies ? kTbTileSites : 1u;
+  uint64_t es = R + 2u * kh, stride = align_up(es, 64), area = 3 * stride;
+  if (tile != 1) {
+    if (tile % 8u != 0 || tile <= 2u * kh || tile > (1u << 20)) return MCLG_E_INVAL;
+    es = tile;
+    stride = align_up(es, 64);
+    area = align_up(3 * stride + 18 * kh, 128);
+    if (2 * area * g >= (1ull << 31)) return MCLG_E_UNSUPPORTED;
   }
-  // the copy's random-number keys wrap around the lattice at most once
-  if ((uint64_t)t.es + 512u > L) return MCLG_E_UNSUPPORTED;
-  tb = t;
-  grid = g;
-  records_at = align_up((uint64_t)g * t.bstride * sizeof(uint16_t), 256);
-  bytes = records_at + (uint64_t)steps * g * kMom3Rec * sizeof(uint64_t);
+  if (es + 512u > L) return MCLG_E_UNSUPPORTED;
+  bytes = align_up(g * area * sizeof(uint16_t), 256) + steps * g * kMom3Rec * sizeof(uint64_t);
   return MCLG_OK;
 }
 
 int mclg_blocked_bytes(mclg_ctx *c, uint32_t steps, uint32_t tile, uint64_t *scratch_bytes) {
   if (!c || !scratch_bytes) return MCLG_E_INVAL;
-  TbLaunch tb;
-  uint32_t grid = 0;
-  uint64_t records_at = 0;
-  return blocked_geometry(c, steps, tile, tb, grid, *scratch_bytes, records_at);
+  return blocked_bytes(c, steps, tile, *scratch_bytes);
 }
 
 int mclg_set_blocked(mclg_ctx *c, uint32_t steps, uint32_t tile, void *scratch,
@@ -671,84 +659,22 @@ int mclg_set_blocked(mclg_ctx *c, uint32_t steps, uint32_t tile, void *scratch,
   if (!c) return MCLG_E_INVAL;
   if (c->d2) return MCLG_E_UNSUPPORTED;
   if (steps <= 1) {
-    c->tb = TbLaunch{};
-    c->tb_grid = 0;
+    c->blocked = false;
     return MCLG_OK;
   }
-  TbLaunch tb;
-  uint32_t grid = 0;
-  uint64_t need = 0, records_at = 0;
-  int rc = blocked_geometry(c, steps, tile, tb, grid, need, records_at);
+  uint64_t need = 0;
+  const int rc = blocked_bytes(c, steps, tile, need);
   if (rc) return rc;
   if (!scratch || scratch_bytes < need) return MCLG_E_INVAL;
-  tb.scratch = static_cast<uint16_t *>(scratch);
-  if (tb.reps) {
-    // each block's replicas: the longest-work-first greedy assignment, with a
-    // replica's work per step taken as its chunks of 512 sites plus 10 (a
-    // step's fixed cost, about ten chunks')
-    std::vector<uint32_t> order(c->n);
-    for (uint32_t r = 0; r < c->n; ++r) order[r] = r;
-    auto work = [&](uint32_t r) { return (c->L[r] + 511u) / 512u + 10u; };
-    std::stable_sort(order.begin(), order.end(),
-                     [&](uint32_t x, uint32_t y) { return work(x) > work(y); });
-    std::vector<std::vector<uint32_t>> lists(grid);
-    std::vector<std::pair<uint64_t, uint32_t>> heap;  // (work, block), min-heap
-    for (uint32_t b = 0; b < grid; ++b) heap.push_back({0, b});
-    auto cmp = [](const std::pair<uint64_t, uint32_t> &x, const std::pair<uint64_t, uint32_t> &y) {
-      return x > y;
-    };
-    std::make_heap(heap.begin(), heap.end(), cmp);
-    for (uint32_t r : order) {
-      std::pop_heap(heap.begin(), heap.end(), cmp);
-      heap.back().first += work(r);
-      lists[heap.back().second].push_back(r);
-      std::push_heap(heap.begin(), heap.end(), cmp);
-    }
-    std::vector<uint32_t> first(grid + 1u, 0), items;
-    for (uint32_t b = 0; b < grid; ++b) {
-      first[b] = (uint32_t)items.size();
-      items.insert(items.end(), lists[b].begin(), lists[b].end());
-    }
-    first[grid] = (uint32_t)items.size();
-    uint32_t *lst = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(scratch) + records_at);
-    hipError_t e = hipMemcpyAsync(lst, items.data(), sizeof(uint32_t) * items.size(),
-                                  hipMemcpyHostToDevice, c->stream);
-    if (!e) e = hipMemcpyAsync(lst + items.size(), first.data(), sizeof(uint32_t) * first.size(),
-                               hipMemcpyHostToDevice, c->stream);
-    if (!e) e = hipStreamSynchronize(c->stream);
-    if (e) return c->hip(e);
-    tb.items = lst;
-    tb.item_first = lst + items.size();
-  } else {
-    tb.records =
-        reinterpret_cast<unsigned long long *>(static_cast<uint8_t *>(scratch) + records_at);
-  }
-  c->tb = tb;
-  c->tb_grid = grid;
+  c->blocked = true;
   return MCLG_OK;
 }
 
 int mclg_step(mclg_ctx *c, uint64_t n_steps) {
   if (!c) return MCLG_E_INVAL;
   if (c->d2) return d2q9_step(*c->d2, n_steps);
-  if (c->tb.steps <= 1) {
-    bool done = false;
-    hipError_t e = c->step_reg(n_steps, done);
-    if (e || done) return c->hip(e);
-  }
-  // whole blocks of tb.steps steps first
-  const uint32_t K = c->tb.steps;
-  if (K > 1) {
-    for (; n_steps >= K; n_steps -= K) {
-      if (c->t_pending >= (1u << 30)) {
-        hipError_t e = c->flush_t();
-        if (e) return c->hip(e);
-      }
-      hipError_t e = c->launch_blocked(c->tb);
-      if (e) return c->hip(e);
-      for (auto &t : c->t) t += K;  // (the launch advances the device counters itself)
-    }
-  }
+  if (const RegWay *w = c->way(n_steps, false))
+    return c->hip(c->step_way(*w, n_steps, 0, RegLog(), nullptr));
   for (uint64_t i = 0; i < n_steps; ++i) {
     if (c->t_pending >= (1u << 30)) {
       hipError_t e = c->flush_t();
@@ -816,7 +742,7 @@ static int read_err(mclg_ctx *c) {
   hipError_t e = hipMemcpyAsync(&err, c->err(), sizeof(err), hipMemcpyDeviceToHost, c->stream);
   if (!e) e = hipStreamSynchronize(c->stream);
   if (e) return c->hip(e);
-  return (err & 4u) ? MCLG_E_INTERNAL : err ? MCLG_E_RANGE : MCLG_OK;
+  return err ? MCLG_E_RANGE : MCLG_OK;
 }
 
 int mclg_check(mclg_ctx *c) {
@@ -878,51 +804,29 @@ int mclg_step_log(mclg_ctx *c, uint64_t every, uint64_t n_logs, const int32_t *t
       (flags & ~(uint32_t)MCLG_MOMENTS_DIGEST) || n_logs > (1ull << 62) / every)
     return MCLG_E_INVAL;
   const uint32_t dig = (flags & MCLG_MOMENTS_DIGEST) ? 1u : 0u;
-  const uint32_t K = c->tb.steps;
-  if (!(K > 1 && c->tb.T == 0 && !c->tb.reps && n_modes <= 2 && !(n_modes == 2 && dig))) {
-    // steps, then the moment kernels, per log (partial sums in the workspace)
-    unsigned long long *part = reinterpret_cast<unsigned long long *>(c->ws + c->lay.o_mpart);
-    for (uint64_t j = 0; j < n_logs; ++j) {
-      int rc = mclg_step(c, every);
-      if (rc) return rc;
-      MomArgs m = c->mom_args(part, reinterpret_cast<long long *>(dev_out + j * c->n));
-      m.twiddle = twiddle;
-      m.n_modes = n_modes;
-      m.digest = dig;
-      hipError_t e = c->flush_t();
-      if (!e) e = launch_moments3(c->stream, m);
-      if (e) return c->hip(e);
-    }
-    return MCLG_OK;
-  }
-  // launches of K steps (the last one shorter); each sums the logs that fall
-  // in it, at steps every, 2 every, ... of the call.  With the digest or the
-  // Galilean acceptance a launch also ends at each log (the kernel sums those
-  // only as it writes the sites back).
-  const bool at_end_only = dig || (c->flags & MCLG_FLAG_GALILEAN);
   const uint64_t total = every * n_logs;
-  for (uint64_t c0 = 0; c0 < total;) {
-    if (c->t_pending >= (1u << 30)) {
-      hipError_t e = c->flush_t();
-      if (e) return c->hip(e);
-    }
-    const uint64_t o1 = every - c0 % every;  // the first log after c0, relative
-    const uint32_t S =
-        (uint32_t)std::min<uint64_t>(std::min<uint64_t>(K, total - c0), at_end_only ? o1 : K);
-    TbLaunch b = c->tb;
-    b.steps = S;
-    if (o1 <= S) {
-      b.n_logs = (uint32_t)((S - o1) / every + 1u);
-      b.log = 1u + 2u * n_modes + dig;
-      b.log_first = (uint32_t)o1;
-      b.log_every = (uint32_t)std::min<uint64_t>(every, K);  // (one log when every > K)
-      b.tw = twiddle;
-      b.out = reinterpret_cast<long long *>(dev_out + ((c0 + o1) / every - 1u) * c->n);
-    }
-    hipError_t e = c->launch_blocked(b);
+  if (total == 0) return MCLG_OK;
+  const RegWay *w = c->way(total, true);
+  if (w && c->log_room(*w) > 0) {
+    // launches that sum the logs that fall in them
+    RegLog lg;
+    lg.n_modes = n_modes;
+    lg.digest = dig;
+    lg.tw = twiddle;
+    return c->hip(c->step_way(*w, total, every, lg, reinterpret_cast<long long *>(dev_out)));
+  }
+  // steps, then the moment kernels, per log (partial sums in the workspace)
+  unsigned long long *part = reinterpret_cast<unsigned long long *>(c->ws + c->lay.o_mpart);
+  for (uint64_t j = 0; j < n_logs; ++j) {
+    int rc = mclg_step(c, every);
+    if (rc) return rc;
+    MomArgs m = c->mom_args(part, reinterpret_cast<long long *>(dev_out + j * c->n));
+    m.twiddle = twiddle;
+    m.n_modes = n_modes;
+    m.digest = dig;
+    hipError_t e = c->flush_t();
+    if (!e) e = launch_moments3(c->stream, m);
     if (e) return c->hip(e);
-    c->t[0] += S;
-    c0 += S;
   }
   return MCLG_OK;
 }
@@ -963,8 +867,7 @@ int mclg_set_schedule(mclg_ctx *c, uint32_t groups, uint32_t threads, uint32_t l
   c->sch.groups = groups;
   c->sch.threads = threads;
   c->sch.lds_budget = lds_budget;
-  c->tb = TbLaunch{};  // its geometry depends on the schedule: set it again
-  c->tb_grid = 0;
+  c->blocked = false;  // to be asked for again under the new schedule
   // graphs still in flight on the stream use the old tiles and images
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e) return c->hip(e);

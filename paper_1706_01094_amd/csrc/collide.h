@@ -217,9 +217,6 @@ constexpr int kRsrcWord3 = 0x00020000;  // raw buffer, 32-bit data format (gfx9)
 // states that do not fit the caches: non-temporal, the lines are not
 // expected to be reused before they leave).
 constexpr int kStreamingPolicy = 2;  // nt
-// sc1: coherent across the device's L2s (data another block reads in the
-// same launch)
-constexpr int kDevicePolicy = 16;
 template <int CP = 0>
 __device__ __forceinline__ void bload4(Rsrc r, uint32_t voff, uint32_t soff, uint32_t (&v)[4]) {
   const auto q = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, CP);
@@ -378,35 +375,6 @@ __device__ __forceinline__ void apply_pair(uint32_t &a, uint32_t &b, uint32_t &c
   c = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, c) + d);
   // (one multiply-add; the compiler would split it into a shift and a subtraction)
   asm("v_pk_mad_u16 %0, %1, %2, %0" : "+v"(b) : "v"(dp), "s"(0xfffefffeu));
-}
-
-// Eight consecutive elements pos .. pos + 7 (mod n) of the array at byte
-// offset `arr` of r: one 16-byte access unless they wrap around n.
-__device__ __forceinline__ void load8_wrap(Rsrc r, uint32_t arr, uint32_t pos, uint32_t n,
-                                           uint32_t (&v)[4]) {
-  if (pos + 8u <= n) {
-    bload4(r, 2u * pos, arr, v);
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    uint32_t q = pos + (uint32_t)e;
-    q -= q >= n ? n : 0u;
-    set16(v, e, bload2(r, 2u * q, arr));
-  }
-}
-__device__ __forceinline__ void store8_wrap(Rsrc r, uint32_t arr, uint32_t pos, uint32_t n,
-                                            const uint32_t (&v)[4]) {
-  if (pos + 8u <= n) {
-    bstore4(r, 2u * pos, arr, v);
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    uint32_t q = pos + (uint32_t)e;
-    q -= q >= n ? n : 0u;
-    bstore2(r, 2u * q, arr, get16(v, e));
-  }
 }
 
 }  // namespace

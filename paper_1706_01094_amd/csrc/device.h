@@ -144,60 +144,6 @@ struct StepLaunch {
 
 hipError_t launch_step(const Schedule &sch, hipStream_t s, const StepLaunch &a);
 
-// Several steps of one lattice per launch (temporal blocking).  Block b owns
-// the sites [b R, b R + R) and keeps a copy of them and of kh more sites on
-// each side (es = R + 2 kh sites) in its own part of `scratch`, a periodic
-// lattice of es sites in the shifted layout.  It copies the region in at
-// step t, and after a grid-wide barrier (every block has read the state)
-// advances its copy `steps` steps (steps <= kh): the sites within j of the
-// copy's ends are wrong after j steps, the owned sites stay exact, and the
-// random numbers are keyed by each site's place in the lattice.  It then
-// writes its owned sites back at step t + steps.  Block 0 advances the
-// slot's step counter by `steps` once every block has read it.  The barrier
-// counts arrivals in `bar` across launches (never reset): this launch's
-// blocks have all arrived when it reaches bar_target.
-constexpr uint32_t kTbMaxSteps = 256;
-struct TbLaunch {
-  uint16_t *scratch = nullptr;  // grid x bstride elements
-  uint32_t stride = 0;          // elements per array of a block's copy (>= es)
-  uint32_t R = 0;               // owned sites per block (a multiple of 8)
-  uint32_t kh = 0;              // extra sites on each side (a multiple of 8)
-  uint32_t es = 0;              // R + 2 kh
-  uint32_t steps = 0;           // steps of the launch
-  // Tiles (T > 0, for lattices whose blocks' copies would not stay in the
-  // caches): block b goes through its region in tiles of T sites, each copied
-  // with kh extra sites on each side (es = T + 2 kh) into the copy area,
-  // advanced `steps` steps and written back before the next; see k_step_tt.
-  uint32_t T = 0;
-  uint64_t bstride = 0;         // elements of scratch per block
-  // Replicas (reps != 0, a context of several lattices; see k_step_tr): block
-  // b advances whole replicas, items[item_first[b] .. item_first[b + 1]),
-  // each copied whole (stride >= the largest L), with no grid barrier.
-  uint32_t reps = 0;
-  const uint32_t *items = nullptr, *item_first = nullptr;
-  uint32_t *bar = nullptr;      // arrivals of every blocked launch of the context
-  uint32_t bar_target = 0;      // arrivals before this launch + its grid
-  // Logs (n_logs > 0): the moments (mclg_moments_t) of the state after steps
-  // log_first, log_first + log_every, ... (the last at most `steps`) of the
-  // launch; log = 1 + 2 n_modes + digest, at most 5 (two modes without the
-  // digest).  Logs before the last step: only without the digest and the
-  // Galilean acceptance.  Block b writes its partial record of log j (kMom3Rec values) at
-  // records + (j grid + b) kMom3Rec with device-coherent stores; after a
-  // second barrier (bar_target + grid) block b adds the records of logs b,
-  // b + grid, ... into out + j kMom3Out.  tw: the lattice's [2 n_modes][L]
-  // twiddles.
-  uint32_t log = 0, n_logs = 0, log_first = 0, log_every = 0;
-  const int32_t *tw = nullptr;
-  unsigned long long *records = nullptr;
-  long long *out = nullptr;
-};
-hipError_t launch_step_blocked(const Schedule &sch, hipStream_t s, const StepLaunch &a,
-                               const TbLaunch &tb, uint32_t grid);
-// Blocks of the blocked kernel that fit the device at once (the grid it
-// needs: every block must be resident for the barrier).
-hipError_t step_blocked_occupancy(const Schedule &sch, uint32_t lds_bytes, uint32_t n_cu,
-                                  uint32_t &max_blocks);
-
 // Largest lattice (sites per replica or job): the step kernel addresses a
 // slot's three arrays (6 bytes per site, 256-byte padded) with 32-bit byte
 // offsets.
@@ -221,6 +167,19 @@ hipError_t step_occupancy(const Schedule &sch, uint32_t lds_bytes, uint32_t n_cu
 uint32_t step_lds_bytes(const Schedule &sch, uint32_t image_bytes);
 
 // ---- Steps on sites held in registers (kernels_reg.hip) -----------------
+// Logs: the moments (mclg_moments_t) of the states after steps first, first +
+// every, ... (n of them) of a launch.  Every wave writes one record of
+// kMom3Rec values per log and lattice, at records + ((log x lattices +
+// lattice) x stride + wave) kMom3Rec; their sums go to out, in the order of
+// mclg_step_log.  hold: sites per wave, where a lattice has that many waves'
+// records (0: all `stride`).
+struct RegLog {
+  uint32_t first = 0, every = 0, n = 0;
+  uint32_t n_modes = 0, digest = 0, stride = 0, hold = 0, pad = 0;
+  const int32_t *tw = nullptr;
+  unsigned long long *records = nullptr;
+  long long *out = nullptr;
+};
 // Ring: lattices order[0 .. n) that fit a block's registers, `steps` steps
 // in one launch.  A wave holds up to 256 Q sites.  team = 0: a block per
 // lattice; team = k: k lattices of at most 256 Q sites per block, a wave
@@ -228,6 +187,7 @@ uint32_t step_lds_bytes(const Schedule &sch, uint32_t image_bytes);
 struct RingLaunch {
   const uint32_t *order = nullptr;  // slots
   uint32_t n = 0, team = 0, steps = 0;
+  RegLog log;
 };
 // Tiles: block b advances units[unit_first[b] .. unit_first[b + 1]), each a
 // whole lattice (split = 0: x0 = 0, x1 = L) or a part of one between two
@@ -248,15 +208,21 @@ struct TileLaunch {
   const StripDev *strips = nullptr;
   uint16_t *strip_data = nullptr;   // n_strips x 3 x 2 kh
   uint32_t n_strips = 0, kh = 0, steps = 0;
+  RegLog log;                       // one lattice only
 };
 constexpr uint32_t kRingExchangeBytes = 128;
+constexpr uint32_t kRegWaves = 16;  // waves per block
+// Whether the collision images of C hold fixed records (see LdsImage).
+constexpr bool images_fixed(int32_t C) { return C >= 0 && C <= 20; }
+// Whether the kernels exist for 4 Q sites per lane and these rules.
+bool reg_has(uint32_t Q, bool galilean, bool fixed, bool logs);
 uint32_t reg_lds_bytes(uint32_t image_bytes, uint32_t waves);
 // Allows the kernels the LDS of a 16-wave block with images of image_bytes.
 hipError_t reg_setup(uint32_t image_bytes);
 hipError_t launch_ring(hipStream_t s, const StepLaunch &a, const RingLaunch &rl, uint32_t Q,
                        uint32_t waves);
 hipError_t launch_tiles(hipStream_t s, const StepLaunch &a, const TileLaunch &tl, uint32_t Q,
-                        uint32_t waves, uint32_t grid);
+                        uint32_t waves, uint32_t grid, const uint32_t *order);
 
 hipError_t launch_init_poisson(hipStream_t s, uint16_t *state, const SlotDev *slots,
                                const uint32_t *tslot, const TileDev *tiles, uint32_t n_tiles,

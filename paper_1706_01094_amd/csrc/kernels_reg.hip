@@ -17,6 +17,7 @@
 //     ends, and is written back after at most kh steps.
 #include "collide.h"
 #include "device.h"
+#include "mom3_sum.h"
 #include "rng.h"
 
 #include <algorithm>
@@ -93,7 +94,7 @@ __device__ __forceinline__ uint32_t exact_move(const uint4 e, const Env &E, uint
 // site 8C + k is in it; of `cols`: some lane's is; F entries so far), which
 // is resolved at the end of the step.  A chunk with more such sites than the
 // queue holds is left as it is (bit C of `dense`) for dense_chunks.
-template <int Q, int C>
+template <int Q, int C, bool FIXED>
 __device__ __forceinline__ void collide_chunk(Sites<Q> &R, uint32_t &und, uint32_t &cols,
                                               uint32_t &dense, uint32_t &F, const Env &E,
                                               uint32_t x, uint32_t pos, const Span &S,
@@ -123,7 +124,7 @@ __device__ __forceinline__ void collide_chunk(Sites<Q> &R, uint32_t &und, uint32
   uint32_t d[NP], n = 0;
 #pragma unroll
   for (int j = 0; j < NP; ++j) {
-    d[j] = finish_pair<true>(s[2 * j], s[2 * j + 1], r[2 * j], r[2 * j + 1], E.lv, mk[2 * j],
+    d[j] = finish_pair<FIXED>(s[2 * j], s[2 * j + 1], r[2 * j], r[2 * j + 1], E.lv, mk[2 * j],
                              mk[2 * j + 1]);
   }
   if (S.slow) {
@@ -276,7 +277,7 @@ __device__ __forceinline__ void flag_saturated(const Sites<Q> &R, const Env &E, 
 
 // One step's collisions of the wave's sites; xw: the lattice site at
 // position 0 (below L).
-template <int Q, bool GAL>
+template <int Q, bool GAL, bool FIXED>
 __device__ __forceinline__ void collide(Sites<Q> &R, const Env &E, uint32_t xw, const Span &S,
                                         uint32_t t, bool collisions) {
   uint32_t pos = E.lane * (4u * Q);
@@ -293,9 +294,9 @@ __device__ __forceinline__ void collide(Sites<Q> &R, const Env &E, uint32_t xw, 
     const uint32_t y = xw + pos + o;
     return y >= E.Lp ? y - E.Lp : y;
   };
-  collide_chunk<Q, 0>(R, und, cols, dense, F, E, at(0u), pos, S, t);
-  if constexpr (Q >= 4) collide_chunk<Q, 1>(R, und, cols, dense, F, E, at(8u), pos + 8u, S, t);
-  if constexpr (Q >= 6) collide_chunk<Q, 2>(R, und, cols, dense, F, E, at(16u), pos + 16u, S, t);
+  collide_chunk<Q, 0, FIXED>(R, und, cols, dense, F, E, at(0u), pos, S, t);
+  if constexpr (Q >= 4) collide_chunk<Q, 1, FIXED>(R, und, cols, dense, F, E, at(8u), pos + 8u, S, t);
+  if constexpr (Q >= 6) collide_chunk<Q, 2, FIXED>(R, und, cols, dense, F, E, at(16u), pos + 16u, S, t);
   if (F) resolve_step<Q, GAL>(R, und, cols, F, E, xw, S, t);
   if (dense) dense_chunks<Q, GAL>(R, dense, E, at(0u), pos, S, t);
 }
@@ -464,13 +465,164 @@ __device__ __forceinline__ void copy_image(uint4 *lds, const uint8_t *pool, cons
   }
 }
 // ---------------------------------------------------------------------------
+// Moments of the sites a wave holds
+// ---------------------------------------------------------------------------
+// The second argument of the kernels, in the kernel's argument segment: what
+// a log needs is read where it is used (see kernel_args).
+template <class Launch>
+__device__ __forceinline__ const RegLog *log_args() {
+  constexpr size_t at = (sizeof(StepLaunch) + alignof(Launch) - 1) / alignof(Launch) * alignof(Launch);
+  const char *k = (const char *)kernel_args();
+  asm volatile("" : "+s"(k));
+  return reinterpret_cast<const RegLog *>(k + at + offsetof(Launch, log));
+}
+
+// Adds the moments of the wave's own sites (record slots as in moments.h) to
+// `rec`, the wave's record of this log, or stores them there (`fresh`).
+// The sums take the lane's words one pair of sites at a time, rotating them,
+// so that a log in the middle of the steps needs few registers.
+template <int Q>
+__device__ __attribute__((noinline)) void log_sites(Sites<Q> R, uint32_t xw, uint32_t Lp, uint32_t L,
+                                                    uint32_t own_lo, uint32_t own_hi,
+                                                    const RegLog *lg, const int32_t *tw,
+                                                    unsigned long long *rec, bool fresh) {
+  const uint32_t lane = threadIdx.x & 63u;
+  using namespace mom3;
+  constexpr int W = 2 * Q;
+  uint32_t pos = lane * (4u * Q);
+  asm volatile("" : "+v"(pos));
+  uint32_t x0 = xw + pos;
+  x0 -= x0 >= Lp ? Lp : 0u;
+  const uint32_t n_modes = lg->n_modes;
+  const bool dig = lg->digest != 0u;
+  {
+    uint32_t s0 = 0, s1 = 0, s2 = 0, odd = 0, mx = 0;
+    u64 q[6] = {}, d = 0;
+    uint32_t at = pos, x = x0;
+#pragma unroll 1
+    for (int j = 0; j < W; ++j) {
+#pragma unroll
+      for (uint32_t h = 0; h < 2u; ++h) {
+        const bool own = at + h >= own_lo && at + h < own_hi;
+        const uint32_t a = own ? (R.m[0] >> (16u * h)) & 0xffffu : 0u;
+        const uint32_t b = own ? (R.z[0] >> (16u * h)) & 0xffffu : 0u;
+        const uint32_t c = own ? (R.p[0] >> (16u * h)) & 0xffffu : 0u;
+        s0 += a;
+        s1 += b;
+        s2 += c;
+        q[0] += (u64)a * a;
+        q[1] += (u64)b * b;
+        q[2] += (u64)c * c;
+        q[3] += (u64)a * b;
+        q[4] += (u64)b * c;
+        q[5] += (u64)a * c;
+        odd += b & 1u;
+        mx = max(mx, a + b + c);
+        if (dig) {
+          const uint32_t k = 4u * (x + h) + 1u;
+          if (own)
+            d += (u64)fmix32(fmix32(k) ^ a) + fmix32(fmix32(k + 1u) ^ b) + fmix32(fmix32(k + 2u) ^ c);
+        }
+      }
+      at += 2u;
+      x += 2u;
+      x -= x >= Lp ? Lp : 0u;
+      const uint32_t fm = R.m[0], fz = R.z[0], fp = R.p[0];
+#pragma unroll
+      for (int i = 0; i + 1 < W; ++i) {
+        R.m[i] = R.m[i + 1];
+        R.z[i] = R.z[i + 1];
+        R.p[i] = R.p[i + 1];
+      }
+      R.m[W - 1] = fm;
+      R.z[W - 1] = fz;
+      R.p[W - 1] = fp;
+    }
+    u64 v[16] = {s0, s1, s2, q[0], q[1], q[2], q[3], q[4], q[5], odd, d, 0, 0, 0, 0, 0};
+    mx = wave_max(mx);
+    u64 s = wave_sum_scatter<16>(v, lane);  // lane l: value l / 4
+    const uint32_t slot = lane >> 2;
+    if ((lane & 3u) == 0u && slot < 12u) {
+      if (slot == 11u) s = mx;
+      if (!fresh) {
+        const u64 before = rec[slot];
+        s = slot == 11u ? max(s, before) : s + before;
+      }
+      rec[slot] = s;
+    }
+  }
+  // Fourier sums, one row of the twiddles at a time
+#pragma unroll 1
+  for (uint32_t m = 0; m < 2u * n_modes; ++m) {
+    const int32_t *const row = tw + (uint64_t)m * L;
+    int32_t w[4 * Q];
+#pragma unroll
+    for (int g = 0; g < Q; ++g) {
+      uint32_t x = x0 + 4u * g;
+      x -= x >= Lp ? Lp : 0u;
+      if (x + 4u <= L) {
+        __builtin_memcpy(&w[4 * g], row + x, 16);  // (4-byte aligned)
+      } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 4u; ++e) w[4 * g + e] = x + e < L ? row[x + e] : 0;
+      }
+    }
+    i64 f = 0;
+#pragma unroll
+    for (int k = 0; k < 4 * Q; ++k) {
+      const uint32_t sh = 16u * (k & 1);
+      const uint32_t N = ((R.m[k >> 1] >> sh) & 0xffffu) + ((R.z[k >> 1] >> sh) & 0xffffu) +
+                         ((R.p[k >> 1] >> sh) & 0xffffu);
+      const bool own = pos + k >= own_lo && pos + k < own_hi;
+      f += (i64)(int32_t)(own ? N : 0u) * (i64)w[k];
+    }
+    u64 fs = (u64)f;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) fs += shfl_xor_u64(fs, o);
+    if (lane == 0u) rec[12u + m] = fresh ? fs : rec[12u + m] + fs;
+  }
+}
+
+// The results of a launch's logs from the waves' records: block (j, u) adds
+// the `held` records of lattice u (of `stride`) at log j into its row.
+__global__ void __launch_bounds__(256) k_log_final(StepLaunch a, RegLog lg, const uint32_t *order,
+                                                   uint32_t n, uint32_t t_off) {
+  using namespace mom3;
+  const uint32_t j = blockIdx.x / n, u = blockIdx.x % n, slot = order[u];
+  const SlotDev sl = a.slots[slot];
+  const unsigned long long *const rec = lg.records + ((uint64_t)j * n + u) * lg.stride * kMom3Rec;
+  __shared__ u64 part[8][kMom3Rec];
+  __shared__ u64 T[kMom3Rec];
+  // thread (g, k): value k of records g, g + 8, ...
+  const uint32_t k = threadIdx.x & 31u, g = threadIdx.x >> 5;
+  const uint32_t hold = lg.hold ? (sl.L + lg.hold - 1u) / lg.hold : lg.stride;
+  u64 s = 0;
+  if (k < 12u + 2u * lg.n_modes)
+    for (uint32_t w = g; w < hold; w += 8u) {
+      const u64 y = rec[(uint64_t)w * kMom3Rec + k];
+      s = k == 11u ? max(s, y) : s + y;
+    }
+  part[g][k] = s;
+  __syncthreads();
+  if (threadIdx.x < kMom3Rec) {
+    s = part[0][k];
+    for (uint32_t i = 1; i < 8u; ++i) s = k == 11u ? max(s, part[i][k]) : s + part[i][k];
+    T[k] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < kMom3Out)
+    lg.out[((uint64_t)j * a.n_slots + slot) * kMom3Out + threadIdx.x] = (i64)result_field(
+        threadIdx.x, T, a.tslot[slot] + t_off + lg.first + j * lg.every, sl.L, lg.n_modes);
+}
+
+// ---------------------------------------------------------------------------
 // Lattices that fit a block's registers
 // ---------------------------------------------------------------------------
 // rl.team = 0: the block holds one lattice, order[b], over as many of its
 // waves as it needs.  rl.team = k > 0: each of the block's first k waves holds
 // one, order[b k + wave], all with the same image.  The other waves only help
 // to copy the image.
-template <int Q, bool GAL>
+template <int Q, bool GAL, bool FIXED, bool LOG>
 __global__ void __launch_bounds__(1024) k_ring(StepLaunch a, RingLaunch rl) {
   constexpr uint32_t S = 4u * Q, W = 2 * Q, NS = Q == 1 ? 4 : 8, NC = S / NS;
   extern __shared__ uint4 lds[];
@@ -522,9 +674,22 @@ __global__ void __launch_bounds__(1024) k_ring(StepLaunch a, RingLaunch rl) {
 #pragma unroll
   for (uint32_t j = 0; j < W; ++j)
     ins[j] = (lane == le && (ee >> 1) == j) ? ((ee & 1u) ? 0xffff0000u : 0x0000ffffu) : 0u;
+  uint32_t next = LOG ? rl.log.first : 0u, logs = 0;
+  auto log = [&]() {  // the moments of the state the steps so far reach
+    if (active) {
+      const RegLog *lg = log_args<RingLaunch>();
+      log_sites<Q>(R, first, E.Lp, L, 0u, Sp.end, lg, lg->tw + 2ull * lg->n_modes * sl.dense,
+                   lg->records + (((uint64_t)logs * rl.n + u) * lg->stride + w) * kMom3Rec, true);
+    }
+    ++logs;
+    next = logs < rl.log.n ? next + rl.log.every : 0u;
+  };
   for (uint32_t s = 0; s < rl.steps; ++s) {
-    if (active) collide<Q, GAL>(R, E, first, Sp, t0 + s, coll);
-    if (ns) continue;
+    if (active) collide<Q, GAL, FIXED>(R, E, first, Sp, t0 + s, coll);
+    if (ns) {
+      if (LOG && s + 1u == next) log();
+      continue;
+    }
     uint32_t pl = site_of<Q>(R.p, e1);
     uint32_t mf = __builtin_amdgcn_readfirstlane(R.m[0]) & 0xffffu;
     if (held > 1u) {
@@ -538,6 +703,7 @@ __global__ void __launch_bounds__(1024) k_ring(StepLaunch a, RingLaunch rl) {
     const uint32_t mv = mf * 0x10001u;
 #pragma unroll
     for (uint32_t j = 0; j < W; ++j) R.m[j] = (R.m[j] & ~ins[j]) | (mv & ins[j]);
+    if (LOG && s + 1u == next) log();
   }
   if (active) {
     const uint32_t tm = ns ? 0u : (uint32_t)(((uint64_t)t0 + rl.steps) % L);
@@ -591,7 +757,7 @@ __global__ void __launch_bounds__(64) k_strips(StepLaunch a, TileLaunch tl) {
 // the first 2 kh sites of every further tile when the tile before it was
 // loaded (into the private area); and what lies within kh sites of another
 // block's range from the strips, which k_strips wrote before the launch.
-template <int Q, bool GAL>
+template <int Q, bool GAL, bool FIXED, bool LOG>
 __global__ void __launch_bounds__(1024) k_tile(StepLaunch a, TileLaunch tl) {
   constexpr uint32_t S = 4u * Q, NS = Q == 1 ? 4 : 8, NC = S / NS;
   extern __shared__ uint4 lds[];
@@ -607,6 +773,10 @@ __global__ void __launch_bounds__(1024) k_tile(StepLaunch a, TileLaunch tl) {
   auto carry_at = [&](uint32_t c) { return 6u * slen + c * 12u * kh; };
   uint64_t loaded = ~0ull;
   const uint32_t i0 = tl.unit_first[blockIdx.x], i1 = tl.unit_first[blockIdx.x + 1u];
+  // the wave's records of the launch's logs (of one lattice) start empty
+  for (uint32_t j = 0; LOG && j < tl.log.n; ++j)
+    if (lane < kMom3Rec)
+      tl.log.records[((uint64_t)j * tl.log.stride + blockIdx.x * nw + wave) * kMom3Rec + lane] = 0ull;
   for (uint32_t it = i0; it < i1; ++it) {
     const UnitDev un = tl.units[it];
     const uint32_t slot = __builtin_amdgcn_readfirstlane(un.slot);
@@ -724,9 +894,10 @@ __global__ void __launch_bounds__(1024) k_tile(StepLaunch a, TileLaunch tl) {
       // with positions without sites between them
       const uint32_t pad = Lp - L, p0 = xt < kh ? kh - xt : Lp + kh - xt;
       const bool seam = pad != 0u && !ns && p0 < 64u * S && p0 > pad;
+      uint32_t next = LOG ? tl.log.first : 0u, logs = 0;
       for (uint32_t s = 0; s < tl.steps; ++s) {
-        collide<Q, GAL>(R, E, xw, Sp, t0 + s, coll);
-        if (ns) continue;
+        collide<Q, GAL, FIXED>(R, E, xw, Sp, t0 + s, coll);
+        if (!ns) {
         uint32_t up = 0, down = 0;
         if (seam) {
           up = site_of<Q>(R.p, p0 - 1u - pad);
@@ -736,6 +907,15 @@ __global__ void __launch_bounds__(1024) k_tile(StepLaunch a, TileLaunch tl) {
         if (seam) {
           set_site<Q>(R.p, p0, lane, up);
           set_site<Q>(R.m, p0 - 1u - pad, lane, down);
+        }
+        }
+        if (LOG && s + 1u == next) {
+          const RegLog *lg = log_args<TileLaunch>();
+          log_sites<Q>(R, xw, Lp, L, kh, kh + min(n, L - xt), lg, lg->tw,
+                       lg->records + ((uint64_t)logs * lg->stride + blockIdx.x * nw + wave) * kMom3Rec,
+                       false);
+          ++logs;
+          next = logs < tl.log.n ? next + tl.log.every : 0u;
         }
       }
 #pragma unroll
@@ -763,39 +943,70 @@ uint32_t reg_lds_bytes(uint32_t image_bytes, uint32_t waves) {
 hipError_t reg_setup(uint32_t image_bytes) {
   const uint32_t lds = reg_lds_bytes(image_bytes, 16);
   hipError_t e = hipSuccess;
-#define MCLG_ALLOW(Q, GAL)                                  \
-  if (!e) e = allow_lds(k_ring<Q, GAL>, lds);               \
-  if (!e) e = allow_lds(k_tile<Q, GAL>, lds);
-  MCLG_ALLOW(1, false) MCLG_ALLOW(2, false) MCLG_ALLOW(4, false) MCLG_ALLOW(6, false)
-  MCLG_ALLOW(1, true) MCLG_ALLOW(2, true)
+#define MCLG_ALLOW(...)                                     \
+  if (!e) e = allow_lds(k_ring<__VA_ARGS__>, lds);          \
+  if (!e) e = allow_lds(k_tile<__VA_ARGS__>, lds);
+  MCLG_ALLOW(1, false, true, false) MCLG_ALLOW(2, false, true, false)
+  MCLG_ALLOW(4, false, true, false) MCLG_ALLOW(6, false, true, false)
+  MCLG_ALLOW(1, true, true, false) MCLG_ALLOW(2, true, true, false)
+  MCLG_ALLOW(2, false, false, false) MCLG_ALLOW(2, true, false, false)
+  MCLG_ALLOW(1, false, true, true) MCLG_ALLOW(2, false, true, true)
+  MCLG_ALLOW(4, false, true, true)
 #undef MCLG_ALLOW
   return e;
+}
+
+// The instantiations: images of fixed records for every Q (the Galilean
+// acceptance, whose literal loop needs the registers, for Q <= 2), the others
+// (C = infinity or C > 20) for Q = 2; logs with the constant acceptance and
+// fixed records for Q <= 4 (a log's sums take the registers of two more).
+bool reg_has(uint32_t Q, bool galilean, bool fixed, bool logs) {
+  if (Q != 1 && Q != 2 && Q != 4 && Q != 6) return false;
+  if (logs) return !galilean && fixed && Q <= 4;
+  return fixed ? !galilean || Q <= 2 : Q == 2;
+}
+#define MCLG_REG_LAUNCH(KERNEL, GRID, ARGS)                                              \
+  switch (Q + (a.p.galilean ? 8u : 0u) + (images_fixed(a.p.C) ? 0u : 16u) + (ARGS.log.n ? 32u : 0u)) { \
+    case 1: KERNEL<1, false, true, false><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    case 2: KERNEL<2, false, true, false><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    case 4: KERNEL<4, false, true, false><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    case 6: KERNEL<6, false, true, false><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    case 9: KERNEL<1, true, true, false><<<GRID, block, lds, s>>>(a, ARGS); break;       \
+    case 10: KERNEL<2, true, true, false><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    case 18: KERNEL<2, false, false, false><<<GRID, block, lds, s>>>(a, ARGS); break;    \
+    case 26: KERNEL<2, true, false, false><<<GRID, block, lds, s>>>(a, ARGS); break;     \
+    case 33: KERNEL<1, false, true, true><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    case 34: KERNEL<2, false, true, true><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    case 36: KERNEL<4, false, true, true><<<GRID, block, lds, s>>>(a, ARGS); break;      \
+    default: return hipErrorInvalidValue;                                                \
+  }
+
+static bool log_ok(const RegLog &lg, uint32_t steps, uint32_t stride) {
+  return lg.n == 0 || (lg.first >= 1 && lg.every >= 1 && lg.n_modes <= 8 && lg.records && lg.out &&
+                       (lg.tw || lg.n_modes == 0) && lg.stride >= stride &&
+                       lg.first + (uint64_t)(lg.n - 1u) * lg.every <= steps);
 }
 
 hipError_t launch_ring(hipStream_t s, const StepLaunch &a, const RingLaunch &rl, uint32_t Q,
                        uint32_t waves) {
   if (rl.n == 0 || rl.steps == 0) return hipSuccess;
-  if (waves < 1 || waves > 16 || rl.team > waves) return hipErrorInvalidValue;
+  if (waves < 1 || waves > 16 || rl.team > waves || !log_ok(rl.log, rl.steps, rl.team ? 1u : waves))
+    return hipErrorInvalidValue;
   const dim3 grid(rl.team ? (rl.n + rl.team - 1u) / rl.team : rl.n), block(64u * waves);
   const uint32_t lds = reg_lds_bytes(a.lds_bytes, waves);
-  switch (Q + (a.p.galilean ? 8u : 0u)) {
-    case 1: k_ring<1, false><<<grid, block, lds, s>>>(a, rl); break;
-    case 2: k_ring<2, false><<<grid, block, lds, s>>>(a, rl); break;
-    case 4: k_ring<4, false><<<grid, block, lds, s>>>(a, rl); break;
-    case 6: k_ring<6, false><<<grid, block, lds, s>>>(a, rl); break;
-    case 9: k_ring<1, true><<<grid, block, lds, s>>>(a, rl); break;
-    case 10: k_ring<2, true><<<grid, block, lds, s>>>(a, rl); break;
-    default: return hipErrorInvalidValue;
-  }
+  MCLG_REG_LAUNCH(k_ring, grid, rl)
+  if (rl.log.n) k_log_final<<<rl.log.n * rl.n, 256, 0, s>>>(a, rl.log, rl.order, rl.n, a.t_off);
   return hipGetLastError();
 }
 
 hipError_t launch_tiles(hipStream_t s, const StepLaunch &a, const TileLaunch &tl, uint32_t Q,
-                        uint32_t waves, uint32_t grid) {
+                        uint32_t waves, uint32_t grid, const uint32_t *order) {
   if (tl.steps == 0) return hipSuccess;
-  // the tiles' own sites, the private areas and their number
+  // the tiles' own sites, the private areas and their number; logs of one
+  // lattice only
   if (waves < 1 || waves > 16 || tl.kh % 8u != 0u || tl.steps > tl.kh || 2u * tl.kh >= 256u * Q ||
-      36u * tl.kh > 16u * kOverflowPerWave || grid * waves > kOverflowWaves)
+      36u * tl.kh > 16u * kOverflowPerWave || grid * waves > kOverflowWaves ||
+      !log_ok(tl.log, tl.steps, grid * waves) || (tl.log.n && a.n_slots != 1u))
     return hipErrorInvalidValue;
   if (tl.n_strips) {
     k_strips<<<tl.n_strips, 64, 0, s>>>(a, tl);
@@ -804,15 +1015,8 @@ hipError_t launch_tiles(hipStream_t s, const StepLaunch &a, const TileLaunch &tl
   }
   const dim3 g(grid), block(64u * waves);
   const uint32_t lds = reg_lds_bytes(a.lds_bytes, waves);
-  switch (Q + (a.p.galilean ? 8u : 0u)) {
-    case 1: k_tile<1, false><<<g, block, lds, s>>>(a, tl); break;
-    case 2: k_tile<2, false><<<g, block, lds, s>>>(a, tl); break;
-    case 4: k_tile<4, false><<<g, block, lds, s>>>(a, tl); break;
-    case 6: k_tile<6, false><<<g, block, lds, s>>>(a, tl); break;
-    case 9: k_tile<1, true><<<g, block, lds, s>>>(a, tl); break;
-    case 10: k_tile<2, true><<<g, block, lds, s>>>(a, tl); break;
-    default: return hipErrorInvalidValue;
-  }
+  MCLG_REG_LAUNCH(k_tile, g, tl)
+  if (tl.log.n) k_log_final<<<tl.log.n, 256, 0, s>>>(a, tl.log, order, 1u, a.t_off);
   return hipGetLastError();
 }
 

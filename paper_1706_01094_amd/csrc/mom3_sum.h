@@ -2,8 +2,8 @@
 // block's lanes: the exact integer sums behind the paper's statistics (means
 // and variances of n_i for Eq. (poisson), the correlator of Eq. (corr), N and
 // J, Fourier projections of the density for Eq. (A) and S(k)) and the state
-// digest.  Shared by the moment kernels and by the blocked step kernel, which
-// sums the sites it writes back on a logging launch.
+// digest.  Shared by the moment kernels and by the step kernels that hold the
+// sites in registers, which sum them where a log falls.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -67,10 +67,8 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 // Block-wide combination of the lanes' sums and maxima into one partial
 // record: sums of values 0 .. V-1 in record slots 0 .. W-1 except MS, the
 // maximum in slot MS (value MS is zero).  red and redmx: LDS of 16 x V and 16
-// values (one row per wave, at most 16 waves).  COHERENT: the record is
-// written with device-coherent stores (past the L2 of the block's XCD), for
-// a reader in the same launch.
-template <int V, int W, int MS, bool COHERENT = false>
+// values (one row per wave, at most 16 waves).
+template <int V, int W, int MS>
 __device__ __forceinline__ void block_record(u64 (&v)[V], uint32_t mx, u64 *rec, u64 *red,
                                              uint32_t *redmx) {
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -90,10 +88,7 @@ __device__ __forceinline__ void block_record(u64 (&v)[V], uint32_t mx, u64 *rec,
     } else {
       for (uint32_t w = 0; w < nw; ++w) out += red[w * V + k];
     }
-    if constexpr (COHERENT)
-      __hip_atomic_store(rec + k, out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-      rec[k] = out;
+    rec[k] = out;
   }
 }
 
@@ -102,8 +97,7 @@ __device__ __forceinline__ void block_record(u64 (&v)[V], uint32_t mx, u64 *rec,
 // packed dot products into 32-bit sums (f, in the order of record slots
 // 0..8): each adds at most 8 x 255^2 per window, so f stays below 2^32 as
 // long as a lane adds at most 4096 windows before fold() (the moment kernels:
-// segments of at most 2^23 sites, 2048 per pass of 256 lanes; the blocked
-// step kernel: at most 2^21 sites per block, 8192 per pass of 1024 lanes).
+// segments of at most 2^23 sites, 2048 per pass of 256 lanes).
 // Other windows add exact 64-bit sums.
 template <int NM>
 struct Acc3 {

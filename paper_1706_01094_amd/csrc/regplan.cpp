@@ -15,10 +15,15 @@ UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks) {
   UnitPlan P;
   blocks = std::min(blocks, kPlanBlocks);
   uint64_t total = 0;
-  for (uint32_t r = 0; r < n; ++r) total += L[r];
+  for (uint32_t r = 0; r < n; ++r) {
+    if (L[r] < kMinTiled) continue;
+    total += L[r];
+    ++P.n_long;
+  }
   const uint64_t target = std::max<uint64_t>(kMinPart, (total + blocks - 1) / blocks);
   std::vector<UnitDev> all;
   for (uint32_t r = 0; r < n; ++r) {
+    if (L[r] < kMinTiled) continue;
     // a lattice of up to 5/4 of a block's share stays whole
     uint64_t parts = 4 * L[r] <= 5 * target ? 1 : (L[r] + target - 1) / target;
     if (P.strips.size() + parts > kMaxStrips) parts = 1;
@@ -91,25 +96,26 @@ constexpr double kUnit = 4.0;         // every further unit of a block: image an
 }  // namespace
 
 std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t n, uint32_t blocks,
-                              bool one_image, bool galilean) {
+                              bool one_image, bool galilean, bool fixed) {
   std::vector<RegWay> ways;
   blocks = std::min(blocks, kPlanBlocks);
-  uint64_t longest = 0, shortest = ~0ull, total = 0;
+  uint64_t longest = 0, total = 0;
   bool ragged = false;
   for (uint32_t r = 0; r < n; ++r) {
     longest = std::max(longest, L[r]);
-    shortest = std::min(shortest, L[r]);
     total += L[r];
     ragged |= L[r] % 8 != 0;
   }
   for (uint32_t Q : {1u, 2u, 4u, 6u}) {
-    if (galilean && Q > 2) continue;  // (its literal loop needs the registers)
+    if (!reg_has(Q, galilean, fixed, false)) continue;
+    const bool logs = reg_has(Q, galilean, fixed, true);
     const uint64_t hold = 256ull * Q;
     if (longest <= 16 * hold) {
       RegWay y;
       y.kind = RegWay::kRing;
       y.Q = Q;
       y.most = 1u << 20;
+      y.logs = logs;
       // the lattices in the order of their sizes, one per block
       double sum = 0, most = 0;
       for (uint32_t r = 0; r < n; ++r) {
@@ -129,8 +135,7 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
         ways.push_back(y);
       }
     }
-    // (a tile with its extra sites is shorter than the lattice)
-    if (shortest < 512) continue;
+    if (plan.n_long == 0) continue;
     for (uint32_t kh : {8u, 16u, 32u, 64u, 128u}) {
       if (2 * kh >= hold) continue;
       RegWay y;
@@ -139,6 +144,7 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
       y.kh = kh;
       y.most = ragged ? kh - 8 : kh;
       if (y.most == 0) continue;
+      y.logs = logs && n == 1;
       const uint64_t tmax = hold - 2 * kh;
       double worst = 0, images = 0;
       for (size_t b = 0; b + 1 < plan.first.size(); ++b) {
@@ -155,16 +161,22 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
                     std::max(0.0, images - 1.0) * kUnit +
                     2.0e-6 * (double)std::min<uint64_t>(total, 1u << 25);
       y.step_us = worst;
+      if (plan.n_long < n) {  // and a ring launch for the others
+        y.launch_us += kRingLaunch;
+        y.step_us += ring_step_us(2, 1, false) * std::max(1.0, (double)(n - plan.n_long) / blocks);
+      }
       ways.push_back(y);
     }
   }
   return ways;
 }
 
-const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, double single_us) {
+const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, bool logs,
+                       double single_us) {
   const RegWay *best = nullptr;
   double least = (double)steps * single_us;
   for (const RegWay &w : ways) {
+    if (logs && !w.logs) continue;
     const double launches = w.kind == RegWay::kTile ? (double)((steps + w.most - 1) / w.most) : 1.0;
     const double us = launches * w.launch_us + (double)steps * w.step_us;
     if (us < least) {

@@ -13,9 +13,14 @@ constexpr uint32_t kPlanBlocks = 256;      // blocks of a tile launch, at most
 constexpr uint32_t kMaxStrips = 4 * kPlanBlocks;
 inline uint64_t max_units(uint32_t n) { return (uint64_t)n + kMaxStrips; }
 
-// The units of the tile kernel: every lattice whole or in equal parts, dealt
-// to the blocks longest first.
+// Lattices of fewer sites never go in tiles (a tile with its extra sites must
+// be shorter than its lattice); beside longer ones they take the ring kernel.
+constexpr uint32_t kMinTiled = 512;
+
+// The units of the tile kernel: every lattice of at least kMinTiled sites,
+// whole or in equal parts, dealt to the blocks longest first.
 struct UnitPlan {
+  uint32_t n_long = 0;           // such lattices
   std::vector<UnitDev> units;
   std::vector<uint32_t> first;   // blocks + 1
   std::vector<StripDev> strips;
@@ -28,17 +33,20 @@ struct RegWay {
   enum Kind : uint32_t { kNone = 0, kRing, kTile } kind = kNone;
   uint32_t Q = 0, kh = 0, team = 0;
   uint32_t most = 0;                  // steps per launch, at most
+  bool logs = false;                  // whether a launch can sum logs
   double launch_us = 0, step_us = 0;  // per launch and per step, estimated
 };
 
 // The ways open to a context, with their estimated times; one_image: all
 // lattices share one.
 std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t n, uint32_t blocks,
-                              bool one_image, bool galilean);
+                              bool one_image, bool galilean, bool fixed);
 
-// The quickest way for `steps` steps, or nullptr when one step per launch of
-// the kernels that keep the state in memory (single_us per step) is quicker.
-const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, double single_us);
+// The quickest way for `steps` steps (with logs among them), or nullptr when
+// one step per launch of the kernels that keep the state in memory (single_us
+// per step) is quicker.
+const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, bool logs,
+                       double single_us);
 // Estimated time of one such step over `sites` sites.
 double single_step_us(uint64_t sites);
 

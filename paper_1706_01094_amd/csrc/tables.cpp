@@ -547,7 +547,7 @@ LdsImage build_image(const CollisionTables &tab, double rho, double u, uint32_t 
   im.dim_c = dim_c;
   im.b_lo = best_lo;
   im.nb = nb;
-  im.fixed = tab.C > 0 && tab.C <= 20;
+  im.fixed = images_fixed(tab.C);
   // directory entries are byte offsets of a pair's first record from the
   // image start; absent pairs and the clamped row and column: the never row
   const uint32_t rec0 = im.dir_bytes();

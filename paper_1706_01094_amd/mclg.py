@@ -351,10 +351,10 @@ class Lattice:
         mclg_set_drain(self.ctx, policy)
 
     def set_blocked(self, steps: int, tile: int = 0):
-        """mclg_set_blocked: `steps` steps per launch (temporal blocking) on
-        whole block ranges (tile = 1) or in tiles of `tile` sites (>= 2;
-        0 picks), with a scratch tensor of this lattice's device owned here;
-        steps <= 1 switches it off."""
+        """mclg_set_blocked: several steps per launch (temporal blocking)
+        whatever the drain policy and the grid limit, with a scratch tensor
+        laid out for `steps` and `tile` owned here; steps <= 1 switches it
+        off."""
         if steps <= 1:
             _check(lib().mclg_set_blocked(self.ctx, 0, 0, None, 0), "mclg_set_blocked")
             self._tb = None
@@ -404,8 +404,8 @@ class Lattice:
         replica after them, written into ``out`` (a contiguous int64 tensor of
         at least n_logs * n_replicas * 33 values on the device; log j of
         replica r is row j * n_replicas + r) in stream order, without
-        synchronising; with blocking on, each launch sums the logs that fall
-        in it."""
+        synchronising; launches of several steps sum the logs that fall in
+        them."""
         tw = self._device_out(out, twiddle, n_modes, n_logs)
         _check(lib().mclg_step_log(self.ctx, every, n_logs, tw, n_modes,
                                    MOMENTS_DIGEST if digest else 0, out.data_ptr()),

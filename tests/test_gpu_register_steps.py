@@ -52,7 +52,7 @@ def test_lattices_between_blocks(L):
     run(L, (33, 5) if L > 200000 else (33, 120, 5))
 
 
-@pytest.mark.parametrize("n,lo,hi", [(300, 250, 250), (600, 900, 900), (300, 1, 3000), (40, 513, 30000),
+@pytest.mark.parametrize("n,lo,hi", [(300, 250, 250), (600, 900, 900), (300, 1, 3000), (40, 513, 30000), (60, 400, 60000),
                                      (5, 600, 500000)])
 def test_replicas(n, lo, hi):
     """Equal lattices (several per block, one image), uneven ones with images
@@ -66,9 +66,9 @@ def test_replicas(n, lo, hi):
 
 
 @pytest.mark.parametrize("L", [3001, 100003])
-@pytest.mark.parametrize("kw", [dict(C=0), dict(C=1), dict(C=3, lam=(1, 2)), dict(C=20), dict(C=-1), dict(n_max=24),
+@pytest.mark.parametrize("kw", [dict(C=0), dict(C=1), dict(C=3, lam=(1, 2)), dict(C=20), dict(C=-1), dict(C=21), dict(n_max=24),
                                 dict(flags=FLAG_NO_STREAM), dict(flags=FLAG_GALILEAN, lam=(3, 4)),
-                                dict(flags=FLAG_GALILEAN, n_max=16)], ids=str)
+                                dict(flags=FLAG_GALILEAN, n_max=16), dict(C=30, flags=FLAG_GALILEAN)], ids=str)
 def test_collision_rules(L, kw):
     run(L, (17, 4), u0=0.15, **kw)
 
@@ -97,3 +97,33 @@ def test_no_flag_from_extra_sites():
     counts[0, gap:L // 2] = 40000
     counts[2, L // 2:L - gap] = 40000
     run(L, (24, 7), counts=counts)
+
+
+@pytest.mark.parametrize("L,every", [(1, 1), (255, 3), (4097, 7), (70003, 5), (70003, 150), (300004, 1)])
+@pytest.mark.parametrize("n_modes,digest", [(0, True), (2, False)])
+def test_logs_within_a_launch(L, every, n_modes, digest):
+    """Logs summed from the registers, at steps inside and at the end of a
+    launch and of lattices with positions after their last site, equal the
+    moments read between the steps."""
+    import torch
+    a, b = (Lattice(L, 7, rho=30.0, u0=0.1) for _ in range(2))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    tw = torch.randint(-2**30, 2**30, (2 * n_modes * L,), dtype=torch.int32, device="cuda", generator=g) \
+        if n_modes else None
+    n = 6
+    out, row = (torch.zeros(k * 33, dtype=torch.int64, device="cuda") for k in (n, 1))
+    for l in (a, b):
+        l.step(2)
+    a.step_log(every, n, out, tw, n_modes, digest=digest)
+    assert a.check() == 0
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().reshape(n, 33)
+    for j in range(n):
+        b.step(every)
+        b.moments_to_device(row, tw, n_modes, digest=digest)
+        b.check()
+        torch.cuda.synchronize()
+        assert np.array_equal(got[j], row.cpu().numpy()), j
+    assert a.moments(digest=True) == b.moments(digest=True)
+    a.close()
+    b.close()

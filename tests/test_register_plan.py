@@ -13,6 +13,13 @@ MAIN = r"""
 #include <random>
 #include "regplan.h"
 using namespace mclg;
+// (in the kernels' file, which needs a device compiler)
+namespace mclg {
+bool reg_has(uint32_t Q, bool galilean, bool fixed, bool logs) {
+  if (logs) return !galilean && fixed && Q <= 4;
+  return fixed ? !galilean || Q <= 2 : Q == 2;
+}
+}
 #define REQUIRE(x) if (!(x)) { std::printf("case %d: %s\n", c, #x); return 1; }
 int main() {
   std::mt19937_64 g(7);
@@ -34,18 +41,21 @@ int main() {
       REQUIRE(P.strips[u.er].slot == u.slot && P.strips[u.er].x == u.x1);
       REQUIRE(P.strips[u.el].slot == u.slot && P.strips[u.el].x == (u.x0 ? u.x0 : L[u.slot]));
     }
-    for (uint32_t r = 0; r < n; ++r) REQUIRE(seen[r] == L[r]);
-    for (const RegWay &w : plan_ways(P, L.data(), n, blocks, c % 2, c % 7 == 0)) {
+    // (lattices too short for tiles are no units)
+    for (uint32_t r = 0; r < n; ++r) REQUIRE(seen[r] == (L[r] < kMinTiled ? 0 : L[r]));
+    for (const RegWay &w : plan_ways(P, L.data(), n, blocks, c % 2, c % 7 == 0, c % 11 != 0)) {
       REQUIRE(w.kind != RegWay::kNone && w.most >= 1 && w.step_us > 0 && w.launch_us > 0);
-      uint64_t longest = 0, shortest = ~0ull;
+      REQUIRE(reg_has(w.Q, c % 7 == 0, c % 11 != 0, w.logs));
+      uint64_t longest = 0;
       bool ragged = false;
-      for (uint64_t l : L) { longest = l > longest ? l : longest; shortest = l < shortest ? l : shortest; ragged |= l % 8 != 0; }
+      for (uint64_t l : L) { longest = l > longest ? l : longest; ragged |= l % 8 != 0; }
       if (w.kind == RegWay::kRing) {
         REQUIRE(longest <= 4096ull * w.Q && (w.team == 0 || (longest <= 256ull * w.Q && w.team <= 16)));
       } else {
         // a tile's positions fit a wave and, with its extra sites, the lattice
         REQUIRE(2 * w.kh < 256 * w.Q && w.kh <= kMaxHalo && w.kh % 8 == 0);
-        REQUIRE(w.most + (ragged ? 8 : 0) <= w.kh && shortest >= 512);
+        REQUIRE(w.most + (ragged ? 8 : 0) <= w.kh && P.n_long > 0 && P.units.size() >= P.n_long);
+        REQUIRE(!w.logs || n == 1);
       }
     }
   }
