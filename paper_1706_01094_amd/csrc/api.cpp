@@ -16,6 +16,7 @@
 #include "device.h"
 #include "moments.h"
 #include "regplan.h"
+#include "regrun.h"
 #include "tables.h"
 
 using namespace mclg;
@@ -176,52 +177,22 @@ struct mclg_ctx {
     return sch.threads == 1024 && sch.lds_budget == Schedule().lds_budget &&
            (blocked || (drain_policy == MCLG_DRAIN_AUTO && grid_limit == 0));
   }
-  // `steps` steps of every replica in one launch of way `w`, with the logs
-  // lg.first, ... of them.
-  hipError_t launch_reg(const RegWay &w, uint32_t steps, const RegLog &lg) {
-    const StepLaunch a = launch_args(0, (uint32_t)tiles.size(), 0, n, t_pending);
-    const uint32_t *order = reinterpret_cast<const uint32_t *>(ws + lay.o_list);
-    RingLaunch r;
-    r.steps = steps;
-    if (w.kind == RegWay::kRing) {
-      r.order = order;
-      r.n = n;
-      r.team = w.team;
-      r.log = lg;
-      r.log.stride = log_records(w);
-      r.log.hold = w.team ? 0u : 256u * w.Q;
-      return launch_ring(stream, a, r, w.Q, kRegWaves);
-    }
-    TileLaunch tl;
-    tl.units = reinterpret_cast<const UnitDev *>(ws + lay.o_units);
-    tl.unit_first = reinterpret_cast<const uint32_t *>(ws + lay.o_ufirst);
-    tl.strips = reinterpret_cast<const StripDev *>(ws + lay.o_strips);
-    tl.strip_data = reinterpret_cast<uint16_t *>(ws + lay.o_sdata);
-    tl.n_strips = (uint32_t)units.strips.size();
-    tl.kh = w.kh;
-    tl.steps = steps;
-    tl.log = lg;
-    tl.log.stride = log_records(w);
-    hipError_t e = launch_tiles(stream, a, tl, w.Q, kRegWaves, (uint32_t)units.first.size() - 1, order);
-    if (!e && units.n_long < n) {  // the lattices too short for tiles, last in the order
-      r.order = order + units.n_long;
-      r.n = n - units.n_long;
-      e = launch_ring(stream, a, r, 2, kRegWaves);
-    }
-    return e;
+  RegBufs reg_bufs() const {
+    RegBufs b;
+    b.order = reinterpret_cast<const uint32_t *>(ws + lay.o_list);
+    b.n = n;
+    b.units = reinterpret_cast<const UnitDev *>(ws + lay.o_units);
+    b.first = reinterpret_cast<const uint32_t *>(ws + lay.o_ufirst);
+    b.strips = reinterpret_cast<const StripDev *>(ws + lay.o_strips);
+    b.strip_data = reinterpret_cast<uint16_t *>(ws + lay.o_sdata);
+    return b;
   }
-  // Records per log and lattice, and the logs a launch has room for (the
-  // second half of the overflow region; the tiles' private areas use the
-  // first).
-  uint32_t log_records(const RegWay &w) const {
-    return w.kind == RegWay::kTile ? ((uint32_t)units.first.size() - 1u) * kRegWaves
-           : w.team                ? 1u
-                                   : kRegWaves;
-  }
+  // The logs a launch has room for (the second half of the overflow region;
+  // the tiles' private areas use the first).
   static_assert((uint64_t)kPlanBlocks * kRegWaves * kOverflowPerWave * 16 <= kOverflowBytes / 2,
                 "the private areas stay in the first half");
   uint64_t log_room(const RegWay &w) const {
-    return kOverflowBytes / 2 / (sizeof(uint64_t) * kMom3Rec * n * log_records(w));
+    return kOverflowBytes / 2 / (sizeof(uint64_t) * kMom3Rec * n * log_records(w, units));
   }
   // `total` steps of every replica by way `w`; with every > 0 also the logs
   // after steps every, 2 every, ..., into out.
@@ -241,7 +212,9 @@ struct mclg_ctx {
         if (!lg.n) lg.first = 0;
       }
       hipError_t e = t_pending >= (1u << 30) ? flush_t() : hipSuccess;
-      if (!e) e = launch_reg(w, (uint32_t)k, lg);
+      if (!e)
+        e = launch_way(stream, launch_args(0, (uint32_t)tiles.size(), 0, n, t_pending), w, units,
+                       reg_bufs(), (uint32_t)k, lg);
       if (e) return e;
       t_pending += (uint32_t)k;
       for (auto &x : t) x += (int64_t)k;

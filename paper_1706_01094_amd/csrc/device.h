@@ -187,6 +187,7 @@ struct RegLog {
 struct RingLaunch {
   const uint32_t *order = nullptr;  // slots
   uint32_t n = 0, team = 0, steps = 0;
+  const uint32_t *limit = nullptr;  // by slot: steps of the launch that it takes (null: all)
   RegLog log;
 };
 // Tiles: block b advances units[unit_first[b] .. unit_first[b + 1]), each a
@@ -208,6 +209,7 @@ struct TileLaunch {
   const StripDev *strips = nullptr;
   uint16_t *strip_data = nullptr;   // n_strips x 3 x 2 kh
   uint32_t n_strips = 0, kh = 0, steps = 0;
+  const uint32_t *limit = nullptr;  // as in RingLaunch
   RegLog log;                       // one lattice only
 };
 constexpr uint32_t kRingExchangeBytes = 128;
@@ -241,6 +243,19 @@ hipError_t launch_histogram(hipStream_t s, const uint16_t *state, const SlotDev 
 // tslot[slot_first + i] += add for i < n
 hipError_t launch_add_t(hipStream_t s, uint32_t *tslot, uint32_t slot_first, uint32_t n,
                         uint32_t add);
+// tslot[i] += add[i].
+hipError_t launch_add_each(hipStream_t s, uint32_t *tslot, const uint32_t *add, uint32_t n);
+// Copies of `n` pieces of pinned host memory (whole words) to device memory.
+constexpr uint32_t kUploads = 24;
+struct Uploads {
+  struct {
+    void *dst;
+    const void *src;
+    uint64_t bytes;
+  } piece[kUploads];
+  uint32_t n = 0;
+};
+hipError_t launch_uploads(hipStream_t s, const Uploads &u);
 hipError_t launch_set_t(hipStream_t s, uint32_t *tslot, const uint32_t *slot_list, uint32_t n,
                         uint32_t value);
 

@@ -577,6 +577,20 @@ __global__ void k_add_t(uint32_t *tslot, uint32_t slot_first, uint32_t n, uint32
   for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
     tslot[slot_first + k] += add;
 }
+__global__ void k_add_each(uint32_t *tslot, const uint32_t *add, uint32_t n) {
+  for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
+    tslot[k] += add[k];
+}
+// Bound by the host link's latency: one launch for all pieces of an update
+// (blockIdx.y), read where the host wrote them, in place of a copy of its
+// own for each (about 7 us and 10 us of waiting between queues).
+__global__ void __launch_bounds__(256) k_uploads(Uploads u) {
+  const auto p = u.piece[blockIdx.y];
+  const uint64_t n = p.bytes / 4u, step = (uint64_t)gridDim.x * blockDim.x;
+  const uint32_t *const src = static_cast<const uint32_t *>(p.src);
+  uint32_t *const dst = static_cast<uint32_t *>(p.dst);
+  for (uint64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) dst[i] = src[i];
+}
 __global__ void k_set_t(uint32_t *tslot, const uint32_t *slot_list, uint32_t n, uint32_t value) {
   for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) tslot[slot_list[i]] = value;
 }
@@ -733,6 +747,19 @@ hipError_t launch_add_t(hipStream_t s, uint32_t *tslot, uint32_t slot_first, uin
                         uint32_t add) {
   if (n == 0 || add == 0) return hipSuccess;
   k_add_t<<<std::min<uint32_t>(64, (n + 255) / 256), 256, 0, s>>>(tslot, slot_first, n, add);
+  return hipGetLastError();
+}
+
+hipError_t launch_add_each(hipStream_t s, uint32_t *tslot, const uint32_t *add, uint32_t n) {
+  if (n == 0) return hipSuccess;
+  k_add_each<<<std::min<uint32_t>(64, (n + 255) / 256), 256, 0, s>>>(tslot, add, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_uploads(hipStream_t s, const Uploads &u) {
+  if (u.n == 0) return hipSuccess;
+  if (u.n > kUploads) return hipErrorInvalidValue;
+  k_uploads<<<dim3(32, u.n), 256, 0, s>>>(u);
   return hipGetLastError();
 }
 

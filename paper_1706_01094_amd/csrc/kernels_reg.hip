@@ -637,6 +637,7 @@ __global__ void __launch_bounds__(1024) k_ring(StepLaunch a, RingLaunch rl) {
   const SlotDev sl = a.slots[slot];
   const Mem M = slot_mem(a.state, sl);
   const uint32_t L = M.L;
+  const uint32_t steps = __builtin_amdgcn_readfirstlane(rl.limit ? rl.limit[slot] : rl.steps);
   const uint32_t t0 = __builtin_amdgcn_readfirstlane(a.tslot[slot] + a.t_off);
   const uint32_t first = w * 64u * S;               // the wave's first site
   const uint32_t held = (L + 64u * S - 1u) / (64u * S);  // waves that hold the lattice
@@ -684,7 +685,7 @@ __global__ void __launch_bounds__(1024) k_ring(StepLaunch a, RingLaunch rl) {
     ++logs;
     next = logs < rl.log.n ? next + rl.log.every : 0u;
   };
-  for (uint32_t s = 0; s < rl.steps; ++s) {
+  for (uint32_t s = 0; s < steps; ++s) {
     if (active) collide<Q, GAL, FIXED>(R, E, first, Sp, t0 + s, coll);
     if (ns) {
       if (LOG && s + 1u == next) log();
@@ -706,7 +707,7 @@ __global__ void __launch_bounds__(1024) k_ring(StepLaunch a, RingLaunch rl) {
     if (LOG && s + 1u == next) log();
   }
   if (active) {
-    const uint32_t tm = ns ? 0u : (uint32_t)(((uint64_t)t0 + rl.steps) % L);
+    const uint32_t tm = ns ? 0u : (uint32_t)(((uint64_t)t0 + steps) % L);
 #pragma unroll
     for (uint32_t c = 0; c < NC; ++c) {
       const uint32_t xc = x + NS * c;
@@ -791,7 +792,8 @@ __global__ void __launch_bounds__(1024) k_tile(StepLaunch a, TileLaunch tl) {
     const uint32_t L = M.L, Lp = (L + 7u) & ~7u;
     const uint32_t t0 = __builtin_amdgcn_readfirstlane(a.tslot[slot] + a.t_off);
     const uint32_t tm = ns ? 0u : t0 % L;
-    const uint32_t tmk = ns ? 0u : (uint32_t)(((uint64_t)t0 + tl.steps) % L);
+    const uint32_t steps = __builtin_amdgcn_readfirstlane(tl.limit ? tl.limit[slot] : tl.steps);
+    const uint32_t tmk = ns ? 0u : (uint32_t)(((uint64_t)t0 + steps) % L);
     // the unit's tiles: equal ones, a multiple of four (one or more per SIMD)
     const uint32_t len = ux1 - ux0, tmax = 64u * S - 2u * kh;
     const uint32_t nt = ((len + tmax - 1u) / tmax + 3u) / 4u * 4u;
@@ -895,7 +897,7 @@ __global__ void __launch_bounds__(1024) k_tile(StepLaunch a, TileLaunch tl) {
       const uint32_t pad = Lp - L, p0 = xt < kh ? kh - xt : Lp + kh - xt;
       const bool seam = pad != 0u && !ns && p0 < 64u * S && p0 > pad;
       uint32_t next = LOG ? tl.log.first : 0u, logs = 0;
-      for (uint32_t s = 0; s < tl.steps; ++s) {
+      for (uint32_t s = 0; s < steps; ++s) {
         collide<Q, GAL, FIXED>(R, E, xw, Sp, t0 + s, coll);
         if (!ns) {
         uint32_t up = 0, down = 0;
@@ -990,7 +992,8 @@ static bool log_ok(const RegLog &lg, uint32_t steps, uint32_t stride) {
 hipError_t launch_ring(hipStream_t s, const StepLaunch &a, const RingLaunch &rl, uint32_t Q,
                        uint32_t waves) {
   if (rl.n == 0 || rl.steps == 0) return hipSuccess;
-  if (waves < 1 || waves > 16 || rl.team > waves || !log_ok(rl.log, rl.steps, rl.team ? 1u : waves))
+  if (waves < 1 || waves > 16 || rl.team > waves || !log_ok(rl.log, rl.steps, rl.team ? 1u : waves) ||
+      (rl.log.n && rl.limit))
     return hipErrorInvalidValue;
   const dim3 grid(rl.team ? (rl.n + rl.team - 1u) / rl.team : rl.n), block(64u * waves);
   const uint32_t lds = reg_lds_bytes(a.lds_bytes, waves);
@@ -1006,7 +1009,7 @@ hipError_t launch_tiles(hipStream_t s, const StepLaunch &a, const TileLaunch &tl
   // lattice only
   if (waves < 1 || waves > 16 || tl.kh % 8u != 0u || tl.steps > tl.kh || 2u * tl.kh >= 256u * Q ||
       36u * tl.kh > 16u * kOverflowPerWave || grid * waves > kOverflowWaves ||
-      !log_ok(tl.log, tl.steps, grid * waves) || (tl.log.n && a.n_slots != 1u))
+      !log_ok(tl.log, tl.steps, grid * waves) || (tl.log.n && (a.n_slots != 1u || tl.limit)))
     return hipErrorInvalidValue;
   if (tl.n_strips) {
     k_strips<<<tl.n_strips, 64, 0, s>>>(a, tl);

@@ -2,9 +2,12 @@
 //
 // Jobs are queued on the host, admitted first-fit into a caller-owned device
 // arena (their state stays resident until they finish), and advanced together
-// by the batched stream+collide kernel: every launch covers the tiles of all
-// resident jobs, each job at its own step t (per-slot step counters on the
-// device).  A job's result depends only on (seed, job id, L, steps, rho, u0)
+// by launches that cover the sites of all resident jobs, each job at its own
+// step t (per-slot step counters on the device), several steps per launch on
+// sites held in registers.  A tick is played through on the host first (which
+// jobs finish when, and which queued ones take their places), then run in
+// waves: wave 0 the jobs resident at its start, each for all its steps of the
+// tick; wave w + 1 the jobs that took the places of wave w's finished ones.  A job's result depends only on (seed, job id, L, steps, rho, u0)
 // and the collision parameters, never on what else is resident.
 #include <hip/hip_runtime.h>
 
@@ -20,6 +23,8 @@
 #include "../../include/mclg.h"
 #include "device.h"
 #include "moments.h"
+#include "regplan.h"
+#include "regrun.h"
 #include "tables.h"
 
 using namespace mclg;
@@ -35,8 +40,10 @@ inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 struct SrvLayout {
   uint64_t o_ctrl, o_slots, o_tslot, o_tiles, o_list, o_pdesc, o_pool, o_idesc, o_over, o_ipool,
       o_rowdesc, o_thr, o_row16, bytes, max_tiles;
-  // moments of retiring jobs: segments, runs, partial records, results
-  uint64_t o_mseg, o_mrun, o_mslot, o_mpart, o_mout, max_mom_segs;
+  // steps on sites in registers: units, their blocks, strips and their counts
+  uint64_t o_units, o_ufirst, o_strips, o_sdata, o_limit;
+  // moments of retiring jobs: segments, runs, partial records
+  uint64_t o_mseg, o_mrun, o_mslot, o_mpart, max_mom_segs;
 };
 
 SrvLayout srv_layout(const mclg_server_config *cfg, const CollisionTables *tab,
@@ -61,11 +68,18 @@ SrvLayout srv_layout(const mclg_server_config *cfg, const CollisionTables *tab,
   l.o_mrun = take(sizeof(uint32_t) * (n + 1));
   l.o_mslot = take(sizeof(uint32_t) * n);
   l.o_mpart = take(sizeof(uint64_t) * kMom3Rec * l.max_mom_segs);
-  l.o_mout = take(sizeof(uint64_t) * kMom3Out * n);
   l.o_pdesc = take(sizeof(PoisDesc) * 3 * n);
   l.o_pool = take(sizeof(uint32_t) * kPoisCap * 3 * n);
   l.o_idesc = take(sizeof(ImageDesc) * n);
   l.o_over = take(kOverflowBytes);
+  // (the strips' counts in the half of the overflow region that launches on
+  // sites in registers leave free)
+  l.o_sdata = l.o_over + kOverflowBytes / 2;
+  static_assert((uint64_t)kMaxStrips * 6 * kMaxHalo * sizeof(uint16_t) <= kOverflowBytes / 2, "they fit");
+  l.o_units = take(sizeof(UnitDev) * max_units((uint32_t)n));
+  l.o_limit = take(sizeof(uint32_t) * n);
+  l.o_ufirst = take(sizeof(uint32_t) * (kPlanBlocks + 1));
+  l.o_strips = take(sizeof(StripDev) * kMaxStrips);
   l.o_ipool = take((uint64_t)kImage * n);
   l.o_rowdesc = take(sizeof(uint32_t) * tab->rowdesc.size());
   l.o_thr = take(sizeof(uint32_t) * (tab->thr.size() + 16));  // +16: see count_le_16
@@ -80,7 +94,18 @@ struct Resident {
   uint64_t bytes;
   uint64_t t = 0;
   bool active = false;
+  uint32_t wave = 0, run = 0;  // its entry in the running tick's waves
 };
+// What a wave does with one job.
+struct Run {
+  uint32_t slot = 0;
+  uint64_t job_id = 0, L = 0, off = 0;
+  double rho = 0, u0 = 0;
+  uint64_t steps = 0, t = 0;  // of the tick; the job's, when it finishes
+  size_t place = 0;           // in the order of finishing
+  bool fresh = false, finish = false;
+};
+constexpr size_t kPinned = 4u << 20;  // host memory that uploads and results go through
 
 }  // namespace
 
@@ -97,25 +122,35 @@ struct mclg_server {
   std::map<uint64_t, uint64_t> free_spans;  // offset -> bytes
   uint64_t arena_used = 0;
   std::vector<mclg_job_result> done;
-  // host mirrors of device tables (kept alive across async uploads)
-  std::vector<SlotDev> h_slots;
-  std::vector<TileDev> h_tiles;
-  std::vector<uint32_t> h_list;
-  std::vector<PoisDesc> h_pdesc;
-  std::vector<uint32_t> h_pool;
-  std::vector<ImageDesc> h_idesc;
-  MomPlan h_mplan;  // segments of the jobs being retired
+  std::vector<std::vector<Run>> waves;  // of the running tick
+  uint32_t next_wave = 0;               // of a job admitted now
+  // Pinned memory: pieces of it are handed out until it is used up, and again
+  // from its start after a synchronisation.
+  uint8_t *pin = nullptr;
+  size_t pin_used = 0;
+  Uploads pending;  // pieces to be copied before the next launch
+  // finished jobs whose moments the device writes to pinned memory
+  struct Finished {
+    const mclg_moments_t *at;
+    std::vector<std::pair<uint64_t, uint64_t>> jobs;  // (id, steps), in the moments' order
+    std::vector<size_t> place;                        // in the order of finishing
+  };
+  std::vector<Finished> finished;
+  size_t n_finished = 0;  // of the tick
   // Host images by the (rho, |u0|) they are built for: jobs of equal density
-  // and speed reuse one (the image depends on u0 only through |u0|), and the
-  // cached bytes stay alive while their upload is in flight.
+  // and speed reuse one (the image depends on u0 only through |u0|).
   struct CachedImage {
     std::vector<uint8_t> blob;
     uint32_t dir_bytes = 0, dim_a = 0, dim_c = 0, b_lo = 0, nb = 0, fixed = 0;
   };
   std::map<std::pair<double, double>, CachedImage> image_cache;
-  uint32_t n_tiles = 0, n_active = 0;
+  uint32_t n_active = 0;
   uint32_t lds_bytes = 16, max_blocks = 1, image_budget = kImage, n_cu = 1;
   int last_hip = 0;
+
+  ~mclg_server() {
+    if (pin) (void)hipHostFree(pin);
+  }
 
   uint32_t *err() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl); }
   uint32_t *ticket() { return err() + 1; }
@@ -123,6 +158,7 @@ struct mclg_server {
   uint32_t *d_tslot() { return reinterpret_cast<uint32_t *>(ws + lay.o_tslot); }
   TileDev *d_tiles() { return reinterpret_cast<TileDev *>(ws + lay.o_tiles); }
   uint32_t *d_list() { return reinterpret_cast<uint32_t *>(ws + lay.o_list); }
+  uint32_t *d_limit() { return reinterpret_cast<uint32_t *>(ws + lay.o_limit); }
   TableDev table() {
     TableDev d;
     d.rowdesc = reinterpret_cast<const uint2 *>(ws + lay.o_rowdesc);
@@ -139,6 +175,59 @@ struct mclg_server {
   hipError_t up(void *dst, const void *src, size_t bytes) {
     return bytes ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) : hipSuccess;
   }
+
+  // ---- uploads and results ------------------------------------------------
+  // Waits for the device, takes the results it wrote, and frees the pinned
+  // memory.
+  hipError_t drain() {
+    hipError_t e = hipStreamSynchronize(s);
+    if (e) return e;
+    for (const Finished &f : finished)
+      for (size_t k = 0; k < f.jobs.size(); ++k) {
+        mclg_job_result &res = done[f.place[k]];
+        std::memset(&res, 0, sizeof(res));
+        res.job_id = f.jobs[k].first;
+        res.moments = f.at[k];
+        res.moments.t = (int64_t)f.jobs[k].second;
+      }
+    finished.clear();
+    pin_used = 0;
+    return hipSuccess;
+  }
+  hipError_t send() {
+    hipError_t e = launch_uploads(s, pending);
+    pending.n = 0;
+    return e;
+  }
+  // `bytes` (at most kPinned) of pinned memory.
+  hipError_t take_pinned(size_t bytes, void *&at) {
+    if (pin_used + bytes > kPinned) {
+      hipError_t e = send();
+      if (!e) e = drain();
+      if (e) return e;
+    }
+    at = pin + pin_used;
+    pin_used += align_up(bytes, 64);
+    return hipSuccess;
+  }
+  // A copy of host data to the device, before the next launch after send().
+  hipError_t put(void *dst, const void *src, size_t bytes) {
+    for (size_t at = 0; at < bytes;) {
+      const size_t n = std::min<size_t>(bytes - at, kPinned / 4);
+      void *p = nullptr;
+      hipError_t e = pending.n == kUploads ? send() : hipSuccess;
+      if (!e) e = take_pinned(n, p);
+      if (e) return e;
+      std::memcpy(p, static_cast<const uint8_t *>(src) + at, n);
+      pending.piece[pending.n].dst = static_cast<uint8_t *>(dst) + at;
+      pending.piece[pending.n].src = p;
+      pending.piece[pending.n++].bytes = n;
+      at += n;
+    }
+    return hipSuccess;
+  }
+  template <class T>
+  hipError_t put(void *dst, const std::vector<T> &v) { return put(dst, v.data(), sizeof(T) * v.size()); }
 
   bool alloc(uint64_t bytes, uint64_t &off) {
     for (auto it = free_spans.begin(); it != free_spans.end(); ++it) {
@@ -178,17 +267,16 @@ struct mclg_server {
     a.slots = d_slots();
     a.tslot = d_tslot();
     a.tiles = d_tiles();
-    a.n_tiles = n_tiles;
+    a.n_tiles = 0;
     a.slot_list = d_list();
     a.slot_first = 0;
-    a.n_slots = n_active;
+    a.n_slots = 0;
     a.ticket = ticket();
     a.t_off = 0;
     a.single = 0;
     a.err = err();
     a.tab = table();
     a.p = params();
-    a.p.drain = auto_drain(arena_used);  // by the resident jobs' state
     a.images = d_idesc();
     a.image_pool = ws + lay.o_ipool;
     a.overflow = reinterpret_cast<uint4 *>(ws + lay.o_over);
@@ -209,28 +297,24 @@ struct mclg_server {
     return p;
   }
 
-  // Rebuild the tile and slot lists of the resident jobs and upload them.
-  hipError_t rebuild_lists() {
-    h_tiles.clear();
-    h_list.clear();
-    const uint32_t ts = sch.tile_sites();
-    for (uint32_t i = 0; i < slot.size(); ++i) {
-      if (!slot[i].active) continue;
-      h_list.push_back(i);
-      const uint32_t next = (uint32_t)(h_tiles.size() + (slot[i].job.L + ts - 1) / ts);
-      for (uint64_t x0 = 0; x0 < slot[i].job.L; x0 += ts) h_tiles.push_back(TileDev{i, (uint32_t)x0, next, 0});
-    }
-    if (h_tiles.size() > lay.max_tiles) return hipErrorInvalidValue;
-    n_tiles = (uint32_t)h_tiles.size();
-    n_active = (uint32_t)h_list.size();
-    hipError_t e = up(d_tiles(), h_tiles.data(), sizeof(TileDev) * h_tiles.size());
-    if (!e) e = up(d_list(), h_list.data(), sizeof(uint32_t) * h_list.size());
-    return e;
+  // ---- a tick on the host -------------------------------------------------
+  void enter(uint32_t i, bool fresh, uint32_t wave) {
+    Resident &r = slot[i];
+    if (waves.size() <= wave) waves.resize(wave + 1u);
+    r.wave = wave;
+    r.run = (uint32_t)waves[wave].size();
+    Run x;
+    x.slot = i;
+    x.job_id = r.job.job_id;
+    x.L = r.job.L;
+    x.off = r.arena_off;
+    x.rho = r.job.rho;
+    x.u0 = r.job.u0;
+    x.fresh = fresh;
+    waves[wave].push_back(x);
   }
-
   // Admit queued jobs (FIFO, stop at the first that does not fit).
-  int admit() {
-    std::vector<uint32_t> fresh;
+  void admit() {
     while (!queue.empty()) {
       const mclg_job &j = queue.front();
       uint32_t free_slot = UINT32_MAX;
@@ -245,36 +329,68 @@ struct mclg_server {
       r.bytes = bytes;
       r.t = 0;
       r.active = true;
-      SlotDev &sd = h_slots[free_slot];
-      sd.off = off / sizeof(uint16_t);
+      ++n_active;
+      enter(free_slot, true, next_wave);
+      queue.pop_front();
+    }
+  }
+  void advance(uint64_t k) {
+    for (auto &r : slot)
+      if (r.active) {
+        r.t += k;
+        waves[r.wave][r.run].steps += k;
+      }
+  }
+  // Free the slots of finished jobs.  What is admitted from here on may take
+  // their places, so it runs after them.
+  void retire() {
+    for (auto &r : slot)
+      if (r.active && r.t >= r.job.steps) {
+        Run &x = waves[r.wave][r.run];
+        x.finish = true;
+        x.t = r.t;
+        x.place = n_finished++;
+        next_wave = std::max(next_wave, r.wave + 1u);
+        r.active = false;
+        --n_active;
+        release(r.arena_off, r.bytes);
+      }
+  }
+
+  // ---- a wave on the device -----------------------------------------------
+  hipError_t start_jobs(const std::vector<Run> &wave) {
+    std::vector<uint32_t> fresh, pool;
+    std::vector<TileDev> tiles;
+    const uint32_t ts = sch.tile_sites();
+    hipError_t e = hipSuccess;
+    for (const Run &r : wave) {
+      if (!r.fresh) continue;
+      SlotDev sd{};
+      sd.off = r.off / sizeof(uint16_t);
       sd.dense = 0;
-      sd.L = (uint32_t)j.L;
-      sd.stride = (uint32_t)align_up(j.L, kPad);
-      sd.rid = (uint32_t)j.job_id;
+      sd.L = (uint32_t)r.L;
+      sd.stride = (uint32_t)align_up(r.L, kPad);
+      sd.rid = (uint32_t)r.job_id;
       sd.pad = 0;
       double mu[3];
-      feq(j.rho, j.u0, mu);
+      feq(r.rho, r.u0, mu);
+      PoisDesc pd[3];
       for (int i = 0; i < 3; ++i) {
         uint32_t k_lo = 0;
         std::vector<uint64_t> full;
         poisson_full(mu[i], k_lo, full);
         CompactLaw cl = compact(k_lo, full);
-        PoisDesc &d = h_pdesc[3 * free_slot + i];
-        d.off = (3 * free_slot + i) * kPoisCap;
-        d.k_first = cl.k_first;
-        d.nthr = (uint32_t)cl.thr.size();
-        std::copy(cl.thr.begin(), cl.thr.end(), h_pool.begin() + d.off);
+        pd[i].off = (uint32_t)pool.size();
+        pd[i].k_first = cl.k_first;
+        pd[i].nthr = (uint32_t)cl.thr.size();
+        pool.insert(pool.end(), cl.thr.begin(), cl.thr.end());
       }
       // collision image for this job's density and speed (cached on the host)
-      const auto key = std::make_pair(j.rho, std::fabs(j.u0));
+      const auto key = std::make_pair(r.rho, std::fabs(r.u0));
       auto ci = image_cache.find(key);
       if (ci == image_cache.end()) {
-        if (image_cache.size() >= kImageCacheMax) {
-          hipError_t e = hipStreamSynchronize(s);  // no upload may still read them
-          if (e) return hip(e);
-          image_cache.clear();
-        }
-        LdsImage im = build_image(*tab, j.rho, std::fabs(j.u0), image_budget);
+        if (image_cache.size() >= kImageCacheMax) image_cache.clear();
+        LdsImage im = build_image(*tab, r.rho, std::fabs(r.u0), image_budget);
         CachedImage c;
         c.blob = im.blob();
         c.dir_bytes = im.dir_bytes();
@@ -286,8 +402,8 @@ struct mclg_server {
         ci = image_cache.emplace(key, std::move(c)).first;
       }
       const CachedImage &img = ci->second;
-      ImageDesc &idd = h_idesc[free_slot];
-      idd.off = (uint64_t)free_slot * kImage;
+      ImageDesc idd{};
+      idd.off = (uint64_t)r.slot * kImage;
       idd.bytes = (uint32_t)img.blob.size();
       idd.dir_bytes = img.dir_bytes;
       idd.dim_a = img.dim_a;
@@ -295,91 +411,179 @@ struct mclg_server {
       idd.b_lo = img.b_lo;
       idd.nb = img.nb;
       idd.fixed = img.fixed;
-      if (idd.bytes) {
-        hipError_t e = hipMemcpyAsync(ws + lay.o_ipool + idd.off, img.blob.data(), img.blob.size(),
-                                      hipMemcpyHostToDevice, s);
-        if (e) return hip(e);
-      }
-      fresh.push_back(free_slot);
-      queue.pop_front();
+      if (!e) e = put(ws + lay.o_ipool + idd.off, img.blob);
+      if (!e) e = put(d_slots() + r.slot, &sd, sizeof(sd));
+      if (!e) e = put(d_idesc() + r.slot, &idd, sizeof(idd));
+      if (!e) e = put(ws + lay.o_pdesc + sizeof(PoisDesc) * 3 * r.slot, pd, sizeof(pd));
+      fresh.push_back(r.slot);
+      for (uint64_t x0 = 0; x0 < r.L; x0 += ts) tiles.push_back(TileDev{r.slot, (uint32_t)x0, 0, 0});
     }
-    if (fresh.empty()) return MCLG_OK;
-    // Upload the changed host mirrors; then initialise the new jobs only.
-    std::vector<TileDev> init_tiles;
-    const uint32_t ts = sch.tile_sites();
-    for (uint32_t i : fresh)
-      for (uint64_t x0 = 0; x0 < slot[i].job.L; x0 += ts) init_tiles.push_back(TileDev{i, (uint32_t)x0, 0, 0});
-    if (init_tiles.size() > lay.max_tiles) return MCLG_E_INVAL;
-    hipError_t e = hipSuccess;
-    for (uint32_t i : fresh) {  // only the admitted slots' entries change
-      if (!e) e = up(d_slots() + i, &h_slots[i], sizeof(SlotDev));
-      if (!e) e = up(d_idesc() + i, &h_idesc[i], sizeof(ImageDesc));
-      if (!e) e = up(ws + lay.o_pdesc + sizeof(PoisDesc) * 3 * i, &h_pdesc[3 * i], sizeof(PoisDesc) * 3);
-      if (!e) e = up(ws + lay.o_pool + sizeof(uint32_t) * kPoisCap * 3 * i,
-                     &h_pool[(size_t)kPoisCap * 3 * i], sizeof(uint32_t) * kPoisCap * 3);
-    }
-    // fresh slot ids and their tiles go through the list/tile areas, which
-    // are rebuilt right after
-    if (!e) e = up(d_list(), fresh.data(), sizeof(uint32_t) * fresh.size());
-    if (!e) e = up(d_tiles(), init_tiles.data(), sizeof(TileDev) * init_tiles.size());
+    if (fresh.empty() || e) return e;
+    if (tiles.size() > lay.max_tiles) return hipErrorInvalidValue;
+    e = put(ws + lay.o_pool, pool);
+    if (!e) e = put(d_list(), fresh);
+    if (!e) e = put(d_tiles(), tiles);
+    if (!e) e = send();
     if (!e) e = launch_set_t(s, d_tslot(), d_list(), (uint32_t)fresh.size(), 0u);
     if (!e)
-      e = launch_init_poisson(s, arena, d_slots(), d_tslot(), d_tiles(), (uint32_t)init_tiles.size(),
-                              ts, reinterpret_cast<const PoisDesc *>(ws + lay.o_pdesc),
+      e = launch_init_poisson(s, arena, d_slots(), d_tslot(), d_tiles(), (uint32_t)tiles.size(), ts,
+                              reinterpret_cast<const PoisDesc *>(ws + lay.o_pdesc),
                               reinterpret_cast<const uint32_t *>(ws + lay.o_pool), cfg.seed, err());
-    if (!e) e = hipStreamSynchronize(s);
-    if (!e) e = rebuild_lists();
-    if (!e) e = hipStreamSynchronize(s);
-    return hip(e);
+    return e;
   }
 
-  // Moments (with the state digest) of finished jobs, then free their slots.
-  int retire() {
+  // The steps of a wave's jobs: launches that each job takes part in for as
+  // many steps as it has left.
+  hipError_t step_jobs(std::vector<Run> &wave) {
+    std::stable_sort(wave.begin(), wave.end(), [](const Run &x, const Run &y) { return x.L > y.L; });
+    std::vector<uint64_t> left(wave.size());
+    for (size_t i = 0; i < wave.size(); ++i) left[i] = wave[i].steps;
+    RegBufs b;
+    b.order = d_list();
+    b.units = reinterpret_cast<const UnitDev *>(ws + lay.o_units);
+    b.first = reinterpret_cast<const uint32_t *>(ws + lay.o_ufirst);
+    b.strips = reinterpret_cast<const StripDev *>(ws + lay.o_strips);
+    b.strip_data = reinterpret_cast<uint16_t *>(ws + lay.o_sdata);
+    b.limit = d_limit();
+    UnitPlan units;
+    std::vector<RegWay> ways;
+    std::vector<uint32_t> list, limit(slot.size());
+    std::vector<uint64_t> sites;
+    uint64_t total = 0;
+    bool uploaded = false;  // the list and the units
+    for (;;) {
+      uint64_t most = 0, least = ~0ull;
+      size_t n = 0;
+      for (uint64_t k : left)
+        if (k) {
+          most = std::max(most, k);
+          least = std::min(least, k);
+          ++n;
+        }
+      if (n == 0) return hipSuccess;
+      if (n != list.size()) {  // (jobs leave and none joins)
+        list.clear();
+        sites.clear();
+        total = 0;
+        for (size_t i = 0; i < wave.size(); ++i)
+          if (left[i]) {
+            list.push_back(wave[i].slot);
+            sites.push_back(wave[i].L);
+            total += wave[i].L;
+          }
+        units = plan_units(sites.data(), (uint32_t)n, n_cu);
+        if (units.units.size() > max_units((uint32_t)slot.size())) return hipErrorInvalidValue;
+        ways = plan_ways(units, sites.data(), (uint32_t)n, n_cu, false, false, images_fixed(cfg.C));
+        for (UnitDev &u : units.units) u.slot = list[u.slot];
+        for (StripDev &x : units.strips) x.slot = list[x.slot];
+        uploaded = false;
+      }
+      StepLaunch a = launch_args();
+      a.n_slots = (uint32_t)n;
+      const RegWay *w = pick_way(ways, most, false, single_step_us(total));
+      hipError_t e = hipSuccess;
+      uint64_t m = least;  // the launch's steps
+      if (!w) {
+        std::vector<TileDev> tiles;
+        const uint32_t ts = sch.tile_sites();
+        for (size_t i = 0; i < n; ++i) {
+          const uint32_t next = (uint32_t)(tiles.size() + (sites[i] + ts - 1) / ts);
+          for (uint64_t x0 = 0; x0 < sites[i]; x0 += ts) tiles.push_back(TileDev{list[i], (uint32_t)x0, next, 0});
+        }
+        if (tiles.size() > lay.max_tiles) return hipErrorInvalidValue;
+        a.n_tiles = (uint32_t)tiles.size();
+        a.p.drain = auto_drain(6 * total);  // by the jobs' state
+        e = put(d_tiles(), tiles);
+        if (!e) e = put(d_list(), list);
+        if (!e) e = send();
+        for (uint64_t i = 0; i < m && !e; ++i) e = launch_step(sch, s, a);
+      } else {
+        const uint64_t launches = (most + w->most - 1) / w->most;
+        m = (most + launches - 1) / launches;
+        std::fill(limit.begin(), limit.end(), 0u);
+        for (size_t i = 0; i < wave.size(); ++i) limit[wave[i].slot] = (uint32_t)std::min(left[i], m);
+        e = put(d_limit(), limit);
+        if (!uploaded) {
+          if (!e) e = put(d_list(), list);
+          if (!e) e = put(ws + lay.o_units, units.units);
+          if (!e) e = put(ws + lay.o_ufirst, units.first);
+          if (!e) e = put(ws + lay.o_strips, units.strips);
+          uploaded = true;
+        }
+        if (!e) e = send();
+        b.n = (uint32_t)n;
+        if (!e) e = launch_way(s, a, *w, units, b, (uint32_t)m, RegLog());
+        if (!e) e = launch_add_each(s, d_tslot(), d_limit(), (uint32_t)slot.size());
+      }
+      if (e) return e;
+      for (uint64_t &k : left) k -= std::min(k, m);
+    }
+  }
+
+  // Moments (with the state digest) of a wave's finished jobs.
+  hipError_t finish_jobs(const std::vector<Run> &wave) {
     std::vector<uint32_t> fin;
     std::vector<uint64_t> sites;
-    for (uint32_t i = 0; i < slot.size(); ++i)
-      if (slot[i].active && slot[i].t >= slot[i].job.steps) {
-        fin.push_back(i);
-        sites.push_back(slot[i].job.L);
+    Finished f;
+    for (const Run &r : wave)
+      if (r.finish) {
+        fin.push_back(r.slot);
+        sites.push_back(r.L);
+        f.jobs.emplace_back(r.job_id, r.t);
+        f.place.push_back(r.place);
       }
-    if (fin.empty()) return MCLG_OK;
-    h_mplan = plan_moments(fin.data(), sites.data(), (uint32_t)fin.size());
-    if (h_mplan.segs.size() > lay.max_mom_segs) return MCLG_E_INTERNAL;
-    MomArgs m;
-    m.state = arena;
-    m.slots = d_slots();
-    m.tslot = d_tslot();
-    m.segs = reinterpret_cast<const MomSeg *>(ws + lay.o_mseg);
-    m.n_segs = (uint32_t)h_mplan.segs.size();
-    m.run_seg = reinterpret_cast<const uint32_t *>(ws + lay.o_mrun);
-    m.run_slot = reinterpret_cast<const uint32_t *>(ws + lay.o_mslot);
-    m.n_runs = (uint32_t)fin.size();
-    m.digest = 1u;
-    m.partial = reinterpret_cast<unsigned long long *>(ws + lay.o_mpart);
-    m.out = reinterpret_cast<long long *>(ws + lay.o_mout);
-    hipError_t e = up(ws + lay.o_mseg, h_mplan.segs.data(), sizeof(MomSeg) * h_mplan.segs.size());
-    if (!e) e = up(ws + lay.o_mrun, h_mplan.run_seg.data(), 4 * h_mplan.run_seg.size());
-    if (!e) e = up(ws + lay.o_mslot, h_mplan.run_slot.data(), 4 * h_mplan.run_slot.size());
-    if (!e) e = launch_moments3(s, m);
-    std::vector<mclg_moments_t> h(fin.size());
-    if (!e) e = hipMemcpyAsync(h.data(), ws + lay.o_mout, sizeof(mclg_moments_t) * h.size(),
-                               hipMemcpyDeviceToHost, s);
-    if (!e) e = hipStreamSynchronize(s);
-    if (e) return hip(e);
-    for (size_t k = 0; k < fin.size(); ++k) {
-      const uint32_t i = fin[k];
-      mclg_job_result res;
-      std::memset(&res, 0, sizeof(res));
-      res.job_id = slot[i].job.job_id;
-      res.moments = h[k];
-      res.moments.t = (int64_t)slot[i].t;
-      done.push_back(res);
-      slot[i].active = false;
-      release(slot[i].arena_off, slot[i].bytes);
+    // (a slot is in a wave once, and its results fit the pinned memory)
+    const size_t most = kPinned / 4 / sizeof(mclg_moments_t);
+    for (size_t i0 = 0; i0 < fin.size(); i0 += most) {
+      const uint32_t n = (uint32_t)std::min(most, fin.size() - i0);
+      const MomPlan plan = plan_moments(fin.data() + i0, sites.data() + i0, n);
+      if (plan.segs.size() > lay.max_mom_segs) return hipErrorInvalidValue;
+      MomArgs m;
+      m.state = arena;
+      m.slots = d_slots();
+      m.tslot = d_tslot();
+      m.segs = reinterpret_cast<const MomSeg *>(ws + lay.o_mseg);
+      m.n_segs = (uint32_t)plan.segs.size();
+      m.run_seg = reinterpret_cast<const uint32_t *>(ws + lay.o_mrun);
+      m.run_slot = reinterpret_cast<const uint32_t *>(ws + lay.o_mslot);
+      m.n_runs = n;
+      m.digest = 1u;
+      m.partial = reinterpret_cast<unsigned long long *>(ws + lay.o_mpart);
+      hipError_t e = put(ws + lay.o_mseg, plan.segs);
+      if (!e) e = put(ws + lay.o_mrun, plan.run_seg);
+      if (!e) e = put(ws + lay.o_mslot, plan.run_slot);
+      void *at = nullptr;
+      if (!e) e = take_pinned(sizeof(mclg_moments_t) * n, at);
+      if (!e) e = send();
+      m.out = static_cast<long long *>(at);
+      if (!e) e = launch_moments3(s, m);
+      if (e) return e;
+      Finished part;
+      part.at = static_cast<const mclg_moments_t *>(at);
+      part.jobs.assign(f.jobs.begin() + i0, f.jobs.begin() + i0 + n);
+      part.place.assign(f.place.begin() + i0, f.place.begin() + i0 + n);
+      finished.push_back(std::move(part));
     }
-    e = rebuild_lists();
-    if (!e) e = hipStreamSynchronize(s);
-    return hip(e);
+    return hipSuccess;
+  }
+
+  // What the tick did on the host, on the device.
+  hipError_t run_waves() {
+    const size_t before = done.size();
+    done.resize(before + n_finished);
+    hipError_t e = hipSuccess;
+    for (auto &wave : waves) {
+      for (Run &r : wave) r.place += before;
+      if (!e) e = start_jobs(wave);
+      if (!e) e = step_jobs(wave);
+      if (!e) e = finish_jobs(wave);
+    }
+    if (!e && !finished.empty()) e = drain();
+    if (e) {  // no results of this tick
+      finished.clear();
+      done.resize(before);
+    }
+    return e;
   }
 };
 
@@ -411,10 +615,6 @@ int mclg_server_create(const mclg_server_config *cfg, mclg_server **out) {
   sv->arena = reinterpret_cast<uint16_t *>(cfg->arena);
   sv->s = reinterpret_cast<hipStream_t>(cfg->stream);
   sv->slot.resize(cfg->max_slots);
-  sv->h_slots.assign(cfg->max_slots, SlotDev{});
-  sv->h_pdesc.assign(3ull * cfg->max_slots, PoisDesc{});
-  sv->h_pool.assign((size_t)kPoisCap * 3 * cfg->max_slots, 0);
-  sv->h_idesc.assign(cfg->max_slots, ImageDesc{});
   {
     int dev = 0, v = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -425,11 +625,16 @@ int mclg_server_create(const mclg_server_config *cfg, mclg_server **out) {
     if (!e) sv->n_cu = (uint32_t)std::max(1, v);
     if (!e && sv->n_cu > 256) return MCLG_E_UNSUPPORTED;  // overflow region sized for 256 CUs
     sv->lds_bytes = std::max<uint32_t>(64, sv->image_budget);  // the smallest image is 48 bytes
+    if (!e) e = reg_setup(sv->lds_bytes);
     if (!e) e = step_occupancy(sv->sch, sv->lds_bytes, sv->n_cu, sv->max_blocks);
     if (e) return sv->hip(e);
   }
   uint64_t usable = cfg->arena_bytes / 256 * 256;
   if (usable) sv->free_spans[0] = usable;
+  {
+    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&sv->pin), kPinned, hipHostMallocDefault);
+    if (e) return sv->hip(e);
+  }
   std::vector<uint32_t> ctrl(64, 0), tz(cfg->max_slots, 0);
   const CollisionTables &t = *sv->tab;
   hipError_t e = sv->up(sv->ws + sv->lay.o_ctrl, ctrl.data(), 256);
@@ -461,31 +666,22 @@ int mclg_server_submit(mclg_server *sv, const mclg_job *job) {
 
 int mclg_server_tick(mclg_server *sv, uint32_t k) {
   if (!sv) return MCLG_E_INVAL;
-  int rc = sv->admit();
-  if (rc) return rc;
-  uint32_t left = k;
-  while (left > 0) {
-    if (sv->n_active == 0) {
-      rc = sv->admit();
-      if (rc) return rc;
-      if (sv->n_active == 0) break;
-    }
+  sv->waves.clear();
+  sv->next_wave = 0;
+  sv->n_finished = 0;
+  for (uint32_t i = 0; i < sv->slot.size(); ++i)
+    if (sv->slot[i].active) sv->enter(i, false, 0);
+  sv->admit();
+  for (uint32_t left = k; left > 0 && sv->n_active > 0;) {
     uint64_t chunk = left;
     for (auto &r : sv->slot)
       if (r.active) chunk = std::min<uint64_t>(chunk, r.job.steps - r.t);
-    for (uint64_t i = 0; i < chunk; ++i) {
-      hipError_t e = launch_step(sv->sch, sv->s, sv->launch_args());
-      if (e) return sv->hip(e);
-    }
-    for (auto &r : sv->slot)
-      if (r.active) r.t += chunk;
+    sv->advance(chunk);
     left -= (uint32_t)chunk;
-    rc = sv->retire();
-    if (rc) return rc;
-    rc = sv->admit();
-    if (rc) return rc;
+    sv->retire();
+    sv->admit();
   }
-  return MCLG_OK;
+  return sv->hip(sv->run_waves());
 }
 
 int mclg_server_poll(mclg_server *sv, mclg_job_result *out, uint32_t cap, uint32_t *n_out) {
@@ -497,7 +693,7 @@ int mclg_server_poll(mclg_server *sv, mclg_job_result *out, uint32_t cap, uint32
   uint32_t err = 0;
   hipError_t e = hipMemcpy(&err, sv->err(), sizeof(err), hipMemcpyDeviceToHost);
   if (e) return sv->hip(e);
-  return (err & 4u) ? MCLG_E_INTERNAL : err ? MCLG_E_RANGE : MCLG_OK;
+  return err ? MCLG_E_RANGE : MCLG_OK;
 }
 
 int mclg_server_stats(const mclg_server *sv, uint64_t *queued, uint64_t *resident,
