@@ -19,7 +19,6 @@ constexpr int kVx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 constexpr int kVy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 constexpr uint64_t kW1296[9] = {576, 144, 144, 144, 144, 36, 36, 36, 36};  // 1296 w_i
 constexpr uint64_t kPad = 128;
-constexpr uint32_t kTile = 256;
 constexpr uint32_t kPoisCap9 = 1024;
 
 inline uint64_t up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
@@ -92,22 +91,35 @@ bool build_rules9(const uint32_t *lam, std::vector<uint32_t> &rules, uint32_t &D
   return true;
 }
 
-std::vector<uint32_t> device_rules9(const std::vector<uint32_t> &rules) {
-  std::vector<uint32_t> dev(81 * kRule9DevWords, 0u);
-  for (int p = 0; p < 81; ++p) {
-    const uint32_t *e = &rules[p * kRule9Words];
-    uint32_t *o = &dev[p * kRule9DevWords];
-    for (int q = 0; q < 4; ++q) o[q] = e[q];
-    for (int q = 0; q < 5; ++q) {
-      int32_t K = 0;
-      uint16_t dk[8];
-      for (int j = 0; j < 8; ++j) {
-        K += (int32_t)((e[4 + q] >> (3 * j)) & 7u) - 2;
-        dk[j] = (uint16_t)K;
+std::vector<uint32_t> device_rules9(const std::vector<uint32_t> &rules, uint32_t D, uint32_t &Dq) {
+  std::vector<uint32_t> dev(kRule9DevWords, 0u);
+  uint32_t g = D;
+  for (int p = 0; p < 81; ++p)
+    for (int q = 0; q < 4; ++q) g = std::gcd(g, rules[p * kRule9Words + q]);
+  Dq = D / g;
+  for (int i = 0; i < 9; ++i)
+    for (int j = 0; j < 9; ++j) {
+      const uint32_t *e = &rules[(i * 9 + j) * kRule9Words];
+      uint32_t *wide = &dev[kRule9WideAt + (9 * i + j) * kRule9Wide];
+      uint32_t *half = &dev[kRule9HalfAt + (16 * i + j) * kRule9Half];
+      uint32_t *byte = &dev[kRule9ByteAt + (16 * i + j) * kRule9Byte];
+      for (int q = 0; q < 4; ++q) {
+        wide[q] = e[q];
+        // (used where Dq, and so every c_q / g, is at most 2^15)
+        half[q / 2] += ((kRule9MaxPacked - e[q] / g) & 0xFFFFu) << (16 * (q & 1));
       }
-      for (int m = 0; m < 4; ++m) o[4 + 4 * q + m] = dk[2 * m] | (uint32_t)dk[2 * m + 1] << 16;
+      byte[0] = half[0];
+      byte[1] = half[1];
+      for (int q = 0; q < 5; ++q) {
+        int32_t K = 0;
+        for (int v = 0; v < 8; ++v) {
+          K += (int32_t)((e[4 + q] >> (3 * v)) & 7u) - 2;
+          wide[4 + 4 * q + v / 2] |= (uint32_t)(uint16_t)K << (16 * (v & 1));
+          half[2 + 4 * q + v / 2] -= (uint32_t)K << (16 * (v & 1));
+          byte[2 + 2 * q + v / 4] -= (uint32_t)K << (8 * (v & 3));
+        }
+      }
     }
-  }
   return dev;
 }
 
@@ -115,7 +127,7 @@ int d2q9_layout(const mclg_config *cfg, D2Ctx &d) {
   if (!cfg->Ly || !cfg->lambda9 || cfg->C < 0 || cfg->C > 4096) return MCLG_E_INVAL;
   if (cfg->flags & ~(uint32_t)MCLG_FLAG_NO_STREAM) return MCLG_E_INVAL;
   if (!build_rules9(cfg->lambda9, d.rules, d.D)) return MCLG_E_INVAL;
-  d.rules_dev = device_rules9(d.rules);
+  d.rules_dev = device_rules9(d.rules, d.D, d.Dq);
   d.n = cfg->n_replicas;
   d.flags = cfg->flags;
   d.C = cfg->C;
@@ -144,7 +156,13 @@ int d2q9_layout(const mclg_config *cfg, D2Ctx &d) {
     d.dense[r] = dense;
     elems += 9 * stride;
     dense += 9 * S;
-    for (uint64_t s0 = 0; s0 < S; s0 += kTile) d.tiles.push_back(Tile9{r, (uint32_t)s0});
+    uint32_t x0 = 0;
+    const uint32_t dx = kTileSites9 % (uint32_t)Lx;
+    for (uint64_t s0 = 0; s0 < S; s0 += kTileSites9) {
+      d.tiles.push_back(Tile9{r, (uint32_t)s0, x0});
+      x0 += dx;
+      x0 -= x0 >= Lx ? (uint32_t)Lx : 0u;
+    }
   }
   d.state_bytes = elems * sizeof(uint16_t);
   uint64_t o = 0;
@@ -260,6 +278,7 @@ int d2q9_step(D2Ctx &d, uint64_t n_steps) {
   a.err = reinterpret_cast<uint32_t *>(d.ws + d.o_err);
   a.seed = d.seed;
   a.D = d.D;
+  a.Dq = d.Dq;
   a.no_stream = (d.flags & MCLG_FLAG_NO_STREAM) ? 1u : 0u;
   a.C = d.C;
   for (uint64_t i = 0; i < n_steps; ++i) {

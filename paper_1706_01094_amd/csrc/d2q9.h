@@ -13,7 +13,7 @@
 namespace mclg {
 
 struct D2Ctx {
-  uint32_t n = 0, flags = 0, D = 0;
+  uint32_t n = 0, flags = 0, D = 0, Dq = 0;
   int32_t C = 0;
   uint64_t seed = 0;
   int64_t t = 0;
@@ -21,7 +21,7 @@ struct D2Ctx {
   std::vector<Rep9> reps;
   std::vector<Tile9> tiles;
   std::vector<uint32_t> rules;      // 81 x kRule9Words
-  std::vector<uint32_t> rules_dev;  // 81 x kRule9DevWords
+  std::vector<uint32_t> rules_dev;  // kRule9DevWords
   uint64_t state_bytes = 0, ws_bytes = 0;
   uint64_t o_err = 0, o_reps = 0, o_tiles = 0, o_rules = 0, o_pdesc = 0, o_pool = 0,
            o_dense = 0;
@@ -38,13 +38,25 @@ struct D2Ctx {
 // add up to more than one.
 bool build_rules9(const uint32_t *lambda9, std::vector<uint32_t> &rules, uint32_t &D);
 
-// The rules as the step kernel reads them, per ordered source pair,
-// kRule9DevWords uint32: words 0-3 the cumulative weights (as in the table
-// of mclg.h); then, for q = 0..4, four words holding the change of the
-// partial sums K_j = n_0 + ... + n_j (j = 0..7) as 16-bit two's-complement
-// pairs, K_2m in the low and K_2m+1 in the high half.
-constexpr uint32_t kRule9DevWords = 24;
-std::vector<uint32_t> device_rules9(const std::vector<uint32_t> &rules);
+// The rules as the step kernel reads them: three tables, of which a block
+// holds the one that its sites need.  K_j = n_0 + ... + n_j (j = 0..7).
+// - wide (any N, any D), per ordered source pair p = 9 i + j, 24 words: words
+//   0-3 the cumulative weights c_q; then, for q = 0..4, four words holding the
+//   change of the K_j as 16-bit two's-complement pairs, K_2m in the low and
+//   K_2m+1 in the high half;
+// - half (N < 2^15, Dq <= 2^15, Dq = D / g with g the greatest common divisor
+//   of D and all weights: a target draw u is used as floor(u / g)), per pair p = 16 i + j, 22 words: words 0-1 the
+//   halves 2^15 - c_q / g; then, for q = 0..4, four words, the 32-bit sum of the
+//   changes of the halves 2^15 - K_j, times 2^16 in the high half;
+// - byte (N < 2^7, Dq <= 2^15), per pair p = 16 i + j, 14 words: words 0-1 as
+//   above; then, for q = 0..4, two words of the changes of the bytes
+//   2^7 - K_j alike.
+constexpr uint32_t kRule9Wide = 24, kRule9Half = 22, kRule9Byte = 14;
+constexpr uint32_t kRule9WideAt = 0, kRule9HalfAt = 81 * kRule9Wide,
+                   kRule9ByteAt = kRule9HalfAt + 144 * kRule9Half,
+                   kRule9DevWords = kRule9ByteAt + 144 * kRule9Byte;
+constexpr uint32_t kRule9MaxPacked = 1u << 15;  // Dq of the packed tables, at most
+std::vector<uint32_t> device_rules9(const std::vector<uint32_t> &rules, uint32_t D, uint32_t &Dq);
 
 // Validate a D2Q9 configuration and fill the layout (sizes and offsets).
 int d2q9_layout(const mclg_config *cfg, D2Ctx &d);

@@ -269,8 +269,10 @@ struct Rep9 {
   uint32_t rid, pad;
 };
 struct Tile9 {
-  uint32_t rep, s0;  // replica, first site (multiple of 256)
+  uint32_t rep, s0;  // replica, first site (multiple of kTileSites9)
+  uint32_t x0;       // s0 mod Lx
 };
+constexpr uint32_t kTileSites9 = 256;
 // Collision rules, per ordered source pair (v1, v2), kRule9Words uint32:
 // words 0-3 the cumulative integer weights of the (up to four) targets, D
 // where there is none; words 4-8 the change of the nine counts for target
@@ -286,6 +288,7 @@ struct Step9 {
   uint64_t seed;
   uint64_t t;          // steps taken (the RNG counter uses its low 32 bits)
   uint32_t D, no_stream;
+  uint32_t Dq;         // D divided by the greatest common divisor of it and all weights
   int32_t C;
 };
 hipError_t launch_step9(hipStream_t s, const Step9 &a, uint32_t n_tiles);
