@@ -355,7 +355,7 @@ struct mclg_ctx {
       img_pool.resize((img_pool.size() + 15) / 16 * 16, 0);
       lds_bytes = std::max<uint32_t>(lds_bytes, (uint32_t)(b.size() + 15) / 16 * 16);
     }
-    double cov = 0.0, sites = 0.0;
+    double cov = 0.0, sites = 0.0, crowd = 0.0;
     for (uint32_t r = 0; r < n; ++r) {
       const LdsImage &im = ims[which[r]];
       ImageDesc &d = img_desc[r];
@@ -368,6 +368,7 @@ struct mclg_ctx {
       d.nb = im.nb;
       d.fixed = im.fixed ? 1u : 0u;
       cov += im.coverage * (double)L[r];
+      crowd += crowded_image(im.coverage) ? (double)L[r] : 0.0;
       sites += (double)L[r];
     }
     coverage = sites > 0 ? cov / sites : 0.0;
@@ -382,7 +383,7 @@ struct mclg_ctx {
     if (!e) e = step_occupancy(sch, lds_bytes, n_cu, max_blocks);
     if (!e) e = reg_setup(lds_bytes);
     ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0,
-                     images_fixed(C));
+                     images_fixed(C), crowd / sites);
     return e;
   }
   void drop_graphs() {

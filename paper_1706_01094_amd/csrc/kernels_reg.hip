@@ -93,7 +93,8 @@ __device__ __forceinline__ uint32_t exact_move(const uint4 e, const Env &E, uint
 // their counts; they go to the wave's queue (bit 8C + k of `und`: the lane's
 // site 8C + k is in it; of `cols`: some lane's is; F entries so far), which
 // is resolved at the end of the step.  A chunk with more such sites than the
-// queue holds is left as it is (bit C of `dense`) for dense_chunks.
+// queue has room for only marks them (bit C of `dense`) for dense_chunks (Q = 6:
+// it is left as it is, for dense_sites).
 template <int Q, int C, bool FIXED>
 __device__ __forceinline__ void collide_chunk(Sites<Q> &R, uint32_t &und, uint32_t &cols,
                                               uint32_t &dense, uint32_t &F, const Env &E,
@@ -137,7 +138,14 @@ __device__ __forceinline__ void collide_chunk(Sites<Q> &R, uint32_t &und, uint32
     if (F + n > kQueue) {
       dense |= 1u << C;
 #pragma unroll
-      for (int j = 0; j < NP; ++j) d[j] = 0u;
+      for (int j = 0; j < NP; ++j)
+        if (Q == 6) d[j] = 0u;
+#pragma unroll
+      for (int k = 0; k < NS; ++k)
+        if (Q != 6 && __builtin_amdgcn_inverse_ballot_w64(mk[k])) {
+          d[k >> 1] &= (k & 1) ? 0x0000ffffu : 0xffff0000u;
+          und |= 1u << (K0 + k);
+        }
     } else {
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
@@ -160,12 +168,11 @@ __device__ __forceinline__ void collide_chunk(Sites<Q> &R, uint32_t &und, uint32
   for (int j = 0; j < NP; ++j) apply_pair(R.m[W0 + j], R.z[W0 + j], R.p[W0 + j], d[j]);
 }
 
-// The step's queued draws: lane i resolves entry i exactly, then every lane
-// takes the moves of its own sites back from the queue's LDS.
-template <int Q, bool GAL>
-__device__ __forceinline__ void resolve_step(Sites<Q> &R, uint32_t und, uint32_t cols, uint32_t F,
-                                             const Env &E, uint32_t xw, const Span &S,
-                                             uint32_t t) {
+// Resolves the queue's F entries exactly, lane i entry i; its move, in both
+// halves, takes the place of entry i (word i of the queue's LDS).
+template <bool GAL>
+__device__ __forceinline__ void resolve_queue(uint32_t F, const Env &E, uint32_t xw, const Span &S,
+                                              uint32_t t) {
   uint32_t *const res = reinterpret_cast<uint32_t *>(E.queue);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -183,6 +190,16 @@ __device__ __forceinline__ void resolve_step(Sites<Q> &R, uint32_t und, uint32_t
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The queued draws: resolved, then every lane takes the moves of its own
+// sites back from the queue's LDS.  The queue is empty again.
+template <int Q, bool GAL>
+__device__ __forceinline__ void resolve_step(Sites<Q> &R, uint32_t &und, uint32_t &cols, uint32_t &F,
+                                             const Env &E, uint32_t xw, const Span &S,
+                                             uint32_t t) {
+  uint32_t *const res = reinterpret_cast<uint32_t *>(E.queue);
+  resolve_queue<GAL>(F, E, xw, S, t);
   uint32_t base = 0;
 #pragma unroll
   for (int k = 0; k < 4 * Q; ++k) {
@@ -194,18 +211,88 @@ __device__ __forceinline__ void resolve_step(Sites<Q> &R, uint32_t und, uint32_t
     apply_pair(R.m[k >> 1], R.z[k >> 1], R.p[k >> 1], d);
     base += (uint32_t)__popcll(mk);
   }
-  // the results are read before the next step's entries are written
+  und &= ~cols;
+  F = cols = 0u;
+  // the results are read before the next entries are written
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
 
-// The chunks with more undecided sites than the queue holds, every site from
-// the global rows, each lane its own.  An iteration of the outer loop handles
+// The undecided sites of the chunks in `dense`, in batches of up to 64 that
+// go through the queue.  An iteration of the outer loop handles the lane's
+// first four sites, drawn anew, and rotates its words by four sites, so the
+// registers are fixed and the code is short.  Its cost goes with the number
+// of undecided sites: 2^24 sites of density 100 and mean velocity 0.2, where
+// 12 % are, took 72 us per step with a batch per site of a lane (every site
+// of such a chunk) and take 45
+// (Q = 4).
+template <int Q, bool GAL>
+__device__ __forceinline__ void dense_chunks(Sites<Q> &R, uint32_t dense, uint32_t und, const Env &E,
+                                             uint32_t x, uint32_t pos, uint32_t xw, const Span &S,
+                                             uint32_t t) {
+  constexpr int W = 2 * Q;
+  const uint32_t *const res = reinterpret_cast<const uint32_t *>(E.queue);
+#pragma unroll 1
+  for (uint32_t q = 0; q < (uint32_t)Q; ++q) {
+    if (dense & (1u << (q >> 1))) {
+      uint32_t r[4], at[4], d[2] = {0u, 0u}, n = 0;
+      draw_words<4>(r, x, t, E);
+#pragma unroll
+      for (uint32_t k = 0; k < 4u; ++k) {
+        const bool mine = (und & (1u << k)) != 0u;
+        const uint64_t mk = __ballot(mine);
+        at[k] = mine ? n + lanes_below(mk) : ~0u;  // the site's place among them
+        n += (uint32_t)__popcll(mk);
+      }
+#pragma unroll 1
+      for (uint32_t b0 = 0; b0 < n; b0 += kQueue) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+          const uint32_t wa = R.m[k >> 1], wb = R.z[k >> 1], wc = R.p[k >> 1];
+          if (at[k] - b0 < kQueue)
+            E.queue[at[k] - b0] =
+                make_uint4(pos + k, __builtin_amdgcn_perm(wb, wa, (k & 1u) ? 0x07060302u : 0x05040100u),
+                           (k & 1u) ? wc >> 16 : wc & 0xffffu, r[k]);
+        }
+        resolve_queue<GAL>(min(n - b0, kQueue), E, xw, S, t);
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k)
+          if (at[k] - b0 < kQueue)
+            d[k >> 1] |= res[at[k] - b0] & ((k & 1u) ? 0xffff0000u : 0x0000ffffu);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+      apply_pair(R.m[0], R.z[0], R.p[0], d[0]);
+      apply_pair(R.m[1], R.z[1], R.p[1], d[1]);
+    }
+    und >>= 4;
+    x += 4u;
+    x -= x >= E.Lp ? E.Lp : 0u;
+    pos += 4u;
+    if constexpr (W > 2) {
+      const uint32_t m0 = R.m[0], m1 = R.m[1], z0 = R.z[0], z1 = R.z[1], p0 = R.p[0], p1 = R.p[1];
+#pragma unroll
+      for (int j = 0; j + 2 < W; ++j) {
+        R.m[j] = R.m[j + 2];
+        R.z[j] = R.z[j + 2];
+        R.p[j] = R.p[j + 2];
+      }
+      R.m[W - 2] = m0; R.m[W - 1] = m1;
+      R.z[W - 2] = z0; R.z[W - 1] = z1;
+      R.p[W - 2] = p0; R.p[W - 1] = p1;
+    }
+  }
+}
+
+// The same for Q = 6, every site of the chunks from the global rows, each lane
+// its own (batches need the registers that six times four sites take: at
+// density 50, which has no such chunks, 28.5 us per step of 2^24 sites
+// instead of 25.7; plan_ways keeps lattices with many of them from Q = 6).  An iteration of the outer loop handles
 // the lane's first four sites and rotates its words by four sites, one of
 // the inner loop the first site of those, so the registers are fixed and the
 // code is short.
 template <int Q, bool GAL>
-__device__ __forceinline__ void dense_chunks(Sites<Q> &R, uint32_t dense, const Env &E, uint32_t x,
+__device__ __forceinline__ void dense_sites(Sites<Q> &R, uint32_t dense, const Env &E, uint32_t x,
                                              uint32_t pos, const Span &S, uint32_t t) {
   constexpr int W = 2 * Q;
 #pragma unroll 1
@@ -275,6 +362,7 @@ __device__ __forceinline__ void flag_saturated(const Sites<Q> &R, const Env &E, 
   }
 }
 
+constexpr uint32_t kFlushAt = 28;
 // One step's collisions of the wave's sites; xw: the lattice site at
 // position 0 (below L).
 template <int Q, bool GAL, bool FIXED>
@@ -295,10 +383,20 @@ __device__ __forceinline__ void collide(Sites<Q> &R, const Env &E, uint32_t xw, 
     return y >= E.Lp ? y - E.Lp : y;
   };
   collide_chunk<Q, 0, FIXED>(R, und, cols, dense, F, E, at(0u), pos, S, t);
-  if constexpr (Q >= 4) collide_chunk<Q, 1, FIXED>(R, und, cols, dense, F, E, at(8u), pos + 8u, S, t);
-  if constexpr (Q >= 6) collide_chunk<Q, 2, FIXED>(R, und, cols, dense, F, E, at(16u), pos + 16u, S, t);
+  // Emptied early where the next chunk's would not fit with these (Q = 6: see
+  // dense_sites).
+  if constexpr (Q >= 4) {
+    if (Q == 4 && F > kFlushAt) resolve_step<Q, GAL>(R, und, cols, F, E, xw, S, t);
+    collide_chunk<Q, 1, FIXED>(R, und, cols, dense, F, E, at(8u), pos + 8u, S, t);
+  }
+  if constexpr (Q >= 6) {
+    collide_chunk<Q, 2, FIXED>(R, und, cols, dense, F, E, at(16u), pos + 16u, S, t);
+  }
   if (F) resolve_step<Q, GAL>(R, und, cols, F, E, xw, S, t);
-  if (dense) dense_chunks<Q, GAL>(R, dense, E, at(0u), pos, S, t);
+  if (dense) {
+    if constexpr (Q == 6) dense_sites<Q, GAL>(R, dense, E, at(0u), pos, S, t);
+    else dense_chunks<Q, GAL>(R, dense, und, E, at(0u), pos, xw, S, t);
+  }
 }
 
 constexpr int kDppShl1 = 0x130, kDppRol1 = 0x134;  // lane i takes lane i + 1 (rol: 63 takes 0)

@@ -37,10 +37,15 @@ struct RegWay {
   double launch_us = 0, step_us = 0;  // per launch and per step, estimated
 };
 
+// Whether a wave's step of 1536 sites leaves more undecided than its queue of
+// 64 takes, for an image that decides `coverage` of them.
+inline bool crowded_image(double coverage) { return coverage < 1.0 - 64.0 / 1536.0; }
+
 // The ways open to a context, with their estimated times; one_image: all
-// lattices share one.
+// lattices share one; crowded: the share of the sites in lattices of crowded
+// images.
 std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t n, uint32_t blocks,
-                              bool one_image, bool galilean, bool fixed);
+                              bool one_image, bool galilean, bool fixed, double crowded);
 
 // The quickest way for `steps` steps (with logs among them), or nullptr when
 // one step per launch of the kernels that keep the state in memory (single_us

@@ -142,8 +142,10 @@ struct mclg_server {
   struct CachedImage {
     std::vector<uint8_t> blob;
     uint32_t dir_bytes = 0, dim_a = 0, dim_c = 0, b_lo = 0, nb = 0, fixed = 0;
+    bool crowded = false;
   };
   std::map<std::pair<double, double>, CachedImage> image_cache;
+  std::vector<char> slot_crowded;  // whether the image of the slot's job is (see crowded_image)
   uint32_t n_active = 0;
   uint32_t lds_bytes = 16, max_blocks = 1, image_budget = kImage, n_cu = 1;
   int last_hip = 0;
@@ -399,9 +401,11 @@ struct mclg_server {
         c.b_lo = im.b_lo;
         c.nb = im.nb;
         c.fixed = im.fixed ? 1u : 0u;
+        c.crowded = crowded_image(im.coverage);
         ci = image_cache.emplace(key, std::move(c)).first;
       }
       const CachedImage &img = ci->second;
+      slot_crowded[r.slot] = img.crowded;
       ImageDesc idd{};
       idd.off = (uint64_t)r.slot * kImage;
       idd.bytes = (uint32_t)img.blob.size();
@@ -465,15 +469,18 @@ struct mclg_server {
         list.clear();
         sites.clear();
         total = 0;
+        uint64_t crowd = 0;
         for (size_t i = 0; i < wave.size(); ++i)
           if (left[i]) {
+            crowd += slot_crowded[wave[i].slot] ? wave[i].L : 0u;
             list.push_back(wave[i].slot);
             sites.push_back(wave[i].L);
             total += wave[i].L;
           }
         units = plan_units(sites.data(), (uint32_t)n, n_cu);
         if (units.units.size() > max_units((uint32_t)slot.size())) return hipErrorInvalidValue;
-        ways = plan_ways(units, sites.data(), (uint32_t)n, n_cu, false, false, images_fixed(cfg.C));
+        ways = plan_ways(units, sites.data(), (uint32_t)n, n_cu, false, false, images_fixed(cfg.C),
+                         (double)crowd / (double)total);
         for (UnitDev &u : units.units) u.slot = list[u.slot];
         for (StripDev &x : units.strips) x.slot = list[x.slot];
         uploaded = false;
@@ -615,6 +622,7 @@ int mclg_server_create(const mclg_server_config *cfg, mclg_server **out) {
   sv->arena = reinterpret_cast<uint16_t *>(cfg->arena);
   sv->s = reinterpret_cast<hipStream_t>(cfg->stream);
   sv->slot.resize(cfg->max_slots);
+  sv->slot_crowded.assign(cfg->max_slots, 0);
   {
     int dev = 0, v = 0;
     hipError_t e = hipGetDevice(&dev);

@@ -43,9 +43,10 @@ int main() {
     }
     // (lattices too short for tiles are no units)
     for (uint32_t r = 0; r < n; ++r) REQUIRE(seen[r] == (L[r] < kMinTiled ? 0 : L[r]));
-    for (const RegWay &w : plan_ways(P, L.data(), n, blocks, c % 2, c % 7 == 0, c % 11 != 0)) {
+    for (const RegWay &w : plan_ways(P, L.data(), n, blocks, c % 2, c % 7 == 0, c % 11 != 0, c % 3 ? 0.05 : 0.3)) {
       REQUIRE(w.kind != RegWay::kNone && w.most >= 1 && w.step_us > 0 && w.launch_us > 0);
       REQUIRE(reg_has(w.Q, c % 7 == 0, c % 11 != 0, w.logs));
+      REQUIRE(w.Q != 6 || c % 3);
       uint64_t longest = 0;
       bool ragged = false;
       for (uint64_t l : L) { longest = l > longest ? l : longest; ragged |= l % 8 != 0; }
