@@ -78,13 +78,18 @@ __device__ __forceinline__ uint32_t fold16(uint32_t hi, uint32_t lo) {
   return __builtin_amdgcn_alignbit(hi, lo, 16);
 }
 
-// The exact outcome of one site as a move of its n_0 by -2 d.
-template <bool GAL>
-__device__ __forceinline__ uint32_t exact_move(const uint4 e, const Env &E, uint32_t t, bool own) {
+// The launch's arguments, read where they are used.
+__device__ __forceinline__ const void *kernel_args_now() {
   KernArgs *ka = kernel_args();
   asm volatile("" : "+s"(ka));
-  const StepLaunch *k = (const StepLaunch *)ka;
-  const uint32_t bn = resolve_queued<GAL>(e, k->p, k->tab, t, E.rid, k->err, own);
+  return (const void *)ka;
+}
+
+// The exact outcome of one site as a move of its n_0 by -2 d.
+template <bool GAL, bool MANY>
+__device__ __forceinline__ uint32_t exact_move(const uint4 e, const Env &E, uint32_t t, bool own) {
+  const StepLaunch *k = static_cast<const StepLaunch *>(kernel_args_now());
+  const uint32_t bn = resolve_queued<GAL, MANY>(e, k->p, k->tab, t, E.rid, k->err, own);
   return (uint32_t)(((int32_t)(e.y >> 16) - (int32_t)bn) >> 1);
 }
 
@@ -170,7 +175,7 @@ __device__ __forceinline__ void collide_chunk(Sites<Q> &R, uint32_t &und, uint32
 
 // Resolves the queue's F entries exactly, lane i entry i; its move, in both
 // halves, takes the place of entry i (word i of the queue's LDS).
-template <bool GAL>
+template <bool GAL, bool MANY>
 __device__ __forceinline__ void resolve_queue(uint32_t F, const Env &E, uint32_t xw, const Span &S,
                                               uint32_t t) {
   uint32_t *const res = reinterpret_cast<uint32_t *>(E.queue);
@@ -183,7 +188,7 @@ __device__ __forceinline__ void resolve_queue(uint32_t F, const Env &E, uint32_t
     const bool own = e.x >= S.own_lo && e.x < S.own_hi;
     e.x += xw;
     e.x -= e.x >= E.Lp ? E.Lp : 0u;
-    d2 = (exact_move<GAL>(e, E, t, own) & 0xffffu) * 0x10001u;
+    d2 = (exact_move<GAL, MANY>(e, E, t, own) & 0xffffu) * 0x10001u;
   }
   __builtin_amdgcn_wave_barrier();  // every entry is read before a result is written over it
   res[E.lane] = d2;
@@ -199,7 +204,7 @@ __device__ __forceinline__ void resolve_step(Sites<Q> &R, uint32_t &und, uint32_
                                              const Env &E, uint32_t xw, const Span &S,
                                              uint32_t t) {
   uint32_t *const res = reinterpret_cast<uint32_t *>(E.queue);
-  resolve_queue<GAL>(F, E, xw, S, t);
+  resolve_queue<GAL, false>(F, E, xw, S, t);
   uint32_t base = 0;
 #pragma unroll
   for (int k = 0; k < 4 * Q; ++k) {
@@ -237,13 +242,29 @@ __device__ __forceinline__ void dense_chunks(Sites<Q> &R, uint32_t dense, uint32
     if (dense & (1u << (q >> 1))) {
       uint32_t r[4], at[4], d[2] = {0u, 0u}, n = 0;
       draw_words<4>(r, x, t, E);
+      // the sites without a row first: their sub-collisions one by one take
+      // many times what a row does, for a whole batch
+      const uint32_t n_max = static_cast<const StepLaunch *>(kernel_args_now())->p.n_max;
+      uint32_t lit = 0;
 #pragma unroll
       for (uint32_t k = 0; k < 4u; ++k) {
-        const bool mine = (und & (1u << k)) != 0u;
-        const uint64_t mk = __ballot(mine);
-        at[k] = mine ? n + lanes_below(mk) : ~0u;  // the site's place among them
-        n += (uint32_t)__popcll(mk);
+        const uint32_t sh = 16u * (k & 1u);
+        const uint32_t N = ((R.m[k >> 1] >> sh) & 0xffffu) + ((R.z[k >> 1] >> sh) & 0xffffu) +
+                           ((R.p[k >> 1] >> sh) & 0xffffu);
+        lit |= N > n_max ? und & (1u << k) : 0u;
+        at[k] = ~0u;
       }
+      auto number = [&](uint32_t which) {  // the sites' places among the undecided
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+          const bool mine = (which & (1u << k)) != 0u;
+          const uint64_t mk = __ballot(mine);
+          at[k] = mine ? n + lanes_below(mk) : at[k];
+          n += (uint32_t)__popcll(mk);
+        }
+      };
+      if (__ballot(lit != 0u) != 0u) number(lit);
+      number(und & ~lit);
 #pragma unroll 1
       for (uint32_t b0 = 0; b0 < n; b0 += kQueue) {
 #pragma unroll
@@ -254,7 +275,7 @@ __device__ __forceinline__ void dense_chunks(Sites<Q> &R, uint32_t dense, uint32
                 make_uint4(pos + k, __builtin_amdgcn_perm(wb, wa, (k & 1u) ? 0x07060302u : 0x05040100u),
                            (k & 1u) ? wc >> 16 : wc & 0xffffu, r[k]);
         }
-        resolve_queue<GAL>(min(n - b0, kQueue), E, xw, S, t);
+        resolve_queue<GAL, true>(min(n - b0, kQueue), E, xw, S, t);
 #pragma unroll
         for (uint32_t k = 0; k < 4u; ++k)
           if (at[k] - b0 < kQueue)
@@ -305,7 +326,7 @@ __device__ __forceinline__ void dense_sites(Sites<Q> &R, uint32_t dense, const E
         const uint32_t at = pos + k;
         uint32_t d = 0;
         if (!S.slow || at < S.end)
-          d = exact_move<GAL>(make_uint4(x + k, __builtin_amdgcn_perm(R.z[0], R.m[0], 0x05040100u),
+          d = exact_move<GAL, true>(make_uint4(x + k, __builtin_amdgcn_perm(R.z[0], R.m[0], 0x05040100u),
                                          R.p[0] & 0xffffu, r[0]),
                               E, t, at >= S.own_lo && at < S.own_hi) & 0xffffu;
         apply_pair(R.m[0], R.z[0], R.p[0], d);

@@ -140,7 +140,7 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
       }
     }
     if (plan.n_long == 0) continue;
-    for (uint32_t kh : {8u, 16u, 32u, 64u, 128u}) {
+    for (uint32_t kh : {8u, 16u, 24u, 32u, 48u, 64u, 128u}) {
       if (2 * kh >= hold) continue;
       RegWay y;
       y.kind = RegWay::kTile;

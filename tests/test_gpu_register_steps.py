@@ -81,6 +81,16 @@ def test_more_misses_than_the_queue_holds(L):
     run(L, (3, 20), counts=counts)
 
 
+@pytest.mark.parametrize("L", [900, 60005])
+@pytest.mark.parametrize("kw", [dict(C=10), dict(C=3, lam=(2, 3)), dict(C=30), dict(C=10, lam=(3 << 20, 7 << 20))], ids=str)
+def test_sites_without_a_row_among_others(L, kw):
+    """Half of the sites past n_max, whose sub-collisions go one by one, none
+    in the image; the last case rejects a third of the acceptance draws."""
+    counts = np.full((3, L), 20, dtype=np.uint16)
+    counts[1, ::3] = 19
+    run(L, (1, 12), counts=counts, n_max=60, **kw)
+
+
 @pytest.mark.parametrize("L", [500, 40003])
 def test_overflow_is_flagged_and_kept(L):
     counts = synth.random_counts(L, seed=5)
