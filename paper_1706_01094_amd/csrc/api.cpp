@@ -356,6 +356,7 @@ struct mclg_ctx {
       lds_bytes = std::max<uint32_t>(lds_bytes, (uint32_t)(b.size() + 15) / 16 * 16);
     }
     double cov = 0.0, sites = 0.0, crowd = 0.0;
+    std::vector<float> cost(n);
     for (uint32_t r = 0; r < n; ++r) {
       const LdsImage &im = ims[which[r]];
       ImageDesc &d = img_desc[r];
@@ -368,6 +369,7 @@ struct mclg_ctx {
       d.nb = im.nb;
       d.fixed = im.fixed ? 1u : 0u;
       cov += im.coverage * (double)L[r];
+      cost[r] = C ? site_cost(im.coverage) : 1.0f;
       crowd += crowded_image(im.coverage) ? (double)L[r] : 0.0;
       sites += (double)L[r];
     }
@@ -379,11 +381,19 @@ struct mclg_ctx {
       e = hipMemcpyAsync(ws + lay.o_ipool, img_pool.data(), img_pool.size(), hipMemcpyHostToDevice, stream);
     if (!e) e = hipMemcpyAsync(img_desc_dev(), img_desc.data(), sizeof(ImageDesc) * n,
                                hipMemcpyHostToDevice, stream);
+    units = plan_units(L.data(), n, n_cu, cost.data());
+    if (units.units.size() > max_units(n)) return hipErrorInvalidValue;
+    if (!e) e = hipMemcpyAsync(ws + lay.o_units, units.units.data(), sizeof(UnitDev) * units.units.size(),
+                               hipMemcpyHostToDevice, stream);
+    if (!e) e = hipMemcpyAsync(ws + lay.o_ufirst, units.first.data(), sizeof(uint32_t) * units.first.size(),
+                               hipMemcpyHostToDevice, stream);
+    if (!e) e = hipMemcpyAsync(ws + lay.o_strips, units.strips.data(), sizeof(StripDev) * units.strips.size(),
+                               hipMemcpyHostToDevice, stream);
     if (!e) e = hipStreamSynchronize(stream);
     if (!e) e = step_occupancy(sch, lds_bytes, n_cu, max_blocks);
     if (!e) e = reg_setup(lds_bytes);
     ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0,
-                     images_fixed(C), crowd / sites);
+                     images_fixed(C), crowd / sites, cost.data());
     return e;
   }
   void drop_graphs() {
@@ -547,12 +557,6 @@ int mclg_init(const mclg_config *cfg, const mclg_init_spec *init, mclg_ctx **out
   if (!e) c->n_cu = (uint32_t)std::max(1, v);
   if (e) return c->hip(e);
   if (c->n_cu > 256) return MCLG_E_UNSUPPORTED;  // overflow region sized for 256 CUs
-  c->units = plan_units(c->L.data(), c->n, c->n_cu);
-  if (c->units.units.size() > max_units(c->n)) return MCLG_E_INTERNAL;
-  e = up(lay.o_units, c->units.units.data(), sizeof(UnitDev) * c->units.units.size());
-  if (!e) e = up(lay.o_ufirst, c->units.first.data(), sizeof(uint32_t) * c->units.first.size());
-  if (!e) e = up(lay.o_strips, c->units.strips.data(), sizeof(StripDev) * c->units.strips.size());
-  if (e) return c->hip(e);
   e = moments_scratch(&c->scratch);
   if (e) return c->hip(e);
   // what density and velocity each replica's image should target

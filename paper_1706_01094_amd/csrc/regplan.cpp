@@ -8,16 +8,18 @@ namespace mclg {
 
 namespace {
 constexpr uint64_t kMinPart = 256;  // sites of a part, at least (>= kMaxHalo)
-static_assert(kMinPart >= kMaxHalo, "a part holds the sites of both its strips' halves");
+static_assert(kMinPart >= 2 * kMaxHalo, "a part holds the sites of both its strips' halves at any cost");
 }  // namespace
 
-UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks) {
+UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks, const float *cost) {
   UnitPlan P;
   blocks = std::min(blocks, kPlanBlocks);
+  // the work of s sites of lattice r, in sites of cost 1
+  auto weigh = [&](uint32_t r, uint64_t s) { return cost ? (uint64_t)((double)s * cost[r]) : s; };
   uint64_t total = 0;
   for (uint32_t r = 0; r < n; ++r) {
     if (L[r] < kMinTiled) continue;
-    total += L[r];
+    total += weigh(r, L[r]);
     ++P.n_long;
   }
   const uint64_t target = std::max<uint64_t>(kMinPart, (total + blocks - 1) / blocks);
@@ -25,7 +27,8 @@ UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks) {
   for (uint32_t r = 0; r < n; ++r) {
     if (L[r] < kMinTiled) continue;
     // a lattice of up to 5/4 of a block's share stays whole
-    uint64_t parts = 4 * L[r] <= 5 * target ? 1 : (L[r] + target - 1) / target;
+    const uint64_t work = weigh(r, L[r]);
+    uint64_t parts = 4 * work <= 5 * target ? 1 : (work + target - 1) / target;
     if (P.strips.size() + parts > kMaxStrips) parts = 1;
     const uint64_t len = (((L[r] + parts - 1) / parts) + 7) / 8 * 8;
     parts = (L[r] + len - 1) / len;
@@ -50,7 +53,7 @@ UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks) {
   // units of one image follow each other
   std::vector<uint32_t> order(all.size());
   std::iota(order.begin(), order.end(), 0u);
-  auto work = [&](uint32_t i) { return (uint64_t)(all[i].x1 - all[i].x0) + 2048u; };
+  auto work = [&](uint32_t i) { return weigh(all[i].slot, all[i].x1 - all[i].x0) + 2048u; };
   std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return work(x) > work(y); });
   std::vector<std::pair<uint64_t, uint32_t>> heap;
   for (uint32_t b = 0; b < blocks; ++b) heap.push_back({0, b});
@@ -96,16 +99,20 @@ constexpr double kUnit = 4.0;         // every further unit of a block: image an
 }  // namespace
 
 std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t n, uint32_t blocks,
-                              bool one_image, bool galilean, bool fixed, double crowded) {
+                              bool one_image, bool galilean, bool fixed, double crowded,
+                              const float *cost) {
   std::vector<RegWay> ways;
   blocks = std::min(blocks, kPlanBlocks);
   uint64_t longest = 0, total = 0;
+  double weight = 0;  // mean cost of a site
   bool ragged = false;
   for (uint32_t r = 0; r < n; ++r) {
     longest = std::max(longest, L[r]);
     total += L[r];
+    weight += (cost ? cost[r] : 1.0) * (double)L[r];
     ragged |= L[r] % 8 != 0;
   }
+  weight /= (double)total;
   for (uint32_t Q : {1u, 2u, 4u, 6u}) {
     if (!reg_has(Q, galilean, fixed, false)) continue;
     // A step's undecided sites past the queue's 64 cost every site of their
@@ -156,7 +163,8 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
         for (uint32_t i = plan.first[b]; i < plan.first[b + 1]; ++i) {
           const uint64_t len = plan.units[i].x1 - plan.units[i].x0;
           const uint64_t nt = ((len + tmax - 1) / tmax + 3) / 4;  // per SIMD
-          us += tile_step_us(Q, (double)nt, (double)((nt + 3) / 4));
+          us += tile_step_us(Q, (double)nt, (double)((nt + 3) / 4)) *
+                (cost ? cost[plan.units[i].slot] / weight : 1.0);
         }
         worst = std::max(worst, us);
         images = std::max(images, (double)(plan.first[b + 1] - plan.first[b]));

@@ -17,15 +17,25 @@ inline uint64_t max_units(uint32_t n) { return (uint64_t)n + kMaxStrips; }
 // be shorter than its lattice); beside longer ones they take the ring kernel.
 constexpr uint32_t kMinTiled = 512;
 
+// The time of a site of a lattice whose image decides `coverage` of them, that
+// of one with all decided as 1 (2^24 sites, Q = 4, us per step: all 22.4, all
+// but 0.3 % 27.5, 2 % 34.7, 11 % 42; most of it is paid for the first few of a
+// wave's step).
+inline float site_cost(double coverage) {
+  const double m = coverage < 1.0 ? 1.0 - coverage : 0.0;
+  return (float)(1.0 + 0.95 * m / (m + 0.01));
+}
+
 // The units of the tile kernel: every lattice of at least kMinTiled sites,
-// whole or in equal parts, dealt to the blocks longest first.
+// whole or in equal parts, dealt to the blocks longest first (cost: of a site
+// of each lattice, from 1 to 2; null: 1).
 struct UnitPlan {
   uint32_t n_long = 0;           // such lattices
   std::vector<UnitDev> units;
   std::vector<uint32_t> first;   // blocks + 1
   std::vector<StripDev> strips;
 };
-UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks);
+UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks, const float *cost = nullptr);
 
 // One way to take steps: the kernel, its sites per lane (4 Q) and, for the
 // tiles, the sites on each side (steps per launch, at most).
@@ -45,7 +55,8 @@ inline bool crowded_image(double coverage) { return coverage < 1.0 - 64.0 / 1536
 // lattices share one; crowded: the share of the sites in lattices of crowded
 // images.
 std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t n, uint32_t blocks,
-                              bool one_image, bool galilean, bool fixed, double crowded);
+                              bool one_image, bool galilean, bool fixed, double crowded,
+                              const float *cost = nullptr);
 
 // The quickest way for `steps` steps (with logs among them), or nullptr when
 // one step per launch of the kernels that keep the state in memory (single_us

@@ -142,10 +142,10 @@ struct mclg_server {
   struct CachedImage {
     std::vector<uint8_t> blob;
     uint32_t dir_bytes = 0, dim_a = 0, dim_c = 0, b_lo = 0, nb = 0, fixed = 0;
-    bool crowded = false;
+    double coverage = 1.0;
   };
   std::map<std::pair<double, double>, CachedImage> image_cache;
-  std::vector<char> slot_crowded;  // whether the image of the slot's job is (see crowded_image)
+  std::vector<double> slot_coverage;  // of the image of the slot's job
   uint32_t n_active = 0;
   uint32_t lds_bytes = 16, max_blocks = 1, image_budget = kImage, n_cu = 1;
   int last_hip = 0;
@@ -401,11 +401,11 @@ struct mclg_server {
         c.b_lo = im.b_lo;
         c.nb = im.nb;
         c.fixed = im.fixed ? 1u : 0u;
-        c.crowded = crowded_image(im.coverage);
+        c.coverage = im.coverage;
         ci = image_cache.emplace(key, std::move(c)).first;
       }
       const CachedImage &img = ci->second;
-      slot_crowded[r.slot] = img.crowded;
+      slot_coverage[r.slot] = img.coverage;
       ImageDesc idd{};
       idd.off = (uint64_t)r.slot * kImage;
       idd.bytes = (uint32_t)img.blob.size();
@@ -453,6 +453,7 @@ struct mclg_server {
     std::vector<RegWay> ways;
     std::vector<uint32_t> list, limit(slot.size());
     std::vector<uint64_t> sites;
+    std::vector<float> cost;
     uint64_t total = 0;
     bool uploaded = false;  // the list and the units
     for (;;) {
@@ -468,19 +469,22 @@ struct mclg_server {
       if (n != list.size()) {  // (jobs leave and none joins)
         list.clear();
         sites.clear();
+        cost.clear();
         total = 0;
         uint64_t crowd = 0;
         for (size_t i = 0; i < wave.size(); ++i)
           if (left[i]) {
-            crowd += slot_crowded[wave[i].slot] ? wave[i].L : 0u;
+            const double cov = slot_coverage[wave[i].slot];
+            crowd += crowded_image(cov) ? wave[i].L : 0u;
+            cost.push_back(cfg.C ? site_cost(cov) : 1.0f);
             list.push_back(wave[i].slot);
             sites.push_back(wave[i].L);
             total += wave[i].L;
           }
-        units = plan_units(sites.data(), (uint32_t)n, n_cu);
+        units = plan_units(sites.data(), (uint32_t)n, n_cu, cost.data());
         if (units.units.size() > max_units((uint32_t)slot.size())) return hipErrorInvalidValue;
         ways = plan_ways(units, sites.data(), (uint32_t)n, n_cu, false, false, images_fixed(cfg.C),
-                         (double)crowd / (double)total);
+                         (double)crowd / (double)total, cost.data());
         for (UnitDev &u : units.units) u.slot = list[u.slot];
         for (StripDev &x : units.strips) x.slot = list[x.slot];
         uploaded = false;
@@ -622,7 +626,7 @@ int mclg_server_create(const mclg_server_config *cfg, mclg_server **out) {
   sv->arena = reinterpret_cast<uint16_t *>(cfg->arena);
   sv->s = reinterpret_cast<hipStream_t>(cfg->stream);
   sv->slot.resize(cfg->max_slots);
-  sv->slot_crowded.assign(cfg->max_slots, 0);
+  sv->slot_coverage.assign(cfg->max_slots, 1.0);
   {
     int dev = 0, v = 0;
     hipError_t e = hipGetDevice(&dev);

@@ -27,7 +27,10 @@ int main() {
     const uint32_t n = c < 100 ? 1 : 1 + g() % (c % 3 ? 40 : 1500), blocks = c % 5 ? 256 : 1 + g() % 300;
     std::vector<uint64_t> L(n);
     for (auto &l : L) l = 1 + g() % (1ull << (1 + g() % (n == 1 ? 29 : 21)));
-    const UnitPlan P = plan_units(L.data(), n, blocks);
+    std::vector<float> cost(n, 1.0f);
+    if (c % 2) for (auto &x : cost) x = site_cost(1.0 - 0.2 * (g() % 1000) / 1000);
+    for (float x : cost) REQUIRE(x >= 1.0f && x < 2.0f);
+    const UnitPlan P = plan_units(L.data(), n, blocks, c % 2 ? cost.data() : nullptr);
     const uint32_t nb = blocks < kPlanBlocks ? blocks : kPlanBlocks;
     REQUIRE(P.first.size() == nb + 1 && P.first[0] == 0 && P.first[nb] == P.units.size());
     REQUIRE(P.units.size() <= max_units(n) && P.strips.size() <= kMaxStrips);
@@ -43,7 +46,8 @@ int main() {
     }
     // (lattices too short for tiles are no units)
     for (uint32_t r = 0; r < n; ++r) REQUIRE(seen[r] == (L[r] < kMinTiled ? 0 : L[r]));
-    for (const RegWay &w : plan_ways(P, L.data(), n, blocks, c % 2, c % 7 == 0, c % 11 != 0, c % 3 ? 0.05 : 0.3)) {
+    for (const RegWay &w : plan_ways(P, L.data(), n, blocks, c % 2, c % 7 == 0, c % 11 != 0, c % 3 ? 0.05 : 0.3,
+                                        c % 2 ? cost.data() : nullptr)) {
       REQUIRE(w.kind != RegWay::kNone && w.most >= 1 && w.step_us > 0 && w.launch_us > 0);
       REQUIRE(reg_has(w.Q, c % 7 == 0, c % 11 != 0, w.logs));
       REQUIRE(w.Q != 6 || c % 3);
