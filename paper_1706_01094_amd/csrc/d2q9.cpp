@@ -263,6 +263,8 @@ int d2q9_init(D2Ctx &d, const mclg_config *cfg, const mclg_init_spec *init) {
   if (!e && init->kind == MCLG_INIT_COUNTS)
     e = launch_init9_counts(d.stream, d.state, reps, tiles, (uint32_t)d.tiles.size(),
                             reinterpret_cast<const uint64_t *>(d.ws + d.o_dense), init->counts);
+  if (!e && d.n <= kMomPinned)
+    e = hipHostMalloc(reinterpret_cast<void **>(&d.pin), 8ull * (kMom9Out * d.n + 1u), hipHostMallocDefault);
   // the host vectors above must outlive the copies
   if (!e) e = hipStreamSynchronize(d.stream);
   d.t = 0;
@@ -346,6 +348,15 @@ int d2q9_moments(D2Ctx &d, mclg_moments9_t *out) {
   m.n_runs = d.n;
   m.partial = reinterpret_cast<unsigned long long *>(d.ws + d.o_mpart);
   m.out = reinterpret_cast<long long *>(d.ws + d.o_mout);
+  if (d.pin) {
+    m.out = d.pin;
+    m.err = reinterpret_cast<const uint32_t *>(d.ws + d.o_err);
+    hipError_t e = launch_moments9(d.stream, m);
+    if (!e) e = hipStreamSynchronize(d.stream);
+    if (e) return hip_rc(d, e);
+    std::memcpy(out, d.pin, sizeof(mclg_moments9_t) * d.n);
+    return d.pin[(uint64_t)d.n * kMom9Out] ? MCLG_E_RANGE : MCLG_OK;
+  }
   hipError_t e = launch_moments9(d.stream, m);
   if (!e) e = hipMemcpyAsync(out, d.ws + d.o_mout, sizeof(mclg_moments9_t) * d.n,
                              hipMemcpyDeviceToHost, d.stream);

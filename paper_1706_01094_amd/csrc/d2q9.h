@@ -30,7 +30,11 @@ struct D2Ctx {
   uint16_t *state = nullptr;
   uint8_t *ws = nullptr;
   hipStream_t stream = nullptr;
+  long long *pin = nullptr;  // results of the moments and the error word (up to kMomPinned replicas)
   int last_hip = 0;
+  ~D2Ctx() {
+    if (pin) (void)hipHostFree(pin);
+  }
 };
 
 // Collision rule table of mclg.h for lambda9 (18 values); false when a

@@ -71,7 +71,15 @@ struct MomArgs {
   uint32_t digest = 0;               // D1Q3: also sum the state digest
   unsigned long long *partial = nullptr;  // n_segs records
   long long *out = nullptr;                // run j's result at out[j * kMom*Out]
+  uint32_t t_off = 0;                // D1Q3: steps past tslot
+  const uint32_t *err = nullptr;     // its word goes after the last run's result
 };
+// Results a context reads through pinned memory, which the kernels write
+// themselves, with a segment per run in one launch: ten steps and the moments
+// of 13 D2Q9 lattices of 1000 sites took 139 us with a final pass, two copies
+// and two waits and take 87 without.  More replicas than this go through the
+// workspace and a copy.
+constexpr uint32_t kMomPinned = 4096;
 
 // Static partial-record area of the allocation-free moments call: 8 MiB per
 // GPU (32768 D1Q3 records), for devices 0 .. kMomScratchDevices - 1.

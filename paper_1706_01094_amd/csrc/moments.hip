@@ -140,11 +140,12 @@ __global__ void __launch_bounds__(256) k_mom3(const uint16_t *__restrict__ state
                                               const uint32_t *__restrict__ tslot,
                                               const MomSeg *__restrict__ segs, uint32_t no_stream,
                                               const int32_t *__restrict__ twiddle,
-                                              u64 *__restrict__ partial) {
+                                              u64 *__restrict__ partial, uint32_t t_off,
+                                              i64 *__restrict__ direct, const uint32_t *err) {
   const MomSeg sg = segs[blockIdx.x];
   const SlotDev sl = slots[sg.slot];
   const uint32_t L = sl.L;
-  const uint32_t tm = no_stream ? 0u : tslot[sg.slot] % L;
+  const uint32_t tm = no_stream ? 0u : (tslot[sg.slot] + t_off) % L;
   const Rsrc rs = make_rsrc(state + sl.off, 6u * sl.stride);
   const uint32_t ab = 2u * sl.stride;
   const int32_t *tw = NM > 0 ? twiddle + 2ull * NM * sl.dense : nullptr;
@@ -212,7 +213,20 @@ __global__ void __launch_bounds__(256) k_mom3(const uint16_t *__restrict__ state
   constexpr int V = W <= 16 ? 16 : 32;
   u64 v[V];
   const uint32_t mx = fold<NM, V>(A, v);
-  write_partial<V, W, 11>(v, mx, partial + (uint64_t)blockIdx.x * kMom3Rec);
+  u64 *const rec = partial + (uint64_t)blockIdx.x * kMom3Rec;
+  write_partial<V, W, 11>(v, mx, rec);
+  // with a segment per run its record is the run's: no final pass
+  if (direct) {
+    __shared__ u64 T[kMom3Rec];
+    __threadfence_block();
+    __syncthreads();
+    if (threadIdx.x < W) T[threadIdx.x] = rec[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x < kMom3Out)
+      direct[(uint64_t)blockIdx.x * kMom3Out + threadIdx.x] =
+          (i64)result_field(threadIdx.x, T, tslot[sg.slot] + t_off, L, NM);
+    if (err && blockIdx.x == 0 && threadIdx.x == 0) direct[(uint64_t)gridDim.x * kMom3Out] = (i64)*err;
+  }
 }
 
 // Sums of the partial records [s0, s1) of one run in the final pass (one
@@ -269,14 +283,16 @@ __global__ void __launch_bounds__(1024) k_mom3_final(const u64 *__restrict__ par
                                                      const uint32_t *__restrict__ run_slot,
                                                      const SlotDev *__restrict__ slots,
                                                      const uint32_t *__restrict__ tslot,
-                                                     uint32_t n_modes, i64 *__restrict__ out) {
+                                                     uint32_t n_modes, i64 *__restrict__ out,
+                                                     uint32_t t_off, const uint32_t *err) {
   __shared__ u64 T[kMom3Rec];
   const uint32_t j = blockIdx.x, slot = run_slot[j];
   sum_run<kMom3Rec, 11>(partial, run_seg[j], run_seg[j + 1], 6u + n_modes, T);
   const uint32_t k = threadIdx.x;
+  if (err && j == 0u && k == kMom3Out) out[(uint64_t)gridDim.x * kMom3Out] = (i64)*err;
   if (k >= kMom3Out) return;
   out[(uint64_t)j * kMom3Out + k] =
-      (i64)result_field(k, T, k == 0u ? tslot[slot] : 0u, k == 1u ? slots[slot].L : 0u, n_modes);
+      (i64)result_field(k, T, k == 0u ? tslot[slot] + t_off : 0u, k == 1u ? slots[slot].L : 0u, n_modes);
 }
 
 // ---- D2Q9 ----------------------------------------------------------------
@@ -304,11 +320,32 @@ __device__ __forceinline__ void load_row9(Rsrc rs, uint32_t stride, uint32_t Lx,
     load16(rs, 2u * ((uint32_t)i * stride + yr[kVy9[i] + 1] + xc[kVx9[i] + 1]), w[i]);
 }
 
+// Result k in the field order of mclg_moments9_t: t, sites, sum n_i, sum n_i
+// n_j (i <= j), sum N, sum Jx, sum Jy (from the per-velocity sums), max N.
+__device__ __forceinline__ i64 result_field9(uint32_t k, const u64 *T, uint64_t t, uint32_t S) {
+  u64 v = 0;
+  if (k == 0u) {
+    v = t;
+  } else if (k == 1u) {
+    v = S;
+  } else if (k < 56u) {
+    v = T[k - 2u];
+  } else if (k == 59u) {
+    v = T[kMom9Max];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+      v += (u64)(k == 56u ? 1 : k == 57u ? kVx9[i] : kVy9[i]) * T[i];
+  }
+  return (i64)v;
+}
+
 __global__ void __launch_bounds__(256) k_mom9(const uint16_t *__restrict__ state,
                                               const Rep9 *__restrict__ reps, uint64_t t,
                                               uint32_t no_stream,
                                               const MomSeg *__restrict__ segs,
-                                              u64 *__restrict__ partial) {
+                                              u64 *__restrict__ partial, i64 *__restrict__ direct,
+                                              const uint32_t *err) {
   __shared__ u64 big[45];
   __shared__ u64 red64[4][64];
   __shared__ uint32_t redmx[4];
@@ -444,36 +481,31 @@ __global__ void __launch_bounds__(256) k_mom9(const uint16_t *__restrict__ state
     }
     rec[k] = o;
   }
+  // with a segment per run its record is the run's: no final pass
+  if (direct) {
+    __shared__ u64 T[kMom9Rec];
+    __threadfence_block();
+    __syncthreads();
+    if (threadIdx.x < kMom9Used) T[threadIdx.x] = rec[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x < kMom9Out)
+      direct[(uint64_t)blockIdx.x * kMom9Out + threadIdx.x] = result_field9(threadIdx.x, T, t, rp.S);
+    if (err && blockIdx.x == 0 && threadIdx.x == 0) direct[(uint64_t)gridDim.x * kMom9Out] = (i64)*err;
+  }
 }
 
-// Final pass, one block per run j: the replica's result in the field order
-// of mclg_moments9_t: t, sites, sum n_i, sum n_i n_j (i <= j), sum N, sum
-// Jx, sum Jy (from the per-velocity sums), max N.
+// Final pass, one block per run j.
 __global__ void __launch_bounds__(1024) k_mom9_final(const u64 *__restrict__ partial,
                                                      const uint32_t *__restrict__ run_seg,
                                                      const uint32_t *__restrict__ run_slot,
                                                      const Rep9 *__restrict__ reps, uint64_t t,
-                                                     i64 *__restrict__ out) {
+                                                     i64 *__restrict__ out, const uint32_t *err) {
   __shared__ u64 T[kMom9Rec];
   const uint32_t j = blockIdx.x, slot = run_slot[j];
   sum_run<kMom9Rec, kMom9Max>(partial, run_seg[j], run_seg[j + 1], kMom9Used / 2u, T);
   const uint32_t k = threadIdx.x;
-  if (k >= kMom9Out) return;
-  u64 v = 0;
-  if (k == 0u) {
-    v = t;
-  } else if (k == 1u) {
-    v = reps[slot].S;
-  } else if (k < 56u) {
-    v = T[k - 2u];
-  } else if (k == 59u) {
-    v = T[kMom9Max];
-  } else {
-#pragma unroll
-    for (int i = 0; i < 9; ++i)
-      v += (u64)(k == 56u ? 1 : k == 57u ? kVx9[i] : kVy9[i]) * T[i];
-  }
-  out[(uint64_t)j * kMom9Out + k] = (i64)v;
+  if (err && j == 0u && k == kMom9Out) out[(uint64_t)gridDim.x * kMom9Out] = (i64)*err;
+  if (k < kMom9Out) out[(uint64_t)j * kMom9Out + k] = result_field9(k, T, t, reps[slot].S);
 }
 
 // Threads per block of the final pass: 1024 when runs have many records
@@ -482,14 +514,17 @@ uint32_t final_threads(const MomArgs &a) {
   return a.n_segs >= 64u * a.n_runs ? 1024u : 256u;
 }
 
+// Where k_mom3 and k_mom9 write the results themselves (or null).
+long long *direct(const MomArgs &a) { return a.n_segs == a.n_runs ? a.out : nullptr; }
+
 template <int NM>
 hipError_t launch3(hipStream_t s, const MomArgs &a) {
   if (a.digest)
     k_mom3<NM, true><<<a.n_segs, 256, 0, s>>>(a.state, a.slots, a.tslot, a.segs, a.no_stream,
-                                              a.twiddle, a.partial);
+                                              a.twiddle, a.partial, a.t_off, direct(a), a.err);
   else
     k_mom3<NM, false><<<a.n_segs, 256, 0, s>>>(a.state, a.slots, a.tslot, a.segs, a.no_stream,
-                                               a.twiddle, a.partial);
+                                               a.twiddle, a.partial, a.t_off, direct(a), a.err);
   return hipGetLastError();
 }
 
@@ -564,19 +599,20 @@ hipError_t launch_moments3(hipStream_t s, const MomArgs &a) {
     case 7: e = launch3<7>(s, a); break;
     default: e = launch3<8>(s, a); break;
   }
-  if (e) return e;
+  if (e || direct(a)) return e;
   k_mom3_final<<<a.n_runs, final_threads(a), 0, s>>>(a.partial, a.run_seg, a.run_slot, a.slots,
-                                                     a.tslot, a.n_modes, a.out);
+                                                     a.tslot, a.n_modes, a.out, a.t_off, a.err);
   return hipGetLastError();
 }
 
 hipError_t launch_moments9(hipStream_t s, const MomArgs &a) {
   if (a.n_runs == 0) return hipSuccess;
-  k_mom9<<<a.n_segs, 256, 0, s>>>(a.state, a.reps, a.t9, a.no_stream, a.segs, a.partial);
+  k_mom9<<<a.n_segs, 256, 0, s>>>(a.state, a.reps, a.t9, a.no_stream, a.segs, a.partial, direct(a),
+                                   a.err);
   hipError_t e = hipGetLastError();
-  if (e) return e;
+  if (e || direct(a)) return e;
   k_mom9_final<<<a.n_runs, final_threads(a), 0, s>>>(a.partial, a.run_seg, a.run_slot, a.reps,
-                                                     a.t9, a.out);
+                                                     a.t9, a.out, a.err);
   return hipGetLastError();
 }
 
