@@ -292,6 +292,10 @@ struct Step9 {
   int32_t C;
 };
 hipError_t launch_step9(hipStream_t s, const Step9 &a, uint32_t n_tiles);
+// `steps` steps of lattices of up to kBlockSites9 sites in one launch.
+constexpr uint32_t kBlockSites9 = 1024;
+hipError_t launch_steps9(hipStream_t s, const Step9 &a, uint32_t n_reps, uint32_t max_sites,
+                         uint32_t steps);
 hipError_t launch_init9_poisson(hipStream_t s, uint16_t *state, const Rep9 *reps,
                                 const Tile9 *tiles, uint32_t n_tiles, const PoisDesc *desc,
                                 const uint32_t *pool, uint64_t seed, uint32_t *err);

@@ -331,6 +331,54 @@ __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles
   }
 }
 
+// `steps` steps of lattices of up to 1024 sites, one per block, a site per
+// thread: the counts stay in LDS, in the same shifted layout, between one read
+// and one write of the state.  Without the state's way through memory and a
+// launch per step; bound by the instructions of a block's 16 waves on one CU.
+// Us per step: a lattice of 16 x 16 sites 6.4 with a launch each and 3.0 here,
+// 13 of 100 x 10 sites 7.4 and 6.1.
+__global__ void __launch_bounds__(1024) k_steps9(Step9 a, uint32_t steps) {
+  extern __shared__ __align__(16) uint16_t counts[];  // 9 arrays of S
+  __shared__ __align__(16) uint32_t rules[kRulesLds];
+  __shared__ uint32_t needs[2];
+  const Rep9 rp = a.reps[blockIdx.x];
+  const uint32_t S = rp.S, s = min(threadIdx.x, S - 1u), x = s % rp.Lx;
+  for (uint32_t i = 0; i < 9u; ++i)
+    for (uint32_t e = threadIdx.x; e < S; e += blockDim.x) counts[i * S + e] = *at9(a.state, rp, (int)i, e);
+  uint32_t held = 0;
+  if (threadIdx.x < 2u) needs[threadIdx.x] = a.Dq > kRule9MaxPacked ? 3u : 1u;
+  uint32_t tx = a.no_stream ? 0u : (uint32_t)(a.t % rp.Lx), ty = a.no_stream ? 0u : (uint32_t)(a.t % rp.Ly);
+  for (uint32_t k = 0; k < steps; ++k) {
+    __syncthreads();  // the counts of this step are in place
+    const Site9 ph(s, x, tx, ty, rp.Lx, S);
+    uint32_t n[9], N = 0;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+      n[j] = counts[(uint32_t)j * S + ph.e[j]];
+      N += n[j];
+    }
+    bool act = threadIdx.x < S;
+    if (act && N > 65535u) atomicOr(a.err, kErrOverflow);
+    act = act && N >= 2u && N <= 65535u;
+    if (__ballot(act && N >= 0x80u) != 0u)
+      atomicMax(&needs[k & 1u], __ballot(act && N >= 0x8000u) != 0u ? 3u : 2u);
+    hold_rules(a, rules, &needs[k & 1u], held);
+    if (act) {
+      collide_site(n, N, rules, held, a, s, rp.rid);
+#pragma unroll
+      for (int j = 0; j < 9; ++j) counts[(uint32_t)j * S + ph.e[j]] = (uint16_t)n[j];
+    }
+    ++a.t;
+    if (!a.no_stream) {
+      tx = tx + 1u == rp.Lx ? 0u : tx + 1u;
+      ty = ty + 1u == rp.Ly ? 0u : ty + 1u;
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = 0; i < 9u; ++i)
+    for (uint32_t e = threadIdx.x; e < S; e += blockDim.x) *at9(a.state, rp, (int)i, e) = counts[i * S + e];
+}
+
 // Poisson start: site s draws Philox blocks (s, j, replica, 1), j = 0, 1, 2;
 // word w of block j serves velocity 4 j + w.  At t = 0 the layout is
 // unshifted.
@@ -430,6 +478,14 @@ hipError_t launch_step9(hipStream_t s, const Step9 &a, uint32_t n_tiles) {
   // chip even out their ends.  4096 x 4096 sites at density 36, us per step:
   // 2048 blocks 383, 8192 345, 32768 349, a block per tile 363.
   k_step9<<<std::min<uint32_t>(n_tiles, 8192u), kTileSites9, 0, s>>>(a, n_tiles);
+  return hipGetLastError();
+}
+
+hipError_t launch_steps9(hipStream_t s, const Step9 &a, uint32_t n_reps, uint32_t max_sites,
+                         uint32_t steps) {
+  if (n_reps == 0 || steps == 0 || a.C <= 0) return hipSuccess;
+  if (max_sites > kBlockSites9) return hipErrorInvalidValue;
+  k_steps9<<<n_reps, (max_sites + 63u) / 64u * 64u, 18u * max_sites, s>>>(a, steps);
   return hipGetLastError();
 }
 

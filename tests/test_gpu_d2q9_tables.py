@@ -54,3 +54,31 @@ def test_blocks_that_change_tables():
     assert o.step(2) == 0
     same9(g, o, 1)
     g.close()
+
+
+@pytest.mark.parametrize("Lx,Ly", [(1, 1), (1, 7), (2, 2), (64, 1), (13, 5), (32, 16), (31, 33), (1024, 1)])
+def test_several_steps_in_a_launch(Lx, Ly):
+    """Lattices of up to 1024 sites, whole in a block's LDS: sites that need
+    each of the tables, empty ones, and lengths of one row or column."""
+    rng = np.random.default_rng(Lx)
+    n = [Lx, max(1, Lx - 1), 3]
+    rows = []
+    for lx in n:
+        c = rng.integers(0, 9, size=(9, Ly * lx)).astype(np.uint16)
+        c[:, ::5] = 0
+        c[:, 0] += 40
+        rows.append(c.reshape(-1))
+    g, o = pair9(n, [Ly] * 3, 8, counts=np.concatenate(rows))
+    for k in (20, 6, 17):
+        g.step(k)
+        assert o.step(k) == 0
+        same9(g, o, 3)
+    g.close()
+    c = np.zeros((9, Ly, Lx), dtype=np.uint16)
+    c[:] = 3
+    c[:, 0, 0] = 4000
+    g, o = pair9(Lx, Ly, 8, counts=c.reshape(-1))
+    g.step(18)
+    assert o.step(18) == 0
+    same9(g, o, 1)
+    g.close()
