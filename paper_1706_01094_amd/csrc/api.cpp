@@ -372,6 +372,7 @@ struct mclg_ctx {
       d.b_lo = im.b_lo;
       d.nb = im.nb;
       d.fixed = im.fixed ? 1u : 0u;
+      d.skew = image_skew(im.coverage);
       cov += im.coverage * (double)L[r];
       cost[r] = C ? site_cost(im.coverage) : 1.0f;
       crowd += crowded_image(im.coverage) ? (double)L[r] : 0.0;

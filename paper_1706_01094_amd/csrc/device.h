@@ -93,7 +93,7 @@ struct ImageDesc {
   uint32_t dir_bytes = 0;
   uint32_t dim_a = 0, dim_c = 0, b_lo = 0, nb = 0;
   uint32_t fixed = 0;      // records with the window of moves around none (see LdsImage)
-  uint32_t pad = 0;
+  uint32_t skew = 0;       // of a SIMD's waves in a tile launch (see k_tile), at most 21
 };
 
 struct PoisDesc {

@@ -703,29 +703,35 @@ __device__ __attribute__((noinline)) void log_sites(Sites<Q> R, uint32_t xw, uin
 }
 
 // The results of a launch's logs from the waves' records: block (j, u) adds
-// the `held` records of lattice u (of `stride`) at log j into its row.
-__global__ void __launch_bounds__(256) k_log_final(StepLaunch a, RegLog lg, const uint32_t *order,
-                                                   uint32_t n, uint32_t t_off) {
+// the `held` records of lattice u (of `stride`) at log j into its row.  Bound
+// by the latency of its loads, eight in flight per thread: the 4096 records
+// of a tile launch take 19 us (140 with one at a time in 256 threads).
+__global__ void __launch_bounds__(1024) k_log_final(StepLaunch a, RegLog lg, const uint32_t *order,
+                                                    uint32_t n, uint32_t t_off) {
   using namespace mom3;
   const uint32_t j = blockIdx.x / n, u = blockIdx.x % n, slot = order[u];
   const SlotDev sl = a.slots[slot];
   const unsigned long long *const rec = lg.records + ((uint64_t)j * n + u) * lg.stride * kMom3Rec;
-  __shared__ u64 part[8][kMom3Rec];
+  __shared__ u64 part[32][kMom3Rec];
   __shared__ u64 T[kMom3Rec];
-  // thread (g, k): value k of records g, g + 8, ...
-  const uint32_t k = threadIdx.x & 31u, g = threadIdx.x >> 5;
+  // thread (g, k): value k of records g, g + G, ...
+  const uint32_t k = threadIdx.x & 31u, g = threadIdx.x >> 5, G = blockDim.x >> 5;
   const uint32_t hold = lg.hold ? (sl.L + lg.hold - 1u) / lg.hold : lg.stride;
   u64 s = 0;
   if (k < 12u + 2u * lg.n_modes)
-    for (uint32_t w = g; w < hold; w += 8u) {
-      const u64 y = rec[(uint64_t)w * kMom3Rec + k];
-      s = k == 11u ? max(s, y) : s + y;
+    for (uint32_t w = g; w < hold; w += 8u * G) {
+      u64 y[8];
+#pragma unroll
+      for (uint32_t i = 0; i < 8u; ++i)
+        y[i] = w + i * G < hold ? rec[(uint64_t)(w + i * G) * kMom3Rec + k] : 0ull;
+#pragma unroll
+      for (uint32_t i = 0; i < 8u; ++i) s = k == 11u ? max(s, y[i]) : s + y[i];
     }
   part[g][k] = s;
   __syncthreads();
   if (threadIdx.x < kMom3Rec) {
     s = part[0][k];
-    for (uint32_t i = 1; i < 8u; ++i) s = k == 11u ? max(s, part[i][k]) : s + part[i][k];
+    for (uint32_t i = 1; i < G; ++i) s = k == 11u ? max(s, part[i][k]) : s + part[i][k];
     T[k] = s;
   }
   __syncthreads();
@@ -913,13 +919,33 @@ __global__ void __launch_bounds__(1024) k_tile(StepLaunch a, TileLaunch tl) {
     const uint32_t tm = ns ? 0u : t0 % L;
     const uint32_t steps = __builtin_amdgcn_readfirstlane(tl.limit ? tl.limit[slot] : tl.steps);
     const uint32_t tmk = ns ? 0u : (uint32_t)(((uint64_t)t0 + steps) % L);
-    // the unit's tiles: equal ones, a multiple of four (one or more per SIMD)
+    // The unit's tiles, equal ones, dealt to the waves.  A SIMD issues for its
+    // oldest wave first, so that with as many tiles for each of its four the
+    // youngest ends long after the others, alone.  Wave 4 g + j gets them in
+    // the ratio (64 + 3 s) : (64 + s) : (64 - s) : (64 - 3 s) of its g.  s is
+    // the image's skew, smaller where more sites wait for a row (image_skew),
+    // and smaller for few tiles, of which whole ones go to a wave: none up to
+    // one per wave.  2^27 sites, Q = 6, us per step at s = 0: 203, 4: 188, 8:
+    // 177, 10: 171, 12: 175, 16: 192.
     const uint32_t len = ux1 - ux0, tmax = 64u * S - 2u * kh;
-    const uint32_t nt = ((len + tmax - 1u) / tmax + 3u) / 4u * 4u;
+    const uint32_t nt = max((len + tmax - 1u) / tmax, 4u);  // (T + 2 kh <= L, see kMinTiled)
     const uint32_t T = ((len + nt - 1u) / nt + 7u) / 8u * 8u;
     const uint32_t ntile = (len + T - 1u) / T;
-    const uint32_t per = ntile / nw, more = ntile % nw;
-    const uint32_t ta = wave * per + min(wave, more), tb = ta + per + (wave < more ? 1u : 0u);
+    const uint32_t group = wave >> 2, groups = nw >> 2;
+    const uint32_t skew =
+        __builtin_amdgcn_readfirstlane(ntile > nw ? im.skew * (ntile - nw) / ntile : 0u);
+    auto share = [&](uint32_t g) {  // tiles of each of the group's waves, rounded down
+      return ntile * (64u + (groups - 1u) * skew - 2u * skew * g) / (256u * groups);
+    };
+    uint32_t ta = (wave & 3u) * share(group), left = ntile;
+    for (uint32_t g = 0; g < groups; ++g) {
+      left -= 4u * share(g);
+      ta += g < group ? 4u * share(g) : 0u;
+    }
+    // (fewer than 4 groups are left: one each for the oldest)
+    const uint32_t tb0 = ta + share(group);
+    ta += min(wave, left);
+    const uint32_t tb = tb0 + min(wave, left) + (wave < left ? 1u : 0u);
     const uint32_t X0 = ux0 + ta * T, end = min(ux1, ux0 + tb * T);  // the wave's run
     const uint32_t endp = (end + 7u) & ~7u, ux1p = (ux1 + 7u) & ~7u;
     const Rsrc lrs = __builtin_amdgcn_make_buffer_rsrc(
@@ -1126,7 +1152,7 @@ hipError_t launch_tiles(hipStream_t s, const StepLaunch &a, const TileLaunch &tl
   if (tl.steps == 0) return hipSuccess;
   // the tiles' own sites, the private areas and their number; logs of one
   // lattice only
-  if (waves < 1 || waves > 16 || tl.kh % 8u != 0u || tl.steps > tl.kh || 2u * tl.kh >= 256u * Q ||
+  if (waves < 4 || waves > 16 || waves % 4u || tl.kh % 8u != 0u || tl.steps > tl.kh || 2u * tl.kh >= 256u * Q ||
       36u * tl.kh > 16u * kOverflowPerWave || grid * waves > kOverflowWaves ||
       !log_ok(tl.log, tl.steps, grid * waves) || (tl.log.n && (a.n_slots != 1u || tl.limit)))
     return hipErrorInvalidValue;
@@ -1138,7 +1164,7 @@ hipError_t launch_tiles(hipStream_t s, const StepLaunch &a, const TileLaunch &tl
   const dim3 g(grid), block(64u * waves);
   const uint32_t lds = reg_lds_bytes(a.lds_bytes, waves);
   MCLG_REG_LAUNCH(k_tile, g, tl)
-  if (tl.log.n) k_log_final<<<tl.log.n, 256, 0, s>>>(a, tl.log, order, 1u, a.t_off);
+  if (tl.log.n) k_log_final<<<tl.log.n, 1024, 0, s>>>(a, tl.log, order, 1u, a.t_off);
   return hipGetLastError();
 }
 

@@ -78,12 +78,16 @@ UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks, const float 
 namespace {
 // Times on MI355X (us), fitted to measured steps of lattices of 256 to 2^27
 // sites at rho = 50.  A wave that is alone on its SIMD takes 0.72 + 0.58 Q for
-// a step of its 256 Q sites (latency), and a SIMD with many of them 0.27 +
-// 0.28 Q for each (issue); `per_simd` waves in `turns` turns take a little
-// more than the larger of the two.
-double tile_step_us(uint32_t Q, double per_simd, double turns) {
-  const double issue = per_simd * (0.27 + 0.28 * Q), wait = turns * (0.72 + 0.58 * Q);
-  return std::sqrt(std::sqrt(issue * issue * issue * issue + wait * wait * wait * wait));
+// a step of its 256 Q sites (latency); a SIMD with one or more for each of its
+// four waves issues for 0.14 + 0.283 Q per tile (as dealt by k_tile), and a
+// little for the end where not all have one; with fewer, 0.27 + 0.28 Q.  Both
+// together take a little more than the larger of the two.
+double tile_step_us(uint32_t Q, uint64_t tiles) {
+  const double n = tiles > 16 ? (double)tiles / 4.0 : (double)((tiles + 3) / 4);
+  const double issue = tiles > 16 ? (0.14 + 0.283 * Q) * (n + 0.3 + 0.2 * Q) : n * (0.27 + 0.28 * Q);
+  const double wait = std::max(1.0, (double)tiles / 16.0) * (0.72 + 0.58 * Q);
+  const double most = std::max(issue, wait), x = std::min(issue, wait) / most;
+  return most * std::sqrt(std::sqrt(1.0 + x * x * x * x));
 }
 // A lattice in one block's registers: without the private areas and the
 // extra sites, but with a barrier per step when several waves hold it.
@@ -93,7 +97,16 @@ double ring_step_us(uint32_t Q, uint32_t waves, bool together) {
   return step + (together && waves > 1 ? 0.5 + 0.1 * Q : 0.0);
 }
 constexpr double kRingLaunch = 5.0;   // launch, image and the sites' way in and out
-constexpr double kTileLaunch = 9.0;   // the same for the tiles
+// The same for the tiles; to it comes the state's way in and out, of which the
+// registers of Q = 6 leave more uncovered.  Measured, us per launch at 2^20,
+// 2^22, 2^24 and 2^27 sites: Q <= 4 16, 23, 45 and 125, Q = 6 19, 32, 55 and
+// 200.
+constexpr double kTileLaunch = 12.0;
+double state_us(uint32_t Q, uint64_t sites) {
+  const double s = (double)sites, most = (double)(1u << 24);
+  return 1.6e-6 * std::min(s, most) + 0.9e-6 * std::max(0.0, s - most) + (Q < 6 ? 0.0 : 6.0 + 0.45e-6 * s);
+}
+constexpr double kTileLogs = 25.0;    // the logs' records and their sum
 constexpr double kStripsLaunch = 2.5;
 constexpr double kUnit = 4.0;         // every further unit of a block: image and barriers
 }  // namespace
@@ -162,8 +175,7 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
         double us = 0;
         for (uint32_t i = plan.first[b]; i < plan.first[b + 1]; ++i) {
           const uint64_t len = plan.units[i].x1 - plan.units[i].x0;
-          const uint64_t nt = ((len + tmax - 1) / tmax + 3) / 4;  // per SIMD
-          us += tile_step_us(Q, (double)nt, (double)((nt + 3) / 4)) *
+          us += tile_step_us(Q, std::max<uint64_t>(4, (len + tmax - 1) / tmax)) *
                 (cost ? cost[plan.units[i].slot] / weight : 1.0);
         }
         worst = std::max(worst, us);
@@ -171,7 +183,7 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
       }
       y.launch_us = kTileLaunch + (plan.strips.empty() ? 0.0 : kStripsLaunch) +
                     std::max(0.0, images - 1.0) * kUnit +
-                    2.0e-6 * (double)std::min<uint64_t>(total, 1u << 25);
+                    state_us(Q, total);
       y.step_us = worst;
       if (plan.n_long < n) {  // and a ring launch for the others
         y.launch_us += kRingLaunch;
@@ -190,7 +202,8 @@ const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, bool log
   for (const RegWay &w : ways) {
     if (logs && !w.logs) continue;
     const double launches = w.kind == RegWay::kTile ? (double)((steps + w.most - 1) / w.most) : 1.0;
-    const double us = launches * w.launch_us + (double)steps * w.step_us;
+    const double us = launches * (w.launch_us + (logs && w.kind == RegWay::kTile ? kTileLogs : 0.0)) +
+                      (double)steps * w.step_us;
     if (us < least) {
       least = us;
       best = &w;

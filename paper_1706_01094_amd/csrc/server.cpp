@@ -415,6 +415,7 @@ struct mclg_server {
       idd.b_lo = img.b_lo;
       idd.nb = img.nb;
       idd.fixed = img.fixed;
+      idd.skew = image_skew(img.coverage);
       if (!e) e = put(ws + lay.o_ipool + idd.off, img.blob);
       if (!e) e = put(d_slots() + r.slot, &sd, sizeof(sd));
       if (!e) e = put(d_idesc() + r.slot, &idd, sizeof(idd));
