@@ -173,7 +173,6 @@ int d2q9_layout(const mclg_config *cfg, D2Ctx &d) {
   };
   d.o_err = take(256);
   d.o_reps = take(sizeof(Rep9) * d.n);
-  d.o_tiles = take(sizeof(Tile9) * d.tiles.size());
   d.o_rules = take(sizeof(uint32_t) * d.rules_dev.size());
   {
     std::vector<uint32_t> ids(d.n);
@@ -187,11 +186,13 @@ int d2q9_layout(const mclg_config *cfg, D2Ctx &d) {
   d.o_mseg = take(sizeof(MomSeg) * d.mplan.segs.size());
   d.o_mrun = take(sizeof(uint32_t) * d.mplan.run_seg.size());
   d.o_mslot = take(sizeof(uint32_t) * d.mplan.run_slot.size());
+  d.o_dense = take(sizeof(uint64_t) * d.n);
+  d.o_pdesc = take(sizeof(PoisDesc) * 9 * d.n);
+  // (up to here d2q9_init uploads in one piece)
+  d.o_tiles = take(sizeof(Tile9) * d.tiles.size());
+  d.o_pool = take(sizeof(uint32_t) * kPoisCap9 * 9 * d.n);
   d.o_mpart = take(sizeof(uint64_t) * kMom9Rec * d.mplan.segs.size());
   d.o_mout = take(sizeof(uint64_t) * kMom9Out * d.n);
-  d.o_pdesc = take(sizeof(PoisDesc) * 9 * d.n);
-  d.o_pool = take(sizeof(uint32_t) * kPoisCap9 * 9 * d.n);
-  d.o_dense = take(sizeof(uint64_t) * d.n);
   d.ws_bytes = o;
   return MCLG_OK;
 }
@@ -242,16 +243,20 @@ int d2q9_init(D2Ctx &d, const mclg_config *cfg, const mclg_init_spec *init) {
     return bytes ? hipMemcpyAsync(d.ws + off, src, bytes, hipMemcpyHostToDevice, d.stream)
                  : hipSuccess;
   };
-  std::vector<uint32_t> zero(64, 0u);
-  hipError_t e = put(d.o_err, zero.data(), 256);
-  if (!e) e = put(d.o_reps, d.reps.data(), sizeof(Rep9) * d.n);
+  // the small tables in one copy (each takes the host some 10 us)
+  std::vector<uint8_t> head(d.o_tiles, 0);
+  auto lay = [&](uint64_t off, const void *src, size_t bytes) {
+    if (bytes) std::memcpy(head.data() + off, src, bytes);
+  };
+  lay(d.o_reps, d.reps.data(), sizeof(Rep9) * d.n);
+  lay(d.o_rules, d.rules_dev.data(), sizeof(uint32_t) * d.rules_dev.size());
+  lay(d.o_mseg, d.mplan.segs.data(), sizeof(MomSeg) * d.mplan.segs.size());
+  lay(d.o_mrun, d.mplan.run_seg.data(), sizeof(uint32_t) * d.mplan.run_seg.size());
+  lay(d.o_mslot, d.mplan.run_slot.data(), sizeof(uint32_t) * d.mplan.run_slot.size());
+  lay(d.o_dense, d.dense.data(), sizeof(uint64_t) * d.n);
+  lay(d.o_pdesc, pdesc.data(), sizeof(PoisDesc) * pdesc.size());
+  hipError_t e = put(0, head.data(), head.size());
   if (!e) e = put(d.o_tiles, d.tiles.data(), sizeof(Tile9) * d.tiles.size());
-  if (!e) e = put(d.o_rules, d.rules_dev.data(), sizeof(uint32_t) * d.rules_dev.size());
-  if (!e) e = put(d.o_dense, d.dense.data(), sizeof(uint64_t) * d.n);
-  if (!e) e = put(d.o_mseg, d.mplan.segs.data(), sizeof(MomSeg) * d.mplan.segs.size());
-  if (!e) e = put(d.o_mrun, d.mplan.run_seg.data(), sizeof(uint32_t) * d.mplan.run_seg.size());
-  if (!e) e = put(d.o_mslot, d.mplan.run_slot.data(), sizeof(uint32_t) * d.mplan.run_slot.size());
-  if (!e && !pool.empty()) e = put(d.o_pdesc, pdesc.data(), sizeof(PoisDesc) * pdesc.size());
   if (!e && !pool.empty()) e = put(d.o_pool, pool.data(), sizeof(uint32_t) * pool.size());
   const Rep9 *reps = reinterpret_cast<const Rep9 *>(d.ws + d.o_reps);
   const Tile9 *tiles = reinterpret_cast<const Tile9 *>(d.ws + d.o_tiles);
@@ -263,8 +268,6 @@ int d2q9_init(D2Ctx &d, const mclg_config *cfg, const mclg_init_spec *init) {
   if (!e && init->kind == MCLG_INIT_COUNTS)
     e = launch_init9_counts(d.stream, d.state, reps, tiles, (uint32_t)d.tiles.size(),
                             reinterpret_cast<const uint64_t *>(d.ws + d.o_dense), init->counts);
-  if (!e && d.n <= kMomPinned)
-    e = hipHostMalloc(reinterpret_cast<void **>(&d.pin), 8ull * (kMom9Out * d.n + 1u), hipHostMallocDefault);
   // the host vectors above must outlive the copies
   if (!e) e = hipStreamSynchronize(d.stream);
   d.t = 0;
@@ -286,11 +289,11 @@ int d2q9_step(D2Ctx &d, uint64_t n_steps) {
   uint32_t sites = 0;
   for (const Rep9 &r : d.reps) sites = std::max(sites, r.S);
   // One launch for all steps where that is quicker than one for each.  Us per
-  // step, separate and together: 256 sites 6.4 and 3.0 + 4.1 per launch, 20000
-  // lattices of them 130 and 92 + 68; 1000 sites 7.4 and 6.1 + 5.5 (their waves
-  // share one CU instead of four), 4096 lattices of them 107 and 98 + 98.
-  const uint64_t from = sites <= 512u ? 2u : d.n <= 256u ? 6u : 16u;
-  if (sites <= kBlockSites9 && n_steps >= from) {
+  // step, separate and together (2 steps, 64 steps): 256 sites 5.3 and 4.7, 3.1,
+  // 20000 lattices of them 114 and 110, 93; 500 sites 5.8 and 5.7, 4.0, 4096 of
+  // them 55 and 50, 40; but 1000 sites 5.9 and 6.8 (6 steps), 6.2, 4096 of them
+  // 94 and 103 (16 steps), 99: their waves share one CU instead of four.
+  if (sites <= kBlockSites9 && n_steps >= 2) {
     while (n_steps) {
       const uint32_t k = (uint32_t)std::min<uint64_t>(n_steps, 1u << 16);
       a.t = (uint64_t)d.t;
@@ -366,6 +369,12 @@ int d2q9_moments(D2Ctx &d, mclg_moments9_t *out) {
   m.n_runs = d.n;
   m.partial = reinterpret_cast<unsigned long long *>(d.ws + d.o_mpart);
   m.out = reinterpret_cast<long long *>(d.ws + d.o_mout);
+  // (not in d2q9_init: contexts that are only stepped need none)
+  if (!d.pin && d.n <= kMomPinned) {
+    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&d.pin), 8ull * (kMom9Out * d.n + 1u),
+                                 hipHostMallocDefault);
+    if (e) return hip_rc(d, e);
+  }
   if (d.pin) {
     m.out = d.pin;
     m.err = reinterpret_cast<const uint32_t *>(d.ws + d.o_err);

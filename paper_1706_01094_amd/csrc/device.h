@@ -293,7 +293,7 @@ struct Step9 {
 };
 hipError_t launch_step9(hipStream_t s, const Step9 &a, uint32_t n_tiles);
 // `steps` steps of lattices of up to kBlockSites9 sites in one launch.
-constexpr uint32_t kBlockSites9 = 1024;
+constexpr uint32_t kBlockSites9 = 512;
 hipError_t launch_steps9(hipStream_t s, const Step9 &a, uint32_t n_reps, uint32_t max_sites,
                          uint32_t steps);
 hipError_t launch_init9_poisson(hipStream_t s, uint16_t *state, const Rep9 *reps,

@@ -230,6 +230,15 @@ __device__ __forceinline__ void collide_wide(u16x2 (&K)[4], const uint4 *rules, 
 // writes between two barriers; all waves of the block call this per tile.
 constexpr uint32_t kRulesLds = 144 * kRule9Half;
 static_assert(kRulesLds >= 81 * kRule9Wide && kRulesLds >= 144 * kRule9Byte, "room for each table");
+struct Table9 {
+  const uint4 *src;
+  uint32_t n;  // 16-byte pieces
+};
+__device__ __forceinline__ Table9 table9(const Step9 &a, uint32_t which) {
+  const uint32_t at = which == 1u ? kRule9ByteAt : which == 2u ? kRule9HalfAt : kRule9WideAt;
+  const uint32_t words = which == 1u ? 144 * kRule9Byte : which == 2u ? 144 * kRule9Half : 81 * kRule9Wide;
+  return Table9{reinterpret_cast<const uint4 *>(a.rules + at), words / 4u};
+}
 __device__ __forceinline__ void hold_rules(const Step9 &a, uint32_t *rules, uint32_t *needs,
                                            uint32_t &held) {
   // (a barrier that waits for the LDS only: the last tile's stores stay in
@@ -240,10 +249,8 @@ __device__ __forceinline__ void hold_rules(const Step9 &a, uint32_t *rules, uint
   const uint32_t need = __builtin_amdgcn_readfirstlane(max(held, *needs));
   if (need == held) return;
   // (every wave's: it read the old table in an earlier tile, if at all)
-  const uint32_t at = need == 1u ? kRule9ByteAt : need == 2u ? kRule9HalfAt : kRule9WideAt;
-  const uint32_t words = need == 1u ? 144 * kRule9Byte : need == 2u ? 144 * kRule9Half : 81 * kRule9Wide;
-  const uint4 *const src = reinterpret_cast<const uint4 *>(a.rules + at);
-  for (uint32_t i = threadIdx.x; i < words / 4u; i += blockDim.x) reinterpret_cast<uint4 *>(rules)[i] = src[i];
+  const Table9 tb = table9(a, need);
+  for (uint32_t i = threadIdx.x; i < tb.n; i += blockDim.x) reinterpret_cast<uint4 *>(rules)[i] = tb.src[i];
   held = need;
   __syncthreads();
 }
@@ -291,8 +298,13 @@ __device__ __forceinline__ void collide_site(uint32_t (&n)[9], uint32_t N, const
 __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles) {
   __shared__ __align__(16) uint32_t rules[kRulesLds];
   __shared__ uint32_t needs[2];
-  uint32_t held = 0, par = 0;
-  if (threadIdx.x < 2u) needs[threadIdx.x] = a.Dq > kRule9MaxPacked ? 3u : 1u;
+  // (the narrowest table that Dq allows comes in beside the rest, not after the
+  // first tile's counts: the steps of small lattices are a chain of latencies)
+  const uint32_t first = a.Dq > kRule9MaxPacked ? 3u : 1u;
+  uint32_t held = first, par = 0;
+  const Table9 tb = table9(a, first);
+  for (uint32_t i = threadIdx.x; i < tb.n; i += blockDim.x) reinterpret_cast<uint4 *>(rules)[i] = tb.src[i];
+  if (threadIdx.x < 2u) needs[threadIdx.x] = first;
   __syncthreads();
   uint32_t rep = ~0u, tx = 0, ty = 0;
   Rep9 rp{};
@@ -331,13 +343,14 @@ __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles
   }
 }
 
-// `steps` steps of lattices of up to 1024 sites, one per block, a site per
+// `steps` steps of lattices of up to 512 sites, one per block, a site per
 // thread: the counts stay in LDS, in the same shifted layout, between one read
 // and one write of the state.  Without the state's way through memory and a
-// launch per step; bound by the instructions of a block's 16 waves on one CU.
-// Us per step: a lattice of 16 x 16 sites 6.4 with a launch each and 3.0 here,
-// 13 of 100 x 10 sites 7.4 and 6.1.
-__global__ void __launch_bounds__(1024) k_steps9(Step9 a, uint32_t steps) {
+// launch per step; bound by the latency of a wave's sub-collisions, two waves
+// per SIMD.  Us per step: a lattice of 16 x 16 sites 5.3 with a launch each and
+// 3.1 here, of 25 x 20 sites 5.8 and 4.0.  (With 1000 sites the 16 waves on one
+// CU take 6.2, where four blocks of k_step9 take 5.9.)
+__global__ void __launch_bounds__(kBlockSites9) k_steps9(Step9 a, uint32_t steps) {
   extern __shared__ __align__(16) uint16_t counts[];  // 9 arrays of S
   __shared__ __align__(16) uint32_t rules[kRulesLds];
   __shared__ uint32_t needs[2];
@@ -345,8 +358,10 @@ __global__ void __launch_bounds__(1024) k_steps9(Step9 a, uint32_t steps) {
   const uint32_t S = rp.S, s = min(threadIdx.x, S - 1u), x = s % rp.Lx;
   for (uint32_t i = 0; i < 9u; ++i)
     for (uint32_t e = threadIdx.x; e < S; e += blockDim.x) counts[i * S + e] = *at9(a.state, rp, (int)i, e);
-  uint32_t held = 0;
-  if (threadIdx.x < 2u) needs[threadIdx.x] = a.Dq > kRule9MaxPacked ? 3u : 1u;
+  uint32_t held = a.Dq > kRule9MaxPacked ? 3u : 1u;  // (see k_step9)
+  const Table9 tb = table9(a, held);
+  for (uint32_t i = threadIdx.x; i < tb.n; i += blockDim.x) reinterpret_cast<uint4 *>(rules)[i] = tb.src[i];
+  if (threadIdx.x < 2u) needs[threadIdx.x] = held;
   uint32_t tx = a.no_stream ? 0u : (uint32_t)(a.t % rp.Lx), ty = a.no_stream ? 0u : (uint32_t)(a.t % rp.Ly);
   for (uint32_t k = 0; k < steps; ++k) {
     __syncthreads();  // the counts of this step are in place
