@@ -210,7 +210,7 @@ int mclg_sizes(const mclg_config *cfg, uint64_t *state_bytes, uint64_t *workspac
  * synchronise the stream.  On success *out owns a host context. */
 int mclg_init(const mclg_config *cfg, const mclg_init_spec *init, mclg_ctx **out);
 
-/* Enqueue n_steps steps of every replica (one batched launch per step). */
+/* Enqueue n_steps steps of every replica, as many per launch as is quickest. */
 int mclg_step(mclg_ctx *ctx, uint64_t n_steps);
 
 /* Enqueue n_steps steps of one replica only (one launch per step): the plain
@@ -328,9 +328,10 @@ int mclg_set_drain(mclg_ctx *ctx, uint32_t policy);
  * neighbours at t, so whoever holds a range of sites and k more on each side
  * can advance it k steps alone).  mclg_step picks by itself between one step
  * per launch on sites in memory and several on sites held in registers, by
- * the lattices' sizes and the call's steps, unless mclg_set_schedule,
- * mclg_set_drain or mclg_set_grid_limit made a choice of launches; with
- * blocking on, it picks whatever the drain policy and the grid limit are.
+ * the lattices' sizes and the call's steps, unless mclg_set_schedule (other
+ * than 1024 threads, or an image of less than 128 KiB), mclg_set_drain or
+ * mclg_set_grid_limit made a choice of launches; with blocking on, it picks
+ * whatever the drain policy and the grid limit are.
  * The bits are the same either way.
  *   steps, tile: kept for programs that lay out their scratch by them; the
  *     launches choose their own.  tile is 0 or 1, or for one lattice a

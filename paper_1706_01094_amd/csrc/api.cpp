@@ -27,6 +27,8 @@ constexpr uint32_t kPadElems = 128;     // array stride granularity (256 B)
 constexpr uint32_t kMinTileSites = 512; // chunk of the step kernel
 constexpr uint32_t kPoisCap = 1024;     // thresholds per initial Poisson law
 constexpr uint32_t kMaxImage = 160 * 1024; // largest LDS collision image
+// Smallest image budget of a schedule that still takes the register kernels.
+constexpr uint32_t kRegImage = 128 * 1024;
 
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
@@ -176,9 +178,11 @@ struct mclg_ctx {
   // The launch choices mclg_set_schedule, mclg_set_drain and
   // mclg_set_grid_limit make belong to the kernels that keep the state in
   // memory: with any of them set, those kernels run, unless several steps per
-  // launch were asked for as well.
+  // launch were asked for as well.  A schedule of 1024 threads is what the
+  // register kernels run with too, and its image budget serves both alike, so
+  // they keep such a context down to kRegImage bytes.
   bool reg_launch() const {
-    return sch.threads == 1024 && sch.lds_budget == Schedule().lds_budget &&
+    return sch.threads == 1024 && sch.lds_budget >= kRegImage &&
            (blocked || (drain_policy == MCLG_DRAIN_AUTO && grid_limit == 0));
   }
   RegBufs reg_bufs() const {

@@ -17,13 +17,15 @@ from paper_1706_01094_amd.mclg import E_RANGE, FLAG_GALILEAN, FLAG_NO_STREAM, La
 pytestmark = pytest.mark.gpu
 
 
-def run(L, steps, rho=30.0, u0=0.1, counts=None, check=0, **kw):
+def run(L, steps, rho=30.0, u0=0.1, counts=None, check=0, schedule=None, **kw):
     print("[gpu] case", L if np.ndim(L) == 0 else (len(L), L[:4]), steps, kw, flush=True)
     sys.stdout.flush()
     Ls = np.atleast_1d(np.asarray(L, dtype=np.uint64))
     rhos, u0s = np.broadcast_to(rho, Ls.shape), np.broadcast_to(u0, Ls.shape)
     init = {"counts": counts} if counts is not None else {"rho": rho, "u0": u0}
     g = Lattice(Ls, 83, **init, **kw)
+    if schedule is not None:
+        g.set_schedule(*schedule)
     o = O.OracleSim(Ls, 83, **kw)
     for r in range(len(Ls)):
         if counts is not None:
@@ -79,6 +81,14 @@ def test_more_misses_than_the_queue_holds(L):
     same density): all draws come from the global rows."""
     counts = np.full((3, L), 60, dtype=np.uint16)
     run(L, (3, 20), counts=counts)
+
+
+@pytest.mark.parametrize("L", [3001, 100003])
+@pytest.mark.parametrize("lds", [(128 << 10) - 16, 128 << 10, 146176, 160 << 10])
+def test_image_budgets_of_a_schedule(L, lds):
+    """Around the smallest budget that takes these kernels, and the largest;
+    dense, so that the images differ."""
+    run(L, (3, 40), rho=90.0, u0=0.2, schedule=(1, 1024, lds))
 
 
 @pytest.mark.parametrize("L", [900, 60005])
