@@ -3,7 +3,7 @@
 One step = one fused stream + Monte Carlo collide pass over every site of the
 workload (D1Q3, L = 2^24, rho = 50, u0 = 0.1, C = 10, lambda = 1, Poisson
 initial state, seed 2).  Prints one JSON line with site updates per second,
-the HBM roofline of the fused kernel, and the oracle timed on the host; the
+the roofline of the fused kernel, and the oracle timed on the host; the
 other workloads (an HBM-resident lattice, the 1024-replica batch, the
 density wave, the served trace, D2Q9, and the headline lattice at lower
 densities and without collisions, which shows what bounds its step) follow
@@ -40,9 +40,10 @@ TRAFFIC_FILES = {
     "batched_blocked": os.path.join(PROFILES, "traffic_stream_collide_1024_replicas_blocked.json"),
 }
 TRAFFIC_FILE = TRAFFIC_FILES["plain"]
-# the sources the D1Q3 step kernel is compiled from
+# the sources of the D1Q3 step kernels and of the plan of their launches
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1706_01094_amd", "csrc", f)
-               for f in ("kernels.hip", "rng.h", "device.h", "mom3_sum.h", "moments.h")]
+               for f in ("kernels.hip", "kernels_reg.hip", "collide.h", "rng.h", "device.h",
+                         "mom3_sum.h", "moments.h", "regplan.cpp")]
 
 # the D2Q9 step kernel: its sources and its counted VALU instructions per site
 D2Q9_SRCS = [os.path.join(ROOT, "paper_1706_01094_amd", "csrc", f)
@@ -73,6 +74,16 @@ def _counter_record(which: str, steps_per_launch: int = 1):
     if d.get("kernel_sha256_16") != kernel_hash():
         return None
     return d if d.get("steps_per_launch", 1) == steps_per_launch else None
+
+
+def counted_steps(which: str) -> int:
+    """Steps per launch of the committed counter run of this workload (the
+    library chooses them for the number of steps of a call)."""
+    try:
+        with open(TRAFFIC_FILES[which]) as f:
+            return int(json.load(f).get("steps_per_launch", 1))
+    except (OSError, ValueError):
+        return 1
 
 
 def measured_traffic(which: str = "plain", steps_per_launch: int = 1):
@@ -153,8 +164,8 @@ def run_plain(args, torch, M):
             if 6 * L <= INFINITY_CACHE_BYTES else "hbm"}
     K = args.blocked if not args.graph else 1
     if K > 1:
-        lat.set_blocked(K)  # K steps per launch (temporal blocking)
-    info["steps_per_launch"] = max(1, K)
+        lat.set_blocked(K)  # several steps per launch, also with --schedule
+    info["steps_per_launch"] = counted_steps("plain") if K > 1 else 1
     lat.step(args.warmup)
     torch.cuda.synchronize()
     e0, e1 = _events(torch, stream)
@@ -177,8 +188,10 @@ def run_plain(args, torch, M):
     if rc != 0:
         raise SystemExit(f"device error {rc}")
     if K > 1 and args.single_steps:
-        # the same lattice with one step per launch, for comparison
+        # the same lattice with one step per launch, for comparison (a fixed
+        # drain policy, the one its size would get, keeps to those kernels)
         lat.set_blocked(1)
+        lat.set_drain(M.DRAIN_DEFERRED)
         lat.step(20)
         torch.cuda.synchronize()
         e0, e1 = _events(torch, stream)
@@ -191,6 +204,7 @@ def run_plain(args, torch, M):
             "steps": args.single_steps, "ms_per_step": ms1,
             "site_updates_per_s": L / (ms1 / 1e3),
             "frac": BYTES_PER_SITE_UPDATE * L / (ms1 / 1e3) / 1e9 / HBM_PEAK_GBS}
+        lat.set_drain(M.DRAIN_AUTO)
     stats = plain_statistics(lat, args.stat_logs)
     lat.close()
     return L, gpu_ms, wall, info, stats
@@ -220,7 +234,6 @@ def run_probe(args, torch, M):
     w = synth.PLAIN_LARGE
     L = 1 << 27
     lat = M.Lattice(L, w["seed"], C=10, lam=(1, 1), n_max=255, rho=w["rho"], u0=w["u0"])
-    lat.step(5)
 
     def timed(steps):
         torch.cuda.synchronize()
@@ -231,18 +244,22 @@ def run_probe(args, torch, M):
         torch.cuda.synchronize()
         return e0.elapsed_time(e1) / steps
 
-    # one step per launch: the kernel streams the state from HBM at every step
+    # one step per launch (a fixed drain policy, the one its size would get,
+    # keeps to those kernels): the state streams from HBM at every step
+    lat.set_drain(M.DRAIN_PATCH)
+    lat.step(5)
     ms = timed(args.probe_steps)
+    lat.set_drain(M.DRAIN_AUTO)
     blocked = None
     K = args.probe_blocked
     if K > 1:
-        # several steps per launch in tiles (their copies go between the L2s
-        # and the Infinity Cache): the state is read and written once per launch
-        lat.set_blocked(K)
+        # several steps per launch in tiles held in registers: the state is
+        # read and written once per launch
         lat.step(K)
         n = max(1, args.probe_steps // K) * K
         bms = timed(n)
         ach = BYTES_PER_SITE_UPDATE * L / (bms / 1e3) / 1e9
+        K = counted_steps("probe_blocked")
         btr = measured_traffic("probe_blocked", K)
         blocked = {"steps_per_launch": K, "steps": n, "ms_per_step": bms,
                    "site_updates_per_s": L / (bms / 1e3), "achieved_GBps": ach,
@@ -326,7 +343,8 @@ def batched_observables(lat, torch, man, samples: int, every: int) -> dict:
 
 def run_batched(args, torch, M):
     """1024 independent replicas of uneven L and density: plain per-replica
-    launches vs one batched launch per step vs captured HIP graphs."""
+    launches vs batched launches (several steps each, as the library picks
+    for the tuned schedule) vs captured HIP graphs of one step per launch."""
     import synth
     from paper_1706_01094_amd import autotune
     man = synth.replica_manifest()
@@ -363,8 +381,8 @@ def run_batched(args, torch, M):
         out[mode] = {"steps": args.batched_steps, "ms": ms, "us_per_step":
                      1e3 * ms / args.batched_steps, "site_updates_per_s": rate,
                      "hbm_frac": BYTES_PER_SITE_UPDATE * rate / 1e9 / HBM_PEAK_GBS}
-    # several steps per launch: each block advances whole replicas, K steps
-    # on copies in the caches (the state is read and written once per launch)
+    # several steps per launch, whatever the tuned schedule (the state is read
+    # and written once per launch)
     K = args.batched_blocked
     out["blocked"] = None
     if K > 1:
@@ -383,6 +401,7 @@ def run_batched(args, torch, M):
             torch.cuda.synchronize()
             ms = e0.elapsed_time(e1)
             rate = sites * nb / (ms / 1e3)
+            K = counted_steps("batched_blocked")
             btr = measured_traffic("batched_blocked", K)
             out["blocked"] = {"steps_per_launch": K, "steps": nb, "ms": ms,
                               "us_per_step": 1e3 * ms / nb, "site_updates_per_s": rate,
@@ -393,11 +412,12 @@ def run_batched(args, torch, M):
                               "valu_issue_frac": valu_issue_frac("batched_blocked",
                                                                  ms / 1e3 * K / nb, K)}
             lat.set_blocked(1)
+    # the graph's launches take one step each
     traffic = measured_traffic("batched")
     out["traffic"] = traffic
     out["traffic_over_algorithmic"] = None if traffic is None else \
         traffic / (BYTES_PER_SITE_UPDATE * sites)
-    out["valu_issue_frac"] = valu_issue_frac("batched", out["batched"]["us_per_step"] / 1e6)
+    out["valu_issue_frac"] = valu_issue_frac("batched", out["graph"]["us_per_step"] / 1e6)
     # plain: one launch per replica per step
     n = len(man["L"])
     e0, e1 = _events(torch, lat.stream)
@@ -454,7 +474,7 @@ def run_wave(args, torch, M):
     del warm
     lat = M.Lattice(L, w["seed"], counts=counts)
     if K > 1:
-        lat.set_blocked(K)  # launches of K steps, each summing the logs in it
+        lat.set_blocked(K)  # (each launch sums the logs in it)
     logs = w["steps"] // w["log_every"]
     rec = torch.zeros((logs, words), dtype=torch.int64, device=lat.device)
     lat.stream.wait_stream(torch.cuda.current_stream(lat.device))
@@ -479,7 +499,7 @@ def run_wave(args, torch, M):
     ss = float(np.sum(tw[1].astype(np.float64) ** 2))
     amp = host[:, off_sin].astype(np.float64) * float(1 << 24) / ss
     return {"workload": "d1q3_L4M_wave_rho40", "steps": w["steps"], "logs": logs,
-            "steps_per_launch": max(1, K), "gpu_ms": ms, "wall_s": wall,
+            "gpu_ms": ms, "wall_s": wall,
             "site_updates_per_s_incl_logging": L * w["steps"] / (ms / 1e3),
             "amplitude_expected_initial": w["rho"] * w["amp"],
             "amplitude_first": float(amp[0]), "amplitude_last": float(amp[-1]),
@@ -589,15 +609,15 @@ def run_d2q9(args, torch, M):
 
 
 def run_bound(args, torch, M):
-    """What bounds the blocked step: the headline lattice (L = 2^24, `--blocked`
-    steps per launch) at the headline density, at lower densities (fewer
-    misses of the LDS image) and with no collisions at all (C = 0: the
-    kernel only streams the blocks' copies), each timed over `--bound-steps`
-    steps after one warm-up launch."""
+    """What bounds the step: the headline lattice (L = 2^24, several steps per
+    launch) at the headline density, at lower densities (fewer misses of the
+    LDS image) and with no collisions at all (C = 0: the sites stay in
+    registers and only stream), each timed over `--bound-steps` steps after
+    a warm-up call of `--blocked` steps."""
     import synth
     w = synth.PLAIN_LARGE
     L, K = w["L"], max(2, args.blocked)
-    out = {"L": L, "steps_per_launch": K, "cases": []}
+    out = {"L": L, "cases": []}
     for C, rho, u0 in ((10, w["rho"], w["u0"]), (10, 20.0, 0.0), (10, 5.0, 0.0), (0, w["rho"], w["u0"])):
         lat = M.Lattice(L, w["seed"], C=C, lam=(1, 1), n_max=255, rho=rho, u0=u0)
         lat.set_blocked(K)
@@ -648,6 +668,22 @@ def run_moments(args, torch, M):
     return out
 
 
+def roofline(achieved: float, ms_per_step: float, K: int) -> dict:
+    """The headline's roofline.  One step per launch: 12 B per site update
+    against the HBM peak.  Several steps per launch read and write the state
+    once for all of them and are bound by VALU issue (the counted
+    instructions of a launch of K steps); the rate at 12 B per site update
+    stands beside it."""
+    hbm = {"achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS}
+    rest = {"steps_per_launch": K, "traffic": measured_traffic("plain", K)}
+    issue = valu_issue_frac("plain", ms_per_step * K / 1e3, K)
+    if K == 1 or issue is None:
+        return {"bound": "hbm", **hbm, **rest, "valu_issue_frac": issue}
+    return {"bound": "alu", "achieved": issue * VALU_PEAK_G, "peak": VALU_PEAK_G,
+            "unit": "G VALU wave-instructions/s", "frac": issue, **rest,
+            "at_12_bytes_per_update": hbm}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -672,17 +708,18 @@ def main():
     ap.add_argument("--probe-steps", type=int, default=200)
     ap.add_argument("--stat-logs", type=int, default=10)
     ap.add_argument("--blocked", type=int, default=256,
-                    help="steps per launch of the L = 2^24 workload (temporal blocking; 1: off)")
+                    help="several steps per launch for the L = 2^24 workload, with scratch "
+                         "for this many (1: as the library picks)")
     ap.add_argument("--single-steps", type=int, default=2000,
                     help="steps of the one-step-per-launch comparison of the blocked run")
     ap.add_argument("--batched-blocked", type=int, default=128,
-                    help="steps per launch of the batched run's blocked variant (1: off)")
+                    help="steps per call of the batched run's variant with scratch (1: off)")
     ap.add_argument("--probe-blocked", type=int, default=128,
-                    help="steps per launch of the L = 2^27 probe's blocked run, in tiles "
-                         "(1: off)")
+                    help="steps per call of the L = 2^27 probe with several steps per "
+                         "launch (1: off)")
     ap.add_argument("--wave-blocked", type=int, default=250,
-                    help="steps per launch of the density wave (each launch sums the logs "
-                         "that fall in it; 1: off)")
+                    help="scratch for this many steps per launch of the density wave "
+                         "(1: none)")
     ap.add_argument("--serve-window", type=float, default=10.0)
     ap.add_argument("--serve-limit", type=float, default=120.0)
     ap.add_argument("--bound-steps", type=int, default=1024,
@@ -746,15 +783,7 @@ def main():
         "config": {"workload": "d1q3_L16M_rho50_u0.1", "L": L, "rho": 50.0, "u0": 0.1, "C": 10,
                    "lambda": 1, "n_max": 255, "seed": 2, "launch": "graph" if args.graph else "plain",
                    "schedule": args.schedule or "default", **info},
-        # the dominant kernel's launches: K steps each (12 B per site update
-        # algorithmic, K L site updates per launch); traffic per launch
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS,
-                     "steps_per_launch": info["steps_per_launch"],
-                     "traffic": measured_traffic("plain", info["steps_per_launch"]),
-                     "valu_issue_frac": valu_issue_frac(
-                         "plain", ms_per_step * info["steps_per_launch"] / 1e3,
-                         info["steps_per_launch"])},
+        "roofline": roofline(achieved, ms_per_step, info["steps_per_launch"]),
         "statistics": stats,
     }
     if args.only == "plain":
