@@ -332,7 +332,7 @@ __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles
       N += n[j];
     }
     if (act && N > 65535u) atomicOr(a.err, kErrOverflow);
-    act = act && N >= 2u && N <= 65535u;
+    act = act && N >= 2u && N <= 65535u && a.C > 0;
     if (__ballot(act && N >= 0x80u) != 0u)
       atomicMax(&needs[par], __ballot(act && N >= 0x8000u) != 0u ? 3u : 2u);
     hold_rules(a, rules, &needs[par], held);
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__(kBlockSites9) k_steps9(Step9 a, uint32_t steps
     }
     bool act = threadIdx.x < S;
     if (act && N > 65535u) atomicOr(a.err, kErrOverflow);
-    act = act && N >= 2u && N <= 65535u;
+    act = act && N >= 2u && N <= 65535u && a.C > 0;
     if (__ballot(act && N >= 0x80u) != 0u)
       atomicMax(&needs[k & 1u], __ballot(act && N >= 0x8000u) != 0u ? 3u : 2u);
     hold_rules(a, rules, &needs[k & 1u], held);
@@ -488,7 +488,7 @@ __global__ void __launch_bounds__(256) k_histogram9(const uint16_t *__restrict__
 }  // namespace
 
 hipError_t launch_step9(hipStream_t s, const Step9 &a, uint32_t n_tiles) {
-  if (n_tiles == 0 || a.C <= 0) return hipSuccess;
+  if (n_tiles == 0) return hipSuccess;  // (without sub-collisions a step still flags overflows)
   // Several tiles per block share a table; four times the blocks that fit the
   // chip even out their ends.  4096 x 4096 sites at density 36, us per step:
   // 2048 blocks 383, 8192 345, 32768 349, a block per tile 363.
@@ -498,7 +498,7 @@ hipError_t launch_step9(hipStream_t s, const Step9 &a, uint32_t n_tiles) {
 
 hipError_t launch_steps9(hipStream_t s, const Step9 &a, uint32_t n_reps, uint32_t max_sites,
                          uint32_t steps) {
-  if (n_reps == 0 || steps == 0 || a.C <= 0) return hipSuccess;
+  if (n_reps == 0 || steps == 0) return hipSuccess;
   if (max_sites > kBlockSites9) return hipErrorInvalidValue;
   k_steps9<<<n_reps, (max_sites + 63u) / 64u * 64u, 18u * max_sites, s>>>(a, steps);
   return hipGetLastError();
