@@ -767,6 +767,7 @@ int mclg_moments(mclg_ctx *c, const int32_t *twiddle, uint32_t n_modes, uint32_t
     m.err = c->err();
     m.t_off = c->t_pending;
     hipError_t e = launch_moments3(s, m);
+    if (!e) c->t_pending = 0;  // (the kernels brought the counters up to date)
     if (!e) e = hipStreamSynchronize(s);
     if (e) return c->hip(e);
     std::memcpy(out, c->pin, sizeof(mclg_moments_t) * c->n);

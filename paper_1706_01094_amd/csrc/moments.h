@@ -59,7 +59,7 @@ struct MomArgs {
   const uint16_t *state = nullptr;
   const SlotDev *slots = nullptr;    // D1Q3
   const Rep9 *reps = nullptr;        // D2Q9
-  const uint32_t *tslot = nullptr;   // D1Q3: per-slot step counters
+  uint32_t *tslot = nullptr;         // D1Q3: per-slot step counters
   uint64_t t9 = 0;                   // D2Q9: steps taken
   uint32_t no_stream = 0;
   const MomSeg *segs = nullptr;
@@ -71,7 +71,9 @@ struct MomArgs {
   uint32_t digest = 0;               // D1Q3: also sum the state digest
   unsigned long long *partial = nullptr;  // n_segs records
   long long *out = nullptr;                // run j's result at out[j * kMom*Out]
-  uint32_t t_off = 0;                // D1Q3: steps past tslot
+  // D1Q3: steps past tslot, by which the runs' counters are advanced (as a call
+  // of mclg_moments always left them: a program may record a graph after it)
+  uint32_t t_off = 0;
   const uint32_t *err = nullptr;     // its word goes after the last run's result
 };
 // Results a context reads through pinned memory, which the kernels write

@@ -137,7 +137,7 @@ __device__ __forceinline__ void clear_slow(Eight<NM> &E) {
 template <int NM, bool DIG>
 __global__ void __launch_bounds__(256) k_mom3(const uint16_t *__restrict__ state,
                                               const SlotDev *__restrict__ slots,
-                                              const uint32_t *__restrict__ tslot,
+                                              uint32_t *tslot,
                                               const MomSeg *__restrict__ segs, uint32_t no_stream,
                                               const int32_t *__restrict__ twiddle,
                                               u64 *__restrict__ partial, uint32_t t_off,
@@ -145,7 +145,8 @@ __global__ void __launch_bounds__(256) k_mom3(const uint16_t *__restrict__ state
   const MomSeg sg = segs[blockIdx.x];
   const SlotDev sl = slots[sg.slot];
   const uint32_t L = sl.L;
-  const uint32_t tm = no_stream ? 0u : (tslot[sg.slot] + t_off) % L;
+  const uint32_t t = tslot[sg.slot] + t_off;
+  const uint32_t tm = no_stream ? 0u : t % L;
   const Rsrc rs = make_rsrc(state + sl.off, 6u * sl.stride);
   const uint32_t ab = 2u * sl.stride;
   const int32_t *tw = NM > 0 ? twiddle + 2ull * NM * sl.dense : nullptr;
@@ -224,7 +225,9 @@ __global__ void __launch_bounds__(256) k_mom3(const uint16_t *__restrict__ state
     __syncthreads();
     if (threadIdx.x < kMom3Out)
       direct[(uint64_t)blockIdx.x * kMom3Out + threadIdx.x] =
-          (i64)result_field(threadIdx.x, T, tslot[sg.slot] + t_off, L, NM);
+          (i64)result_field(threadIdx.x, T, t, L, NM);
+    // (every thread has read the counter, which no other block of this launch uses)
+    if (t_off && threadIdx.x == 0) tslot[sg.slot] = t;
     if (err && blockIdx.x == 0 && threadIdx.x == 0) direct[(uint64_t)gridDim.x * kMom3Out] = (i64)*err;
   }
 }
@@ -282,7 +285,7 @@ __global__ void __launch_bounds__(1024) k_mom3_final(const u64 *__restrict__ par
                                                      const uint32_t *__restrict__ run_seg,
                                                      const uint32_t *__restrict__ run_slot,
                                                      const SlotDev *__restrict__ slots,
-                                                     const uint32_t *__restrict__ tslot,
+                                                     uint32_t *tslot,
                                                      uint32_t n_modes, i64 *__restrict__ out,
                                                      uint32_t t_off, const uint32_t *err) {
   __shared__ u64 T[kMom3Rec];
@@ -291,8 +294,9 @@ __global__ void __launch_bounds__(1024) k_mom3_final(const u64 *__restrict__ par
   const uint32_t k = threadIdx.x;
   if (err && j == 0u && k == kMom3Out) out[(uint64_t)gridDim.x * kMom3Out] = (i64)*err;
   if (k >= kMom3Out) return;
-  out[(uint64_t)j * kMom3Out + k] =
-      (i64)result_field(k, T, k == 0u ? tslot[slot] + t_off : 0u, k == 1u ? slots[slot].L : 0u, n_modes);
+  const uint32_t t = k == 0u ? tslot[slot] + t_off : 0u;
+  out[(uint64_t)j * kMom3Out + k] = (i64)result_field(k, T, t, k == 1u ? slots[slot].L : 0u, n_modes);
+  if (t_off && k == 0u) tslot[slot] = t;
 }
 
 // ---- D2Q9 ----------------------------------------------------------------
