@@ -209,6 +209,13 @@ struct mclg_ctx {
   // after steps every, 2 every, ..., into out.
   hipError_t step_way(const RegWay &w, uint64_t total, uint64_t every, RegLog lg, long long *out) {
     const uint64_t room = every ? log_room(w) : 0;
+    // Recorded into a program's graph, the launches advance the device's
+    // counters themselves, so that every replay goes on from the one before.
+    hipStreamCaptureStatus recorded = hipStreamCaptureStatusNone;
+    if (stream) {
+      hipError_t e = hipStreamIsCapturing(stream, &recorded);
+      if (e) return e;
+    }
     for (uint64_t done = 0; done < total;) {
       const uint64_t left = total - done, launches = (left + w.most - 1) / w.most;
       uint64_t k = (left + launches - 1) / launches;
@@ -227,7 +234,12 @@ struct mclg_ctx {
         e = launch_way(stream, launch_args(0, (uint32_t)tiles.size(), 0, n, t_pending), w, units,
                        reg_bufs(), (uint32_t)k, lg);
       if (e) return e;
-      t_pending += (uint32_t)k;
+      if (recorded == hipStreamCaptureStatusActive) {
+        e = launch_add_t(stream, tslot(), 0, n, (uint32_t)k);
+        if (e) return e;
+      } else {
+        t_pending += (uint32_t)k;
+      }
       for (auto &x : t) x += (int64_t)k;
       done += k;
     }

@@ -62,3 +62,45 @@ def test_steps_and_moments(L, kw, warm):
         assert torch.equal(ra, rb), k
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("L", [[300], [60005], L5[:3]], ids=len)
+def test_logs(L):
+    print("[gpu] case", L, flush=True)
+    a, b = two(L)
+    ra, rb = rows(a, 6), rows(b, 6)
+    for l, r in ((a, ra), (b, rb)):
+        l.step_log(2, 6, r, digest=True)
+        l.moments()
+    g = recorded(a, lambda: a.step_log(3, 6, ra, digest=True))
+    for k in range(4):
+        replay(g, a)
+        b.step_log(3, 6, rb, digest=True)
+        assert b.check() == 0
+        assert torch.equal(ra, rb), k
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("pending", [0, 5])
+def test_blocked_replicas(pending):
+    """The steps taken before need not be in the device's counters yet."""
+    a, b = two(L5, blocked=8)
+    ra, rb = rows(a), rows(b)
+    for l, r in ((a, ra), (b, rb)):
+        l.step(16)
+        l.moments_to_device(r, digest=True)
+        if pending:
+            l.step(pending)
+    torch.cuda.synchronize()
+    g = recorded(a, lambda: a.step(16))
+    for k in range(4):
+        replay(g, a)
+        b.step(16)
+    a.moments_to_device(ra, digest=True)
+    b.moments_to_device(rb, digest=True)
+    assert a.check() == 0 and b.check() == 0
+    torch.cuda.synchronize()
+    assert torch.equal(ra, rb)
+    a.close()
+    b.close()
