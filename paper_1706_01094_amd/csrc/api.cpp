@@ -185,7 +185,7 @@ struct mclg_ctx {
   // register kernels run with too, and its image budget serves both alike, so
   // they keep such a context down to kRegImage bytes.
   bool reg_launch() const {
-    return sch.threads == 1024 && sch.lds_budget >= kRegImage &&
+    return sch.threads == 64u * kRegWaves && sch.lds_budget >= kRegImage &&
            (blocked || (drain_policy == MCLG_DRAIN_AUTO && grid_limit == 0));
   }
   RegBufs reg_bufs() const {
@@ -415,9 +415,15 @@ struct mclg_ctx {
                                hipMemcpyHostToDevice, stream);
     if (!e) e = hipStreamSynchronize(stream);
     if (!e) e = step_occupancy(sch, lds_bytes, n_cu, max_blocks);
-    if (!e) e = reg_setup(lds_bytes);
-    ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0,
-                     images_fixed(C), crowd / sites, cost.data());
+    // The register kernels' 16 waves need their queues beside the image: of
+    // the schedules of fewer threads, which never take them, an image may leave
+    // no room for that.
+    ways.clear();
+    if (sch.threads == 64u * kRegWaves) {
+      if (!e) e = reg_setup(lds_bytes);
+      ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0,
+                       images_fixed(C), crowd / sites, cost.data());
+    }
     return e;
   }
   void drop_graphs() {
