@@ -329,9 +329,9 @@ int mclg_set_drain(mclg_ctx *ctx, uint32_t policy);
  * can advance it k steps alone).  mclg_step picks by itself between one step
  * per launch on sites in memory and several on sites held in registers, by
  * the lattices' sizes and the call's steps, unless mclg_set_schedule (other
- * than 1024 threads, or an image of less than 128 KiB), mclg_set_drain or
- * mclg_set_grid_limit made a choice of launches; with blocking on, it picks
- * whatever the drain policy and the grid limit are.
+ * than 1024 threads), mclg_set_drain or mclg_set_grid_limit made a choice of
+ * launches; with blocking on, it picks whatever the drain policy and the grid
+ * limit are.
  * The bits are the same either way.
  *   steps, tile: kept for programs that lay out their scratch by them; the
  *     launches choose their own.  tile is 0 or 1, or for one lattice a
@@ -353,6 +353,17 @@ int mclg_set_blocked(mclg_ctx *ctx, uint32_t steps, uint32_t tile, void *scratch
 /* Expected fraction of site updates whose draw is decided from LDS (from the
  * product-Poisson law the images were built for) and the LDS bytes per block. */
 int mclg_lds_coverage(const mclg_ctx *ctx, double *expected_fraction, uint32_t *lds_bytes);
+
+/* What mclg_step(ctx, n_steps) launches for a D1Q3 context as it is set up now
+ * (host only; nothing is launched).  D2Q9: MCLG_E_UNSUPPORTED. */
+typedef struct {
+  uint64_t launches;         /* of the step kernel */
+  uint32_t steps_per_launch; /* of the longest of them */
+  uint32_t sites_per_lane;   /* sites a lane holds in registers; 0: the state stays in memory */
+  uint32_t extra_sites;      /* on each side of a tile; 0: lattices whole in a block, or in memory */
+  uint32_t pad;
+} mclg_step_plan_t;
+int mclg_step_plan(const mclg_ctx *ctx, uint64_t n_steps, mclg_step_plan_t *out);
 
 int mclg_destroy(mclg_ctx *ctx);
 const char *mclg_strerror(int code);

@@ -27,11 +27,6 @@ constexpr uint32_t kPadElems = 128;     // array stride granularity (256 B)
 constexpr uint32_t kMinTileSites = 512; // chunk of the step kernel
 constexpr uint32_t kPoisCap = 1024;     // thresholds per initial Poisson law
 constexpr uint32_t kMaxImage = 160 * 1024; // largest LDS collision image
-// Smallest image budget of a schedule that still takes the register kernels.
-// Us per step with it, state in memory and in registers: 1024 replicas 471 and
-// 258, 2^24 sites 38.4 and 26.0.  Smaller images, asked for by hand only, were
-// not measured there and stay with the kernels that were tuned over them.
-constexpr uint32_t kRegImage = 128 * 1024;
 
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
@@ -182,10 +177,13 @@ struct mclg_ctx {
   // mclg_set_grid_limit make belong to the kernels that keep the state in
   // memory: with any of them set, those kernels run, unless several steps per
   // launch were asked for as well.  A schedule of 1024 threads is what the
-  // register kernels run with too, and its image budget serves both alike, so
-  // they keep such a context down to kRegImage bytes.
+  // register kernels run with too, and its image budget serves both alike.  Us
+  // per step with the state in memory and in registers, images of 128, 96, 64,
+  // 16 and 0 KiB: 2^24 sites of density 50 38 and 26, 41 and 30, 54 and 35, 104
+  // and 67, 193 and 98; 1024 replicas 466 and 250, 528 and 293, 636 and 384,
+  // 1124 and 756, 1603 and 877.
   bool reg_launch() const {
-    return sch.threads == 64u * kRegWaves && sch.lds_budget >= kRegImage &&
+    return sch.threads == 64u * kRegWaves &&
            (blocked || (drain_policy == MCLG_DRAIN_AUTO && grid_limit == 0));
   }
   RegBufs reg_bufs() const {
@@ -925,6 +923,19 @@ int mclg_lds_coverage(const mclg_ctx *c, double *expected_fraction, uint32_t *ld
   if (!c || !expected_fraction || !lds_bytes) return MCLG_E_INVAL;
   *expected_fraction = c->coverage;
   *lds_bytes = c->lds_bytes;
+  return MCLG_OK;
+}
+
+int mclg_step_plan(const mclg_ctx *c, uint64_t n_steps, mclg_step_plan_t *out) {
+  if (c && c->d2) return MCLG_E_UNSUPPORTED;
+  if (!c || !out) return MCLG_E_INVAL;
+  *out = mclg_step_plan_t{n_steps, n_steps ? 1u : 0u, 0u, 0u, 0u};
+  if (const RegWay *w = c->way(n_steps, false)) {
+    out->launches = (n_steps + w->most - 1) / w->most;
+    out->steps_per_launch = (uint32_t)((n_steps + out->launches - 1) / out->launches);
+    out->sites_per_lane = 4u * w->Q;
+    out->extra_sites = w->kh;
+  }
   return MCLG_OK;
 }
 

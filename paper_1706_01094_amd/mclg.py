@@ -70,6 +70,11 @@ class mclg_moments_t(ct.Structure):
                 "digest": self.digest & 0xFFFFFFFFFFFFFFFF}
 
 
+class mclg_step_plan_t(ct.Structure):
+    _fields_ = [("launches", u64), ("steps_per_launch", u32), ("sites_per_lane", u32),
+                ("extra_sites", u32), ("pad", u32)]
+
+
 class mclg_server_config(ct.Structure):
     _fields_ = [("abi_version", u32), ("max_slots", u32), ("seed", u64), ("C", i32),
                 ("lambda_num", u32), ("lambda_den", u32), ("n_max", u32), ("stream", vp),
@@ -112,6 +117,7 @@ _SIGS = {
     "mclg_blocked_bytes": [vp, u32, u32, P(u64)],
     "mclg_set_blocked": [vp, u32, u32, vp, u64],
     "mclg_lds_coverage": [vp, P(dbl), P(u32)],
+    "mclg_step_plan": [vp, u64, P(mclg_step_plan_t)],
     "mclg_destroy": [vp],
     "mclg_strerror": [ct.c_int],
     "mclg_last_hip_error": [vp],
@@ -368,6 +374,13 @@ class Lattice:
 
     def lds_coverage(self):
         return mclg_lds_coverage(self.ctx)
+
+    def step_plan(self, n: int) -> dict:
+        """mclg_step_plan: what step(n) launches for this lattice."""
+        p = mclg_step_plan_t()
+        _check(lib().mclg_step_plan(self.ctx, n, ct.byref(p)), "mclg_step_plan")
+        return {"launches": p.launches, "steps_per_launch": p.steps_per_launch,
+                "sites_per_lane": p.sites_per_lane, "extra_sites": p.extra_sites}
 
     def check(self) -> int:
         return mclg_check(self.ctx)
