@@ -7,8 +7,8 @@
 namespace mclg {
 
 namespace {
-constexpr uint64_t kMinPart = 256;  // sites of a part, at least (>= kMaxHalo)
-static_assert(kMinPart >= 2 * kMaxHalo, "a part holds the sites of both its strips' halves at any cost");
+constexpr uint64_t kMinPart = 256;  // work of a block, at least, in sites of cost 1
+static_assert(kMaxHalo % 8 == 0, "a part of kMaxHalo sites ends at a multiple of 8");
 }  // namespace
 
 UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks, const float *cost) {
@@ -30,7 +30,9 @@ UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks, const float 
     const uint64_t work = weigh(r, L[r]);
     uint64_t parts = 4 * work <= 5 * target ? 1 : (work + target - 1) / target;
     if (P.strips.size() + parts > kMaxStrips) parts = 1;
-    const uint64_t len = (((L[r] + parts - 1) / parts) + 7) / 8 * 8;
+    // (no part is shorter than the sites on each side of a tile; parts of equal
+    // work would be, where a site costs nearly 2)
+    const uint64_t len = std::max<uint64_t>(kMaxHalo, ((L[r] + parts - 1) / parts + 7) / 8 * 8);
     parts = (L[r] + len - 1) / len;
     if (parts > 1 && L[r] - (parts - 1) * len < kMaxHalo) --parts;  // (the last part takes the rest)
     const uint32_t s0 = (uint32_t)P.strips.size();
