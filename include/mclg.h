@@ -424,7 +424,9 @@ int mclg_server_create(const mclg_server_config *cfg, mclg_server **out);
 int mclg_server_submit(mclg_server *srv, const mclg_job *job);
 /* Admit queued jobs while slots and arena space allow (first-fit, FIFO
  * order), then enqueue k batched steps of every resident job; jobs that
- * reach their step count are retired (moments computed, space freed). */
+ * reach their step count are retired (moments computed, space freed).  After
+ * an error the tick's jobs are queued again, ahead of the others, and start
+ * over: none is lost, and none has a result of that tick. */
 int mclg_server_tick(mclg_server *srv, uint32_t k);
 /* Copy up to cap finished results to out; *n_out = number copied. */
 int mclg_server_poll(mclg_server *srv, mclg_job_result *out, uint32_t cap, uint32_t *n_out);

@@ -90,6 +90,7 @@ SrvLayout srv_layout(const mclg_server_config *cfg, const CollisionTables *tab,
 
 struct Resident {
   mclg_job job;
+  uint64_t nth = 0;     // in the order of admission
   uint64_t arena_off;   // bytes
   uint64_t bytes;
   uint64_t t = 0;
@@ -99,8 +100,8 @@ struct Resident {
 // What a wave does with one job.
 struct Run {
   uint32_t slot = 0;
-  uint64_t job_id = 0, L = 0, off = 0;
-  double rho = 0, u0 = 0;
+  mclg_job job{};
+  uint64_t nth = 0, off = 0;
   uint64_t steps = 0, t = 0;  // of the tick; the job's, when it finishes
   size_t place = 0;           // in the order of finishing
   bool fresh = false, finish = false;
@@ -124,6 +125,7 @@ struct mclg_server {
   std::vector<mclg_job_result> done;
   std::vector<std::vector<Run>> waves;  // of the running tick
   uint32_t next_wave = 0;               // of a job admitted now
+  uint64_t n_admitted = 0;
   // Pinned memory: pieces of it are handed out until it is used up, and again
   // from its start after a synchronisation.
   uint8_t *pin = nullptr;
@@ -307,11 +309,9 @@ struct mclg_server {
     r.run = (uint32_t)waves[wave].size();
     Run x;
     x.slot = i;
-    x.job_id = r.job.job_id;
-    x.L = r.job.L;
+    x.job = r.job;
+    x.nth = r.nth;
     x.off = r.arena_off;
-    x.rho = r.job.rho;
-    x.u0 = r.job.u0;
     x.fresh = fresh;
     waves[wave].push_back(x);
   }
@@ -327,6 +327,7 @@ struct mclg_server {
       if (!alloc(bytes, off)) break;
       Resident &r = slot[free_slot];
       r.job = j;
+      r.nth = n_admitted++;
       r.arena_off = off;
       r.bytes = bytes;
       r.t = 0;
@@ -370,12 +371,12 @@ struct mclg_server {
       SlotDev sd{};
       sd.off = r.off / sizeof(uint16_t);
       sd.dense = 0;
-      sd.L = (uint32_t)r.L;
-      sd.stride = (uint32_t)align_up(r.L, kPad);
-      sd.rid = (uint32_t)r.job_id;
+      sd.L = (uint32_t)r.job.L;
+      sd.stride = (uint32_t)align_up(r.job.L, kPad);
+      sd.rid = (uint32_t)r.job.job_id;
       sd.pad = 0;
       double mu[3];
-      feq(r.rho, r.u0, mu);
+      feq(r.job.rho, r.job.u0, mu);
       PoisDesc pd[3];
       for (int i = 0; i < 3; ++i) {
         uint32_t k_lo = 0;
@@ -388,11 +389,11 @@ struct mclg_server {
         pool.insert(pool.end(), cl.thr.begin(), cl.thr.end());
       }
       // collision image for this job's density and speed (cached on the host)
-      const auto key = std::make_pair(r.rho, std::fabs(r.u0));
+      const auto key = std::make_pair(r.job.rho, std::fabs(r.job.u0));
       auto ci = image_cache.find(key);
       if (ci == image_cache.end()) {
         if (image_cache.size() >= kImageCacheMax) image_cache.clear();
-        LdsImage im = build_image(*tab, r.rho, std::fabs(r.u0), image_budget);
+        LdsImage im = build_image(*tab, r.job.rho, std::fabs(r.job.u0), image_budget);
         CachedImage c;
         c.blob = im.blob();
         c.dir_bytes = im.dir_bytes();
@@ -421,7 +422,7 @@ struct mclg_server {
       if (!e) e = put(d_idesc() + r.slot, &idd, sizeof(idd));
       if (!e) e = put(ws + lay.o_pdesc + sizeof(PoisDesc) * 3 * r.slot, pd, sizeof(pd));
       fresh.push_back(r.slot);
-      for (uint64_t x0 = 0; x0 < r.L; x0 += ts) tiles.push_back(TileDev{r.slot, (uint32_t)x0, 0, 0});
+      for (uint64_t x0 = 0; x0 < r.job.L; x0 += ts) tiles.push_back(TileDev{r.slot, (uint32_t)x0, 0, 0});
     }
     if (fresh.empty() || e) return e;
     if (tiles.size() > lay.max_tiles) return hipErrorInvalidValue;
@@ -440,7 +441,7 @@ struct mclg_server {
   // The steps of a wave's jobs: launches that each job takes part in for as
   // many steps as it has left.
   hipError_t step_jobs(std::vector<Run> &wave) {
-    std::stable_sort(wave.begin(), wave.end(), [](const Run &x, const Run &y) { return x.L > y.L; });
+    std::stable_sort(wave.begin(), wave.end(), [](const Run &x, const Run &y) { return x.job.L > y.job.L; });
     std::vector<uint64_t> left(wave.size());
     for (size_t i = 0; i < wave.size(); ++i) left[i] = wave[i].steps;
     RegBufs b;
@@ -476,11 +477,11 @@ struct mclg_server {
         for (size_t i = 0; i < wave.size(); ++i)
           if (left[i]) {
             const double cov = slot_coverage[wave[i].slot];
-            crowd += crowded_image(cov) ? wave[i].L : 0u;
+            crowd += crowded_image(cov) ? wave[i].job.L : 0u;
             cost.push_back(cfg.C ? site_cost(cov) : 1.0f);
             list.push_back(wave[i].slot);
-            sites.push_back(wave[i].L);
-            total += wave[i].L;
+            sites.push_back(wave[i].job.L);
+            total += wave[i].job.L;
           }
         units = plan_units(sites.data(), (uint32_t)n, n_cu, cost.data());
         if (units.units.size() > max_units((uint32_t)slot.size())) return hipErrorInvalidValue;
@@ -540,8 +541,8 @@ struct mclg_server {
     for (const Run &r : wave)
       if (r.finish) {
         fin.push_back(r.slot);
-        sites.push_back(r.L);
-        f.jobs.emplace_back(r.job_id, r.t);
+        sites.push_back(r.job.L);
+        f.jobs.emplace_back(r.job.job_id, r.t);
         f.place.push_back(r.place);
       }
     // (a slot is in a wave once, and its results fit the pinned memory)
@@ -579,6 +580,24 @@ struct mclg_server {
     return hipSuccess;
   }
 
+  // After an error the host's account of the tick is not the device's state:
+  // its jobs, finished ones too, go back to the head of the queue in the order
+  // of their admission, and run anew when they are admitted again.
+  void start_over() {
+    std::vector<const Run *> runs;
+    for (const auto &wave : waves)
+      for (const Run &r : wave) runs.push_back(&r);
+    std::sort(runs.begin(), runs.end(), [](const Run *x, const Run *y) { return x->nth > y->nth; });
+    for (const Run *r : runs) queue.push_front(r->job);
+    for (Resident &r : slot) r.active = false;
+    n_active = 0;
+    free_spans.clear();
+    if (const uint64_t usable = cfg.arena_bytes / 256 * 256) free_spans[0] = usable;
+    arena_used = 0;
+    pending.n = 0;
+    if (!hipStreamSynchronize(s)) pin_used = 0;
+  }
+
   // What the tick did on the host, on the device.
   hipError_t run_waves() {
     const size_t before = done.size();
@@ -594,6 +613,7 @@ struct mclg_server {
     if (e) {  // no results of this tick
       finished.clear();
       done.resize(before);
+      start_over();
     }
     return e;
   }
