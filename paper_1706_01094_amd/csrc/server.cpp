@@ -740,7 +740,9 @@ int mclg_server_stats(const mclg_server *sv, uint64_t *queued, uint64_t *residen
 
 int mclg_server_destroy(mclg_server *sv) {
   if (!sv) return MCLG_E_INVAL;
-  if (sv->s) (void)hipStreamSynchronize(sv->s);
+  // (on the null stream too: a tick may have left launches that read the pinned
+  // memory)
+  (void)hipStreamSynchronize(sv->s);
   delete sv;
   return MCLG_OK;
 }

@@ -1,8 +1,11 @@
 """The server's host side over a device that fails (host side, compiled here;
 the HIP calls and the kernels are stand-ins that work on host memory, one of
-which returns an error): a failed tick loses no job."""
+which returns an error): a failed tick loses no job, and the pinned memory that
+the device reads is never freed before the device is done with it."""
 import os
 import subprocess
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(__file__))
 CSRC = os.path.join(ROOT, "paper_1706_01094_amd", "csrc")
@@ -17,6 +20,7 @@ MAIN = r"""
 #include "regplan.h"
 #include "../../include/mclg.h"
 using namespace mclg;
+static bool busy = false, freed_busy = false;
 static long calls = 0, fail_at = 0;  // the fail_at-th call from now on fails
 static hipError_t call() { return fail_at && ++calls == fail_at ? hipErrorOutOfMemory : hipSuccess; }
 extern "C" {
@@ -26,16 +30,16 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
   return e;
 }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return call(); }
+hipError_t hipStreamSynchronize(hipStream_t) { busy = false; return call(); }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::malloc(n); return hipSuccess; }
-hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipHostFree(void *p) { freed_busy |= busy; std::free(p); return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int) {
   *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 160 * 1024;
   return hipSuccess;
 }
 }
-static hipError_t launch() { return call(); }
+static hipError_t launch() { hipError_t e = call(); busy |= !e; return e; }
 static std::map<const void *, uint64_t> start;  // of a job's state: its id
 namespace mclg {
 bool reg_has(uint32_t Q, bool g, bool f, bool l) { return l ? !g && f && Q <= 4 : f ? !g || Q <= 2 : Q == 2; }
@@ -151,6 +155,7 @@ static int ticks() {
         REQUIRE(got.count(i) && got[i].t == (int64_t)j.steps && got[i].sites == (int64_t)j.L && got[i].sum_n[0] == i);
       }
       mclg_server_destroy(sv);
+      REQUIRE(!freed_busy);
       std::free(c.arena);
       std::free(c.workspace);
     }
@@ -158,20 +163,52 @@ static int ticks() {
   }
   return 0;
 }
-int main() {
-  if (ticks()) return 1;
+// Left with work in flight on the null stream.
+static int end() {
+  mclg_server_config c{};
+  c.abi_version = MCLG_ABI_VERSION;
+  c.max_slots = 1;
+  c.C = 2;
+  c.lambda_num = c.lambda_den = 1;
+  c.n_max = 40;
+  c.arena_bytes = 60000;
+  uint64_t need = 0;
+  fail_at = 0;
+  busy = freed_busy = false;
+  uint32_t tick = 0;
+  long at = 0;
+  REQUIRE(mclg_server_sizes(&c, &need) == MCLG_OK);
+  c.arena = std::malloc(c.arena_bytes);
+  c.workspace = std::malloc(need);
+  c.workspace_bytes = need;
+  mclg_server *sv = nullptr;
+  const mclg_job j{0, 1000, 50, 5.0, 0.0};
+  REQUIRE(mclg_server_create(&c, &sv) == MCLG_OK && mclg_server_submit(sv, &j) == MCLG_OK && mclg_server_tick(sv, 3) == MCLG_OK);
+  REQUIRE(busy);
+  mclg_server_destroy(sv);
+  REQUIRE(!freed_busy);
+  return 0;
+}
+int main(int argc, char **argv) {
+  if (argc > 1 ? end() : ticks()) return 1;
   std::puts("ok");
 }
 """
 MAIN = MAIN.replace("    REQUIRE_LAST\n", "")
 
 
-def test_no_job_is_lost(tmp_path):
-    src = tmp_path / "main.cpp"
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("server")
+    src, exe = tmp / "main.cpp", tmp / "main"
     src.write_text(MAIN)
-    exe = tmp_path / "main"
     subprocess.run(["g++", "-O1", "-std=c++17", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC,
                     "-o", str(exe), str(src)] + [os.path.join(CSRC, f) for f in ("server.cpp", "regplan.cpp", "tables.cpp")],
                    check=True)
-    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    return str(exe)
+
+
+@pytest.mark.parametrize("args", [[], ["end"]], ids=["ticks", "end"])
+def test_server_over_a_failing_device(program, args):
+    out = subprocess.run([program] + args, capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
