@@ -5,7 +5,8 @@ bytes).  Every schedule gives identical bits (the image only caches table
 rows; misses read the exact rows), so the tuner is free to pick the fastest.
 It times candidates on a scratch lattice with the same replica sizes and
 densities as the target -- the target's own state is never stepped -- and
-caches the winner in a JSON file keyed by a signature of the workload shape.
+caches the winner in a JSON file keyed by a signature of the workload shape
+and of the library's build: what a schedule launches is the build's choice.
 """
 from __future__ import annotations
 
@@ -30,8 +31,15 @@ CACHE_PATH = os.environ.get(
     "MCLG_AUTOTUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "mclg_autotune.json"))
 
 
+def _build_id() -> str:
+    """Hash of the library that is loaded (or would be)."""
+    with open(M.LIB_PATH, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
 def signature(L, rho, u0, C: int, lam, n_max: int, device_name: str) -> str:
-    """Workload shape: sizes bucketed to powers of two, densities to integers."""
+    """Workload shape (sizes bucketed to powers of two, densities to integers)
+    and build."""
     Ls = np.atleast_1d(np.asarray(L, dtype=np.float64))
     r = np.broadcast_to(np.asarray(rho, dtype=np.float64), Ls.shape)
     u = np.broadcast_to(np.asarray(0.0 if u0 is None else u0, dtype=np.float64), Ls.shape)
@@ -39,7 +47,7 @@ def signature(L, rho, u0, C: int, lam, n_max: int, device_name: str) -> str:
         "n": int(len(Ls)), "sites_log2": int(np.round(np.log2(Ls.sum()))),
         "L_hist": np.bincount(np.round(np.log2(Ls)).astype(int), minlength=32).tolist(),
         "rho": int(np.round(np.average(r, weights=Ls))), "u": round(float(np.average(np.abs(u), weights=Ls)), 2),
-        "C": C, "lam": list(lam), "n_max": n_max, "device": device_name,
+        "C": C, "lam": list(lam), "n_max": n_max, "device": device_name, "build": _build_id(),
     }
     return hashlib.sha256(json.dumps(key, sort_keys=True).encode()).hexdigest()[:24]
 
