@@ -101,8 +101,8 @@ std::vector<uint32_t> device_rules9(const std::vector<uint32_t> &rules, uint32_t
     for (int j = 0; j < 9; ++j) {
       const uint32_t *e = &rules[(i * 9 + j) * kRule9Words];
       uint32_t *wide = &dev[kRule9WideAt + (9 * i + j) * kRule9Wide];
-      uint32_t *half = &dev[kRule9HalfAt + (16 * i + j) * kRule9Half];
-      uint32_t *byte = &dev[kRule9ByteAt + (16 * i + j) * kRule9Byte];
+      uint32_t *half = &dev[kRule9HalfAt + (9 * i + j) * kRule9Half];
+      uint32_t *byte = &dev[kRule9ByteAt + (9 * i + j) * kRule9Byte];
       for (int q = 0; q < 4; ++q) {
         wide[q] = e[q];
         // (used where Dq, and so every c_q / g, is at most 2^15)
@@ -267,9 +267,29 @@ int d2q9_init(D2Ctx &d, const mclg_config *cfg, const mclg_init_spec *init) {
                              reinterpret_cast<uint32_t *>(d.ws + d.o_err));
   if (!e && init->kind == MCLG_INIT_COUNTS)
     e = launch_init9_counts(d.stream, d.state, reps, tiles, (uint32_t)d.tiles.size(),
-                            reinterpret_cast<const uint64_t *>(d.ws + d.o_dense), init->counts);
+                            reinterpret_cast<const uint64_t *>(d.ws + d.o_dense), init->counts,
+                            reinterpret_cast<uint32_t *>(d.ws + d.o_err) + 1);
+  uint32_t full = 0;  // tiles with a site for the half table
+  if (!e && init->kind == MCLG_INIT_COUNTS && d.Dq <= kRule9MaxPacked)
+    e = hipMemcpyAsync(&full, d.ws + d.o_err + 4, sizeof(full), hipMemcpyDeviceToHost, d.stream);
   // the host vectors above must outlive the copies
   if (!e) e = hipStreamSynchronize(d.stream);
+  // The table that at least half of the tiles need.  A narrower one before it
+  // costs the steps of lattices with a tile or two per block, and it costs the
+  // tiles that could do with less.  434 x 1813 sites, us per step beginning with
+  // bytes and with halves: density 36 25.4 and 28.4, 90 25.6 and 28.4, 100 28.4
+  // and 28.6, 110 29.1 and 28.5, 360 29.1 and 28.5; 177 x 15 sites of density
+  // 360 6.8 and 6.5.  (At densities of 100 and more a Poisson law gives half of
+  // the tiles of 256 sites one of 128 particles.)
+  if (init->kind == MCLG_INIT_POISSON) {
+    uint64_t dense = 0, all = 0;
+    for (uint32_t r = 0; r < d.n; ++r) {
+      all += d.reps[r].S;
+      dense += init->rho[r] >= 100.0 ? d.reps[r].S : 0u;
+    }
+    full = 2 * dense >= all ? (uint32_t)d.tiles.size() : 0u;
+  }
+  d.first_table = d.Dq > kRule9MaxPacked ? 3u : 2ull * full >= d.tiles.size() ? 2u : 1u;
   d.t = 0;
   return hip_rc(d, e);
 }
@@ -284,6 +304,7 @@ int d2q9_step(D2Ctx &d, uint64_t n_steps) {
   a.seed = d.seed;
   a.D = d.D;
   a.Dq = d.Dq;
+  a.first_table = d.first_table;
   a.no_stream = (d.flags & MCLG_FLAG_NO_STREAM) ? 1u : 0u;
   a.C = d.C;
   uint32_t sites = 0;

@@ -14,6 +14,7 @@ namespace mclg {
 
 struct D2Ctx {
   uint32_t n = 0, flags = 0, D = 0, Dq = 0;
+  uint32_t first_table = 1;  // that the step kernels read to begin with (see Step9)
   int32_t C = 0;
   uint64_t seed = 0;
   int64_t t = 0;
@@ -49,16 +50,18 @@ bool build_rules9(const uint32_t *lambda9, std::vector<uint32_t> &rules, uint32_
 //   change of the K_j as 16-bit two's-complement pairs, K_2m in the low and
 //   K_2m+1 in the high half;
 // - half (N < 2^15, Dq <= 2^15, Dq = D / g with g the greatest common divisor
-//   of D and all weights: a target draw u is used as floor(u / g)), per pair p = 16 i + j, 22 words: words 0-1 the
+//   of D and all weights: a target draw u is used as floor(u / g)), per pair p, 22 words: words 0-1 the
 //   halves 2^15 - c_q / g; then, for q = 0..4, four words, the 32-bit sum of the
 //   changes of the halves 2^15 - K_j, times 2^16 in the high half;
-// - byte (N < 2^7, Dq <= 2^15), per pair p = 16 i + j, 14 words: words 0-1 as
+// - byte (N < 2^7, Dq <= 2^15), per pair p, 14 words: words 0-1 as
 //   above; then, for q = 0..4, two words of the changes of the bytes
 //   2^7 - K_j alike.
 constexpr uint32_t kRule9Wide = 24, kRule9Half = 22, kRule9Byte = 14;
-constexpr uint32_t kRule9WideAt = 0, kRule9HalfAt = 81 * kRule9Wide,
-                   kRule9ByteAt = kRule9HalfAt + 144 * kRule9Half,
-                   kRule9DevWords = kRule9ByteAt + 144 * kRule9Byte;
+// (each table starts at, and is read in, 16-byte pieces)
+constexpr uint32_t rule9_words(uint32_t per_pair) { return (81u * per_pair + 3u) / 4u * 4u; }
+constexpr uint32_t kRule9WideAt = 0, kRule9HalfAt = kRule9WideAt + rule9_words(kRule9Wide),
+                   kRule9ByteAt = kRule9HalfAt + rule9_words(kRule9Half),
+                   kRule9DevWords = kRule9ByteAt + rule9_words(kRule9Byte);
 constexpr uint32_t kRule9MaxPacked = 1u << 15;  // Dq of the packed tables, at most
 std::vector<uint32_t> device_rules9(const std::vector<uint32_t> &rules, uint32_t D, uint32_t &Dq);
 

@@ -290,6 +290,8 @@ struct Step9 {
   uint32_t D, no_stream;
   uint32_t Dq;         // D divided by the greatest common divisor of it and all weights
   int32_t C;
+  uint32_t first_table;  // of the rules that a block begins with: 1 bytes, 2 halves (both for
+                         // Dq <= kRule9MaxPacked only), 3 any
 };
 hipError_t launch_step9(hipStream_t s, const Step9 &a, uint32_t n_tiles);
 // `steps` steps of lattices of up to kBlockSites9 sites in one launch.
@@ -301,7 +303,7 @@ hipError_t launch_init9_poisson(hipStream_t s, uint16_t *state, const Rep9 *reps
                                 const uint32_t *pool, uint64_t seed, uint32_t *err);
 hipError_t launch_init9_counts(hipStream_t s, uint16_t *state, const Rep9 *reps,
                                const Tile9 *tiles, uint32_t n_tiles, const uint64_t *dense,
-                               const uint16_t *counts);
+                               const uint16_t *counts, uint32_t *full);  // += tiles with N >= 128
 hipError_t launch_histogram9(hipStream_t s, const uint16_t *state, const Rep9 *reps,
                              const Tile9 *tiles, uint32_t n_tiles, uint32_t n_bins,
                              unsigned long long *hist);

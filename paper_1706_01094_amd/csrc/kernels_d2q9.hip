@@ -174,7 +174,7 @@ __device__ __forceinline__ void collide_packed(uint32_t (&K)[W], const uint32_t 
     uint32_t v = 0;
 #pragma unroll
     for (int i = 0; i < W; ++i) v += __builtin_popcount((R1 + K[i]) & kTop);
-    v <<= 4;
+    v += v << 3;
 #pragma unroll
     for (int i = 0; i < W; ++i) v += __builtin_popcount((R2 + K[i]) & kTop);
     const uint32_t *const rec = rules + v * kStride;
@@ -228,15 +228,15 @@ __device__ __forceinline__ void collide_wide(u16x2 (&K)[4], const uint4 *rules, 
 // The table a block holds: 1 byte, 2 half, 3 wide; it only grows.  A wave's
 // need goes to the place of its tile's parity, which nothing else reads or
 // writes between two barriers; all waves of the block call this per tile.
-constexpr uint32_t kRulesLds = 144 * kRule9Half;
-static_assert(kRulesLds >= 81 * kRule9Wide && kRulesLds >= 144 * kRule9Byte, "room for each table");
+constexpr uint32_t kRulesLds = rule9_words(kRule9Wide);
+static_assert(kRulesLds >= rule9_words(kRule9Half) && kRulesLds >= rule9_words(kRule9Byte), "room for each table");
 struct Table9 {
   const uint4 *src;
   uint32_t n;  // 16-byte pieces
 };
 __device__ __forceinline__ Table9 table9(const Step9 &a, uint32_t which) {
   const uint32_t at = which == 1u ? kRule9ByteAt : which == 2u ? kRule9HalfAt : kRule9WideAt;
-  const uint32_t words = which == 1u ? 144 * kRule9Byte : which == 2u ? 144 * kRule9Half : 81 * kRule9Wide;
+  const uint32_t words = rule9_words(which == 1u ? kRule9Byte : which == 2u ? kRule9Half : kRule9Wide);
   return Table9{reinterpret_cast<const uint4 *>(a.rules + at), words / 4u};
 }
 __device__ __forceinline__ void hold_rules(const Step9 &a, uint32_t *rules, uint32_t *needs,
@@ -291,16 +291,16 @@ __device__ __forceinline__ void collide_site(uint32_t (&n)[9], uint32_t N, const
 // One step of every site: the literal loop of C sub-collisions (Eq. (select),
 // Eq. (omega) with the D2Q9 rules), in place in the shifted layout.  Sites
 // with N < 2 (or C = 0) are left untouched.  A block takes tiles of 256 sites
-// in turn; per tile it holds the narrowest of the three rule tables that its
-// fullest site so far allows.  Sub-collision k reads Philox block (s, t,
+// in turn; it holds the rule table it began with until one of its sites needs a
+// wider one.  Sub-collision k reads Philox block (s, t,
 // replica, 2 | k << 2): words 0, 1, 2 draw the first particle, the second and
 // the target.
 __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles) {
   __shared__ __align__(16) uint32_t rules[kRulesLds];
   __shared__ uint32_t needs[2];
-  // (the narrowest table that Dq allows comes in beside the rest, not after the
+  // (the table that most tiles need comes in beside the rest, not after the
   // first tile's counts: the steps of small lattices are a chain of latencies)
-  const uint32_t first = a.Dq > kRule9MaxPacked ? 3u : 1u;
+  const uint32_t first = a.first_table;
   uint32_t held = first, par = 0;
   const Table9 tb = table9(a, first);
   for (uint32_t i = threadIdx.x; i < tb.n; i += blockDim.x) reinterpret_cast<uint4 *>(rules)[i] = tb.src[i];
@@ -358,7 +358,7 @@ __global__ void __launch_bounds__(kBlockSites9) k_steps9(Step9 a, uint32_t steps
   const uint32_t S = rp.S, s = min(threadIdx.x, S - 1u), x = s % rp.Lx;
   for (uint32_t i = 0; i < 9u; ++i)
     for (uint32_t e = threadIdx.x; e < S; e += blockDim.x) counts[i * S + e] = *at9(a.state, rp, (int)i, e);
-  uint32_t held = a.Dq > kRule9MaxPacked ? 3u : 1u;  // (see k_step9)
+  uint32_t held = a.first_table;  // (see k_step9)
   const Table9 tb = table9(a, held);
   for (uint32_t i = threadIdx.x; i < tb.n; i += blockDim.x) reinterpret_cast<uint4 *>(rules)[i] = tb.src[i];
   if (threadIdx.x < 2u) needs[threadIdx.x] = held;
@@ -422,20 +422,28 @@ __global__ void __launch_bounds__(256) k_init9_poisson(
 }
 
 // Counts given in logical order ([9][Ly][Lx] per replica, replicas packed
-// from dense[rep]); at t = 0 the layout is unshifted.
+// from dense[rep]); at t = 0 the layout is unshifted.  Counts the tiles that
+// hold a site of 128 or more particles.
 __global__ void __launch_bounds__(256) k_init9_counts(uint16_t *__restrict__ state,
                                                       const Rep9 *__restrict__ reps,
                                                       const Tile9 *__restrict__ tiles,
                                                       const uint64_t *__restrict__ dense,
-                                                      const uint16_t *__restrict__ counts) {
+                                                      const uint16_t *__restrict__ counts,
+                                                      uint32_t *full) {
   const Tile9 tile = tiles[blockIdx.x];
   const Rep9 rp = reps[tile.rep];
   const uint32_t s = tile.s0 + threadIdx.x;
-  if (s >= rp.S) return;
-  const uint16_t *src = counts + dense[tile.rep];
+  uint32_t N = 0;
+  if (s < rp.S) {
+    const uint16_t *src = counts + dense[tile.rep];
 #pragma unroll
-  for (uint32_t i = 0; i < 9; ++i)
-    state[rp.off + (uint64_t)i * rp.stride + s] = src[(uint64_t)i * rp.S + s];
+    for (uint32_t i = 0; i < 9; ++i) {
+      const uint16_t n = src[(uint64_t)i * rp.S + s];
+      state[rp.off + (uint64_t)i * rp.stride + s] = n;
+      N += n;
+    }
+  }
+  if (__syncthreads_or(N >= 0x80u) && threadIdx.x == 0) atomicAdd(full, 1u);
 }
 
 // Occupation-number histograms of D2Q9 replicas, as k_histogram: each block
@@ -514,9 +522,9 @@ hipError_t launch_init9_poisson(hipStream_t s, uint16_t *state, const Rep9 *reps
 
 hipError_t launch_init9_counts(hipStream_t s, uint16_t *state, const Rep9 *reps,
                                const Tile9 *tiles, uint32_t n_tiles, const uint64_t *dense,
-                               const uint16_t *counts) {
+                               const uint16_t *counts, uint32_t *full) {
   if (n_tiles == 0) return hipSuccess;
-  k_init9_counts<<<n_tiles, 256, 0, s>>>(state, reps, tiles, dense, counts);
+  k_init9_counts<<<n_tiles, 256, 0, s>>>(state, reps, tiles, dense, counts, full);
   return hipGetLastError();
 }
 
