@@ -162,6 +162,7 @@ struct mclg_ctx {
   // steps on sites in registers (kernels_reg.hip)
   UnitPlan units;
   std::vector<RegWay> ways;
+  SingleStep single;
 
   uint32_t *err() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl); }
   uint32_t *ticket() { return reinterpret_cast<uint32_t *>(ws + lay.o_ctrl) + 1; }
@@ -245,7 +246,7 @@ struct mclg_ctx {
   }
   // The way for `steps` steps, or nullptr for one step per launch.
   const RegWay *way(uint64_t steps, bool logs) const {
-    return reg_launch() ? pick_way(ways, steps, logs, single_step_us(lay.total_sites)) : nullptr;
+    return reg_launch() ? pick_way(ways, steps, logs, single) : nullptr;
   }
   TileDev *tiles_dev() { return reinterpret_cast<TileDev *>(ws + lay.o_tiles); }
   // The moment kernels' arguments; partial records and results go to
@@ -421,6 +422,7 @@ struct mclg_ctx {
       if (!e) e = reg_setup(lds_bytes);
       ways = plan_ways(units, L.data(), n, n_cu, one_image, (flags & MCLG_FLAG_GALILEAN) != 0,
                        images_fixed(C), crowd / sites, cost.data());
+      single = single_step(lay.total_sites, n, one_image, C ? 1.0 - coverage : 0.0, images_fixed(C));
     }
     return e;
   }

@@ -78,6 +78,8 @@ UnitPlan plan_units(const uint64_t *L, uint32_t n, uint32_t blocks, const float 
 }
 
 namespace {
+constexpr uint64_t kCachedSites = 44ull << 20;  // whose counts the Infinity Cache holds
+
 // Times on MI355X (us), fitted to measured steps of lattices of 256 to 2^27
 // sites at rho = 50.  A wave that is alone on its SIMD takes 0.72 + 0.58 Q for
 // a step of its 256 Q sites (latency); a SIMD with one or more for each of its
@@ -107,6 +109,25 @@ constexpr double kTileLaunch = 12.0;
 double state_us(uint32_t Q, uint64_t sites) {
   const double s = (double)sites, most = (double)(1u << 24);
   return 1.6e-6 * std::min(s, most) + 0.9e-6 * std::max(0.0, s - most) + (Q < 6 ? 0.0 : 6.0 + 0.45e-6 * s);
+}
+// A launch of few steps: the state's way in and out is not covered by work,
+// and the estimates' common factors (a site's cost where its image leaves more
+// undecided than at density 50, and that of the kernels with other rules)
+// count against a launch per step, which they are not in.  Us per launch
+// measured (and a launch per step): 2^26 sites, density 50, 1, 2, 3 and 4 steps
+// 280 (176), 326 (352), 396 (528), 461 (704); density 100 347 (200), 439 (400),
+// 557 (601); density 15 268 (174), 291 (349).  2^25 sites, 2 steps, density 50
+// 151 (138), 15 124 (134), 100 201 (260).  Galilean, 2^24 sites, 3, 4 and 6 steps
+// 137 (119), 164 (159), 223 (238); 2^26 sites, 2, 3 and 4 445 (361), 554 (540), 650
+// (713).  C = 30, 2^24 sites, 3, 6 and 8 steps 190 (157), 327 (314), 420 (419).
+void few_steps(RegWay &y, uint64_t sites, double weight, bool galilean, bool fixed) {
+  constexpr double kWeight50 = 1.22;  // site_cost at density 50
+  const double s = (double)sites;
+  const bool cached = sites <= kCachedSites, plain = fixed && !galilean;
+  y.least = 2;
+  y.few_step_us = y.step_us * weight / kWeight50 * (!fixed ? 1.25 : galilean ? 1.18 : 1.0);
+  y.few_launch_us = y.launch_us + (plain ? 0.0 : (cached ? 0.5e-6 : 2.0e-6) * s);
+  y.few_in_us = plain && !cached ? 2.0e-6 * s : 0.0;
 }
 constexpr double kTileLogs = 25.0;    // the logs' records and their sum
 constexpr double kStripsLaunch = 2.5;
@@ -152,6 +173,9 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
       const double rounds = std::max(1.0, (double)n / blocks);
       y.launch_us = kRingLaunch * rounds;
       y.step_us = std::max(most, n > blocks ? sum / blocks + 0.5 * most : 0.0);
+      // (a second round of long lattices: 300 of 20000 sites, one launch of 1,
+      // 2 and 3 steps 44, 64 and 84 us, and a launch per step 30, 60 and 89)
+      y.least = Q == 6 && n > blocks ? 3u : 1u;
       ways.push_back(y);
       if (one_image && n > blocks && longest <= hold) {
         y.team = std::min<uint32_t>(16u, (n + blocks - 1) / blocks);
@@ -187,6 +211,7 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
                     std::max(0.0, images - 1.0) * kUnit +
                     state_us(Q, total);
       y.step_us = worst;
+      few_steps(y, total, weight, galilean, fixed);
       if (plan.n_long < n) {  // and a ring launch for the others
         y.launch_us += kRingLaunch;
         y.step_us += ring_step_us(2, 1, false) * std::max(1.0, (double)(n - plan.n_long) / blocks);
@@ -198,24 +223,46 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
 }
 
 const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, bool logs,
-                       double single_us) {
+                       const SingleStep &single) {
   const RegWay *best = nullptr;
-  double least = (double)steps * single_us;
+  uint64_t launches = 1;
+  double least = (double)steps * single.us;
   for (const RegWay &w : ways) {
     if (logs && !w.logs) continue;
-    const double launches = w.kind == RegWay::kTile ? (double)((steps + w.most - 1) / w.most) : 1.0;
-    const double us = launches * (w.launch_us + (logs && w.kind == RegWay::kTile ? kTileLogs : 0.0)) +
+    const uint64_t n = w.kind == RegWay::kTile ? (steps + w.most - 1) / w.most : 1u;
+    const double us = (double)n * (w.launch_us + (logs && w.kind == RegWay::kTile ? kTileLogs : 0.0)) +
                       (double)steps * w.step_us;
     if (us < least) {
       least = us;
       best = &w;
+      launches = n;
     }
   }
+  if (!best || logs) return best;
+  const uint64_t k = (steps + launches - 1) / launches;  // of a launch
+  if (k < best->least) return nullptr;
+  if (best->kind == RegWay::kTile &&
+      (double)launches * (best->few_launch_us + best->few_in_us / (double)k) + (double)steps * best->few_step_us >=
+          (double)steps * single.few_us)
+    return nullptr;
   return best;
 }
 
-double single_step_us(uint64_t sites) {
-  return sites > (44ull << 20) ? 2.6e-6 * (double)sites : 8.0 + 2.0e-6 * (double)sites;
+// Measured (us per step, without and with undecided sites): 2^24 sites 37.5,
+// 38.4 with 0.3 %, 69 with 10 %; 2^26 174, 176 and 200; of C = 30 (3 %) 52 and
+// 252; 1000 lattices of 1000 sites 27, with an image each 42; 2000 of 30000 167
+// and 234.
+SingleStep single_step(uint64_t sites, uint32_t n, bool one_image, double missed, bool fixed) {
+  const double s = (double)sites;
+  SingleStep y;
+  if (sites > kCachedSites) {
+    y.us = 2.6e-6 * s;
+    y.few_us = y.us * (fixed ? 1.0 + 1.45 * missed : 1.5) + (one_image ? 0.005 : 0.035) * n;
+  } else {
+    y.us = 8.0 + 2.0e-6 * s;
+    y.few_us = (8.0 + 1.85e-6 * s) * (1.0 + 7.7 * missed) * (fixed ? 1.0 : 1.08) + (one_image ? 0.016 : 0.03) * n;
+  }
+  return y;
 }
 
 }  // namespace mclg

@@ -52,6 +52,11 @@ struct RegWay {
   uint32_t most = 0;                  // steps per launch, at most
   bool logs = false;                  // whether a launch can sum logs
   double launch_us = 0, step_us = 0;  // per launch and per step, estimated
+  // Against one step per launch: the fewest steps a launch is taken for, and
+  // the estimates with what all ways share and what few steps don't hide
+  // (few_in_us: divided by the launch's steps).
+  uint32_t least = 1;
+  double few_launch_us = 0, few_in_us = 0, few_step_us = 0;
 };
 
 // Whether a wave's step of 1536 sites leaves more undecided than its queue of
@@ -65,12 +70,18 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
                               bool one_image, bool galilean, bool fixed, double crowded,
                               const float *cost = nullptr);
 
+// One step per launch of the kernels that keep the state in memory, per step:
+// as the ways' estimates were fitted beside it, and with the sites the images
+// don't decide and the lattices' number.
+struct SingleStep {
+  double us = 0, few_us = 0;
+};
+// missed: the share of the sites whose draws the images don't decide.
+SingleStep single_step(uint64_t sites, uint32_t n, bool one_image, double missed, bool fixed);
+
 // The quickest way for `steps` steps (with logs among them), or nullptr when
-// one step per launch of the kernels that keep the state in memory (single_us
-// per step) is quicker.
+// one step per launch is quicker.
 const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, bool logs,
-                       double single_us);
-// Estimated time of one such step over `sites` sites.
-double single_step_us(uint64_t sites);
+                       const SingleStep &single);
 
 }  // namespace mclg

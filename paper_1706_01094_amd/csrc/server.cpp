@@ -453,6 +453,7 @@ struct mclg_server {
     b.limit = d_limit();
     UnitPlan units;
     std::vector<RegWay> ways;
+    SingleStep single;
     std::vector<uint32_t> list, limit(slot.size());
     std::vector<uint64_t> sites;
     std::vector<float> cost;
@@ -474,9 +475,11 @@ struct mclg_server {
         cost.clear();
         total = 0;
         uint64_t crowd = 0;
+        double missed = 0;
         for (size_t i = 0; i < wave.size(); ++i)
           if (left[i]) {
             const double cov = slot_coverage[wave[i].slot];
+            missed += cfg.C ? (1.0 - cov) * (double)wave[i].job.L : 0.0;
             crowd += crowded_image(cov) ? wave[i].job.L : 0u;
             cost.push_back(cfg.C ? site_cost(cov) : 1.0f);
             list.push_back(wave[i].slot);
@@ -487,13 +490,14 @@ struct mclg_server {
         if (units.units.size() > max_units((uint32_t)slot.size())) return hipErrorInvalidValue;
         ways = plan_ways(units, sites.data(), (uint32_t)n, n_cu, false, false, images_fixed(cfg.C),
                          (double)crowd / (double)total, cost.data());
+        single = single_step(total, (uint32_t)n, n == 1, missed / (double)total, images_fixed(cfg.C));
         for (UnitDev &u : units.units) u.slot = list[u.slot];
         for (StripDev &x : units.strips) x.slot = list[x.slot];
         uploaded = false;
       }
       StepLaunch a = launch_args();
       a.n_slots = (uint32_t)n;
-      const RegWay *w = pick_way(ways, most, false, single_step_us(total));
+      const RegWay *w = pick_way(ways, most, false, single);
       hipError_t e = hipSuccess;
       uint64_t m = least;  // the launch's steps
       if (!w) {
