@@ -82,7 +82,7 @@ __device__ __forceinline__ void push_site(uint4 *queue, Rsrc over, uint32_t &F, 
 // Philox draws while they are in flight, then record reads and decisions;
 // the undecided draws are queued with the pre-collision counts before the
 // update.
-template <bool PATCH>
+template <bool PATCH, bool FIXED>
 __device__ __forceinline__ void decide_eight(uint4 &w0, uint4 &w1, uint2 key,
                                              uint32_t (&va)[4], uint32_t (&vb)[4],
                                              uint32_t (&vc)[4], const LdsView &lv, uint4 *queue,
@@ -101,10 +101,10 @@ __device__ __forceinline__ void decide_eight(uint4 &w0, uint4 &w1, uint2 key,
   rec_pair(s4, s5, r4, r5, b45);
   rec_pair(s6, s7, r6, r7, b67);
   uint64_t h0, h1, h2, h3, h4, h5, h6, h7;  // lanes whose site is undecided
-  const uint32_t d01 = finish_pair<false>(s0, s1, w0.x, w0.y, lv, h0, h1);
-  const uint32_t d23 = finish_pair<false>(s2, s3, w0.z, w0.w, lv, h2, h3);
-  const uint32_t d45 = finish_pair<false>(s4, s5, w1.x, w1.y, lv, h4, h5);
-  const uint32_t d67 = finish_pair<false>(s6, s7, w1.z, w1.w, lv, h6, h7);
+  const uint32_t d01 = finish_pair<FIXED>(s0, s1, w0.x, w0.y, lv, h0, h1);
+  const uint32_t d23 = finish_pair<FIXED>(s2, s3, w0.z, w0.w, lv, h2, h3);
+  const uint32_t d45 = finish_pair<FIXED>(s4, s5, w1.x, w1.y, lv, h4, h5);
+  const uint32_t d67 = finish_pair<FIXED>(s6, s7, w1.z, w1.w, lv, h6, h7);
   uint32_t na[4] = {va[0], va[1], va[2], va[3]}, nb[4] = {vb[0], vb[1], vb[2], vb[3]},
            nc[4] = {vc[0], vc[1], vc[2], vc[3]};
   apply_pair(na[0], nb[0], nc[0], d01);
@@ -181,6 +181,7 @@ __device__ __forceinline__ void drain_queue(const uint4 *queue, const uint4 *ove
 // The move decide_eight applied to one undecided site (a, b, c; draw r):
 // the same directory and record reads from the LDS image, one site in
 // 32-bit arithmetic with the 16-bit wrap-around of the packed form.
+template <bool FIXED>
 __device__ __forceinline__ uint32_t image_move(uint32_t a, uint32_t b, uint32_t c, uint32_t r,
                                                const LdsView &lv) {
   const uint32_t lo = min(min(a, c), lv.da2 & 0xffffu), hi = min(max(a, c), lv.dc2 & 0xffffu);
@@ -189,7 +190,7 @@ __device__ __forceinline__ uint32_t image_move(uint32_t a, uint32_t b, uint32_t 
   SiteLook sl;
   sl.q = lds_u4(row + 16u * bi);
   uint64_t miss;
-  return site_finish<false>(sl, r, lv, miss) & 0xffffu;
+  return site_finish<FIXED>(sl, r, lv, miss) & 0xffffu;
 }
 
 // Resolve the draws queued by the current chunk before its store
@@ -199,7 +200,7 @@ __device__ __forceinline__ uint32_t image_move(uint32_t a, uint32_t b, uint32_t 
 // 1 KB holds the chunk's 512 patches once its entries have been read.  Every
 // lane then adds its eight patches to its counts (zero for decided sites), so
 // the chunk's vector stores write the final counts.
-template <bool GAL>
+template <bool GAL, bool FIXED>
 __device__ __forceinline__ void patch_chunk(uint4 *queue, const uint4 *over, uint32_t F,
                                             uint32_t lane, uint32_t xs, const SlotView &v,
                                             const LdsView &lv, const StepParams &p,
@@ -225,7 +226,7 @@ __device__ __forceinline__ void patch_chunk(uint4 *queue, const uint4 *over, uin
     uint4 e = i < kQueue ? e0 : over[i - kQueue];
     const uint32_t pos = e.x, b = e.y >> 16;
     // C = 0 queues only overflowing sites and applies no move
-    const uint32_t dw = p.C != 0 ? image_move(e.y & 0xffffu, b, e.z, e.w, lv) : 0u;
+    const uint32_t dw = p.C != 0 ? image_move<FIXED>(e.y & 0xffffu, b, e.z, e.w, lv) : 0u;
     e.x = xs + pos;
     const uint32_t bn = resolve_queued<GAL>(e, p, tab, v.t, v.rid, err);
     const uint32_t d = (uint32_t)(((int32_t)b - (int32_t)bn) >> 1);
@@ -322,7 +323,10 @@ __device__ __forceinline__ uint32_t grab_chunk(uint32_t *ctr, uint32_t lane) {
 // update has no races.  Undecided draws wait in the wave's queue, which is
 // drained between chunks once it nears capacity, and at the end of the
 // slot's segment.
-template <int MAXT, bool GAL, int MODE>
+// FIXED: the images hold fixed records (see LdsImage), whose decision needs no
+// masks that depend on the image: 2^24 sites of density 50, 37.8 us per step
+// and 38.4 with them, 2^22 14.6 and 15.3.
+template <int MAXT, bool GAL, int MODE, bool FIXED>
 __global__ void __launch_bounds__(MAXT) k_step(StepLaunch a) {
   constexpr bool PATCH = MODE == kDrainPatch;
   // patched drains are the policy for states larger than the caches: their
@@ -462,14 +466,14 @@ __global__ void __launch_bounds__(MAXT) k_step(StepLaunch a) {
         if (p.C != 0) {
           uint4 w0 = make_uint4(x8 >> 2, t, sv.rid, 0u);
           uint4 w1 = make_uint4((x8 >> 2) + 1u, t, sv.rid, 0u);
-          decide_eight<PATCH>(w0, w1, key, cur.m, cur.z, cur.p, lv, queue, ovr, F, slow, x8, L,
+          decide_eight<PATCH, FIXED>(w0, w1, key, cur.m, cur.z, cur.p, lv, queue, ovr, F, slow, x8, L,
                               cw.xs);
         } else {
           queue_saturated<PATCH>(cur.m, cur.z, cur.p, queue, ovr, F, slow, x8, L, cw.xs);
         }
         if constexpr (PATCH) {
           if (F) {
-            patch_chunk<GAL>(queue, over, F, lane, cw.xs, sv, lv, p, a.tab, a.err, cur.m,
+            patch_chunk<GAL, FIXED>(queue, over, F, lane, cw.xs, sv, lv, p, a.tab, a.err, cur.m,
                              cur.z, cur.p);
             F = 0;
           }
@@ -645,23 +649,26 @@ __global__ void __launch_bounds__(256) k_histogram(
 
 }  // namespace
 
-// Sets the dynamic LDS limit of the six instantiations for this block size
+// Sets the dynamic LDS limit of the twelve instantiations for this block size
 // and returns the smallest of their occupancies.
-template <int MAXT, bool GAL, int MODE>
+template <int MAXT, bool GAL, int MODE, bool FIXED>
 static hipError_t occupancy_one(uint32_t threads, uint32_t lds, int &blocks) {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_step<MAXT, GAL, MODE>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_step<MAXT, GAL, MODE, FIXED>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e) return e;
   int b = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_step<MAXT, GAL, MODE>, (int)threads, lds);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_step<MAXT, GAL, MODE, FIXED>, (int)threads, lds);
   blocks = std::min(blocks, b);
   return e;
 }
 template <int MAXT, bool GAL>
 static hipError_t occupancy_modes(uint32_t threads, uint32_t lds, int &blocks) {
-  hipError_t e = occupancy_one<MAXT, GAL, kDrainDeferred>(threads, lds, blocks);
-  if (!e) e = occupancy_one<MAXT, GAL, kDrainChunk>(threads, lds, blocks);
-  if (!e) e = occupancy_one<MAXT, GAL, kDrainPatch>(threads, lds, blocks);
+  hipError_t e = occupancy_one<MAXT, GAL, kDrainDeferred, true>(threads, lds, blocks);
+  if (!e) e = occupancy_one<MAXT, GAL, kDrainChunk, true>(threads, lds, blocks);
+  if (!e) e = occupancy_one<MAXT, GAL, kDrainPatch, true>(threads, lds, blocks);
+  if (!e) e = occupancy_one<MAXT, GAL, kDrainDeferred, false>(threads, lds, blocks);
+  if (!e) e = occupancy_one<MAXT, GAL, kDrainChunk, false>(threads, lds, blocks);
+  if (!e) e = occupancy_one<MAXT, GAL, kDrainPatch, false>(threads, lds, blocks);
   return e;
 }
 template <int MAXT>
@@ -690,13 +697,18 @@ hipError_t step_occupancy(const Schedule &sch, uint32_t lds_bytes, uint32_t n_cu
   return hipSuccess;
 }
 
+template <int MAXT, bool GAL, bool FIXED>
+static void launch_fixed(dim3 grid, dim3 block, uint32_t lds, hipStream_t s, const StepLaunch &a) {
+  switch (a.p.drain) {
+    case kDrainChunk: k_step<MAXT, GAL, kDrainChunk, FIXED><<<grid, block, lds, s>>>(a); break;
+    case kDrainPatch: k_step<MAXT, GAL, kDrainPatch, FIXED><<<grid, block, lds, s>>>(a); break;
+    default: k_step<MAXT, GAL, kDrainDeferred, FIXED><<<grid, block, lds, s>>>(a); break;
+  }
+}
 template <int MAXT, bool GAL>
 static void launch_mode(dim3 grid, dim3 block, uint32_t lds, hipStream_t s, const StepLaunch &a) {
-  switch (a.p.drain) {
-    case kDrainChunk: k_step<MAXT, GAL, kDrainChunk><<<grid, block, lds, s>>>(a); break;
-    case kDrainPatch: k_step<MAXT, GAL, kDrainPatch><<<grid, block, lds, s>>>(a); break;
-    default: k_step<MAXT, GAL, kDrainDeferred><<<grid, block, lds, s>>>(a); break;
-  }
+  if (images_fixed(a.p.C)) launch_fixed<MAXT, GAL, true>(grid, block, lds, s, a);
+  else launch_fixed<MAXT, GAL, false>(grid, block, lds, s, a);
 }
 
 hipError_t launch_step(const Schedule &sch, hipStream_t s, const StepLaunch &a) {
