@@ -32,6 +32,11 @@
  *     exception crosses the ABI;
  *   - device memory is owned by the caller (e.g. torch tensors) and must stay
  *     alive until mclg_destroy; the library never allocates device memory;
+ *   - pinned host memory is the library's, given back by mclg_destroy: a
+ *     context keeps what the results of mclg_moments take (264 bytes per
+ *     replica, from mclg_init on) or those of mclg_moments9 (480, from its first
+ *     call on), for up to 4096 replicas, a server 4 MiB; a context that can get
+ *     none copies the results instead;
  *   - host arrays passed in are copied before the call returns;
  *   - device work is enqueued on the caller's stream in stream order; calls
  *     that return host data synchronise that stream;

@@ -588,9 +588,8 @@ int mclg_init(const mclg_config *cfg, const mclg_init_spec *init, mclg_ctx **out
   if (e) return c->hip(e);
   if (c->n_cu > 256) return MCLG_E_UNSUPPORTED;  // overflow region sized for 256 CUs
   e = moments_scratch(&c->scratch);
-  if (!e && c->n <= kMomPinned)
-    e = hipHostMalloc(reinterpret_cast<void **>(&c->pin), 8ull * (kMom3Out * c->n + 1u), hipHostMallocDefault);
   if (e) return c->hip(e);
+  if (c->n <= kMomPinned) c->pin = pinned_results((uint64_t)kMom3Out * c->n + 1u);
   // what density and velocity each replica's image should target
   c->est_rho.assign(c->n, 0.0);
   c->est_u.assign(c->n, 0.0);

@@ -391,11 +391,7 @@ int d2q9_moments(D2Ctx &d, mclg_moments9_t *out) {
   m.partial = reinterpret_cast<unsigned long long *>(d.ws + d.o_mpart);
   m.out = reinterpret_cast<long long *>(d.ws + d.o_mout);
   // (not in d2q9_init: contexts that are only stepped need none)
-  if (!d.pin && d.n <= kMomPinned) {
-    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&d.pin), 8ull * (kMom9Out * d.n + 1u),
-                                 hipHostMallocDefault);
-    if (e) return hip_rc(d, e);
-  }
+  if (!d.pin && d.n <= kMomPinned) d.pin = pinned_results((uint64_t)kMom9Out * d.n + 1u);
   if (d.pin) {
     m.out = d.pin;
     m.err = reinterpret_cast<const uint32_t *>(d.ws + d.o_err);

@@ -82,6 +82,14 @@ struct MomArgs {
 // and two waits and take 87 without.  More replicas than this go through the
 // workspace and a copy.
 constexpr uint32_t kMomPinned = 4096;
+// `words` of it, or null where the host has none to give (the results are
+// copied then).
+inline long long *pinned_results(uint64_t words) {
+  void *p = nullptr;
+  if (!hipHostMalloc(&p, 8u * words, hipHostMallocDefault)) return static_cast<long long *>(p);
+  (void)hipGetLastError();  // (not the next call's)
+  return nullptr;
+}
 
 // Static partial-record area of the allocation-free moments call: 8 MiB per
 // GPU (32768 D1Q3 records), for devices 0 .. kMomScratchDevices - 1.
