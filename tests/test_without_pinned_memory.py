@@ -101,7 +101,7 @@ MomPlan plan_moments(const uint32_t *slots, const uint64_t *sites, uint32_t n) {
 int main() {
   const uint64_t L[2] = {40, 9}, Ly[2] = {3, 5};
   uint32_t lam[18];
-  for (int i = 0; i < 18; ++i) lam[i] = 1 + (i & 1);
+  for (int i = 0; i < 18; ++i) lam[i] = i & 1 ? 8 : 1;
   const double rho[2] = {5, 6}, u[2] = {0, 0};
   for (int lattice : {MCLG_D1Q3, MCLG_D2Q9})
     for (bool b : {false, true}) {
