@@ -245,8 +245,8 @@ struct mclg_ctx {
     return hipSuccess;
   }
   // The way for `steps` steps, or nullptr for one step per launch.
-  const RegWay *way(uint64_t steps, bool logs) const {
-    return reg_launch() ? pick_way(ways, steps, logs, single) : nullptr;
+  const RegWay *way(uint64_t steps) const {
+    return reg_launch() ? pick_way(ways, steps, single) : nullptr;
   }
   TileDev *tiles_dev() { return reinterpret_cast<TileDev *>(ws + lay.o_tiles); }
   // The moment kernels' arguments; partial records and results go to
@@ -682,7 +682,7 @@ int mclg_set_blocked(mclg_ctx *c, uint32_t steps, uint32_t tile, void *scratch,
 int mclg_step(mclg_ctx *c, uint64_t n_steps) {
   if (!c) return MCLG_E_INVAL;
   if (c->d2) return d2q9_step(*c->d2, n_steps);
-  if (const RegWay *w = c->way(n_steps, false))
+  if (const RegWay *w = c->way(n_steps))
     return c->hip(c->step_way(*w, n_steps, 0, RegLog(), nullptr));
   for (uint64_t i = 0; i < n_steps; ++i) {
     if (c->t_pending >= (1u << 30)) {
@@ -827,7 +827,9 @@ int mclg_step_log(mclg_ctx *c, uint64_t every, uint64_t n_logs, const int32_t *t
   const uint32_t dig = (flags & MCLG_MOMENTS_DIGEST) ? 1u : 0u;
   const uint64_t total = every * n_logs;
   if (total == 0) return MCLG_OK;
-  const RegWay *w = c->way(total, true);
+  const RegWay *w = c->reg_launch()
+                        ? pick_log_way(c->ways, every, n_logs, c->lay.total_sites, n_modes, dig != 0u, c->single)
+                        : nullptr;
   if (w && c->log_room(*w) > 0) {
     // launches that sum the logs that fall in them
     RegLog lg;
@@ -931,7 +933,7 @@ int mclg_step_plan(const mclg_ctx *c, uint64_t n_steps, mclg_step_plan_t *out) {
   if (c && c->d2) return MCLG_E_UNSUPPORTED;
   if (!c || !out) return MCLG_E_INVAL;
   *out = mclg_step_plan_t{n_steps, n_steps ? 1u : 0u, 0u, 0u, 0u};
-  if (const RegWay *w = c->way(n_steps, false)) {
+  if (const RegWay *w = c->way(n_steps)) {
     out->launches = (n_steps + w->most - 1) / w->most;
     out->steps_per_launch = (uint32_t)((n_steps + out->launches - 1) / out->launches);
     out->sites_per_lane = 4u * w->Q;

@@ -222,30 +222,71 @@ std::vector<RegWay> plan_ways(const UnitPlan &plan, const uint64_t *L, uint32_t 
   return ways;
 }
 
-const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, bool logs,
-                       const SingleStep &single) {
+namespace {
+uint64_t launches_of(const RegWay &w, uint64_t steps) {
+  return w.kind == RegWay::kTile ? (steps + w.most - 1) / w.most : 1u;
+}
+// As the ways' estimates are compared with each other.
+const RegWay *least_of(const std::vector<RegWay> &ways, uint64_t steps, bool logs, double least) {
   const RegWay *best = nullptr;
-  uint64_t launches = 1;
-  double least = (double)steps * single.us;
   for (const RegWay &w : ways) {
     if (logs && !w.logs) continue;
-    const uint64_t n = w.kind == RegWay::kTile ? (steps + w.most - 1) / w.most : 1u;
-    const double us = (double)n * (w.launch_us + (logs && w.kind == RegWay::kTile ? kTileLogs : 0.0)) +
+    const double us = (double)launches_of(w, steps) *
+                          (w.launch_us + (logs && w.kind == RegWay::kTile ? kTileLogs : 0.0)) +
                       (double)steps * w.step_us;
     if (us < least) {
       least = us;
       best = &w;
-      launches = n;
     }
   }
-  if (!best || logs) return best;
-  const uint64_t k = (steps + launches - 1) / launches;  // of a launch
-  if (k < best->least) return nullptr;
-  if (best->kind == RegWay::kTile &&
-      (double)launches * (best->few_launch_us + best->few_in_us / (double)k) + (double)steps * best->few_step_us >=
-          (double)steps * single.few_us)
-    return nullptr;
   return best;
+}
+// As they are with other launches.
+double few_us(const RegWay &w, uint64_t steps) {
+  const uint64_t n = launches_of(w, steps), k = (steps + n - 1) / n;
+  if (w.kind == RegWay::kRing) return w.launch_us + (double)steps * w.step_us;
+  return (double)n * (w.few_launch_us + w.few_in_us / (double)k) + (double)steps * w.few_step_us;
+}
+}  // namespace
+
+const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, const SingleStep &single) {
+  const RegWay *const best = least_of(ways, steps, false, (double)steps * single.us);
+  if (!best) return nullptr;
+  const uint64_t n = launches_of(*best, steps);
+  if ((steps + n - 1) / n < best->least) return nullptr;
+  if (best->kind == RegWay::kTile && few_us(*best, steps) >= (double)steps * single.few_us) return nullptr;
+  return best;
+}
+
+// A log from the registers and one from memory, us, and what a launch of tiles
+// with logs adds to one without (the kernels with logs cover little of the way
+// in and out).  Measured, in launches with logs and with the moment kernels
+// after each interval (every x logs): 2^27 sites 1 x 4 2740 and 1910, 2 x 8 5800
+// and 6340, 3 x 1 1400 and 930, 10 x 4 8520 and 8080; 2^25 1 x 4 690 and 450, 3
+// x 6 1370 and 1410; 2^24 1 x 4 307 and 274, 1 x 16 1000 and 1090, 10 x 16 4630
+// and 4730; 2^22 5 x 1 84 and 71, 10 x 16 with a mode 1290 and 1580.
+const RegWay *pick_log_way(const std::vector<RegWay> &ways, uint64_t every, uint64_t n_logs, uint64_t sites,
+                           uint32_t n_modes, bool digest, const SingleStep &single) {
+  const uint64_t steps = every * n_logs;
+  const RegWay *const best = least_of(ways, steps, true, (double)steps * single.us);
+  if (!best) return nullptr;
+  const uint64_t n = launches_of(*best, steps), k = (steps + n - 1) / n;
+  if (k < best->least) return nullptr;
+  const double s = (double)sites;
+  const bool large = sites > (24ull << 20);
+  const RegWay *const w = pick_way(ways, every, single);
+  const double apart = (w ? few_us(*w, every) + 14.0 + 0.2e-6 * s : (double)every * single.few_us) + 14.0 +
+                       s * (0.9e-6 + (large ? 1.6e-6 : 0.85e-6) * n_modes + (digest ? 0.55e-6 : 0.0));
+  double within = (double)n_logs * 2.0;
+  if (best->kind == RegWay::kRing) {
+    within += few_us(*best, steps);
+  } else {
+    within += (double)n * (best->few_launch_us + kTileLogs +
+                           (large ? 3.6e-6 * s / (1.0 + 0.07 * (double)k) : 1.0e-6 * s / (double)k)) +
+              (large ? 0.9 : 1.0) * (double)steps * best->few_step_us +
+              (double)n_logs * s * ((large ? 2.6e-6 : 2.1e-6) + 1.4e-6 * n_modes + (digest ? 0.4e-6 : 0.0));
+  }
+  return within < (double)n_logs * apart ? best : nullptr;
 }
 
 // Measured (us per step, without and with undecided sites): 2^24 sites 37.5,

@@ -79,9 +79,14 @@ struct SingleStep {
 // missed: the share of the sites whose draws the images don't decide.
 SingleStep single_step(uint64_t sites, uint32_t n, bool one_image, double missed, bool fixed);
 
-// The quickest way for `steps` steps (with logs among them), or nullptr when
-// one step per launch is quicker.
-const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, bool logs,
-                       const SingleStep &single);
+// The quickest way for `steps` steps, or nullptr when one step per launch is
+// quicker.
+const RegWay *pick_way(const std::vector<RegWay> &ways, uint64_t steps, const SingleStep &single);
+
+// The quickest way for n_logs times `every` steps with the moments of `sites`
+// sites after each, or nullptr where it is quicker to take every interval by
+// itself and sum its state in memory.
+const RegWay *pick_log_way(const std::vector<RegWay> &ways, uint64_t every, uint64_t n_logs, uint64_t sites,
+                           uint32_t n_modes, bool digest, const SingleStep &single);
 
 }  // namespace mclg

@@ -497,7 +497,7 @@ struct mclg_server {
       }
       StepLaunch a = launch_args();
       a.n_slots = (uint32_t)n;
-      const RegWay *w = pick_way(ways, most, false, single);
+      const RegWay *w = pick_way(ways, most, single);
       hipError_t e = hipSuccess;
       uint64_t m = least;  // the launch's steps
       if (!w) {

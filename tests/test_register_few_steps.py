@@ -27,7 +27,7 @@ static bool reg(std::vector<uint64_t> L, uint64_t steps, double coverage, bool g
   const UnitPlan P = plan_units(L.data(), n, 256, cost.data());
   const std::vector<RegWay> ways = plan_ways(P, L.data(), n, 256, one_image, galilean, fixed,
                                              crowded_image(coverage) ? 1.0 : 0.0, cost.data());
-  return pick_way(ways, steps, false, single_step(sites, n, one_image, 1.0 - coverage, fixed)) != nullptr;
+  return pick_way(ways, steps, single_step(sites, n, one_image, 1.0 - coverage, fixed)) != nullptr;
 }
 #define REQUIRE(x) if (!(x)) { std::printf("%s\n", #x); return 1; }
 int main() {
