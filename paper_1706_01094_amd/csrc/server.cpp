@@ -148,6 +148,19 @@ struct mclg_server {
   };
   std::map<std::pair<double, double>, CachedImage> image_cache;
   std::vector<double> slot_coverage;  // of the image of the slot's job
+  // The jobs of the last launch (their places in the order of admission) and
+  // what is made of them; what of it is on the device.
+  struct Planned {
+    std::vector<uint64_t> jobs, sites;
+    std::vector<uint32_t> list;
+    uint64_t total = 0;
+    UnitPlan units;
+    std::vector<RegWay> ways;
+    SingleStep single;
+    bool list_up = false, units_up = false;
+    uint32_t n_tiles = 0;  // 0: not on the device
+  };
+  Planned planned;
   uint32_t n_active = 0;
   uint32_t lds_bytes = 16, max_blocks = 1, image_budget = kImage, n_cu = 1;
   int last_hip = 0;
@@ -426,6 +439,8 @@ struct mclg_server {
     }
     if (fresh.empty() || e) return e;
     if (tiles.size() > lay.max_tiles) return hipErrorInvalidValue;
+    planned.list_up = false;
+    planned.n_tiles = 0;
     e = put(ws + lay.o_pool, pool);
     if (!e) e = put(d_list(), fresh);
     if (!e) e = put(d_tiles(), tiles);
@@ -438,27 +453,50 @@ struct mclg_server {
     return e;
   }
 
+  // The lists that launches read, for the jobs of `left` that have steps left:
+  // made anew only when those are others than the last ones, and uploaded only
+  // when the device holds others (a tick of few steps is no longer than its
+  // uploads).
+  hipError_t plan_jobs(const std::vector<Run> &wave, const std::vector<uint64_t> &left, size_t n) {
+    Planned &p = planned;
+    bool same = p.jobs.size() == n;
+    for (size_t i = 0, k = 0; same && i < wave.size(); ++i)
+      if (left[i]) same = p.jobs[k++] == wave[i].nth;
+    if (same) return hipSuccess;
+    p = Planned();
+    uint64_t crowd = 0;
+    double missed = 0;
+    std::vector<float> cost;
+    for (size_t i = 0; i < wave.size(); ++i)
+      if (left[i]) {
+        const double cov = slot_coverage[wave[i].slot];
+        missed += cfg.C ? (1.0 - cov) * (double)wave[i].job.L : 0.0;
+        crowd += crowded_image(cov) ? wave[i].job.L : 0u;
+        cost.push_back(cfg.C ? site_cost(cov) : 1.0f);
+        p.jobs.push_back(wave[i].nth);
+        p.list.push_back(wave[i].slot);
+        p.sites.push_back(wave[i].job.L);
+        p.total += wave[i].job.L;
+      }
+    p.units = plan_units(p.sites.data(), (uint32_t)n, n_cu, cost.data());
+    if (p.units.units.size() > max_units((uint32_t)slot.size())) {
+      p = Planned();
+      return hipErrorInvalidValue;
+    }
+    p.ways = plan_ways(p.units, p.sites.data(), (uint32_t)n, n_cu, false, false, images_fixed(cfg.C),
+                       (double)crowd / (double)p.total, cost.data());
+    p.single = single_step(p.total, (uint32_t)n, n == 1, missed / (double)p.total, images_fixed(cfg.C));
+    for (UnitDev &u : p.units.units) u.slot = p.list[u.slot];
+    for (StripDev &x : p.units.strips) x.slot = p.list[x.slot];
+    return hipSuccess;
+  }
+
   // The steps of a wave's jobs: launches that each job takes part in for as
   // many steps as it has left.
   hipError_t step_jobs(std::vector<Run> &wave) {
     std::stable_sort(wave.begin(), wave.end(), [](const Run &x, const Run &y) { return x.job.L > y.job.L; });
     std::vector<uint64_t> left(wave.size());
     for (size_t i = 0; i < wave.size(); ++i) left[i] = wave[i].steps;
-    RegBufs b;
-    b.order = d_list();
-    b.units = reinterpret_cast<const UnitDev *>(ws + lay.o_units);
-    b.first = reinterpret_cast<const uint32_t *>(ws + lay.o_ufirst);
-    b.strips = reinterpret_cast<const StripDev *>(ws + lay.o_strips);
-    b.strip_data = reinterpret_cast<uint16_t *>(ws + lay.o_sdata);
-    b.limit = d_limit();
-    UnitPlan units;
-    std::vector<RegWay> ways;
-    SingleStep single;
-    std::vector<uint32_t> list, limit(slot.size());
-    std::vector<uint64_t> sites;
-    std::vector<float> cost;
-    uint64_t total = 0;
-    bool uploaded = false;  // the list and the units
     for (;;) {
       uint64_t most = 0, least = ~0ull;
       size_t n = 0;
@@ -469,68 +507,61 @@ struct mclg_server {
           ++n;
         }
       if (n == 0) return hipSuccess;
-      if (n != list.size()) {  // (jobs leave and none joins)
-        list.clear();
-        sites.clear();
-        cost.clear();
-        total = 0;
-        uint64_t crowd = 0;
-        double missed = 0;
-        for (size_t i = 0; i < wave.size(); ++i)
-          if (left[i]) {
-            const double cov = slot_coverage[wave[i].slot];
-            missed += cfg.C ? (1.0 - cov) * (double)wave[i].job.L : 0.0;
-            crowd += crowded_image(cov) ? wave[i].job.L : 0u;
-            cost.push_back(cfg.C ? site_cost(cov) : 1.0f);
-            list.push_back(wave[i].slot);
-            sites.push_back(wave[i].job.L);
-            total += wave[i].job.L;
-          }
-        units = plan_units(sites.data(), (uint32_t)n, n_cu, cost.data());
-        if (units.units.size() > max_units((uint32_t)slot.size())) return hipErrorInvalidValue;
-        ways = plan_ways(units, sites.data(), (uint32_t)n, n_cu, false, false, images_fixed(cfg.C),
-                         (double)crowd / (double)total, cost.data());
-        single = single_step(total, (uint32_t)n, n == 1, missed / (double)total, images_fixed(cfg.C));
-        for (UnitDev &u : units.units) u.slot = list[u.slot];
-        for (StripDev &x : units.strips) x.slot = list[x.slot];
-        uploaded = false;
-      }
+      hipError_t e = plan_jobs(wave, left, n);
+      if (e) return e;
+      Planned &p = planned;
       StepLaunch a = launch_args();
       a.n_slots = (uint32_t)n;
-      const RegWay *w = pick_way(ways, most, single);
-      hipError_t e = hipSuccess;
+      if (!p.list_up) e = put(d_list(), p.list);
+      const RegWay *w = pick_way(p.ways, most, p.single);
       uint64_t m = least;  // the launch's steps
       if (!w) {
-        std::vector<TileDev> tiles;
         const uint32_t ts = sch.tile_sites();
-        for (size_t i = 0; i < n; ++i) {
-          const uint32_t next = (uint32_t)(tiles.size() + (sites[i] + ts - 1) / ts);
-          for (uint64_t x0 = 0; x0 < sites[i]; x0 += ts) tiles.push_back(TileDev{list[i], (uint32_t)x0, next, 0});
+        if (!p.n_tiles) {
+          std::vector<TileDev> tiles;
+          for (size_t i = 0; i < n; ++i) {
+            const uint32_t next = (uint32_t)(tiles.size() + (p.sites[i] + ts - 1) / ts);
+            for (uint64_t x0 = 0; x0 < p.sites[i]; x0 += ts) tiles.push_back(TileDev{p.list[i], (uint32_t)x0, next, 0});
+          }
+          if (tiles.size() > lay.max_tiles) e = hipErrorInvalidValue;
+          if (!e) e = put(d_tiles(), tiles);
+          if (!e) p.n_tiles = (uint32_t)tiles.size();
         }
-        if (tiles.size() > lay.max_tiles) return hipErrorInvalidValue;
-        a.n_tiles = (uint32_t)tiles.size();
-        a.p.drain = auto_drain(6 * total);  // by the jobs' state
-        e = put(d_tiles(), tiles);
-        if (!e) e = put(d_list(), list);
+        a.n_tiles = p.n_tiles;
+        a.p.drain = auto_drain(6 * p.total);  // by the jobs' state
         if (!e) e = send();
+        if (!e) p.list_up = true;
         for (uint64_t i = 0; i < m && !e; ++i) e = launch_step(sch, s, a);
       } else {
         const uint64_t launches = (most + w->most - 1) / w->most;
         m = (most + launches - 1) / launches;
-        std::fill(limit.begin(), limit.end(), 0u);
-        for (size_t i = 0; i < wave.size(); ++i) limit[wave[i].slot] = (uint32_t)std::min(left[i], m);
-        e = put(d_limit(), limit);
-        if (!uploaded) {
-          if (!e) e = put(d_list(), list);
-          if (!e) e = put(ws + lay.o_units, units.units);
-          if (!e) e = put(ws + lay.o_ufirst, units.first);
-          if (!e) e = put(ws + lay.o_strips, units.strips);
-          uploaded = true;
+        // alone on the device, and all of them for as many steps: no limits
+        const bool all = waves.size() == 1 && n == wave.size() && least >= m;
+        if (!all) {
+          std::vector<uint32_t> limit(slot.size(), 0u);
+          for (size_t i = 0; i < wave.size(); ++i) limit[wave[i].slot] = (uint32_t)std::min(left[i], m);
+          if (!e) e = put(d_limit(), limit);
+        }
+        if (!p.units_up) {
+          if (!e) e = put(ws + lay.o_units, p.units.units);
+          if (!e) e = put(ws + lay.o_ufirst, p.units.first);
+          if (!e) e = put(ws + lay.o_strips, p.units.strips);
         }
         if (!e) e = send();
+        if (!e) p.list_up = p.units_up = true;
+        RegBufs b;
+        b.order = d_list();
         b.n = (uint32_t)n;
-        if (!e) e = launch_way(s, a, *w, units, b, (uint32_t)m, RegLog());
-        if (!e) e = launch_add_each(s, d_tslot(), d_limit(), (uint32_t)slot.size());
+        b.units = reinterpret_cast<const UnitDev *>(ws + lay.o_units);
+        b.first = reinterpret_cast<const uint32_t *>(ws + lay.o_ufirst);
+        b.strips = reinterpret_cast<const StripDev *>(ws + lay.o_strips);
+        b.strip_data = reinterpret_cast<uint16_t *>(ws + lay.o_sdata);
+        b.limit = all ? nullptr : d_limit();
+        if (!e) e = launch_way(s, a, *w, p.units, b, (uint32_t)m, RegLog());
+        // (a free slot's counter is set when a job takes it)
+        if (!e)
+          e = all ? launch_add_t(s, d_tslot(), 0, (uint32_t)slot.size(), (uint32_t)m)
+                  : launch_add_each(s, d_tslot(), d_limit(), (uint32_t)slot.size());
       }
       if (e) return e;
       for (uint64_t &k : left) k -= std::min(k, m);
@@ -598,6 +629,7 @@ struct mclg_server {
     free_spans.clear();
     if (const uint64_t usable = cfg.arena_bytes / 256 * 256) free_spans[0] = usable;
     arena_used = 0;
+    planned = Planned();
     pending.n = 0;
     if (!hipStreamSynchronize(s)) pin_used = 0;
   }

@@ -1,7 +1,8 @@
 """The server's host side over a device that fails (host side, compiled here;
 the HIP calls and the kernels are stand-ins that work on host memory, one of
-which returns an error): a failed tick loses no job, and the pinned memory that
-the device reads is never freed before the device is done with it."""
+which returns an error): a failed tick loses no job, the pinned memory that
+the device reads is never freed before the device is done with it, and a tick
+with the same jobs as the last one uploads nothing."""
 import os
 import subprocess
 
@@ -21,6 +22,7 @@ MAIN = r"""
 #include "../../include/mclg.h"
 using namespace mclg;
 static bool busy = false, freed_busy = false;
+static size_t uploads = 0;
 static long calls = 0, fail_at = 0;  // the fail_at-th call from now on fails
 static hipError_t call() { return fail_at && ++calls == fail_at ? hipErrorOutOfMemory : hipSuccess; }
 extern "C" {
@@ -56,6 +58,7 @@ hipError_t launch_step(const Schedule &, hipStream_t, const StepLaunch &a) {
 }
 hipError_t launch_uploads(hipStream_t, const Uploads &u) {
   if (!u.n) return hipSuccess;
+  uploads += u.n;
   hipError_t e = launch();
   for (uint32_t k = 0; !e && k < u.n; ++k) std::memcpy(u.piece[k].dst, u.piece[k].src, u.piece[k].bytes);
   return e;
@@ -63,6 +66,11 @@ hipError_t launch_uploads(hipStream_t, const Uploads &u) {
 hipError_t launch_set_t(hipStream_t, uint32_t *t, const uint32_t *list, uint32_t n, uint32_t v) {
   hipError_t e = launch();
   for (uint32_t k = 0; !e && k < n; ++k) t[list[k]] = v;
+  return e;
+}
+hipError_t launch_add_t(hipStream_t, uint32_t *t, uint32_t first, uint32_t n, uint32_t add) {
+  hipError_t e = launch();
+  for (uint32_t k = 0; !e && k < n; ++k) t[first + k] += add;
   return e;
 }
 hipError_t launch_add_each(hipStream_t, uint32_t *t, const uint32_t *add, uint32_t n) {
@@ -189,8 +197,42 @@ static int end() {
   REQUIRE(!freed_busy);
   return 0;
 }
+// Ticks of any length between jobs that join.
+static int steady() {
+  mclg_server_config c{};
+  c.abi_version = MCLG_ABI_VERSION;
+  c.max_slots = 9;
+  c.C = 2;
+  c.lambda_num = c.lambda_den = 1;
+  c.n_max = 40;
+  c.arena_bytes = 900000;
+  uint64_t need = 0;
+  fail_at = 0;
+  uint32_t tick = 0;
+  long at = 0;
+  REQUIRE(mclg_server_sizes(&c, &need) == MCLG_OK);
+  c.arena = std::malloc(c.arena_bytes);
+  c.workspace = std::malloc(need);
+  c.workspace_bytes = need;
+  mclg_server *sv = nullptr;
+  REQUIRE(mclg_server_create(&c, &sv) == MCLG_OK);
+  for (uint32_t i = 0; i < 4; ++i) {
+    const mclg_job j{i, 500 + 9000ull * i, 100000, 5.0, 0.0};
+    REQUIRE(mclg_server_submit(sv, &j) == MCLG_OK);
+    const uint32_t lengths[] = {1, 40, 2, 300};
+    for (int round = 0; round < 3; ++round)
+      for (uint32_t k : lengths) {
+        tick = k;
+        uploads = 0;
+        REQUIRE(mclg_server_tick(sv, k) == MCLG_OK);
+        REQUIRE(round == 0 || uploads == 0);
+      }
+  }
+  REQUIRE(mclg_server_destroy(sv) == MCLG_OK);
+  return 0;
+}
 int main(int argc, char **argv) {
-  if (argc > 1 ? end() : ticks()) return 1;
+  if (argc < 2 ? ticks() : argv[1][0] == 'e' ? end() : steady()) return 1;
   std::puts("ok");
 }
 """
@@ -208,7 +250,7 @@ def program(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("args", [[], ["end"]], ids=["ticks", "end"])
+@pytest.mark.parametrize("args", [[], ["end"], ["steady"]], ids=["ticks", "end", "steady"])
 def test_server_over_a_failing_device(program, args):
     out = subprocess.run([program] + args, capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
