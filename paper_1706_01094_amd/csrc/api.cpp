@@ -211,9 +211,9 @@ struct mclg_ctx {
     // Recorded into a program's graph, the launches advance the device's
     // counters themselves, so that every replay goes on from the one before.
     hipStreamCaptureStatus recorded = hipStreamCaptureStatusNone;
-    if (stream) {
-      hipError_t e = hipStreamIsCapturing(stream, &recorded);
-      if (e) return e;
+    if (stream && hipStreamIsCapturing(stream, &recorded)) {
+      (void)hipGetLastError();  // (a handle that cannot be asked is not recorded)
+      recorded = hipStreamCaptureStatusNone;
     }
     for (uint64_t done = 0; done < total;) {
       const uint64_t left = total - done, launches = (left + w.most - 1) / w.most;
