@@ -149,9 +149,9 @@ __device__ __forceinline__ void draws(uint32_t (&r)[3], uint4 w, uint32_t N, con
 // The sub-collision loop of one site with N < 2^7 (W = 2: bytes) or 2^15
 // (W = 4: halves) particles, Dq <= 2^15.  Bound by the vector instructions:
 // 69 of them (bytes; 100 with packed 16-bit sums for all), 33 of them the
-// block's.  4096 x 4096 sites, C = 10, us per step at densities 36 and 360:
-// 441 and 440 before, 345 and 406 now; two sites per lane with 32-bit loads,
-// and loads one tile ahead, gained nothing on it.  K[] packs the differences 2^7 - K_j
+// block's.  4096 x 4096 sites, C = 10, us per step at densities 36 and 360 (70
+// steps after the first five): 456 and 441 before, 361 and 404 now; two sites per
+// lane with 32-bit loads, and loads one tile ahead, gained nothing on it.  K[] packs the differences 2^7 - K_j
 // (2^15 - K_j).  Adding r to each gives no carry, and its top bit is set
 // exactly when K_j <= r: a count is an addition, a mask and a population
 // count per word, where differences of 16-bit sums took three instructions
@@ -332,7 +332,7 @@ __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles
       N += n[j];
     }
     if (act && N > 65535u) atomicOr(a.err, kErrOverflow);
-    act = act && N >= 2u && N <= 65535u && a.C > 0;
+    act = act && N >= 2u && N <= 65535u;
     if (__ballot(act && N >= 0x80u) != 0u)
       atomicMax(&needs[par], __ballot(act && N >= 0x8000u) != 0u ? 3u : 2u);
     hold_rules(a, rules, &needs[par], held);
@@ -347,8 +347,8 @@ __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles
 // thread: the counts stay in LDS, in the same shifted layout, between one read
 // and one write of the state.  Without the state's way through memory and a
 // launch per step; bound by the latency of a wave's sub-collisions, two waves
-// per SIMD.  Us per step: a lattice of 16 x 16 sites 5.3 with a launch each and
-// 3.1 here, of 25 x 20 sites 5.8 and 4.0.  (With 1000 sites the 16 waves on one
+// per SIMD.  Us per step: a lattice of 16 x 16 sites 5.7 with a launch each and
+// 3.1 here, of 25 x 20 sites 6.1 and 3.9.  (With 1000 sites the 16 waves on one
 // CU take 6.2, where four blocks of k_step9 take 5.9.)
 __global__ void __launch_bounds__(kBlockSites9) k_steps9(Step9 a, uint32_t steps) {
   extern __shared__ __align__(16) uint16_t counts[];  // 9 arrays of S
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__(kBlockSites9) k_steps9(Step9 a, uint32_t steps
     }
     bool act = threadIdx.x < S;
     if (act && N > 65535u) atomicOr(a.err, kErrOverflow);
-    act = act && N >= 2u && N <= 65535u && a.C > 0;
+    act = act && N >= 2u && N <= 65535u;
     if (__ballot(act && N >= 0x80u) != 0u)
       atomicMax(&needs[k & 1u], __ballot(act && N >= 0x8000u) != 0u ? 3u : 2u);
     hold_rules(a, rules, &needs[k & 1u], held);
