@@ -311,9 +311,10 @@ int d2q9_step(D2Ctx &d, uint64_t n_steps) {
   for (const Rep9 &r : d.reps) sites = std::max(sites, r.S);
   // One launch for all steps where that is quicker than one for each.  Us per
   // step, separate and together (2 steps, 64 steps): 256 sites 5.7 and 4.7, 3.1,
-  // 20000 lattices of them 128 and 122, 92; 500 sites 6.1 and 5.6, 3.9, 4096 of
-  // them 58 and 55, 39; but 1000 sites 5.9 and 6.8 (6 steps), 6.2, 4096 of them
-  // 94 and 103 (16 steps), 99: their waves share one CU instead of four.
+  // 20000 lattices of them 128 and 122, 92; 500 sites 6.2 and 5.6, 3.9, 4096 of
+  // them 59 and 55, 39; but (both ways timed in another run) 1000 sites 5.9 and
+  // 6.8 (6 steps), 6.2, 4096 of them 94 and 103 (16 steps), 99: their waves share
+  // one CU instead of four.
   if (sites <= kBlockSites9 && n_steps >= 2) {
     while (n_steps) {
       const uint32_t k = (uint32_t)std::min<uint64_t>(n_steps, 1u << 16);

@@ -348,7 +348,7 @@ __global__ void __launch_bounds__(kTileSites9) k_step9(Step9 a, uint32_t n_tiles
 // and one write of the state.  Without the state's way through memory and a
 // launch per step; bound by the latency of a wave's sub-collisions, two waves
 // per SIMD.  Us per step: a lattice of 16 x 16 sites 5.7 with a launch each and
-// 3.1 here, of 25 x 20 sites 6.1 and 3.9.  (With 1000 sites the 16 waves on one
+// 3.1 here, of 25 x 20 sites 6.2 and 3.9.  (With 1000 sites the 16 waves on one
 // CU take 6.2, where four blocks of k_step9 take 5.9.)
 __global__ void __launch_bounds__(kBlockSites9) k_steps9(Step9 a, uint32_t steps) {
   extern __shared__ __align__(16) uint16_t counts[];  // 9 arrays of S
