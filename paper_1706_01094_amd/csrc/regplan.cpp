@@ -289,8 +289,9 @@ const RegWay *pick_log_way(const std::vector<RegWay> &ways, uint64_t every, uint
   return within < (double)n_logs * apart ? best : nullptr;
 }
 
-// Measured (us per step, without and with undecided sites): 2^24 sites 37.5,
-// 38.4 with 0.3 %, 69 with 10 %; 2^26 174, 176 and 200; of C = 30 (3 %) 52 and
+// Measured (us per step, without and with undecided sites, 0.6 us more at 2^24
+// than k_step takes since it has instances of its own for one image and fixed
+// windows): 2^24 sites 37.5, 38.4 with 0.3 %, 69 with 10 %; 2^26 174, 176 and 200; of C = 30 (3 %) 52 and
 // 252; 1000 lattices of 1000 sites 27, with an image each 42; 2000 of 30000 167
 // and 234.
 SingleStep single_step(uint64_t sites, uint32_t n, bool one_image, double missed, bool fixed) {
