@@ -38,17 +38,22 @@ TRAFFIC_FILES = {
     "batched": os.path.join(PROFILES, "traffic_stream_collide_1024_replicas.json"),
     "probe_blocked": os.path.join(PROFILES, "traffic_stream_collide_L128M_tiles.json"),
     "batched_blocked": os.path.join(PROFILES, "traffic_stream_collide_1024_replicas_blocked.json"),
+    # the same workload in a call of 20 steps, which go in one launch
+    "plain_20_steps": os.path.join(PROFILES, "traffic_stream_collide_L16M_20_steps.json"),
 }
 TRAFFIC_FILE = TRAFFIC_FILES["plain"]
 # the sources of the D1Q3 step kernels and of the plan of their launches
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1706_01094_amd", "csrc", f)
                for f in ("kernels.hip", "kernels_reg.hip", "collide.h", "rng.h", "device.h",
-                         "mom3_sum.h", "moments.h", "regplan.cpp")]
+                         "mom3_sum.h", "moments.h", "regplan.h", "regplan.cpp", "regrun.h")]
 
 # the D2Q9 step kernel: its sources and its counted VALU instructions per site
 D2Q9_SRCS = [os.path.join(ROOT, "paper_1706_01094_amd", "csrc", f)
              for f in ("kernels_d2q9.hip", "rng.h", "device.h", "d2q9.h")]
+# (the first record is of the kernel with one wave per 64 sites, before the
+# present one, whose waves take several times 64)
 D2Q9_VALU_FILE = os.path.join(PROFILES, "valu_d2q9_4096x4096.json")
+D2Q9_TILES_FILE = os.path.join(PROFILES, "valu_d2q9_4096x4096_tiles.json")
 # VALU issue of MI355X: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD
 # every 4 cycles (16 lanes wide), 2.4 GHz
 VALU_PEAK_G = 256 * 4 / 4 * 2.4
@@ -62,40 +67,38 @@ def kernel_hash(paths=None) -> str:
     return h.hexdigest()[:16]
 
 
-def _counter_record(which: str, steps_per_launch: int = 1):
+def _counter_record(which: str, steps_per_launch: int = 1, plan: dict | None = None):
     """The committed rocprofv3 counter record of this workload, if it was
     taken on the current kernel source with launches of the same number of
-    steps."""
-    try:
-        with open(TRAFFIC_FILES[which]) as f:
-            d = json.load(f)
-    except (OSError, ValueError):
-        return None
-    if d.get("kernel_sha256_16") != kernel_hash():
-        return None
-    return d if d.get("steps_per_launch", 1) == steps_per_launch else None
+    steps; with `plan` (Lattice.step_plan of the timed call) also the same
+    kernel and tiles."""
+    for name in (which, which + "_20_steps"):
+        if name not in TRAFFIC_FILES:
+            continue
+        try:
+            with open(TRAFFIC_FILES[name]) as f:
+                d = json.load(f)
+        except (OSError, ValueError):
+            continue
+        if d.get("kernel_sha256_16") != kernel_hash() or d.get("steps_per_launch", 1) != steps_per_launch:
+            continue
+        if plan is not None and any(d.get(k) != plan[k] for k in ("sites_per_lane", "extra_sites")):
+            continue
+        return d
+    return None
 
 
-def counted_steps(which: str) -> int:
-    """Steps per launch of the committed counter run of this workload (the
-    library chooses them for the number of steps of a call)."""
-    try:
-        with open(TRAFFIC_FILES[which]) as f:
-            return int(json.load(f).get("steps_per_launch", 1))
-    except (OSError, ValueError):
-        return 1
-
-
-def measured_traffic(which: str = "plain", steps_per_launch: int = 1):
+def measured_traffic(which: str = "plain", steps_per_launch: int = 1, plan: dict | None = None):
     """Memory-side bytes per launch from the committed counter runs, or None."""
-    d = _counter_record(which, steps_per_launch)
+    d = _counter_record(which, steps_per_launch, plan)
     return None if d is None else d.get("bytes_per_launch")
 
 
-def valu_issue_frac(which: str, seconds_per_launch: float, steps_per_launch: int = 1):
+def valu_issue_frac(which: str, seconds_per_launch: float, steps_per_launch: int = 1,
+                    plan: dict | None = None):
     """The step launch's VALU issue time (its counted VALU wave instructions
     at the 614.4 G/s issue peak) over its measured duration, or None."""
-    d = _counter_record(which, steps_per_launch)
+    d = _counter_record(which, steps_per_launch, plan)
     if d is None or "sq_insts_valu_per_dispatch" not in d:
         return None
     return d["sq_insts_valu_per_dispatch"] / (VALU_PEAK_G * 1e9) / seconds_per_launch
@@ -165,7 +168,10 @@ def run_plain(args, torch, M):
     K = args.blocked if not args.graph else 1
     if K > 1:
         lat.set_blocked(K)  # several steps per launch, also with --schedule
-    info["steps_per_launch"] = counted_steps("plain") if K > 1 else 1
+    # what the timed call launches
+    plan = {"launches": args.steps, "steps_per_launch": 1, "sites_per_lane": 0, "extra_sites": 0} \
+        if args.graph else lat.step_plan(args.steps)
+    info.update(plan)
     lat.step(args.warmup)
     torch.cuda.synchronize()
     e0, e1 = _events(torch, stream)
@@ -187,7 +193,7 @@ def run_plain(args, torch, M):
     rc = lat.check()
     if rc != 0:
         raise SystemExit(f"device error {rc}")
-    if K > 1 and args.single_steps:
+    if plan["sites_per_lane"] and args.single_steps:
         # the same lattice with one step per launch, for comparison (a fixed
         # drain policy, the one its size would get, keeps to those kernels)
         lat.set_blocked(1)
@@ -259,15 +265,16 @@ def run_probe(args, torch, M):
         n = max(1, args.probe_steps // K) * K
         bms = timed(n)
         ach = BYTES_PER_SITE_UPDATE * L / (bms / 1e3) / 1e9
-        K = counted_steps("probe_blocked")
-        btr = measured_traffic("probe_blocked", K)
-        blocked = {"steps_per_launch": K, "steps": n, "ms_per_step": bms,
+        plan = lat.step_plan(n)
+        K = plan["steps_per_launch"]
+        btr = measured_traffic("probe_blocked", K, plan)
+        blocked = {**plan, "steps": n, "ms_per_step": bms,
                    "site_updates_per_s": L / (bms / 1e3), "achieved_GBps": ach,
                    "frac": ach / HBM_PEAK_GBS,
                    "traffic_per_launch": btr,
                    "traffic_over_algorithmic": None if btr is None else
                    btr / (BYTES_PER_SITE_UPDATE * L * K),
-                   "valu_issue_frac": valu_issue_frac("probe_blocked", bms * K / 1e3, K)}
+                   "valu_issue_frac": valu_issue_frac("probe_blocked", bms * K / 1e3, K, plan)}
     rc = lat.check()
     lat.close()
     if rc != 0:
@@ -401,16 +408,17 @@ def run_batched(args, torch, M):
             torch.cuda.synchronize()
             ms = e0.elapsed_time(e1)
             rate = sites * nb / (ms / 1e3)
-            K = counted_steps("batched_blocked")
-            btr = measured_traffic("batched_blocked", K)
-            out["blocked"] = {"steps_per_launch": K, "steps": nb, "ms": ms,
+            plan = lat.step_plan(nb)
+            K = plan["steps_per_launch"]
+            btr = measured_traffic("batched_blocked", K, plan)
+            out["blocked"] = {**plan, "steps": nb, "ms": ms,
                               "us_per_step": 1e3 * ms / nb, "site_updates_per_s": rate,
                               "hbm_frac": BYTES_PER_SITE_UPDATE * rate / 1e9 / HBM_PEAK_GBS,
                               "traffic_per_launch": btr,
                               "traffic_over_algorithmic": None if btr is None else
                               btr / (BYTES_PER_SITE_UPDATE * sites * K),
                               "valu_issue_frac": valu_issue_frac("batched_blocked",
-                                                                 ms / 1e3 * K / nb, K)}
+                                                                 ms / 1e3 * K / nb, K, plan)}
             lat.set_blocked(1)
     # the graph's launches take one step each
     traffic = measured_traffic("batched")
@@ -593,18 +601,19 @@ def run_d2q9(args, torch, M):
            "steps": args.d2q9_steps, "ms_per_step": ms / args.d2q9_steps,
            "site_updates_per_s": rate, "hbm_GBps": 36.0 * rate / 1e9,
            "check": rc, "mass_per_site": m["sum_N"] / sites, "roofline": None}
-    # ALU roofline: VALU wave instructions per site (one lane per site) from
+    # ALU roofline: VALU wave instructions per 64 sites (one lane per site) from
     # the committed counter run, valid while the kernel's sources are the same
     try:
-        with open(D2Q9_VALU_FILE) as f:
+        with open(D2Q9_TILES_FILE) as f:
             v = json.load(f)
     except (OSError, ValueError):
         v = {}
     if v.get("kernel_sha256_16") == kernel_hash(D2Q9_SRCS):
-        achieved = v["valu_insts_per_wave"] * rate / 64 / 1e9
+        per_64 = v["sq_insts_valu_per_dispatch"] / (v["sites"] / 64)
+        achieved = per_64 * rate / 64 / 1e9
         out["roofline"] = {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_G,
                            "unit": "G VALU wave-instructions/s", "frac": achieved / VALU_PEAK_G,
-                           "valu_insts_per_wave": v["valu_insts_per_wave"]}
+                           "valu_insts_per_64_sites": per_64}
     return out
 
 
@@ -668,20 +677,23 @@ def run_moments(args, torch, M):
     return out
 
 
-def roofline(achieved: float, ms_per_step: float, K: int) -> dict:
+def roofline(achieved: float, ms_per_step: float, plan: dict) -> dict:
     """The headline's roofline.  One step per launch: 12 B per site update
     against the HBM peak.  Several steps per launch read and write the state
     once for all of them and are bound by VALU issue (the counted
-    instructions of a launch of K steps); the rate at 12 B per site update
-    stands beside it."""
+    instructions of such a launch, where one of this plan was counted); the
+    rate at 12 B per site update stands beside it."""
     hbm = {"achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS}
-    rest = {"steps_per_launch": K, "traffic": measured_traffic("plain", K)}
-    issue = valu_issue_frac("plain", ms_per_step * K / 1e3, K)
-    if K == 1 or issue is None:
+    K = plan["steps_per_launch"]
+    held = plan["sites_per_lane"] > 0
+    rest = {"steps_per_launch": K, "traffic": measured_traffic("plain", K, plan if held else None)}
+    issue = valu_issue_frac("plain", ms_per_step * K / 1e3, K, plan if held else None)
+    if not held:
         return {"bound": "hbm", **hbm, **rest, "valu_issue_frac": issue}
-    return {"bound": "alu", "achieved": issue * VALU_PEAK_G, "peak": VALU_PEAK_G,
-            "unit": "G VALU wave-instructions/s", "frac": issue, **rest,
-            "at_12_bytes_per_update": hbm}
+    alu = {"achieved": None, "peak": VALU_PEAK_G, "unit": "G VALU wave-instructions/s", "frac": None}
+    if issue is not None:
+        alu.update(achieved=issue * VALU_PEAK_G, frac=issue)
+    return {"bound": "alu", **alu, **rest, "at_12_bytes_per_update": hbm}
 
 
 def main():
@@ -783,7 +795,7 @@ def main():
         "config": {"workload": "d1q3_L16M_rho50_u0.1", "L": L, "rho": 50.0, "u0": 0.1, "C": 10,
                    "lambda": 1, "n_max": 255, "seed": 2, "launch": "graph" if args.graph else "plain",
                    "schedule": args.schedule or "default", **info},
-        "roofline": roofline(achieved, ms_per_step, info["steps_per_launch"]),
+        "roofline": roofline(achieved, ms_per_step, info),
         "statistics": stats,
     }
     if args.only == "plain":
